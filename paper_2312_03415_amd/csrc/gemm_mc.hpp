@@ -74,6 +74,14 @@ __device__ __forceinline__ void mc_wait_piece(int k, V (&o)[8]) {
   }
 }
 
+// All eight pieces have arrived.  For epilogues that branch (guarded stores): the compiler may copy a register at a
+// block boundary, so nothing may still be in flight there.
+template <typename V>
+__device__ __forceinline__ void mc_wait_pieces(V (&o)[8]) {
+  asm volatile("s_waitcnt lgkmcnt(0)"
+               : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]), "+v"(o[3]), "+v"(o[4]), "+v"(o[5]), "+v"(o[6]), "+v"(o[7]));
+}
+
 // The kernel body is a device function (the buffer-descriptor builtins exist only in device code).
 // BQ: B of segment 0 is int4 with fp16 group scales (GemmArgs::Bscale).  The B half of a K tile then
 // does not go to LDS by LDS-DMA: every lane fetches, for each of its four 16-byte LDS slots, the eight

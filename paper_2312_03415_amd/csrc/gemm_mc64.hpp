@@ -88,10 +88,15 @@ struct Mc64Tile {
   static_assert(IPW == 8, "two groups of four loads per operand tile and wave, each group sharing one LDS base");
 };
 
-// PLAIN (decided on the host): M and N are multiples of the tile and
-//   1: the launch has no addend, bias, scale, mask or split: every tile takes the short 16-bit epilogue;
-//   2: the launch is a split contraction: every tile writes fp32 partials;
+// PLAIN (decided on the host):
+//   1: no addend, bias, scale, mask or split, M and N multiples of the tile: every tile takes the short 16-bit epilogue;
+//   3: the same with a bias and / or ragged M, N: the bias is added to the accumulators, stores are guarded;
+//   2: a split contraction, M and N multiples of the tile: every tile writes fp32 partials;
+//   4: the same with ragged M, N: stores are guarded;
 //   0: everything else (general epilogue).
+// Bound by the pattern and number of its store instructions: the general epilogue stores 8 bytes per lane, two rows of
+// 256 bytes per instruction, behind its options' branches; 3 stores 16 bytes per lane like 1.  Y = X W + bias at
+// 4096 x 2048 -> 8192 (two tiles per compute unit): 148 us with the general epilogue, 126 with 3 (118 without a bias).
 template <typename T, int AL, int BL, int PLAIN>
 __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
   using P = Mc64Tile<AL, BL>;
@@ -407,6 +412,17 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
     int seq, split, u0, u1, m0, n0;
     split_range(w, seq, split, u0, u1);
     tile_origin(seq, m0, n0);
+    // PLAIN 3: this lane's bias (columns 16 b + 4 grp .. + 3 of the wave's 128), requested ahead of the K loop so that
+    // the epilogue does not wait for it; columns beyond N read the last four in range and are never stored
+    [[maybe_unused]] i32x2 bias2[8];
+    if constexpr (PLAIN == 3) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        int n = n0 + wn * 128 + 16 * b + 4 * grp;
+        n = n < g.N ? n : g.N - 4;
+        bias2[b] = g.bias != nullptr ? *reinterpret_cast<const i32x2*>(static_cast<const T*>(g.bias) + n) : i32x2{0, 0};
+      }
+    }
     static_for<64>([&](auto e) { acc[decltype(e)::value >> 3][decltype(e)::value & 7] = f32x4{0.f, 0.f, 0.f, 0.f}; });
 
     for (int u = u0; u < u1; ++u) {
@@ -444,7 +460,7 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
 
     // ---- epilogue (the next work item's first tiles keep arriving meanwhile)
     asm volatile("s_nop 7\n\ts_nop 7");  // the last MFMAs' results, read by hand below
-    if constexpr (PLAIN == 1) {
+    if constexpr (PLAIN == 1 || PLAIN == 3) {
       // Row-contiguous stores: two row blocks (32 rows x 128 columns of this wave) at a time go through a private
       // 8 KB LDS area, row r at r * 256 bytes: 8-byte pieces in the accumulator layout in (a lane holds columns
       // 16 b + 4 grp .. + 3 of its row: piece 4 b + grp of 32; pairs of pieces are rotated by the row against bank
@@ -453,6 +469,7 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
       const uint32_t stg_base = (uint32_t)(uintptr_t)((mc_lds_void_t*)stg);
       const int rr = lane >> 4, rc = lane & 15;              // read side: row within a group of 4, 16-byte chunk
       T* gp = static_cast<T*>(g.C) + (int64_t)(m0 + wm * 128 + rr) * g.ldc + (n0 + wn * 128 + rc * 8);
+      [[maybe_unused]] const bool n_ok = n0 + wn * 128 + rc * 8 < g.N;  // N is a multiple of 8: valid together
       typedef float f32x2_t __attribute__((ext_vector_type(2)));
       typedef T tx2_t __attribute__((ext_vector_type(2)));
       static_for<4>([&](auto a2c) {
@@ -467,6 +484,11 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
           asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x1) : "a"(acc[a][b][1]));
           asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x2) : "a"(acc[a][b][2]));
           asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x3) : "a"(acc[a][b][3]));
+          if constexpr (PLAIN == 3) {
+            T b4[4];
+            *reinterpret_cast<i32x2*>(b4) = bias2[b];
+            x0 += (float)b4[0]; x1 += (float)b4[1]; x2 += (float)b4[2]; x3 += (float)b4[3];
+          }
           const f32x2_t lo = {x0, x1}, hi2 = {x2, x3};
           i32x2 v = {(int)__builtin_bit_cast(unsigned, __builtin_convertvector(lo, tx2_t)),
                      (int)__builtin_bit_cast(unsigned, __builtin_convertvector(hi2, tx2_t))};
@@ -483,15 +505,17 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
           asm volatile("ds_read_b128 %0, %1" : "=v"(o[k]) : "v"(addr) : "memory");
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PLAIN == 3) mc_wait_pieces(o);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          mc_wait_piece(k, o);
-          *reinterpret_cast<i32x4*>(gp + (int64_t)(a2 * 32 + 4 * k) * g.ldc) = o[k];
+          if constexpr (PLAIN == 1) mc_wait_piece(k, o);
+          if (PLAIN == 1 || (n_ok && m0 + wm * 128 + rr + a2 * 32 + 4 * k < g.M))
+            *reinterpret_cast<i32x4*>(gp + (int64_t)(a2 * 32 + 4 * k) * g.ldc) = o[k];
           __builtin_amdgcn_sched_barrier(0);
         }
       });
     } else {
-      // fp32 partials of a split contraction (PLAIN == 2), or the general epilogue (ragged tiles, addend, bias, scale,
+      // fp32 partials of a split contraction (PLAIN == 2, 4), or the general epilogue (ragged tiles, addend, bias, scale,
       // mask, partials of a ragged split).  One row block (16 rows x 128 fp32 columns of this wave = 8 KB) at a time
       // passes through the wave's LDS area, row r at r * 512 bytes: 16-byte pieces in the accumulator layout in (piece
       // 4 b + grp of 32, rotated by the row against bank conflicts), two rows x 512 bytes per instruction out, so that
@@ -548,11 +572,14 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
           }
         }
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PLAIN != 2) mc_wait_pieces(o);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-          mc_wait_piece(k, o);
+          if constexpr (PLAIN == 2) mc_wait_piece(k, o);
           const int m = m0 + wm * 128 + a * 16 + 2 * k + rr;
-          if constexpr (PLAIN == 2) {
+          if constexpr (PLAIN == 4) {
+            if (m < g.M && n_ok) *reinterpret_cast<f32x4*>(g.partial + ((int64_t)split * g.M + m) * g.N + n) = o[k];
+          } else if constexpr (PLAIN == 2) {
             *reinterpret_cast<f32x4*>(g.partial + ((int64_t)split * g.M + m) * g.N + n) = o[k];
           } else {
             if (m < g.M && n_ok) {

@@ -256,3 +256,31 @@ def test_split_contraction_over_whole_tiles(layout, dtype):
         rl.runlora_gemm(A, B, C2, a_strided=a_str, b_kcontig=b_kc, D=D, tile_cfg=7, splits=splits, alpha=0.5, bias=bias)
         torch.cuda.synchronize()
         assert relerr(to_f64(C2), 0.5 * want + Dh + biash[None, :]) < TOL[dtype], splits
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("layout", ["NN", "NT"])
+@pytest.mark.parametrize("shape", [(256, 512), (256, 264), (8, 8), (511, 520), (257, 248)])
+def test_matrix_core_bias_and_ragged_stores(shape, layout, dtype):
+    """The short epilogues with a bias and guarded stores (whole tiles, one row or eight columns into a tile, one short of
+    it), whole and split contraction, integer-valued: bit for bit, and nothing outside the output is written."""
+    import torch
+    _, b_kc = LAYOUTS[layout]
+    M, N = shape
+    K = 136
+    rng = np.random.default_rng(7)
+    Ah = rng.integers(-2, 3, size=(M, K)).astype(np.float64)
+    Bh = rng.integers(-1, 2, size=(N, K) if b_kc else (K, N)).astype(np.float64)
+    bh = rng.integers(-9, 10, size=(N,)).astype(np.float64)
+    A, B, bias = (to_device(synth.store(v, dtype), dtype) for v in (Ah, Bh, bh))
+    want = oracle.matmul(Ah, Bh, tb=b_kc) + bh
+    assert np.abs(want).max() <= 256   # exact in bf16's 8-bit significand
+    for splits in (1, 3):
+        buf = torch.full((M + 2, N + 16), 7.0, dtype=torch_dtype(dtype), device="cuda")
+        C = buf[1:M + 1, 8:N + 8]
+        rl.runlora_gemm(A, B, C, b_kcontig=b_kc, tile_cfg=7, splits=splits, bias=bias)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_f64(C), want), splits
+        edge = to_f64(buf)
+        edge[1:M + 1, 8:N + 8] = 7.0
+        assert np.array_equal(edge, np.full_like(edge, 7.0)), splits
