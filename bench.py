@@ -32,7 +32,8 @@ import numpy as np
 
 MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f16": 2500.0, "f32": 157.3}
 HBM_PEAK_GBPS = 8000.0
-TILE_NAMES = ["256x256", "128x128", "128x32", "128x64", "32x128", "64x128", "256x256mc3", "256x256mc", "stream32", "stream64", "stream128", "merge"]
+TILE_NAMES = ["256x256", "128x128", "128x32", "128x64", "32x128", "64x128", "256x256mc3", "256x256mc", "stream32", "stream64", "stream128", "merge",
+              "128x128mt", "128x128mt4", "256x128mt", "128x64mt", "64x128mt"]
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 

@@ -362,6 +362,9 @@ size_t runlora_workspace_bytes_w(int fwd, int bwd, int64_t n, int64_t i, int64_t
  *              dense operands); 8 = the
  *              streaming kernel for rank-r products (N <= 128, no second segment, no addend:
  *              4 wavefronts per 32 output rows split the contraction)
+ *              12..16 = the middle-sized matrix-core kernel (K tile 64, 16x16x32 products, 16-bit types, fp32
+ *              falls back to 1): 12 / 13 = 128x128 with 2 / 4 LDS stages, 14 = 256x128, 15 = 128x64, 16 = 64x128
+ *              (9..11 are not tile ids)
  *   trans_out  1 = store C transposed, as [N,M] with ldc >= M (streaming kernel only); else 0
  *   splits     0 = heuristic, n > 0 = split the contraction n ways (fp32 partials in the
  *              workspace, summed in a fixed order)
@@ -399,7 +402,7 @@ size_t runlora_gemm_workspace_bytes(const rl_gemm_t* g);
  * durations (what a kernel trace reports for them, added up), main_us the first (main) kernel's alone, kernels
  * how many were timed; us then also holds the handling of those events.  Otherwise kernel_us = main_us = us
  * and kernels = 0.
- * tile_cfg names the kernel that ran the step: 0..7 as in rl_gemm_t, 8 / 9 / 10 = the streaming kernel with up to
+ * tile_cfg names the kernel that ran the step: 0..7 and 12..16 as in rl_gemm_t, 8 / 9 / 10 = the streaming kernel with up to
  * 32 / 64 / 128 output columns, 11 = the W + alpha A B kernel (also the default chain's rank-r updates).
  * Events are host objects created at enable and destroyed at disable; no device memory.
  */

@@ -126,7 +126,7 @@ void describe_step(const Step& s, rl_step_time_t* r) {
     r->flops = 2.0 * (double)s.mg.I * (double)s.mg.O * (double)s.mg.R;
     r->bytes = e * (2.0 * (double)s.mg.I * (double)s.mg.O + (double)s.mg.R * (double)(s.mg.I + s.mg.O));
     r->M = s.mg.I; r->N = s.mg.O; r->K = s.mg.R;
-    r->tile_cfg = CFG_COUNT + 3;
+    r->tile_cfg = CFG_STREAM + 3;
     r->splits = 1;
     r->a_strided = 0; r->b_kcontig = 0;
     return;
@@ -146,7 +146,7 @@ void describe_step(const Step& s, rl_step_time_t* r) {
       r->bytes += e * ((double)k.M * k.K + (double)k.K * k.N + (double)k.M * k.N);
     }
     r->M = s.sk[0].M; r->N = s.sk[0].N; r->K = s.sk[0].K;
-    r->tile_cfg = CFG_COUNT + (s.skplan.rt == 1 ? 0 : (s.skplan.rt == 2 ? 1 : 2));
+    r->tile_cfg = CFG_STREAM + (s.skplan.rt == 1 ? 0 : (s.skplan.rt == 2 ? 1 : 2));
     r->splits = s.skplan.splits;
     r->a_strided = s.sk[0].a_strided; r->b_kcontig = s.sk[0].b_kcontig;
     return;
@@ -825,9 +825,9 @@ static int check_gemm(const rl_gemm_t* g, GemmDesc* d, GemmPlan* plan) {
   if (g->M < 1 || g->N < 1 || g->K < 1 || g->K2 < 0) return RL_ERR_SHAPE;
   if (g->M > (1LL << 30) || g->N > (1LL << 30) || g->K > (1LL << 30) || g->K2 > (1LL << 30)) return RL_ERR_SHAPE;
   if (g->K2 > 0 && (!g->A2 || !g->B2)) return RL_ERR_NULL;
-  if (g->tile_cfg < -1 || g->tile_cfg > CFG_COUNT || g->splits < 0) return RL_ERR_VARIANT;
+  if ((g->tile_cfg != -1 && g->tile_cfg != CFG_STREAM && !cfg_is_tile(g->tile_cfg)) || g->splits < 0) return RL_ERR_VARIANT;
   if (g->trans_out != 0 && g->trans_out != 1) return RL_ERR_VARIANT;
-  if (g->tile_cfg == CFG_COUNT) {  // the streaming kernel
+  if (g->tile_cfg == CFG_STREAM) {  // the streaming kernel
     if (g->N > 128 || g->K2 > 0 || g->D) return RL_ERR_UNSUPPORTED;
     const int64_t esz = g->dtype == RL_F32 ? 4 : 2;
     const int64_t a_rows = g->a_strided ? g->K : g->M, b_rows = g->b_kcontig ? g->N : g->K;
@@ -858,10 +858,10 @@ static int check_gemm(const rl_gemm_t* g, GemmDesc* d, GemmPlan* plan) {
   d->alpha = g->alpha != 0.f ? g->alpha : 1.f;
   if (g->bias) {
     if ((reinterpret_cast<uintptr_t>(g->bias) & 15) != 0) return RL_ERR_ALIGN;
-    if (g->tile_cfg == CFG_COUNT) return RL_ERR_UNSUPPORTED;  // the streaming kernel has no bias path
+    if (g->tile_cfg == CFG_STREAM) return RL_ERR_UNSUPPORTED;  // the streaming kernel has no bias path
     d->bias = g->bias;
   }
-  if (g->tile_cfg != CFG_COUNT) *plan = gemm_plan(dt, g->M, g->N, g->K, g->K2, g->tile_cfg, g->splits);
+  if (g->tile_cfg != CFG_STREAM) *plan = gemm_plan(dt, g->M, g->N, g->K, g->K2, g->tile_cfg, g->splits);
   return RL_OK;
 }
 
@@ -882,7 +882,7 @@ extern "C" size_t runlora_gemm_workspace_bytes(const rl_gemm_t* g) {
   GemmDesc d;
   GemmPlan plan;
   if (check_gemm(g, &d, &plan) != RL_OK) return 0;
-  if (g->tile_cfg == CFG_COUNT) {
+  if (g->tile_cfg == CFG_STREAM) {
     SkinnyDesc k;
     SkinnyPlan sp;
     gemm_as_skinny(g, &k, &sp);
@@ -898,7 +898,7 @@ extern "C" int runlora_gemm(const rl_gemm_t* g, const rl_opts_t* opts) {
   if (rc != RL_OK) return rc;
   SkinnyDesc k;
   SkinnyPlan sp;
-  const bool streaming = g->tile_cfg == CFG_COUNT;
+  const bool streaming = g->tile_cfg == CFG_STREAM;
   if (streaming) {
     gemm_as_skinny(g, &k, &sp);
     plan.partial_bytes = sp.partial_bytes;

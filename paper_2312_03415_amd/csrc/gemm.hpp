@@ -52,8 +52,17 @@ enum TileCfg {
             // (the int4 route of the frozen weight runs here)
   CFG_MC4,  // matrix-core kernel (gemm_mc64.hpp, 16-bit types): 256x256x64, 4 waves, 2 LDS stages, 16x16x32 products
             // (the id the heuristics pick for dense B)
+  CFG_STREAM,  // id of the streaming kernel in rl_gemm_t (8); 8..11 name the streaming and merge kernels in profile records
+  // middle-sized matrix-core kernel (gemm_mt.hpp, 16-bit types): K tile 64, 4 waves, 16x16x32 products
+  CFG_MT128 = 12,  // 128x128, 2 LDS stages, two workgroups per compute unit
+  CFG_MT128D,      // 128x128, 4 LDS stages, one workgroup per compute unit
+  CFG_MT256,       // 256x128, 3 LDS stages, one workgroup per compute unit
+  CFG_MTN64,       // 128x64, 3 LDS stages, two workgroups per compute unit
+  CFG_MTM64,       // 64x128, 3 LDS stages, two workgroups per compute unit
   CFG_COUNT
 };
+inline bool cfg_is_mt(int cfg) { return cfg >= CFG_MT128 && cfg < CFG_COUNT; }
+inline bool cfg_is_tile(int cfg) { return cfg >= 0 && cfg < CFG_COUNT && (cfg < CFG_STREAM || cfg_is_mt(cfg)); }
 
 struct GemmPlan {
   int cfg = CFG_MID;
@@ -61,11 +70,13 @@ struct GemmPlan {
   int nbm = 1, nbn = 1;
   int splits = 1;            // > 1: fp32 partials + fixed-order reduce
   int tiles_per_split = 1;
-  size_t partial_bytes = 0;  // scratch needed when splits > 1 (or by the tail launch)
+  // scratch to provide for partials (of the launch or of the tail launch); may be more than the plan uses (gemm_plan)
+  size_t partial_bytes = 0;
   // > 0: the output columns [tail_n0, N) are a launch of their own, planned by gemm_plan on that
   // sub-problem (a few tiles with the contraction split), so that the main launch is whole rounds of
   // one tile per compute unit instead of ending on a mostly idle round
   int64_t tail_n0 = 0;
+  int tail_cfg = -1, tail_splits = 0;  // that launch's tile shape and K split
 };
 
 // Tile shape and K split for a problem; depends on shapes and dtype only (never on pointers), so
@@ -73,6 +84,12 @@ struct GemmPlan {
 // override the heuristics (used by the tuning sweeps and tests).
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg = -1,
                    int force_splits = 0, bool b_int4 = false);
+
+// Modelled time in us of one launch of the middle-sized kernel (CFG_MT*) or of CFG_MC4: `wgs` workgroups (output tiles x
+// K slices) of `ktiles` K tiles each.
+double mt_time_us(int cfg, int64_t wgs, int64_t ktiles);
+// ... and of the partials' round trip and the reduce pass behind a contraction split `splits` ways.
+double split_time_us(int64_t M, int64_t N, int splits);
 
 // Plan for the one-pass LoRA forward (GemmDesc::fuse_t): a tile shape of the generic engine, the contraction whole.
 GemmPlan gemm_plan_fused(int dtype, int64_t M, int64_t N, int64_t K0, int64_t R);

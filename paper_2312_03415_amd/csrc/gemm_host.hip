@@ -8,9 +8,10 @@ namespace rl {
 
 thread_local KernelEvents g_kernel_events;
 
-static const int kTileBM[CFG_COUNT] = {256, 128, 128, 128, 32, 64, 256, 256};
-static const int kTileBN[CFG_COUNT] = {256, 128, 32, 64, 128, 128, 256, 256};
-static const int kTileBK16[CFG_COUNT] = {64, 64, 64, 64, 64, 64, 32, 64};  // K tile, 16-bit types
+// (ids 8..11 are no tile GEMMs)
+static const int kTileBM[CFG_COUNT] = {256, 128, 128, 128, 32, 64, 256, 256, 0, 0, 0, 0, 128, 128, 256, 128, 64};
+static const int kTileBN[CFG_COUNT] = {256, 128, 32, 64, 128, 128, 256, 256, 0, 0, 0, 0, 128, 128, 128, 64, 128};
+static const int kTileBK16[CFG_COUNT] = {64, 64, 64, 64, 64, 64, 32, 64, 0, 0, 0, 0, 64, 64, 64, 64, 64};  // K tile, 16-bit types
 
 // Slices of a contraction of length K for `tiles` output tiles of the matrix-core kernel (one 256x256 workgroup per
 // compute unit).  In units of a whole tile's time (0.024 us per k): s slices take ceil(tiles * s / 256) rounds of 1 / s
@@ -29,6 +30,101 @@ static int pick_splits(int64_t tiles, int64_t K, int smin) {
   return best;
 }
 
+// What a launch takes, from sweeps over 32 .. 2048 workgroups and K = 512 .. 4096 (bf16, N(0,1) operands, NN and NT, in
+// us): `full` = one K tile of every resident workgroup, `half` = the same with at most one workgroup per compute unit,
+// `round` = prologue and epilogue of a round of workgroups, `fix` = the launch.  E.g. 256 tiles of 128x128 at K = 4096:
+// 35.8 (128x128, 4 stages) against 46 (2 stages), 59.1 (generic engine, two K slices) and 47.5 (256x256, three slices);
+// 512 of them: 67.6, 60.1, and 60.3 as 256 tiles of 256x128.
+struct LaunchModel { int slots; double full, half, round, fix; };
+static LaunchModel launch_model(int cfg) {
+  switch (cfg) {
+    case CFG_MT128: return {512, 0.80, 0.63, 4.8, 4.0};
+    case CFG_MT128D: return {256, 0.44, 0.44, 4.5, 3.6};
+    case CFG_MT256: return {256, 0.755, 0.755, 8.8, 3.5};
+    case CFG_MTN64: return {512, 0.53, 0.25, 2.3, 5.2};
+    case CFG_MTM64: return {512, 0.51, 0.26, 2.3, 5.2};
+    default: return {256, 1.40, 1.40, 1.7, 10.5};  // CFG_MC4: persistent, the next tile's loads run during an epilogue
+  }
+}
+
+double mt_time_us(int cfg, int64_t wgs, int64_t ktiles) {
+  const LaunchModel m = launch_model(cfg);
+  const int64_t rounds = wgs / m.slots, rest = wgs % m.slots;
+  double us = m.fix + (double)rounds * (m.round + (double)ktiles * m.full);
+  if (rest > 0) {
+    // a round that leaves compute units idle runs up to a sixth faster (clock, cache)
+    const double fill = rest >= 256 ? 1.0 : 0.84 + 0.16 * (double)rest / 256.0;
+    us += m.round + (double)ktiles * (rest <= 256 ? m.half : m.full) * fill;
+  }
+  return us;
+}
+
+// partials written, read back and reduced: 3 us and ~7.5 TB/s (measured 10 while they fit the caches, 6 beyond)
+double split_time_us(int64_t M, int64_t N, int splits) {
+  return splits > 1 ? 3.0 + (double)M * (double)N * (8.0 * splits + 2.0) / 7.5e6 : 0.0;
+}
+
+// Tile shape and K split of a 16-bit product on the matrix-core kernels: the smallest modelled time among 256x256 (whole
+// rounds with cut-off tail columns included), 256x128, 128x128 (two ways), 128x64 and 64x128, each with the contraction
+// in 1 .. 16 slices of at least four K tiles.  cap = scratch bytes the plan may use for partials.
+static bool mt_plan(GemmPlan* out, double* out_us, int64_t M, int64_t N, int64_t K0, int64_t K1, size_t cap, bool tail_ok) {
+  static const int cfgs[] = {CFG_MC4, CFG_MT256, CFG_MT128, CFG_MT128D, CFG_MTN64, CFG_MTM64};
+  const int64_t kt = (K0 + 63) / 64 + (K1 + 63) / 64;
+  double best = 1e30;
+  for (int cfg : cfgs) {
+    const int64_t nbm = (M + kTileBM[cfg] - 1) / kTileBM[cfg], nbn = (N + kTileBN[cfg] - 1) / kTileBN[cfg], tiles = nbm * nbn;
+    if (tiles > (1 << 30)) continue;
+    for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+      const int64_t per = (kt + s - 1) / s;
+      const int used = (int)((kt + per - 1) / per);  // no empty slice
+      if (used != s) continue;
+      const size_t bytes = s > 1 ? (size_t)s * (size_t)M * (size_t)N * sizeof(float) : 0;
+      if (bytes > cap) break;
+      const double us = mt_time_us(cfg, tiles * s, per) + split_time_us(M, N, s);
+      if (us < best) {
+        best = us;
+        *out = GemmPlan{};
+        out->cfg = cfg;
+        out->bk = 64;
+        out->bm = kTileBM[cfg];
+        out->bn = kTileBN[cfg];
+        out->nbm = (int)nbm;
+        out->nbn = (int)nbn;
+        out->splits = s;
+        out->tiles_per_split = (int)per;
+        out->partial_bytes = bytes;
+      }
+    }
+    // 256x256 tiles in whole rounds, the remaining tile columns as a launch of their own
+    if (cfg == CFG_MC4 && tail_ok && tiles > 256 && kt >= 16) {
+      for (int64_t t = nbn - 1; t >= 1 && t >= nbn - 16; --t) {
+        if ((nbm * t) % 256 != 0) continue;
+        GemmPlan tp;
+        double tus = 0;
+        if (!mt_plan(&tp, &tus, M, N - t * 256, K0, K1, cap, false)) break;
+        const double us = mt_time_us(CFG_MC4, nbm * t, kt) + tus;
+        if (us < best) {
+          best = us;
+          *out = GemmPlan{};
+          out->cfg = CFG_MC4;
+          out->bk = 64;
+          out->bm = out->bn = 256;
+          out->nbm = (int)nbm;
+          out->nbn = (int)t;
+          out->tiles_per_split = (int)kt;
+          out->tail_n0 = t * 256;
+          out->tail_cfg = tp.cfg;
+          out->tail_splits = tp.splits;
+          out->partial_bytes = tp.partial_bytes;
+        }
+        break;
+      }
+    }
+  }
+  *out_us = best;
+  return best < 1e30;
+}
+
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg,
                    int force_splits, bool b_int4) {
   GemmPlan p;
@@ -38,9 +134,10 @@ GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int 
     // else on the generic engine's 128x128 tiles
     const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
     cfg = (big_tiles >= 160 || (big_tiles >= 80 && K0 + K1 >= 2048)) ? CFG_MC3 : CFG_MID;
-  } else if (force_cfg >= 0 && force_cfg < CFG_COUNT) {
+  } else if (cfg_is_tile(force_cfg)) {
     cfg = force_cfg;
     if ((cfg == CFG_MC3 || cfg == CFG_MC4) && dtype == DT_F32) cfg = CFG_BIG;  // 16-bit only
+    if (cfg_is_mt(cfg) && dtype == DT_F32) cfg = CFG_MID;
   } else if (M <= 32) {
     cfg = CFG_WIDE32;
   } else if (M <= 64) {
@@ -98,19 +195,28 @@ GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int 
       if (main_tiles % 256 != 0 || tail_tiles < 32) continue;
       p.tail_n0 = (int64_t)t * p.bn;
       p.nbn = t;
+      p.tail_cfg = p.cfg;
+      p.tail_splits = pick_splits((int64_t)p.nbm * ((N - p.tail_n0 + p.bn - 1) / p.bn), K0 + K1, 2);
       p.partial_bytes = gemm_tail_plan(p, dtype, M, N, K0, K1).partial_bytes;
       break;
+    }
+  }
+  // 16-bit products with more than 32 rows and columns run on the matrix-core kernels, with no more scratch than the plan
+  // above, whose need stays the one that is reported: the size of a workspace that callers keep is a matter of the
+  // product, not of the kernel it runs on.
+  if (dtype != DT_F32 && !b_int4 && force_cfg < 0 && force_splits <= 0 && M > 32 && N > 32) {
+    GemmPlan q;
+    double us = 0;
+    if (mt_plan(&q, &us, M, N, K0, K1, p.partial_bytes, true)) {
+      q.partial_bytes = p.partial_bytes;
+      return q;
     }
   }
   return p;
 }
 
 GemmPlan gemm_tail_plan(const GemmPlan& main, int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1) {
-  // same kernel as the main launch with the contraction split (pick_splits)
-  const int64_t nt = N - main.tail_n0;
-  const int64_t tiles = (int64_t)main.nbm * ((nt + main.bn - 1) / main.bn);
-  const int best = pick_splits(tiles, K0 + K1, 2);
-  return gemm_plan(dtype, M, nt, K0, K1, main.cfg, best);
+  return gemm_plan(dtype, M, N - main.tail_n0, K0, K1, main.tail_cfg, main.tail_splits);
 }
 
 GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1) {
@@ -118,10 +224,9 @@ GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1)
 }
 
 GemmPlan gemm_plan_fused(int dtype, int64_t M, int64_t N, int64_t K0, int64_t R) {
-  // the shape rules of gemm_plan with the generic engine's 256x256 tile where the matrix-core kernel would run;
-  // the workgroup that owns an output tile needs the whole contraction of its rows of T: no split
-  int cfg = gemm_plan(dtype, M, N, K0, R).cfg;
-  if (cfg == CFG_MC3 || cfg == CFG_MC4) cfg = CFG_BIG;
+  // the shape rules of gemm_plan for the generic engine (those fp32 runs on); the workgroup that owns an output tile needs
+  // the whole contraction of its rows of T: no split
+  const int cfg = gemm_plan(DT_F32, M, N, K0, R).cfg;
   return gemm_plan(dtype, M, N, K0, R, cfg, 1);
 }
 
@@ -157,13 +262,13 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
     if (e != hipSuccess) return e;
     const GemmPlan pt = gemm_tail_plan(plan, d.dtype, d.M, d.N, d.K[0], d.nseg > 1 ? d.K[1] : 0);
     if (pt.tail_n0 > 0 || pt.partial_bytes > plan.partial_bytes) return hipErrorInvalidValue;
-    return gemm_run(dt, pt, scratch, stream);
+    return gemm_run(dt, pt, pt.splits > 1 ? scratch : nullptr, stream);
   }
   if (plan.splits > 1 && scratch == nullptr) return hipErrorInvalidValue;
   if (d.fuse_t) {
     const bool ok = d.LA != nullptr && d.nseg == 2 && d.K[1] >= 1 && d.K[1] <= kFuseMaxR && d.K[0] >= 1 && !d.a_strided &&
                     !d.b_kcontig && plan.splits == 1 && d.D == nullptr && d.Bscale == nullptr && d.drop_thr == 0 &&
-                    plan.cfg != CFG_MC3 && plan.cfg != CFG_MC4;
+                    plan.cfg != CFG_MC3 && plan.cfg != CFG_MC4 && !cfg_is_mt(plan.cfg);
     if (!ok) return hipErrorInvalidValue;
   }
   int cfg = plan.cfg;
@@ -183,6 +288,20 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
     if ((d.a_strided && d.M < 8) || (!d.b_kcontig && d.N < 8)) ok = false;
     if (!ok) cfg = CFG_BIG;
   }
+  int nbm = plan.nbm, nbn = plan.nbn;
+  if (cfg_is_mt(cfg)) {
+    // gemm_mt.hpp addresses each operand with 31-bit byte offsets; larger ones run on the generic engine (same K tile)
+    bool ok = d.dtype != DT_F32 && plan.bk == 64;
+    for (int s = 0; s < d.nseg; ++s) {
+      const int64_t a_rows = d.a_strided ? d.K[s] : d.M, b_rows = d.b_kcontig ? d.N : d.K[s];
+      if (a_rows * d.lda[s] >= (1LL << 30) || b_rows * d.ldb[s] >= (1LL << 30)) ok = false;
+    }
+    if (!ok) {
+      cfg = CFG_MID;
+      nbm = (int)((d.M + kTileBM[cfg] - 1) / kTileBM[cfg]);
+      nbn = (int)((d.N + kTileBN[cfg] - 1) / kTileBN[cfg]);
+    }
+  }
   GemmArgs a{};
   for (int s = 0; s < 2; ++s) {
     const bool on = s < d.nseg;
@@ -200,8 +319,8 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   a.M = (int)d.M;
   a.N = (int)d.N;
   a.tiles_per_split = plan.splits > 1 ? plan.tiles_per_split : (1 << 30);
-  a.nbm = plan.nbm;
-  a.nbn = plan.nbn;
+  a.nbm = nbm;
+  a.nbn = nbn;
   a.splits = plan.splits;
   a.Bscale = d.Bscale;
   a.ldbs = d.ldbs;
@@ -214,7 +333,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   a.ldla = d.ldla;
   a.R = d.fuse_t ? (int)d.K[1] : 0;
   a.t_alpha = d.t_alpha;
-  dim3 grid((unsigned)(plan.nbm * plan.nbn), (unsigned)plan.splits, 1);
+  dim3 grid((unsigned)(nbm * nbn), (unsigned)plan.splits, 1);
   const int al = d.a_strided ? 1 : 0, bl = d.b_kcontig ? 1 : 0;
   hipError_t e;
   switch (d.dtype) {
