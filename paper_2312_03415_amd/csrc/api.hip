@@ -116,6 +116,22 @@ struct Profiler {
 thread_local Profiler g_prof;
 
 void describe_step(const Step& s, rl_step_time_t* r) {
+  if (s.is_few) {
+    const double e = (double)dtype_size(s.d.dtype);
+    const double n = (double)s.few.n, i = (double)s.few.i, o = (double)s.few.o, k = (double)s.few.r;
+    r->what = s.what;
+    r->us = 0.0;
+    r->kernel_us = 0.0;
+    r->main_us = 0.0;
+    r->kernels = 0;
+    r->flops = 2.0 * n * (i * o + k * (i + o));
+    r->bytes = e * (n * (i + o) + i * o + k * (i + o));
+    r->M = s.few.n; r->N = s.few.o; r->K = s.few.i + s.few.r;
+    r->tile_cfg = CFG_MTM64;
+    r->splits = s.few_plan.splits;
+    r->a_strided = 0; r->b_kcontig = 0;
+    return;
+  }
   if (s.is_merge) {
     const double e = (double)dtype_size(s.d.dtype);
     r->what = s.what;
@@ -198,7 +214,8 @@ int run_schedule(const Schedule& sch, char* ws, hipStream_t stream) {
         g_kernel_events = ke;
       }
     }
-    hipError_t e = s.is_merge ? merge_run(s.d.dtype, s.mg, stream)
+    hipError_t e = s.is_few ? few_run(s.d.dtype, s.few, s.few_plan, partial, stream)
+                   : s.is_merge ? merge_run(s.d.dtype, s.mg, stream)
                    : s.nsk > 0 ? skinny_run(s.d.dtype, s.nsk, s.sk, s.skplan, partial, stream)
                                : gemm_run(s.d, s.plan, partial, stream);
     const int kbound = (timed && g_prof.kernel_events) ? g_kernel_events.used : 0;  // pairs the step's launches consumed

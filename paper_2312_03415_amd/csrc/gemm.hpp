@@ -104,6 +104,24 @@ GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1)
 // Enqueue the product.  `scratch` must hold plan.partial_bytes when plan.splits > 1.
 hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hipStream_t stream);
 
+// ---- few-token forward: Y = X W + (t_alpha X A) B + bias in two launches (lora_finish.hpp), 16-bit, dense W -------
+struct FewDesc {
+  const void *X = nullptr, *W = nullptr, *A = nullptr, *B = nullptr, *bias = nullptr;
+  void *Y = nullptr, *T = nullptr;  // T: [n, r] buffer to leave t_alpha X A in, or nullptr
+  int64_t ldx = 0, ldw = 0, lda = 0, ldb = 0, ldy = 0, ldt = 0;
+  int64_t n = 0, i = 0, o = 0, r = 0;
+  float t_alpha = 1.f;
+};
+struct FewPlan {
+  int splits = 0;  // K slices; 0 = the route does not apply
+  int tiles_per_split = 0;
+  double us = 0;   // modelled time
+};
+constexpr int64_t kFewMaxRows = 256, kFewMaxR = 128;
+// scratch_bytes: what the call has for partials whatever route it takes
+FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_bytes);
+hipError_t few_run(int dtype, const FewDesc& d, const FewPlan& plan, float* scratch, hipStream_t stream);
+
 // ---- streaming kernel for the rank-r products (skinny.hpp) --------------------------------------
 // C[M,N<=128] = op(A)[M,K] op(B)[K,N], optionally stored transposed; up to two problems per launch.
 struct SkinnyDesc {
@@ -188,6 +206,9 @@ hipError_t merge_launch_f16(const MergeArgs& a, hipStream_t s);
 
 // per-dtype launchers (one translation unit each)
 struct GemmArgs;
+struct FinishArgs;
+hipError_t finish_launch_bf16(const FinishArgs& a, hipStream_t s);
+hipError_t finish_launch_f16(const FinishArgs& a, hipStream_t s);
 hipError_t gemm_launch_bf16(int cfg, int al, int bl, const GemmArgs& a, dim3 grid, hipStream_t s);
 hipError_t gemm_launch_f16(int cfg, int al, int bl, const GemmArgs& a, dim3 grid, hipStream_t s);
 hipError_t gemm_launch_f32(int cfg, int al, int bl, const GemmArgs& a, dim3 grid, hipStream_t s);

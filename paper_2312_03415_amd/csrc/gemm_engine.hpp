@@ -64,6 +64,8 @@ struct GemmArgs {
   int64_t ldla;
   int R;
   float t_alpha;
+  // gemm_mt.hpp's build with LA: T's fp32 partials, [splits][M][R], next to `partial` (which that build requires)
+  float* partial_t;
 };
 
 // ---- per-type pieces --------------------------------------------------------------------------

@@ -3,6 +3,7 @@
 #include "gemm_engine.hpp"
 #include "skinny.hpp"
 #include "merge.hpp"
+#include "lora_finish.hpp"
 
 namespace rl {
 
@@ -375,6 +376,57 @@ hipError_t splitk_reduce_launch(int dtype, const float* partial, int splits, int
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// ---- few-token forward ---------------------------------------------------------------------------------
+
+// Two launches where [X|T] [W;B] after T = X A takes three or four: taken whenever the scratch the call has anyway holds
+// the partials of at least one slicing.  Up to 256 rows; beyond, the rows fill the chip without a split.
+FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_bytes) {
+  FewPlan best;
+  if (n < 1 || n > kFewMaxRows || r > kFewMaxR || n > (1LL << 30)) return best;
+  const int64_t nbm = (n + 63) / 64, tiles = nbm * ((o + 127) / 128 + (r + 127) / 128);
+  const int64_t kt = (i + 63) / 64;
+  for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+    const int64_t per = (kt + s - 1) / s;
+    if ((kt + per - 1) / per != s) continue;  // no empty slice
+    if ((size_t)s * (size_t)n * (size_t)(o + r) * sizeof(float) > scratch_bytes) break;
+    const double us = mt_time_us(CFG_MTM64, tiles * s, per) + 3.0 + (double)n * (double)(o + r) * (8.0 * s + 2.0) / 7.5e6;
+    if (best.splits == 0 || us < best.us) {
+      best.splits = s;
+      best.tiles_per_split = (int)per;
+      best.us = us;
+    }
+  }
+  return best;
+}
+
+hipError_t few_run(int dtype, const FewDesc& d, const FewPlan& plan, float* scratch, hipStream_t stream) {
+  if (dtype == DT_F32 || plan.splits < 1 || scratch == nullptr || d.n < 1 || d.n > kFewMaxRows || d.r < 1 || d.r > kFewMaxR)
+    return hipErrorInvalidValue;
+  GemmArgs a{};
+  a.A[0] = d.X; a.lda[0] = d.ldx;
+  a.B[0] = d.W; a.ldb[0] = d.ldw;
+  a.K[0] = (int)d.i;
+  a.M = (int)d.n; a.N = (int)d.o;
+  a.partial = scratch;
+  a.partial_t = scratch + (size_t)plan.splits * (size_t)d.n * (size_t)d.o;
+  a.tiles_per_split = plan.tiles_per_split;
+  a.nbm = (int)((d.n + 63) / 64);
+  a.nbn = (int)((d.o + 127) / 128);
+  a.splits = plan.splits;
+  a.alpha = 1.f;
+  a.LA = d.A; a.ldla = d.lda; a.R = (int)d.r;
+  const dim3 grid((unsigned)(a.nbm * (a.nbn + (a.R + 127) / 128)), (unsigned)plan.splits, 1);
+  hipError_t e = dtype == DT_BF16 ? gemm_launch_bf16(CFG_MTM64, 0, 0, a, grid, stream) : gemm_launch_f16(CFG_MTM64, 0, 0, a, grid, stream);
+  if (e != hipSuccess) return e;
+  FinishArgs f{};
+  f.partial = a.partial; f.partial_t = a.partial_t;
+  f.B = d.B; f.ldb = d.ldb; f.bias = d.bias;
+  f.C = d.Y; f.ldc = d.ldy; f.T = d.T; f.ldt = d.ldt;
+  f.M = a.M; f.N = a.N; f.R = a.R; f.splits = plan.splits;
+  f.t_alpha = d.t_alpha;
+  return dtype == DT_BF16 ? finish_launch_bf16(f, stream) : finish_launch_f16(f, stream);
 }
 
 // ---- streaming kernel for the rank-r products -----------------------------------------------------

@@ -27,6 +27,8 @@
 //      that 32 lanes of a transposing read touch
 //  - The LDS reads are inline assembly (reads the compiler tracks would wait for all outstanding LDS-DMA loads); between
 //    their issue and the wait for them there is no branch, and their results are combined only behind the wait.
+//  - XA build: the few-token forward (lora_finish.hpp).  The adapter's A stands next to W as more tile columns, so that one
+//    launch reads X and W once and leaves the fp32 partials of X W and of T = X A.
 //  - Epilogue: the accumulators of 16 rows at a time pass through wave-private LDS (the ring, drained), so that a lane
 //    owns eight consecutive columns of a row: every option (scale, dropout mask, addend, bias) works on those, and a store
 //    instruction writes whole 128-byte lines.
@@ -90,8 +92,9 @@ template <> struct MtFrag<true> {
   __device__ __forceinline__ void touch() { asm volatile("" : "+v"(lo), "+v"(hi)); }
 };
 
-template <typename T, int AL, int BL, int BM, int BN, int NS>
+template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA>
 __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
+  static_assert(!XA || (AL == 0 && BL == 0), "X [M,K], W and A [K,.]");
   using P = MtTile<AL, BL, BM, BN, NS>;
   constexpr int BK = P::BK, TM = P::TM, TN = P::TN;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -103,18 +106,28 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
 
   // ---- workgroup -> output tile: a contiguous run of tiles per XCD (own L2), walked in bands of 8 tile rows
   int m0, n0;
+  [[maybe_unused]] bool t_tile = false;  // XA: this tile's columns are A's
   {
-    const int total = g.nbm * g.nbn;
+    const int nbn = XA ? g.nbn + (g.R + BN - 1) / BN : g.nbn;
+    const int total = g.nbm * nbn;
     const int x = blockIdx.x & 7, slot = blockIdx.x >> 3, q = total >> 3, rem = total & 7;
     const int id = x * q + (x < rem ? x : rem) + slot;
     constexpr int BAND = 8;
-    const int per_band = BAND * g.nbn;
+    const int per_band = BAND * nbn;
     const int band = id / per_band, first_m = band * BAND;
     const int band_rows = (g.nbm - first_m) < BAND ? (g.nbm - first_m) : BAND;
     const int in_band = id - band * per_band;
     m0 = (first_m + in_band % band_rows) * BM;
-    n0 = (in_band / band_rows) * BN;
+    int tile_n = in_band / band_rows;
+    if constexpr (XA) {
+      t_tile = tile_n >= g.nbn;
+      if (t_tile) tile_n -= g.nbn;
+    }
+    n0 = tile_n * BN;
   }
+  const int N = XA && t_tile ? g.R : g.N;
+  const void* const B0 = XA && t_tile ? g.LA : g.B[0];
+  const int64_t ldb0 = XA && t_tile ? g.ldla : g.ldb[0];
   // ---- this workgroup's K tiles (over both segments; blockIdx.y slices them)
   const int K0 = g.K[0], K1 = g.K[1];
   const int nt0 = (K0 + BK - 1) / BK, nt1 = (K1 + BK - 1) / BK;
@@ -150,9 +163,9 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
     const int Ks = seg ? K1 : K0;
     const int k0 = (cu - (seg ? nt0 : 0)) * BK;
     const int kvalid = Ks - k0;
-    const uint32_t lda = (uint32_t)(seg ? g.lda[1] : g.lda[0]), ldb = (uint32_t)(seg ? g.ldb[1] : g.ldb[0]);
+    const uint32_t lda = (uint32_t)(seg ? g.lda[1] : g.lda[0]), ldb = (uint32_t)(seg ? g.ldb[1] : ldb0);
     rsA = make_rsrc(seg ? g.A[1] : g.A[0], extent_bytes(P::A_STR, g.M, Ks, lda));
-    rsB = make_rsrc(seg ? g.B[1] : g.B[0], extent_bytes(P::B_STR, g.N, Ks, ldb));
+    rsB = make_rsrc(seg ? g.B[1] : B0, extent_bytes(P::B_STR, N, Ks, ldb));
     stepA = 2u * (P::A_STR ? (uint32_t)BK * lda : (uint32_t)BK);
     stepB = 2u * (P::B_STR ? (uint32_t)BK * ldb : (uint32_t)BK);
     auto offset = [&](bool strided, int cpr_strided, int swz_strided_row, int p, int base, int dim, uint32_t ld) -> uint32_t {
@@ -171,7 +184,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
 #pragma unroll
     for (int j = 0; j < P::IB; ++j) {
       const int p = (wave * P::IB + j) * 64 + lane;
-      offB[j] = offset(P::B_STR, BN / 8, mt_swz<BN>(p / (BN / 8)), p, n0, g.N, ldb);
+      offB[j] = offset(P::B_STR, BN / 8, mt_swz<BN>(p / (BN / 8)), p, n0, N, ldb);
     }
     // rebuilt at the end, at a segment switch, in front of a segment's partial last tile and behind it
     cnext = u1;
@@ -349,8 +362,9 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
   float* const stg = reinterpret_cast<float*>(smem) + wave * (16 * LD);
   const int prow = lane / LPR, pcol = (lane % LPR) * 8;
   const int n = n0 + wn * P::WTN + pcol;
-  const bool n_ok = n < g.N;  // N is a multiple of 8: the eight columns are valid together
-  const bool split = g.partial != nullptr;
+  const bool n_ok = n < N;  // N is a multiple of 8: the eight columns are valid together
+  float* const part = XA && t_tile ? g.partial_t : g.partial;
+  const bool split = XA || part != nullptr;
   float b8[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) b8[e] = 0.f;
@@ -372,7 +386,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
       f32x4 v1 = *reinterpret_cast<const f32x4*>(stg + r * LD + pcol + 4);
       if (m < g.M && n_ok) {
         if (split) {
-          float* dst = g.partial + ((int64_t)blockIdx.y * g.M + m) * g.N + n;
+          float* dst = part + ((int64_t)blockIdx.y * g.M + m) * N + n;
           *reinterpret_cast<f32x4*>(dst) = v0;
           *reinterpret_cast<f32x4*>(dst + 4) = v1;
         } else {
@@ -403,9 +417,9 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
 #undef MT_FENCE
 }
 
-template <typename T, int AL, int BL, int BM, int BN, int NS>
+template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA = false>
 __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_kernel(GemmArgs g) {
-  gemm_mt_body<T, AL, BL, BM, BN, NS>(g);
+  gemm_mt_body<T, AL, BL, BM, BN, NS, XA>(g);
 }
 
 }  // namespace rl

@@ -176,6 +176,34 @@ struct Builder {
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
     out->steps.push_back(s);
   }
+  // forward1 for a few tokens in two launches; false where it does not apply.  The scratch is what forward1's launches
+  // would take, so that a call's workspace does not depend on the route.
+  bool few_forward(const char* what, Mat X, Mat W, Mat A, Mat B, Mat Y, Mat T, bool keep_T, const void* bias) {
+    if (L.dtype == DT_F32 || L.w_int4 || L.drop_thr || L.n > kFewMaxRows || L.r > kFewMaxR) return false;
+    // gemm_mt.hpp addresses its operands with 31-bit byte offsets
+    if (L.n * X.ld >= (1LL << 30) || L.i * W.ld >= (1LL << 30) || L.i * A.ld >= (1LL << 30)) return false;
+    const SkinnyDesc sd = to_skinny({0, 0, L.n, L.r, L.i, X, A, T, true});
+    size_t bytes = skinny_plan(L.dtype, 1, &sd).partial_bytes;
+    const size_t gemm_bytes = gemm_plan(L.dtype, L.n, L.o, L.i, L.r).partial_bytes;
+    if (gemm_bytes > bytes) bytes = gemm_bytes;
+    const FewPlan plan = rl::few_plan(L.n, L.i, L.o, L.r, bytes);
+    if (plan.splits == 0) return false;
+    if (bytes > max_partial) max_partial = bytes;
+    Step s;
+    s.what = what;
+    s.is_few = true;
+    s.d.dtype = L.dtype;
+    s.few_plan = plan;
+    FewDesc& f = s.few;
+    f.X = X.ptr; f.ldx = X.ld; f.W = W.ptr; f.ldw = W.ld; f.A = A.ptr; f.lda = A.ld; f.B = B.ptr; f.ldb = B.ld;
+    f.Y = const_cast<void*>(Y.ptr); f.ldy = Y.ld;
+    if (keep_T) { f.T = const_cast<void*>(T.ptr); f.ldt = T.ld; }
+    f.bias = bias;
+    f.n = L.n; f.i = L.i; f.o = L.o; f.r = L.r;
+    f.t_alpha = scale();
+    out->steps.push_back(s);
+    return true;
+  }
   void skinny2(const char* what, const char* what1, const Sk& g1, const char* what2, const Sk& g2) {
     bool pair = sk_ok(g1) && sk_ok(g2);
     SkinnyDesc d1, d2;
@@ -254,6 +282,7 @@ bool build_forward(int variant, const LayerDims& L, const FwdOperands& op, void*
       [[fallthrough]];
     case 1: {  // forward1: (XW) + ((XA)B), the sum folded into one contraction over [X|T]
       Mat T = op.keep_T ? op.T : b.scratch(n, r);
+      if (b.few_forward("Y = X [W|A] ; Y += T B", op.X, op.W, op.A, op.B, op.Y, T, op.keep_T, op.bias)) break;
       b.skinny("T = X A", {0, 0, n, r, i, op.X, op.A, T, true, true});
       b.gemm("Y = [X|T] [W;B]", 0, 0, n, o, i, op.X, op.W, op.Y, nullptr, r, &T, &op.B, true, 1.f, op.bias);
       break;

@@ -1,0 +1,65 @@
+"""GPU: forward1 on a few tokens (two launches, up to 256 rows and r <= 128) around the edges of its tiles, row groups and K
+slices: integer-valued layers bit for bit against Eq. 1, Gaussian ones against the fp64 oracle, T = XA kept or not."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import TOL, elem_excess, relerr, to_device, to_f64, torch_dtype
+from paper_2312_03415_amd import binding as rl
+from paper_2312_03415_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def forward(dev, n, i, o, r, dtype, scale, bias, keep):
+    import torch
+    td = torch_dtype(dtype)
+    buf = torch.full((n + 2, o + 16), 7.0, dtype=td, device="cuda")
+    Y = buf[1:n + 1, 8:o + 8]
+    T = torch.full((n, r), float("nan"), dtype=td, device="cuda") if keep else None
+    ws = rl.new_workspace(1, -1, n, i, o, r, rl.dtype_from_name(dtype))
+    saved = rl.new_saved(T)
+    rl.runlora_profile_enable(8)
+    rl.runlora_forward(1, dev["X"], dev["W"], dev["A"], dev["B"], Y, saved, workspace=ws, scale=scale, bias=bias)
+    torch.cuda.synchronize()
+    steps = rl.runlora_profile_collect(8)
+    rl.runlora_profile_disable()
+    edge = to_f64(buf)
+    edge[1:n + 1, 8:o + 8] = 7.0
+    assert np.array_equal(edge, np.full_like(edge, 7.0)), "wrote outside Y"
+    return to_f64(Y), T, [s["what"] for s in steps]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r,few", [(1, 512, 136, 8, True), (2, 520, 128, 16, True), (3, 1096, 264, 24, True), (16, 2048, 72, 128, True),
+                                         (17, 840, 520, 40, True), (64, 1032, 136, 32, True), (255, 648, 392, 8, True), (256, 1000, 120, 16, True),
+                                         (65, 512, 264, 136, False),   # rank beyond the finishing kernel's
+                                         (257, 1000, 120, 16, False),  # one row too many
+                                         (16, 512, 72, 128, False)])   # partials of X A larger than the call's scratch
+def test_few_tokens_exact_on_integers(n, i, o, r, few, dtype):
+    rng = np.random.default_rng(n)
+    draw = lambda shape, p: ((rng.random(shape) < p) * rng.choice([-1.0, 1.0], size=shape))
+    h = {"X": draw((n, i), 0.3), "W": draw((i, o), 0.2), "A": draw((i, r), 0.02), "B": draw((r, o), 0.3), "bias": draw((o,), 0.5)}
+    T = h["X"] @ h["A"]
+    want = h["X"] @ h["W"] + 2.0 * T @ h["B"] + h["bias"]
+    assert np.abs(want).max() <= 256 and np.abs(2 * T).max() <= 256   # integers bf16 holds
+    dev = {k: to_device(synth.store(v, dtype), dtype) for k, v in h.items()}
+    for keep in (False, True):
+        got, kept, what = forward(dev, n, i, o, r, dtype, 2.0, dev["bias"], keep)
+        assert (len(what) == 1) == few, what
+        assert np.array_equal(got, want), (n, i, o, r, keep)
+        if keep:
+            assert np.array_equal(to_f64(kept), 2.0 * T)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r", [(1, 4096, 4096, 16), (48, 4096, 1376, 32), (200, 2048, 2056, 64)])
+def test_few_tokens_against_the_oracle(n, i, o, r, dtype):
+    L = synth.Layer("few", n, i, o, r, dtype, 3)
+    st = synth.layer_inputs(L)
+    dev = {k: to_device(v, dtype) for k, v in st.items()}
+    host = {k: synth.widen(v, dtype) for k, v in st.items()}
+    got, _, what = forward(dev, n, i, o, r, dtype, 0.5, None, False)
+    assert len(what) == 1
+    want = oracle.scaled_forward(host["X"], host["W"], host["A"], host["B"], 0.5)
+    assert relerr(got, want) < TOL[dtype] and elem_excess(got, want, dtype) <= 1.0
