@@ -163,7 +163,8 @@ void describe_step(const Step& s, rl_step_time_t* r) {
     }
     r->M = s.sk[0].M; r->N = s.sk[0].N; r->K = s.sk[0].K;
     r->tile_cfg = CFG_STREAM + (s.skplan.rt == 1 ? 0 : (s.skplan.rt == 2 ? 1 : 2));
-    r->splits = s.skplan.splits;
+    if (s.is_mtpair) r->tile_cfg = s.mtpair.cfg[0];
+    r->splits = s.is_mtpair ? s.mtpair.splits[0] : s.skplan.splits;
     r->a_strided = s.sk[0].a_strided; r->b_kcontig = s.sk[0].b_kcontig;
     return;
   }
@@ -216,6 +217,7 @@ int run_schedule(const Schedule& sch, char* ws, hipStream_t stream) {
     }
     hipError_t e = s.is_few ? few_run(s.d.dtype, s.few, s.few_plan, partial, stream)
                    : s.is_merge ? merge_run(s.d.dtype, s.mg, stream)
+                   : s.is_mtpair ? mt_pair_run(s.d.dtype, s.sk, s.mtpair, partial, stream)
                    : s.nsk > 0 ? skinny_run(s.d.dtype, s.nsk, s.sk, s.skplan, partial, stream)
                                : gemm_run(s.d, s.plan, partial, stream);
     const int kbound = (timed && g_prof.kernel_events) ? g_kernel_events.used : 0;  // pairs the step's launches consumed

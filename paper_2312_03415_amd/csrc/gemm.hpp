@@ -43,6 +43,7 @@ struct GemmDesc {
   int64_t ldla = 0;
   float t_alpha = 1.f;
   bool fuse_t = false;
+  int rotate = 0;  // see GemmArgs::rotate (middle-sized kernel only)
 };
 constexpr int64_t kFuseMaxR = 32;
 
@@ -142,6 +143,20 @@ struct SkinnyPlan {
 };
 inline bool skinny_ok(int64_t N) { return N <= 128; }
 SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d);
+// modelled time of that launch (and its reduce pass) in us
+double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan);
+
+// ---- rank-r products with r > 32 on the middle-sized matrix-core kernel, 16-bit types, no mask ------------------
+// One product (gemm_run with the plan) or two in one launch (mt_pair_run); `cap` = scratch bytes the plan may use.  False
+// where the streaming kernel is modelled faster.
+bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan);
+GemmDesc rank_desc(int dtype, const SkinnyDesc& d);  // the product as gemm_run takes it
+struct MtPairPlan {
+  int cfg[2] = {0, 0}, splits[2] = {1, 1}, tiles_per_split[2] = {0, 0};
+  double us = 0;
+};
+bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan);
+hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, float* scratch, hipStream_t stream);
 hipError_t skinny_run(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan, float* scratch,
                       hipStream_t stream);
 struct SkinnyArgs;
@@ -207,6 +222,11 @@ hipError_t merge_launch_f16(const MergeArgs& a, hipStream_t s);
 // per-dtype launchers (one translation unit each)
 struct GemmArgs;
 struct FinishArgs;
+struct SkinnyArgs;
+hipError_t mt_pair_launch_bf16(int al, int bl0, int bl1, const GemmArgs& g0, const GemmArgs& g1, unsigned grid, hipStream_t s);
+hipError_t mt_pair_launch_f16(int al, int bl0, int bl1, const GemmArgs& g0, const GemmArgs& g1, unsigned grid, hipStream_t s);
+hipError_t skinny_reduce_launch_bf16(const SkinnyArgs& a, int splits0, int splits1, hipStream_t s);
+hipError_t skinny_reduce_launch_f16(const SkinnyArgs& a, int splits0, int splits1, hipStream_t s);
 hipError_t finish_launch_bf16(const FinishArgs& a, hipStream_t s);
 hipError_t finish_launch_f16(const FinishArgs& a, hipStream_t s);
 hipError_t gemm_launch_bf16(int cfg, int al, int bl, const GemmArgs& a, dim3 grid, hipStream_t s);

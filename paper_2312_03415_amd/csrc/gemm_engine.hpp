@@ -66,6 +66,8 @@ struct GemmArgs {
   float t_alpha;
   // gemm_mt.hpp's build with LA: T's fp32 partials, [splits][M][R], next to `partial` (which that build requires)
   float* partial_t;
+  // gemm_mt.hpp: != 0: workgroups of tile row t start `rotate * t` K tiles into their range and wrap around
+  int rotate;
 };
 
 // ---- per-type pieces --------------------------------------------------------------------------

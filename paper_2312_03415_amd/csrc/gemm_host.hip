@@ -330,6 +330,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   a.drop_thr = d.drop_thr;
   a.drop_key = d.drop_key;
   a.drop_cpr = d.drop_cpr;
+  a.rotate = d.rotate;
   a.LA = d.fuse_t ? d.LA : nullptr;
   a.ldla = d.ldla;
   a.R = d.fuse_t ? (int)d.K[1] : 0;
@@ -463,6 +464,178 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d) {
   p.splits = (int)splits;
   p.partial_bytes = splits > 1 ? (size_t)splits * (size_t)outs * sizeof(float) : 0;
   return p;
+}
+
+double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan) {
+  // Rates in TB/s of algorithmic bytes, measured (bf16): up to 32 columns the big operand streams; with 64 and 128 the
+  // waves' re-reads of the short operand bind (paired launches at 8192 x (4096 + 11008) r 128: 118 us; at 4096 x (5120 +
+  // 13824) r 64: 58 us), single launches fill less of the chip.
+  const double e = dtype == DT_F32 ? 4.0 : 2.0;
+  double bytes = 0, outs = 0;
+  for (int w = 0; w < nprob; ++w) {
+    bytes += e * ((double)d[w].M * d[w].K + (double)d[w].K * d[w].N + (double)d[w].M * d[w].N);
+    outs += (double)d[w].M * d[w].N;
+  }
+  double rate = plan.rt == 1 ? (d[0].a_strided ? 4.4 : 4.8) : (plan.rt == 2 ? 2.8 : 2.1);
+  if (nprob == 1) rate *= plan.rt == 1 ? 0.65 : 0.8;
+  return (plan.rt == 1 || nprob == 1 ? 5.0 : 9.0) + bytes / (rate * 1e6) + (plan.splits > 1 ? 3.0 + outs * 8.0 * plan.splits / 7.5e6 : 0.0);
+}
+
+// ---- rank-r products with r > 32 on the middle-sized kernel ------------------------------------------------------
+
+// a streaming-kernel problem as the tile GEMM sees it: C^T = op(B)^T op(A) is turned back into C
+GemmDesc rank_desc(int dtype, const SkinnyDesc& d) {
+  GemmDesc g;
+  g.dtype = dtype;
+  g.alpha = d.alpha;
+  g.C = d.C;
+  g.ldc = d.ldc;
+  g.K[0] = d.K;
+  const bool t = d.trans_out != 0;  // both operands stored [K, .]
+  g.a_strided = d.a_strided;
+  g.b_kcontig = t ? 0 : d.b_kcontig;
+  g.A[0] = t ? d.B : d.A; g.lda[0] = t ? d.ldb : d.lda;
+  g.B[0] = t ? d.A : d.B; g.ldb[0] = t ? d.lda : d.ldb;
+  g.M = t ? d.N : d.M;
+  g.N = t ? d.M : d.N;
+  g.rotate = g.a_strided ? 0 : 5;
+  return g;
+}
+
+// One launch of narrow tiles over operands that come from HBM: 0.53 us per K tile and workgroup (0.45 where a tile's rows
+// are whole lines of a [K, .] operand), twice that where two share a compute unit (see gemm_mt_pair_kernel); never below
+// the operands' bytes at 4.8 TB/s.  Operands that the caches still hold (the activations of a short batch) arrive twice as
+// fast: dA, dB of 1024 x 4096 r 64 take 9.7 us here, 17.5 on the streaming kernel.
+static double rank_time_us(bool a_strided, int64_t wgs, int64_t ktiles, double bytes) {
+  const int64_t rounds = wgs / 512, rest = wgs % 512;
+  const double tk = bytes < 64e6 ? 0.28 : (a_strided ? 0.45 : 0.53);
+  const double us = (bytes < 64e6 ? 5.0 : 7.5) + (double)ktiles * tk * (double)(2 * rounds + (rest > 256 ? 2 : (rest > 0 ? 1 : 0)));
+  const double floor_us = 5.0 + bytes / 4.8e6;
+  return us > floor_us ? us : floor_us;
+}
+
+static bool rank_shape_ok(int dtype, const SkinnyDesc& d) {
+  return dtype != DT_F32 && d.N > 32 && d.M > 32 && d.drop_thr == 0;
+}
+
+bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan) {
+  if (!rank_shape_ok(dtype, d)) return false;
+  const GemmDesc g = rank_desc(dtype, d);
+  const int cfg = g.N == d.N ? CFG_MTN64 : CFG_MTM64;
+  const int64_t nbm = (g.M + kTileBM[cfg] - 1) / kTileBM[cfg], nbn = (g.N + kTileBN[cfg] - 1) / kTileBN[cfg];
+  const int64_t kt = (g.K[0] + 63) / 64;
+  const double bytes = 2.0 * ((double)g.M * g.K[0] + (double)g.K[0] * g.N + (double)g.M * g.N);
+  double best = skinny_time_us(dtype, 1, &d, skinny_plan(dtype, 1, &d));
+  bool found = false;
+  for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+    const int64_t per = (kt + s - 1) / s;
+    if ((kt + per - 1) / per != s) continue;  // no empty slice
+    const size_t part = s > 1 ? (size_t)s * (size_t)g.M * (size_t)g.N * sizeof(float) : 0;
+    if (part > cap) break;
+    const double us = rank_time_us(g.a_strided != 0, nbm * nbn * s, per, bytes) + split_time_us(g.M, g.N, s);
+    if (us >= best) continue;
+    best = us;
+    found = true;
+    *plan = GemmPlan{};
+    plan->cfg = cfg;
+    plan->bk = 64;
+    plan->bm = kTileBM[cfg];
+    plan->bn = kTileBN[cfg];
+    plan->nbm = (int)nbm;
+    plan->nbn = (int)nbn;
+    plan->splits = s;
+    plan->tiles_per_split = (int)per;
+    plan->partial_bytes = part;
+  }
+  return found;
+}
+
+bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan) {
+  if (!rank_shape_ok(dtype, d[0]) || !rank_shape_ok(dtype, d[1])) return false;
+  int64_t tiles[2], kt[2];
+  double bytes = 0, best = 1e30;
+  for (int w = 0; w < 2; ++w) {
+    const GemmDesc g = rank_desc(dtype, d[w]);
+    plan->cfg[w] = g.N == d[w].N ? CFG_MTN64 : CFG_MTM64;
+    tiles[w] = ((g.M + kTileBM[plan->cfg[w]] - 1) / kTileBM[plan->cfg[w]]) * ((g.N + kTileBN[plan->cfg[w]] - 1) / kTileBN[plan->cfg[w]]);
+    kt[w] = (g.K[0] + 63) / 64;
+    bytes += 2.0 * ((double)g.M * g.K[0] + (double)g.K[0] * g.N + (double)g.M * g.N);
+  }
+  // the launches the kernel is built for (gemm_launch.inc)
+  const bool z = !d[0].a_strided && !d[1].a_strided && d[0].b_kcontig && !d[1].b_kcontig && !d[0].trans_out && !d[1].trans_out;
+  const bool g = d[0].a_strided && d[1].a_strided && plan->cfg[0] == CFG_MTN64 && plan->cfg[1] == CFG_MTM64;
+  if (!z && !g) return false;
+  const int64_t longest = kt[0] > kt[1] ? kt[0] : kt[1];
+  for (int s = 1; s <= 16 && (s == 1 || longest / s >= 4); ++s) {
+    const int64_t per = (longest + s - 1) / s;
+    int64_t sp[2], tps[2];
+    size_t part = 0;
+    double us = 0;
+    int64_t wgs = 0;
+    for (int w = 0; w < 2; ++w) {
+      sp[w] = (kt[w] + per - 1) / per;
+      tps[w] = (kt[w] + sp[w] - 1) / sp[w];
+      sp[w] = (kt[w] + tps[w] - 1) / tps[w];
+      wgs += tiles[w] * sp[w];
+      if (sp[w] > 1) {
+        part += (size_t)sp[w] * (size_t)d[w].M * (size_t)d[w].N * sizeof(float);
+        us += (double)d[w].M * (double)d[w].N * (8.0 * sp[w] + 2.0) / 7.5e6;
+      }
+    }
+    if (part > cap) break;
+    us += rank_time_us(d[0].a_strided != 0, wgs, per, bytes) + (part > 0 ? 3.0 : 0.0);
+    if (us < best) {
+      best = us;
+      for (int w = 0; w < 2; ++w) { plan->splits[w] = (int)sp[w]; plan->tiles_per_split[w] = (int)tps[w]; }
+    }
+  }
+  plan->us = best;
+  return best < skinny_time_us(dtype, 2, d, skinny_plan(dtype, 2, d));
+}
+
+hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, float* scratch, hipStream_t stream) {
+  if (dtype == DT_F32) return hipErrorInvalidValue;
+  GemmArgs a[2] = {};
+  SkinnyArgs r{};
+  r.nprob = 2;
+  r.mr = 1;
+  float* part = scratch;
+  unsigned grid = 0;
+  int al = 0, bl[2] = {0, 0};
+  for (int w = 0; w < 2; ++w) {
+    const GemmDesc g = rank_desc(dtype, d[w]);
+    const int64_t a_rows = g.a_strided ? g.K[0] : g.M, b_rows = g.b_kcontig ? g.N : g.K[0];
+    if (a_rows * g.lda[0] >= (1LL << 30) || b_rows * g.ldb[0] >= (1LL << 30)) return hipErrorInvalidValue;  // callers check sk_ok
+    a[w].A[0] = g.A[0]; a[w].B[0] = g.B[0];
+    a[w].lda[0] = g.lda[0]; a[w].ldb[0] = g.ldb[0];
+    a[w].K[0] = (int)g.K[0];
+    a[w].M = (int)g.M; a[w].N = (int)g.N;
+    a[w].C = g.C; a[w].ldc = g.ldc;
+    a[w].alpha = g.alpha;
+    a[w].rotate = g.a_strided ? 0 : 5;
+    a[w].splits = plan.splits[w];
+    a[w].tiles_per_split = plan.tiles_per_split[w];
+    a[w].nbm = (int)((g.M + kTileBM[plan.cfg[w]] - 1) / kTileBM[plan.cfg[w]]);
+    a[w].nbn = (int)((g.N + kTileBN[plan.cfg[w]] - 1) / kTileBN[plan.cfg[w]]);
+    al = g.a_strided;
+    bl[w] = g.b_kcontig;
+    grid += (unsigned)(a[w].nbm * a[w].nbn * a[w].splits);
+    SkinnyProblem& P = r.p[w];  // the reduce pass: [slices][M][N] -> C, scaled
+    P.C = g.C; P.ldc = g.ldc;
+    P.M = (int)g.M; P.N = (int)g.N;
+    P.alpha = g.alpha;
+    if (plan.splits[w] > 1) {
+      if (scratch == nullptr) return hipErrorInvalidValue;
+      a[w].partial = part;
+      P.partial = part;
+      part += (size_t)plan.splits[w] * (size_t)g.M * (size_t)g.N;
+    }
+  }
+  hipError_t e = dtype == DT_BF16 ? mt_pair_launch_bf16(al, bl[0], bl[1], a[0], a[1], grid, stream)
+                                  : mt_pair_launch_f16(al, bl[0], bl[1], a[0], a[1], grid, stream);
+  if (e != hipSuccess || (plan.splits[0] <= 1 && plan.splits[1] <= 1)) return e;
+  return dtype == DT_BF16 ? skinny_reduce_launch_bf16(r, plan.splits[0], plan.splits[1], stream)
+                          : skinny_reduce_launch_f16(r, plan.splits[0], plan.splits[1], stream);
 }
 
 hipError_t skinny_run(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan, float* scratch,

@@ -93,7 +93,7 @@ template <> struct MtFrag<true> {
 };
 
 template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA>
-__device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
+__device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, const int by) {
   static_assert(!XA || (AL == 0 && BL == 0), "X [M,K], W and A [K,.]");
   using P = MtTile<AL, BL, BM, BN, NS>;
   constexpr int BK = P::BK, TM = P::TM, TN = P::TN;
@@ -110,7 +110,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
   {
     const int nbn = XA ? g.nbn + (g.R + BN - 1) / BN : g.nbn;
     const int total = g.nbm * nbn;
-    const int x = blockIdx.x & 7, slot = blockIdx.x >> 3, q = total >> 3, rem = total & 7;
+    const int x = bx & 7, slot = bx >> 3, q = total >> 3, rem = total & 7;
     const int id = x * q + (x < rem ? x : rem) + slot;
     constexpr int BAND = 8;
     const int per_band = BAND * nbn;
@@ -128,10 +128,10 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
   const int N = XA && t_tile ? g.R : g.N;
   const void* const B0 = XA && t_tile ? g.LA : g.B[0];
   const int64_t ldb0 = XA && t_tile ? g.ldla : g.ldb[0];
-  // ---- this workgroup's K tiles (over both segments; blockIdx.y slices them)
+  // ---- this workgroup's K tiles (over both segments; `by` slices them)
   const int K0 = g.K[0], K1 = g.K[1];
   const int nt0 = (K0 + BK - 1) / BK, nt1 = (K1 + BK - 1) / BK;
-  const int u0 = blockIdx.y * g.tiles_per_split;
+  const int u0 = by * g.tiles_per_split;
   int u1 = u0 + g.tiles_per_split;
   if (u1 > nt0 + nt1) u1 = nt0 + nt1;
 
@@ -148,9 +148,13 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
   };
   __amdgpu_buffer_rsrc_t rsA = make_rsrc(g.A[0], 0), rsB = rsA;
   uint32_t offA[P::IA], offB[P::IB], stepA = 0, stepB = 0;
-  int cu = u0, cnext = u0;  // next tile to load; tile at which the state below must be rebuilt
+  // next tile to load, tiles still to load, tile at which the state below must be rebuilt.  The walk may start inside the
+  // range and wrap around (GemmArgs::rotate): row blocks of a rank-r product that all read the same columns of a
+  // power-of-two wide matrix at once crowd a few memory channels.
+  int left = u1 - u0, cu = u0, cnext = u0;
+  if (g.rotate != 0 && left > 0) cu += (int)((uint32_t)(m0 / BM * g.rotate) % (uint32_t)left);
   auto cursor_setup = [&]() {
-    if (cu >= u1) {  // beyond the last tile: loads of nothing
+    if (left <= 0) {  // beyond the last tile: loads of nothing
       stepA = stepB = 0;
 #pragma unroll
       for (int j = 0; j < P::IA; ++j) offA[j] = OOB;
@@ -195,10 +199,13 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
       if (seg_end < cnext) cnext = seg_end;
       if (Ks % BK != 0 && seg_end - 1 < cnext) cnext = seg_end - 1;
     }
+    if (cu + left < cnext) cnext = cu + left;
   };
   auto cursor_advance = [&]() {
     ++cu;
+    --left;
     if (__builtin_expect(cu == cnext, 0)) {
+      if (cu == u1) cu = u0;
       cursor_setup();
     } else {
 #pragma unroll
@@ -386,7 +393,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
       f32x4 v1 = *reinterpret_cast<const f32x4*>(stg + r * LD + pcol + 4);
       if (m < g.M && n_ok) {
         if (split) {
-          float* dst = part + ((int64_t)blockIdx.y * g.M + m) * N + n;
+          float* dst = part + ((int64_t)by * g.M + m) * N + n;
           *reinterpret_cast<f32x4*>(dst) = v0;
           *reinterpret_cast<f32x4*>(dst + 4) = v1;
         } else {
@@ -419,7 +426,27 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g) {
 
 template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA = false>
 __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_kernel(GemmArgs g) {
-  gemm_mt_body<T, AL, BL, BM, BN, NS, XA>(g);
+  gemm_mt_body<T, AL, BL, BM, BN, NS, XA>(g, (int)blockIdx.x, (int)blockIdx.y);
+}
+
+// Two products in one launch (Z1 = dY B^T with Z2 = X A, dA = X^T Z1 with dB = Z2^T dY; r > 32): each fills a part of the
+// chip only, so they run side by side.  Workgroups [0, tiles0 splits0) belong to the first.  Tiles of 128x64 for a
+// product with r columns, 64x128 for one with r rows.  Bound by what a compute unit fetches from HBM: ~45 bytes a ns
+// however many stages are in flight (three and six measure the same), so that a K tile's 24 KB take 0.53 us.  The streaming
+// kernel (skinny.hpp), whose waves re-read the short operand for every 32 rows, against this one: dA, dB of 8192 x (4096 +
+// 11008) r 128 129 / 61 us, Z1, Z2 120 / 97; dA, dB of 4096 x (5120 + 13824) r 64 59 / 29, of 1024 x 4096 r 64 17.5 / 9.7.
+template <typename T, int AL, int BL0, int BL1, int BM0, int BN0, int BM1, int BN1>
+__global__ __launch_bounds__(256, 2) void gemm_mt_pair_kernel(GemmArgs g0, GemmArgs g1) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass has no use for the body and instantiates it twice over (gemm_mt_kernel's)
+  const int tiles0 = g0.nbm * g0.nbn, c0 = tiles0 * g0.splits;
+  const int id = (int)blockIdx.x;
+  if (id < c0) {
+    gemm_mt_body<T, AL, BL0, BM0, BN0, 3, false>(g0, id % tiles0, id / tiles0);
+  } else {
+    const int tiles1 = g1.nbm * g1.nbn, j = id - c0;
+    gemm_mt_body<T, AL, BL1, BM1, BN1, 3, false>(g1, j % tiles1, j / tiles1);
+  }
+#endif
 }
 
 }  // namespace rl

@@ -12,6 +12,7 @@ struct Builder {
   size_t used = 0;
   size_t max_partial = 0;
   Schedule* out;
+  size_t later_partial = 0;  // scratch for partials that a step still to come provides for
   bool failed = false;  // a step this build cannot run (masking X inside the tile GEMM)
 
   Builder(const LayerDims& l, void* ws, Schedule* o) : L(l), base(static_cast<char*>(ws)), out(o) {}
@@ -19,6 +20,15 @@ struct Builder {
   // the LoRA scale as the kernels apply it: under dropout the kept inputs are scaled by 1 / (1 - p)
   float scale() const { return L.drop_thr ? L.scale * 256.f / (256.f - (float)L.drop_thr) : L.scale; }
   uint32_t drop_cpr() const { return (uint32_t)(L.i / 4); }
+
+  // Scratch for partials that the call has anyway: a rank-r product may split its contraction into it, but never makes the
+  // workspace larger.
+  size_t spare() const { return later_partial > max_partial ? later_partial : max_partial; }
+  // the product [M, K0 + K1] x [K0 + K1, N] comes after the rank-r products and brings its own scratch
+  void expect_gemm(int64_t M, int64_t N, int64_t K0, int64_t K1, bool b_is_w) {
+    const GemmPlan p = b_is_w && L.w_int4 ? gemm_plan_int4(L.dtype, M, N, K0, K1) : gemm_plan(L.dtype, M, N, K0, K1);
+    if (p.partial_bytes > later_partial) later_partial = p.partial_bytes;
+  }
 
   // dense [rows, cols] scratch matrix in the layer dtype
   Mat scratch(int64_t rows, int64_t cols) {
@@ -174,6 +184,12 @@ struct Builder {
     s.sk[0] = to_skinny(g);
     s.skplan = skinny_plan(L.dtype, 1, s.sk);
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
+    GemmPlan mp;
+    if (rank_plan(L.dtype, s.sk[0], spare(), &mp)) {  // r > 32
+      s.nsk = 0;
+      s.d = rank_desc(L.dtype, s.sk[0]);
+      s.plan = mp;
+    }
     out->steps.push_back(s);
   }
   // forward1 for a few tokens in two launches; false where it does not apply.  The scratch is what forward1's launches
@@ -229,6 +245,7 @@ struct Builder {
     s.sk[1] = d2;
     s.skplan = skinny_plan(L.dtype, 2, s.sk);
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
+    s.is_mtpair = mt_pair_plan(L.dtype, s.sk, spare(), &s.mtpair);  // r > 32
     out->steps.push_back(s);
   }
 
@@ -283,6 +300,7 @@ bool build_forward(int variant, const LayerDims& L, const FwdOperands& op, void*
     case 1: {  // forward1: (XW) + ((XA)B), the sum folded into one contraction over [X|T]
       Mat T = op.keep_T ? op.T : b.scratch(n, r);
       if (b.few_forward("Y = X [W|A] ; Y += T B", op.X, op.W, op.A, op.B, op.Y, T, op.keep_T, op.bias)) break;
+      if (r > 32) b.expect_gemm(n, o, i, r, true);
       b.skinny("T = X A", {0, 0, n, r, i, op.X, op.A, T, true, true});
       b.gemm("Y = [X|T] [W;B]", 0, 0, n, o, i, op.X, op.W, op.Y, nullptr, r, &T, &op.B, true, 1.f, op.bias);
       break;
@@ -324,6 +342,7 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
     }
     case 1: {  // Algorithm 1
       Mat Z1 = b.scratch(n, r), Z2 = op.have_T ? op.T : b.scratch(n, r);
+      if (dX && !L.drop_thr && r > 32) b.expect_gemm(n, i, o, r, true);
       rank_r_pass(b, op, n, i, o, r, Z1, Z2, dA || dX, dB && !op.have_T, dA, dB);
       if (dX && L.drop_thr) {  // the mask sits between the two products: no concatenated contraction
         b.gemm("dX = dY W^T", 0, 1, n, i, o, op.dY, op.W, op.dX, nullptr, 0, nullptr, nullptr, true);
@@ -366,6 +385,7 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
       if (L.w_int4) return false;
       Mat Z1 = b.scratch(n, r), Z2 = op.have_T ? op.T : b.scratch(n, r), Z3 = op.have_M ? op.M : b.scratch(i, o);
       if (dX && !op.have_M) b.merge("Z3 = W + A B", op.A, op.B, op.W, Z3);
+      if (dX && r > 32) b.expect_gemm(n, i, o, 0, false);
       rank_r_pass(b, op, n, i, o, r, Z1, Z2, dA, dB && !op.have_T, dA, dB);
       if (dX) b.gemm("dX = dY Z3^T", 0, 1, n, i, o, op.dY, Z3, op.dX);
       break;

@@ -48,6 +48,8 @@ struct Step {
   GemmPlan plan;
   SkinnyDesc sk[2];
   SkinnyPlan skplan;
+  bool is_mtpair = false;  // nsk = 2: the two problems run on the middle-sized matrix-core kernel instead (r > 32)
+  MtPairPlan mtpair;
   const char* what = "";  // the product(s) in the paper's notation, e.g. "Z1 = dY B^T"
 };
 

@@ -104,6 +104,8 @@ static double step_time_us(const Step& s) {
   if (s.is_few) return s.few_plan.us;
   if (s.is_merge)
     return e * 2.0 * (double)s.mg.I * (double)s.mg.O / (mc.merge_tbps * 1e12) * 1e6 + mc.merge_fix_us;
+  if (s.is_mtpair) return s.mtpair.us;
+  if (s.nsk > 0 && s.d.dtype != DT_F32 && s.skplan.rt > 1) return skinny_time_us(s.d.dtype, s.nsk, s.sk, s.skplan);
   if (s.nsk > 0) {
     double us = mc.stream_fix_us;  // the measured intercepts already hold the cost of the launch itself
     double outs = 0;

@@ -304,9 +304,11 @@ __global__ __launch_bounds__(NWV * 64) void skinny_kernel(SkinnyArgs g) {
 // Second stage for a K split over workgroups: C = sum over slices (in slice order) of the fp32
 // partials, rounded once; both problems of a paired launch in one go.
 template <typename T>
-__global__ __launch_bounds__(256) void skinny_reduce_kernel(SkinnyArgs g, int splits) {
+__global__ __launch_bounds__(256) void skinny_reduce_kernel(SkinnyArgs g, int splits0, int splits1) {
   for (int w = 0; w < g.nprob; ++w) {
     const SkinnyProblem& P = g.p[w];
+    const int splits = w == 0 ? splits0 : splits1;
+    if (splits <= 1) continue;  // written whole
     const int64_t total = (int64_t)P.M * P.N;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
       // walk the output in its storage order so that stores coalesce
