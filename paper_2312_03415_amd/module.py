@@ -4,13 +4,16 @@ helper that swaps it in for the nn.Linear modules of a model (Section 3 applies 
 attention and MLP linear).
 
 Nothing is computed here: tensors are flattened to [n, d] views, buffers are allocated with torch,
-and every product runs inside the HIP library through binding.runlora_forward / runlora_backward.
+and every product runs inside the HIP library through binding.runlora_forward / runlora_backward.  The LoRA
+layer's node exists twice: in native code (csrc/autograd.cpp), which ordinary calls take, and in Python below,
+for the calls that have to see a Python-level function (tracing, functorch transforms, tensor subclasses, modes).
 
     layer = RunLoRALinear.from_linear(nn_linear, r=16, alpha=32)     # W frozen, A and B trainable
     y = layer(x)                                                     # x [..., d_in] -> [..., d_out]
     wrap_linears(model, r=16, alpha=32, targets=("q_proj", "v_proj"))
     vera = RunVeRALinear(weight, A_shared, B_shared)                 # frozen A, B; trainable vectors d, b
 """
+import ctypes
 import math
 
 import torch
@@ -31,6 +34,21 @@ def _workspace(device, nbytes):
     return ws
 
 
+_native_module = None
+
+
+def _native():
+    """The native autograd node (built with the library, no fallback if it is missing), with the library's entry points."""
+    global _native_module
+    if _native_module is None:
+        lib = rl.lib()
+        from . import _autograd
+        address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+        _autograd.init(address(lib.runlora_forward), address(lib.runlora_backward), address(lib.runlora_workspace_bytes), rl._check)
+        _native_module = _autograd
+    return _native_module
+
+
 class RunLoRAFunction(torch.autograd.Function):
     """y = x W + bias + scale (x A) B with W and bias frozen; gradients for x, A and B (Eq. 1, Eq. 3).
 
@@ -40,6 +58,14 @@ class RunLoRAFunction(torch.autograd.Function):
     dropout = (p, seed) or None: LoRA dropout on the adapter's input (mask defined in runlora.h; the
     backward regenerates it from the seed the forward recorded).
     """
+
+    @classmethod
+    def apply(cls, *args):
+        if cls is RunLoRAFunction:
+            y = _native().lora(*args)
+            if y is not None:
+                return y
+        return super().apply(*args)
 
     @staticmethod
     def forward(ctx, x, W, A, B, bias, scale, pair, keep_merged, dropout=None, keep_t=False):
