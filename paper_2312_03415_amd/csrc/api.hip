@@ -179,7 +179,8 @@ void describe_step(const Step& s, rl_step_time_t* r) {
   r->flops = 2.0 * (double)d.M * (double)d.N * K;
   r->bytes = e * ((double)d.M * K + K * (double)d.N + (double)d.M * (double)d.N * (d.D ? 2.0 : 1.0));
   r->M = d.M; r->N = d.N; r->K = (int64_t)K;
-  r->tile_cfg = s.plan.cfg; r->splits = s.plan.splits;
+  const GemmPlan& plan = s.is_panel ? s.panel.full : s.plan;
+  r->tile_cfg = plan.cfg; r->splits = plan.splits;
   r->a_strided = d.a_strided; r->b_kcontig = d.b_kcontig;
 }
 
@@ -216,6 +217,7 @@ int run_schedule(const Schedule& sch, char* ws, hipStream_t stream) {
       }
     }
     hipError_t e = s.is_few ? few_run(s.d.dtype, s.few, s.few_plan, partial, stream)
+                   : s.is_panel ? int4_panel_gemm(s.d, s.panel, partial, stream)
                    : s.is_merge ? merge_run(s.d.dtype, s.mg, stream)
                    : s.is_mtpair ? mt_pair_run(s.d.dtype, s.sk, s.mtpair, partial, stream)
                    : s.nsk > 0 ? skinny_run(s.d.dtype, s.nsk, s.sk, s.skplan, partial, stream)
@@ -350,6 +352,10 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
   if (use_static) {
     // size the schedule first (no HIP call yet), then lay it out in the fixed array
     if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
+    if (w_int4 && sch.workspace_bytes > kStaticScratchBytes) {  // without panels of W the call may fit
+      L.int4_panels = false;
+      if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
+    }
     if (sch.workspace_bytes > kStaticScratchBytes) {
       std::snprintf(g_hip_error, sizeof(g_hip_error), "runlora_forward_static: this call needs %zu bytes of scratch, the fixed array holds %zu",
                     sch.workspace_bytes, kStaticScratchBytes);
@@ -364,6 +370,10 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
     if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
   } else {
     if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+    if (w_int4 && check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough for the direct route?
+      L.int4_panels = false;
+      if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+    }
     if ((rc = check_workspace(sch, opts)) != RL_OK) return rc;
   }
 
@@ -481,6 +491,10 @@ extern "C" int runlora_backward(int variant, const rl_tensor_t* dY, const rl_sav
   Schedule sch;
   char* ws = opts ? static_cast<char*>(opts->workspace) : nullptr;
   if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+  if (w_int4 && check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough for the direct route?
+    L.int4_panels = false;
+    if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+  }
   if ((rc = check_workspace(sch, opts)) != RL_OK) return rc;
   hipStream_t stream = opts ? static_cast<hipStream_t>(opts->stream) : nullptr;
   return run_schedule(sch, ws, stream);

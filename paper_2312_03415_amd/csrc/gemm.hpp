@@ -102,6 +102,22 @@ GemmPlan gemm_tail_plan(const GemmPlan& main, int dtype, int64_t M, int64_t N, i
 // engine's 128x128 tile.
 GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1);
 
+// A product whose B[0] is int4, with W's columns (rows, for dY W^T) dequantised panel by panel into scratch and multiplied
+// by the dense kernels: a panel is at most kInt4PanelBytes, W as a whole is never written out.  Applies where the model says
+// it beats the kernels that dequantise on their way to LDS (int4_panel.hip).
+constexpr size_t kInt4PanelBytes = 64u << 20;
+struct Int4PanelPlan {
+  int64_t width = 0;        // output columns per panel; 0 = the route does not apply
+  GemmPlan full, last;      // products of a full panel and of the last one
+  size_t panel_bytes = 0;   // scratch of a panel; the products' partials come behind it
+  size_t scratch_bytes = 0;
+  double us = 0;
+};
+Int4PanelPlan int4_panel_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1);
+hipError_t int4_panel_gemm(const GemmDesc& d, const Int4PanelPlan& plan, void* scratch, hipStream_t stream);
+hipError_t int4_panel_run(int dtype, const void* W, int64_t ldw, const void* scales, int64_t lds, void* out, int64_t ldo, int64_t r0,
+                          int64_t rows, int64_t c0, int64_t cols, hipStream_t stream);
+
 // Enqueue the product.  `scratch` must hold plan.partial_bytes when plan.splits > 1.
 hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hipStream_t stream);
 
@@ -170,8 +186,8 @@ hipError_t skinny_launch_f32(int rt, const SkinnyArgs& a, dim3 grid, int splits,
 // launched with the next unused pair bound to its own dispatch, so that the pair's difference is that kernel's
 // duration alone, as a kernel trace reports it.  Pair 0 is the step's first (main) kernel.
 struct KernelEvents {
-  static constexpr int kMax = 4;
-  hipEvent_t start[kMax] = {nullptr, nullptr, nullptr, nullptr}, stop[kMax] = {nullptr, nullptr, nullptr, nullptr};
+  static constexpr int kMax = 16;
+  hipEvent_t start[kMax] = {}, stop[kMax] = {};
   int avail = 0, used = 0;
 };
 extern thread_local KernelEvents g_kernel_events;

@@ -224,6 +224,83 @@ GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1)
   return gemm_plan(dtype, M, N, K0, K1, -1, 0, true);
 }
 
+// What the kernels that dequantise on the way to LDS take, in us (bf16, 4096 x 5120 x 13824: 557 us for three rounds of 256
+// tiles and 162 K tiles of 32, 492 for one of 434; 128x128 tiles of the generic engine as on dense operands).
+static double int4_direct_us(const GemmPlan& p, int64_t M, int64_t N, int64_t K0, int64_t K1) {
+  if (p.tail_n0 > 0) {
+    GemmPlan main = p;
+    main.tail_n0 = 0;
+    const GemmPlan tail = gemm_tail_plan(p, DT_BF16, M, N, K0, K1);
+    return int4_direct_us(main, M, p.tail_n0, K0, K1) + int4_direct_us(tail, M, N - p.tail_n0, K0, K1);
+  }
+  const double wgs = (double)p.nbm * p.nbn * p.splits;
+  const int64_t kt = (K0 + p.bk - 1) / p.bk + (K1 + p.bk - 1) / p.bk;
+  const double per = p.splits > 1 ? (double)p.tiles_per_split : (double)kt;
+  const bool mc = p.cfg == CFG_MC3;
+  const double slots = mc ? 256.0 : 512.0;
+  const double rounds = wgs <= slots ? 1.0 : (double)(int64_t)(wgs / slots + 0.999);
+  const double tk = mc ? 1.14 : (wgs <= 256.0 ? 1.0 : 1.6);
+  return 10.0 + rounds * (per * tk + 6.0) + split_time_us(M, N, p.splits);
+}
+
+Int4PanelPlan int4_panel_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1) {
+  Int4PanelPlan best;
+  if (dtype == DT_F32 || M <= 32 || N <= 32 || K0 < 1) return best;
+  const int64_t fit = (int64_t)(kInt4PanelBytes / (2 * (size_t)K0)) / 256 * 256;
+  if (fit < 256) return best;
+  // candidates: everything in one panel, the widest panel, and the widest whose 256x256 / 256x128 tiles are whole rounds
+  int64_t cand[3] = {N <= fit ? N : fit, 0, 0};
+  const int64_t nbm = (M + 255) / 256;
+  for (int64_t w = fit; w >= 256 && cand[1] == 0; w -= 256)
+    if (w < N && (nbm * (w / 256)) % 256 == 0) cand[1] = w;
+  for (int64_t w = fit; w >= 256 && cand[2] == 0; w -= 256)
+    if (w < N && (nbm * (w / 128)) % 256 == 0) cand[2] = w;
+  best.us = int4_direct_us(gemm_plan_int4(dtype, M, N, K0, K1), M, N, K0, K1);
+  for (int64_t w : cand) {
+    if (w == 0) continue;
+    const int64_t fulls = (N + w - 1) / w - 1, rest = N - fulls * w;
+    Int4PanelPlan p;
+    p.width = w;
+    p.panel_bytes = ((size_t)w * (size_t)K0 * 2 + 255) / 256 * 256;
+    // partials of a split product stay within what one panel may take
+    const size_t cap = kInt4PanelBytes;
+    double uf = 0, ul = 0;
+    if (fulls > 0 && !mt_plan(&p.full, &uf, M, w, K0, K1, 0, true)) continue;
+    if (!mt_plan(&p.last, &ul, M, rest, K0, K1, cap - (p.panel_bytes < cap ? p.panel_bytes : cap), true)) continue;
+    if (fulls == 0) p.full = p.last;
+    p.scratch_bytes = p.panel_bytes + p.last.partial_bytes;
+    p.us = uf * (double)fulls + ul + 4.0 * (double)(fulls + 1) + (double)N * (double)K0 * 2.5 / 4.5e6;
+    if (p.us < best.us) best = p;
+  }
+  return best;
+}
+
+hipError_t int4_panel_gemm(const GemmDesc& d, const Int4PanelPlan& plan, void* scratch, hipStream_t stream) {
+  if (plan.width < 1 || scratch == nullptr || d.Bscale == nullptr || d.D != nullptr || d.drop_thr != 0 || d.a_strided) return hipErrorInvalidValue;
+  char* const panel = static_cast<char*>(scratch);
+  float* const partial = reinterpret_cast<float*>(panel + plan.panel_bytes);
+  for (int64_t n0 = 0; n0 < d.N; n0 += plan.width) {
+    const bool last = n0 + plan.width >= d.N;
+    const int64_t w = last ? d.N - n0 : plan.width;
+    GemmDesc s = d;
+    s.b_int4 = false;
+    s.Bscale = nullptr;
+    s.ldbs = 0;
+    s.N = w;
+    s.B[0] = panel;
+    s.ldb[0] = d.b_kcontig ? d.K[0] : w;
+    hipError_t e = d.b_kcontig ? int4_panel_run(d.dtype, d.B[0], d.ldb[0], d.Bscale, d.ldbs, panel, d.K[0], n0, w, 0, d.K[0], stream)
+                               : int4_panel_run(d.dtype, d.B[0], d.ldb[0], d.Bscale, d.ldbs, panel, w, 0, d.K[0], n0, w, stream);
+    if (e != hipSuccess) return e;
+    if (d.nseg > 1) s.B[1] = static_cast<const char*>(d.B[1]) + (size_t)(d.b_kcontig ? n0 * d.ldb[1] : n0) * 2;
+    s.C = static_cast<char*>(d.C) + (size_t)n0 * 2;
+    if (d.bias) s.bias = static_cast<const char*>(d.bias) + (size_t)n0 * 2;
+    e = gemm_run(s, last ? plan.last : plan.full, partial, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 GemmPlan gemm_plan_fused(int dtype, int64_t M, int64_t N, int64_t K0, int64_t R) {
   // the shape rules of gemm_plan for the generic engine (those fp32 runs on); the workgroup that owns an output tile needs
   // the whole contraction of its rows of T: no split
@@ -508,8 +585,8 @@ GemmDesc rank_desc(int dtype, const SkinnyDesc& d) {
 // fast: dA, dB of 1024 x 4096 r 64 take 9.7 us here, 17.5 on the streaming kernel.
 static double rank_time_us(bool a_strided, int64_t wgs, int64_t ktiles, double bytes) {
   const int64_t rounds = wgs / 512, rest = wgs % 512;
-  const double tk = bytes < 64e6 ? 0.28 : (a_strided ? 0.45 : 0.53);
-  const double us = (bytes < 64e6 ? 5.0 : 7.5) + (double)ktiles * tk * (double)(2 * rounds + (rest > 256 ? 2 : (rest > 0 ? 1 : 0)));
+  const double tk = bytes < 32e6 ? 0.28 : (a_strided ? 0.45 : 0.53);
+  const double us = (bytes < 32e6 ? 5.0 : 7.5) + (double)ktiles * tk * (double)(2 * rounds + (rest > 256 ? 2 : (rest > 0 ? 1 : 0)));
   const double floor_us = 5.0 + bytes / 4.8e6;
   return us > floor_us ? us : floor_us;
 }

@@ -28,6 +28,10 @@ struct Builder {
   void expect_gemm(int64_t M, int64_t N, int64_t K0, int64_t K1, bool b_is_w) {
     const GemmPlan p = b_is_w && L.w_int4 ? gemm_plan_int4(L.dtype, M, N, K0, K1) : gemm_plan(L.dtype, M, N, K0, K1);
     if (p.partial_bytes > later_partial) later_partial = p.partial_bytes;
+    if (b_is_w && L.w_int4 && L.int4_panels) {
+      const size_t panel = int4_panel_plan(L.dtype, M, N, K0, K1).scratch_bytes;
+      if (panel > later_partial) later_partial = panel;
+    }
   }
 
   // dense [rows, cols] scratch matrix in the layer dtype
@@ -85,6 +89,11 @@ struct Builder {
       d.Bscale = B.scales;
       d.ldbs = B.lds;
       s.plan = gemm_plan_int4(L.dtype, M, N, K, K2);
+      if (L.int4_panels && !D && !a_strided && !mask_out) s.panel = int4_panel_plan(L.dtype, M, N, K, K2);
+      if (s.panel.width > 0) {
+        s.is_panel = true;
+        if (s.panel.scratch_bytes > max_partial) max_partial = s.panel.scratch_bytes;
+      }
     } else {
       s.plan = gemm_plan(L.dtype, M, N, K, K2);
     }

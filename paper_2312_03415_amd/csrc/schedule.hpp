@@ -35,11 +35,16 @@ struct LayerDims {
   // W enters through M = W + s AB alone exist with it (forward2, backward 4 / 5 / 7 / 8), where the merge kernel
   // scales W's columns on the way; 16-bit types, r <= 128.
   const float* wcol = nullptr;
+  // an int4 W's products may dequantise panels of it into scratch; false for calls whose scratch holds only what the
+  // direct route takes
+  bool int4_panels = true;
 };
 
 struct Step {
   bool is_merge = false;  // M = W + A B on the merge kernel (mg); otherwise see nsk
   MergeDesc mg;
+  bool is_panel = false;  // d on an int4 W, panel by panel
+  Int4PanelPlan panel;
   bool is_few = false;    // the few-token forward (few, few_plan)
   FewDesc few;
   FewPlan few_plan;

@@ -102,6 +102,7 @@ static double step_time_us(const Step& s) {
   const ModelConstants& mc = model_constants();
   const double e = (double)dtype_size(s.d.dtype);
   if (s.is_few) return s.few_plan.us;
+  if (s.is_panel) return s.panel.us;
   if (s.is_merge)
     return e * 2.0 * (double)s.mg.I * (double)s.mg.O / (mc.merge_tbps * 1e12) * 1e6 + mc.merge_fix_us;
   if (s.is_mtpair) return s.mtpair.us;

@@ -174,3 +174,62 @@ def test_int4_matrix_core_route_with_scale_and_bias():
     Tm = scale * oracle.matmul(host["X"], host["A"])
     assert relerr(to_f64(gB), oracle.matmul(Tm, host["dY"], ta=True)) < TOL["bf16"]
 
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r", [(300, 1096, 1000, 16),    # one panel, rows and columns that end inside a scale group / a tile
+                                     (1237, 4104, 9000, 24),   # two panels of columns forward, ragged last one
+                                     (1100, 9000, 4104, 72)])  # two panels of rows backward
+def test_int4_panels_and_direct_route_agree(n, i, o, r, dtype):
+    """A call with the workspace that runlora_workspace_bytes_w names multiplies dequantised panels of W; one with only what
+    the direct route needs (the figure in the error text) still runs, on the kernels that dequantise on their way to LDS.
+    Unit scales and integer values: both give the same bits, every option included."""
+    import re
+
+    import torch
+    rng = np.random.default_rng(n)
+    td = torch_dtype(dtype)
+    pick = lambda shape, p: to_device(synth.store((rng.random(shape) < p) * rng.choice([-1.0, 1.0], size=shape), dtype), dtype)
+    q = (rng.integers(-7, 8, size=(i, o)) * (rng.random((i, o)) < 0.05)).astype(np.int8)
+    W = rl.Int4Weight.from_host(q, np.ones(((i + 63) // 64, o), dtype=np.float16))
+    X, A, B, dY = pick((n, i), 0.05), pick((i, r), 0.01), pick((r, o), 0.05), pick((n, o), 0.05)
+    bias = pick((o,), 0.5)
+    code = rl.dtype_from_name(dtype)
+    print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
+
+    def run(ws_f, ws_b):
+        Y, dX = torch.empty((n, o), dtype=td, device="cuda"), torch.empty((n, i), dtype=td, device="cuda")
+        saved = rl.new_saved()
+        rl.runlora_profile_enable(32)
+        rl.runlora_forward(1, X, W, A, B, Y, saved, workspace=ws_f, scale=2.0, bias=bias)
+        rl.runlora_backward(1, dY, saved, W, A, B, dX, None, None, workspace=ws_b)
+        torch.cuda.synchronize()
+        steps = [(s["what"], s["tile_cfg"]) for s in rl.runlora_profile_collect(32)]
+        rl.runlora_profile_disable()
+        return Y, dX, steps
+
+    def direct_need(fwd, bwd):
+        tiny = torch.empty(256, dtype=torch.uint8, device="cuda")
+        with pytest.raises(rl.RunLoRAError) as e:
+            if bwd < 0:
+                rl.runlora_forward(fwd, X, W, A, B, torch.empty((n, o), dtype=td, device="cuda"), rl.new_saved(), workspace=tiny)
+            else:
+                s = rl.new_saved()
+                rl.runlora_forward(1, X, W, A, B, torch.empty((n, o), dtype=td, device="cuda"), s, workspace=full)
+                rl.runlora_backward(bwd, dY, s, W, A, B, torch.empty((n, i), dtype=td, device="cuda"), None, None, workspace=tiny)
+        assert e.value.code == rl.RL_ERR_WORKSPACE
+        return torch.empty(int(re.search(r"(\d+) bytes", str(e.value)).group(1)), dtype=torch.uint8, device="cuda")
+
+    full = rl.new_workspace(1, 1, n, i, o, r, code, w_dtype=rl.RL_INT4_G64)
+    small_f, small_b = direct_need(1, -1), direct_need(1, 1)
+    Y0, dX0, direct = run(small_f, small_b)
+    Y1, dX1, panels = run(full, full)
+    if n > 1000:  # (the short layers' direct route splits its contraction and takes more scratch than their panels)
+        assert small_f.numel() < full.numel() and small_b.numel() < full.numel()
+        assert direct != panels, "both calls took the same route"
+    Wq = q.astype(np.float64)
+    want = to_f64(X) @ Wq + 2.0 * (to_f64(X) @ to_f64(A)) @ to_f64(B) + to_f64(bias)
+    want_dX = to_f64(dY) @ Wq.T + 2.0 * (to_f64(dY) @ to_f64(B).T) @ to_f64(A).T
+    assert np.abs(want).max() <= 256 and np.abs(want_dX).max() <= 256   # integers bf16 holds
+    for Y, dX in ((Y0, dX0), (Y1, dX1)):
+        assert np.array_equal(to_f64(Y), want) and np.array_equal(to_f64(dX), want_dX)
