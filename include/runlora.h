@@ -34,7 +34,7 @@
  *   - Element types: RL_F32, RL_F16, RL_BF16 for every tensor of a call (one type per call).
  *     RL_INT4_G64 is allowed for W only (see rl_tensor_t), with RL_F16 / RL_BF16 activations: W is
  *     dequantised (q * scale, rounded to the activation type) inside the GEMMs that read it, or, where
- *     that is faster, in panels of at most 64 MiB in the workspace; it is never written out as a whole.
+ *     that is faster, in panels in the workspace, at most 64 MiB of W at a time.
  *     A workspace that holds only what the direct route needs gets the direct route.  The graphs that need W + AB as a matrix (RL_FWD2, RL_BWD4,
  *     RL_BWD5, RL_BWD7, RL_BWD8) return RL_ERR_UNSUPPORTED for an int4 W.  Accumulation is fp32
  *     throughout; each result is rounded once (nearest even) to the storage type.

@@ -709,10 +709,8 @@ extern "C" int runlora_dora_forward(int variant, const rl_tensor_t* X, const rl_
   nd.sq_partial = v.partial;
   hipError_t e = merge_run(dt, nd, stream);
   if (e != hipSuccess) return set_hip_error(e, "column sums of (W + s A B)^2");
-  if ((e = dora_norm_finish_run(dt, v.partial, v.norm_rows, m, c, v.g, o, stream)) != hipSuccess)
-    return set_hip_error(e, "c, g = m / c");
-  if ((e = dora_colscale_run(dt, B->data, B->ld, v.g, v.Bt.data, v.Bt.ld, r, o, stream)) != hipSuccess)
-    return set_hip_error(e, "B~ = B diag(g)");
+  if ((e = dora_scale_run(dt, v.partial, v.norm_rows, m, c, v.g, B->data, B->ld, v.Bt.data, v.Bt.ld, r, o, stream)) != hipSuccess)
+    return set_hip_error(e, "c, g = m / c, B~ = B diag(g)");
   return runlora_forward(variant, X, W, A, &v.Bt, Y, saved, &v.inner);
 }
 
@@ -768,10 +766,8 @@ extern "C" int runlora_dora_backward(int variant, const rl_tensor_t* dY, const r
     if ((rc = runlora_backward(variant, dY, saved, W, A, &v.Bt, dX, dA, dBt, &v.inner)) != RL_OK) return rc;
   }
   hipStream_t stream = static_cast<hipStream_t>(opts->stream);
-  hipError_t e = dora_g_run(dt, m, c, v.g, o, stream);
-  if (e != hipSuccess) return set_hip_error(e, "g = m / c");
-  if ((e = dora_colscale_run(dt, B->data, B->ld, v.g, v.Bt.data, v.Bt.ld, r, o, stream)) != hipSuccess)
-    return set_hip_error(e, "B~ = B diag(g)");
+  hipError_t e = dora_scale_run(dt, nullptr, 0, m, const_cast<float*>(c), v.g, B->data, B->ld, v.Bt.data, v.Bt.ld, r, o, stream);  // (c is only read)
+  if (e != hipSuccess) return set_hip_error(e, "g = m / c, B~ = B diag(g)");
   if ((rc = runlora_backward(variant, dY, saved, W, A, &v.Bt, dX, dA, dBt, &v.inner)) != RL_OK) return rc;
   if (dB && (e = dora_colscale_run(dt, v.dBt.data, v.dBt.ld, v.g, dB->data, dB->ld, r, o, stream)) != hipSuccess)
     return set_hip_error(e, "dB = dB~ diag(g)");

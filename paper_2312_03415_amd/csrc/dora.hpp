@@ -16,11 +16,10 @@
 
 namespace rl {
 
-// c[j] = sqrt(sum over the `rows` rows of partial[.][j]), g[j] = m[j] / c[j]
-hipError_t dora_norm_finish_run(int dtype, const float* partial, int rows, const void* m, float* c, float* g, int64_t O,
-                                hipStream_t stream);
-// g[j] = m[j] / c[j]
-hipError_t dora_g_run(int dtype, const void* m, const float* c, float* g, int64_t O, hipStream_t stream);
+// g[j] = m[j] / c[j] and out[k,j] = in[k,j] * g[j] (product in fp32, rounded once); c[j] = sqrt(sum over the `rows` rows of
+// partial[.][j]) is formed first unless partial is null
+hipError_t dora_scale_run(int dtype, const float* partial, int rows, const void* m, float* c, float* g, const void* in, int64_t ldi,
+                          void* out, int64_t ldo, int64_t R, int64_t O, hipStream_t stream);
 // out[k,j] = in[k,j] * g[j], product in fp32, rounded once (in == out allowed)
 hipError_t dora_colscale_run(int dtype, const void* in, int64_t ldi, const float* g, void* out, int64_t ldo, int64_t R,
                              int64_t O, hipStream_t stream);

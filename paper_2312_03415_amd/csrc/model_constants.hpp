@@ -52,7 +52,7 @@ inline const ModelConstants& model_constants() {
       5.58,
       2.75,
       6.44,
-      4.95,
+      3.60,  // (W from HBM, as in a model; 4.95 while the Infinity Cache holds part of it)
       2.52,
   };
   return c;

@@ -9,15 +9,32 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// 16 bytes of a row as VE elements (row lengths are multiples of VE, rows 16-byte aligned)
+template <typename T>
+struct Chunk {
+  static constexpr int VE = 16 / (int)sizeof(T);
+  using V4 = __attribute__((__vector_size__(4 * sizeof(int)))) int;
+  T e[VE];
+  __device__ __forceinline__ void load(const T* p) { *reinterpret_cast<V4*>(e) = *reinterpret_cast<const V4*>(p); }
+  __device__ __forceinline__ void store(T* p) const { *reinterpret_cast<V4*>(p) = *reinterpret_cast<const V4*>(e); }
+};
+
+// A thread scales 16 bytes of a row (256 x 8192: 6.6 us with an element per thread, 5.2 so).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void vera_scale_kernel(const T* __restrict__ B, int64_t ldb, const T* __restrict__ d,
                                                               const T* __restrict__ b, T* __restrict__ Bt, int64_t ldt,
                                                               int R, int O) {
-  const int j = blockIdx.x * kThreads + threadIdx.x;
+  constexpr int VE = Chunk<T>::VE;
+  const int j = (blockIdx.x * kThreads + threadIdx.x) * VE;
   const int k = blockIdx.y;
   if (j >= O || k >= R) return;
-  const float v = (float)d[k] * (float)B[(int64_t)k * ldb + j] * (float)b[j];
-  Bt[(int64_t)k * ldt + j] = (T)v;
+  Chunk<T> v, w;
+  v.load(B + (int64_t)k * ldb + j);
+  w.load(b + j);
+  const float dk = (float)d[k];
+#pragma unroll
+  for (int e = 0; e < VE; ++e) v.e[e] = (T)(dk * (float)v.e[e] * (float)w.e[e]);
+  v.store(Bt + (int64_t)k * ldt + j);
 }
 
 // a workgroup owns 32 columns; thread (c, g) sums the rows k = g, g + 8, g + 16, ... of column c in that
@@ -43,16 +60,24 @@ __global__ __launch_bounds__(kThreads) void vera_db_kernel(const T* __restrict__
   }
 }
 
-// one workgroup per row k: every thread sums its columns j = tid, tid + 256, ... in order, then a
-// fixed binary tree over the 256 partial sums
+// one workgroup per row k: every thread sums its 16-byte chunks tid, tid + 256, ... in order, then a fixed binary tree over
+// the 256 partial sums (256 x 8192: 12 us with two bytes per load, 4.8 so)
 template <typename T>
 __global__ __launch_bounds__(kThreads) void vera_dd_kernel(const T* __restrict__ G, int64_t ldg, const T* __restrict__ B,
                                                            int64_t ldb, const T* __restrict__ b, T* __restrict__ dd, int R, int O) {
+  constexpr int VE = Chunk<T>::VE;
   __shared__ float part[kThreads];
   const int k = blockIdx.x;
   float acc = 0.f;
-  for (int j = threadIdx.x; j < O; j += kThreads)
-    acc += (float)G[(int64_t)k * ldg + j] * ((float)B[(int64_t)k * ldb + j] * (float)b[j]);
+#pragma unroll 4
+  for (int j = (int)threadIdx.x * VE; j < O; j += kThreads * VE) {
+    Chunk<T> x, y, w;
+    x.load(G + (int64_t)k * ldg + j);
+    y.load(B + (int64_t)k * ldb + j);
+    w.load(b + j);
+#pragma unroll
+    for (int e = 0; e < VE; ++e) acc += (float)x.e[e] * ((float)y.e[e] * (float)w.e[e]);
+  }
   part[threadIdx.x] = acc;
   __syncthreads();
   for (int w = kThreads / 2; w > 0; w >>= 1) {
@@ -68,7 +93,7 @@ hipError_t scale_t(const void* B, int64_t ldb, const void* d, const void* b, voi
   // gridDim.y is limited to 65535: walk the rows in slabs
   for (int64_t k0 = 0; k0 < R; k0 += 65535) {
     const int rows = (int)((R - k0) < 65535 ? (R - k0) : 65535);
-    dim3 grid((unsigned)((O + kThreads - 1) / kThreads), (unsigned)rows);
+    dim3 grid((unsigned)((O / Chunk<T>::VE + kThreads - 1) / kThreads), (unsigned)rows);
     hipLaunchKernelGGL(vera_scale_kernel<T>, grid, dim3(kThreads), 0, s, static_cast<const T*>(B) + k0 * ldb, ldb,
                        static_cast<const T*>(d) + k0, static_cast<const T*>(b), static_cast<T*>(Bt) + k0 * ldt, ldt, rows, (int)O);
     hipError_t e = hipGetLastError();
