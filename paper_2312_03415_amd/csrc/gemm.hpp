@@ -103,7 +103,7 @@ GemmPlan gemm_tail_plan(const GemmPlan& main, int dtype, int64_t M, int64_t N, i
 GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1);
 
 // A product whose B[0] is int4, with W's columns (rows, for dY W^T) dequantised panel by panel into scratch and multiplied
-// by the dense kernels: a panel is at most kInt4PanelBytes, W as a whole is never written out.  Applies where the model says
+// by the dense kernels: at most kInt4PanelBytes of it at a time.  Applies where the model says
 // it beats the kernels that dequantise on their way to LDS (int4_panel.hip).
 constexpr size_t kInt4PanelBytes = 64u << 20;
 struct Int4PanelPlan {

@@ -87,7 +87,9 @@ static double gemm_time_us(const GemmDesc& d, const GemmPlan& p) {
     if (p.cfg >= 0 && p.cfg < 6) q *= ratio[p.cfg];
   }
   double us = rounds * (ktiles * tm.tk_us[lay] * share * q + (addend ? tm.tfix_d_us : tm.tfix_us));
-  if (p.splits > 1)
+  if (p.splits > 1 && d.dtype != DT_F32 && !d.b_int4)
+    us += split_time_us(d.M, d.N, p.splits);  // (the reduce pass is launched right behind: no gap of its own)
+  else if (p.splits > 1)
     us += (double)d.M * d.N * (4.0 * (p.splits + 1) + (has_d ? e : 0.0) + e) / (mc.reduce_tbps * 1e12) * 1e6 + mc.reduce_fix_us + mc.launch_us;
   return us;
 }
@@ -116,7 +118,8 @@ static double step_time_us(const Step& s) {
       us += bytes / (mc.stream_tbps[k.a_strided ? 1 : 0] * 1e12) * 1e6;
       outs += (double)k.M * k.N;
     }
-    if (s.skplan.splits > 1) us += 4.0 * outs * (s.skplan.splits + 1) / (mc.reduce_tbps * 1e12) * 1e6 + mc.stream_fix_us + mc.launch_us;
+    if (s.skplan.splits > 1 && s.d.dtype != DT_F32) us += 3.0 + outs * 8.0 * s.skplan.splits / 7.5e6;
+    else if (s.skplan.splits > 1) us += 4.0 * outs * (s.skplan.splits + 1) / (mc.reduce_tbps * 1e12) * 1e6 + mc.stream_fix_us + mc.launch_us;
     return us;
   }
   return gemm_time_us(s.d, s.plan);
@@ -185,13 +188,17 @@ extern "C" int runlora_select_by(int criterion, int64_t n, int64_t i, int64_t o,
   L.w_int4 = int4;
   int bf = 1, bb = 1;
   double cf = 0, cb = 0;
+  // Modelled times closer than the model's own error (3 %, or 2.5 us of a short layer) are a tie: the lower id rounds fewer
+  // intermediates to 16 bits (forward1 no W + AB, Algorithm 1 no X^T dY and no W + AB).  fp32 has nothing to lose.
+  const bool strict = criterion == 0 || dt == DT_F32;
+  const double tie = strict ? 1.0 : 0.97, gap = strict ? 0.0 : 2.5;
   for (int v = 1; v <= fmax; ++v) {
     double c = criterion == 0 ? (double)table1_flops(0, v, n, i, o, r) : model_time_us(0, v, L);
-    if (v == 1 || c < cf) { cf = c; bf = v; }  // strict '<': ties go to the lower id
+    if (v == 1 || (c < tie * cf && c < cf - gap)) { cf = c; bf = v; }  // strict '<': ties go to the lower id
   }
   for (int v = 1; v <= bmax; ++v) {
     double c = criterion == 0 ? (double)table1_flops(1, v, n, i, o, r) : model_time_us(1, v, L);
-    if (v == 1 || c < cb) { cb = c; bb = v; }
+    if (v == 1 || (c < tie * cb && c < cb - gap)) { cb = c; bb = v; }
   }
   // The default chain (keeps XA, no fusion) is a legal pair too; under the time criterion it is
   // returned when the model says it beats the best RunLoRA pair (large r at few tokens, where the
