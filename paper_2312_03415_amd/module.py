@@ -49,6 +49,19 @@ def _native():
     return _native_module
 
 
+def _reread(saved, dy, x2, *others):
+    """The forward's record for the input as autograd hands it back (and that input): a saved-tensor hook may have moved it or
+    laid it out anew, so the pointer the forward recorded need not be x2's."""
+    for t in (x2, *others):
+        if t.device != dy.device:
+            raise ValueError(f"a saved tensor came back on another device: {t.device}, not {dy.device}")
+    if x2.stride(-1) != 1 or x2.stride(0) % 8 != 0 or x2.data_ptr() % 16 != 0:
+        x2 = x2.contiguous()
+    saved = type(saved).from_buffer_copy(saved)
+    saved.X, saved.ldx, saved.dtype = x2.data_ptr(), x2.stride(0), rl.dtype_code(x2.dtype)
+    return saved, x2
+
+
 class RunLoRAFunction(torch.autograd.Function):
     """y = x W + bias + scale (x A) B with W and bias frozen; gradients for x, A and B (Eq. 1, Eq. 3).
 
@@ -97,6 +110,7 @@ class RunLoRAFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dy):
         x2, W, A, B = ctx.saved_tensors
+        saved, x2 = _reread(ctx.saved, dy, x2, W, A, B)
         i, o = W.shape
         r = A.shape[1]
         n = x2.shape[0]
@@ -109,7 +123,7 @@ class RunLoRAFunction(torch.autograd.Function):
         dB = torch.empty_like(B) if need_b else None
         code = rl.dtype_code(dy.dtype)
         ws = _workspace(dy.device, rl.runlora_workspace_bytes(-1, ctx.bwd, n, i, o, r, code))
-        rl.runlora_backward(ctx.bwd, dy2, ctx.saved, W, A, B, dx, dA, dB, workspace=ws)
+        rl.runlora_backward(ctx.bwd, dy2, saved, W, A, B, dx, dA, dB, workspace=ws)
         if dx is not None:
             dx = dx.view(ctx.x_shape)
         return dx, None, dA, dB, None, None, None, None, None, None
@@ -202,6 +216,7 @@ class RunVeRAFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dy):
         x2, W, A, B, d, b = ctx.saved_tensors
+        saved, x2 = _reread(ctx.saved, dy, x2, W, A, B, d, b)
         i, o = W.shape
         r = A.shape[1]
         n = x2.shape[0]
@@ -214,7 +229,7 @@ class RunVeRAFunction(torch.autograd.Function):
         db = torch.empty_like(b) if need[5] else None
         code = rl.dtype_code(dy.dtype)
         ws = _workspace(dy.device, rl.runlora_vera_workspace_bytes(-1, ctx.bwd, n, i, o, r, code))
-        rl.runlora_vera_backward(ctx.bwd, dy2, ctx.saved, W, A, B, d, b, dx, dd, db, ws)
+        rl.runlora_vera_backward(ctx.bwd, dy2, saved, W, A, B, d, b, dx, dd, db, ws)
         if dx is not None:
             dx = dx.view(ctx.x_shape)
         return dx, None, None, None, dd, db, None, None, None
@@ -286,6 +301,7 @@ class RunDoRAFunction(torch.autograd.Function):
     @staticmethod
     def backward(ctx, dy):
         x2, W, A, B, m, c, y = ctx.saved_tensors
+        saved, x2 = _reread(ctx.saved, dy, x2, W, A, B, m, c, y)
         i, o = W.shape
         r = A.shape[1]
         n = x2.shape[0]
@@ -299,7 +315,7 @@ class RunDoRAFunction(torch.autograd.Function):
         dm = torch.empty_like(m) if need[4] else None
         code = rl.dtype_code(dy.dtype)
         ws = _workspace(dy.device, rl.runlora_dora_workspace_bytes(-1, ctx.bwd, n, i, o, r, code))
-        rl.runlora_dora_backward(ctx.bwd, dy2, ctx.saved, W, A, B, m, c, y, dx, dA, dB, dm, ws, bias=ctx.bias)
+        rl.runlora_dora_backward(ctx.bwd, dy2, saved, W, A, B, m, c, y, dx, dA, dB, dm, ws, bias=ctx.bias)
         if dx is not None:
             dx = dx.view(ctx.x_shape)
         return dx, None, dA, dB, dm, None, None, None

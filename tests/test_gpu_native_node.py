@@ -115,6 +115,63 @@ def test_saved_tensors_errors_and_refusals_are_the_python_nodes():
         torch.func.grad(lambda t: RunLoRAFunction.apply(t, W, A, B, *extra).float().sum())(x)
 
 
+def under_hooks(fn, unpack, x, W, A, B, dy, extra):
+    """A pass whose saved tensors leave as host copies (their device memory is free for others) and come back as unpack(t)."""
+    import torch
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: t.cpu(), unpack):
+        xs, As, Bs = (t.detach().clone().requires_grad_(True) for t in (x, A, B))
+        y = fn(xs * 1.0, W, As, Bs, *extra)
+    churn = [torch.full((1 << k,), 7.0, device="cuda", dtype=x.dtype) for k in range(9, 18)]
+    grads = torch.autograd.grad(y, (xs, As, Bs), dy)
+    del churn
+    return grads
+
+
+@pytest.mark.parametrize("node", ["python"])
+def test_saved_tensors_that_come_back_changed(node):
+    """What a saved-tensor hook returns is what the backward reads: moved to the host and back, or laid out anew, it gives the
+    plain pass's bits; a type, layout or device that the forward would refuse is refused."""
+    import torch
+    from paper_2312_03415_amd.module import RunLoRAFunction
+    fn = RunLoRAFunction.apply if node == "native" else python_node
+    x, W, A, B, bias, dy = layer(torch.bfloat16)
+    extra = (None, 0.5, (1, 1), False)
+    plain, _ = run(fn, x, W, A, B, dy, extra)
+
+    def wide(t):   # rows apart
+        return torch.cat([t, t], 1)[:, :t.shape[1]]
+    for unpack in (lambda t: t.cuda(), lambda t: wide(t.cuda()), lambda t: t.cuda().t().contiguous().t() if t.shape == x.shape else t.cuda()):
+        got = under_hooks(fn, unpack, x, W, A, B, dy, extra)
+        assert all(torch.equal(g, w) for g, w in zip(got, plain[1:]))
+    only = lambda like, change: lambda t: change(t.cuda()) if t.shape == like.shape else t.cuda()
+    for like, change, error in ((W, lambda t: t.t().contiguous().t(), ValueError), (A, lambda t: t.repeat_interleave(2, 1)[:, ::2], ValueError),
+                                (W, lambda t: t.cpu(), ValueError), (x, lambda t: t.cpu(), ValueError),
+                                (W, lambda t: t.float(), rl.RL_ERR_DTYPE), (B, lambda t: t.half(), rl.RL_ERR_DTYPE),
+                                (x, lambda t: t.float(), rl.RL_ERR_DTYPE)):
+        with pytest.raises(ValueError if error is ValueError else rl.RunLoRAError) as e:
+            under_hooks(fn, only(like, change), x, W, A, B, dy, extra)
+        assert error is ValueError or e.value.code == error, (tuple(like.shape), e.value)
+
+
+def test_other_layers_read_what_a_saved_tensor_hook_returns():
+    import torch
+    from paper_2312_03415_amd.module import RunDoRALinear, RunVeRALinear
+    x, W, A, B, bias, dy = layer(torch.bfloat16)
+    dora, vera = RunDoRALinear(W, 16, bias=bias), RunVeRALinear(W, A, B, bias)
+    with torch.no_grad():
+        dora.lora_A.copy_(A), dora.lora_B.copy_(B), vera.vera_b.copy_(bias)
+    for mod in (dora, vera):
+        params = [p for p in mod.parameters() if p.requires_grad]
+        xs = x.clone().requires_grad_(True)
+        want = torch.autograd.grad(mod(xs * 1.0), [xs, *params], dy)
+        with torch.autograd.graph.saved_tensors_hooks(lambda t: t.cpu(), lambda t: t.cuda()):
+            y = mod(xs * 1.0)
+        churn = [torch.full((1 << k,), 7.0, device="cuda", dtype=x.dtype) for k in range(9, 18)]
+        got = torch.autograd.grad(y, [xs, *params], dy)
+        assert all(torch.equal(g, w) for g, w in zip(got, want)), type(mod).__name__
+        del churn
+
+
 def test_native_node_on_streams_and_threads():
     """Two streams and two threads at once, each with passes of its own: every result is the one computed alone (no scratch
     is shared between calls)."""
