@@ -56,6 +56,14 @@ rl_tensor_t desc(const at::Tensor& t, int code) {
   return rl_tensor_t{t.data_ptr(), t.size(0), t.size(1), t.stride(0), code, nullptr, 0};
 }
 
+// a saved operand as the backward gets it back: a saved-tensor hook may have changed its type, layout or device, so that
+// what held in the forward is checked again (types and sizes by the library, against the descriptor's own)
+rl_tensor_t saved_desc(const at::Tensor& t, const at::Tensor& x) {
+  TORCH_CHECK_VALUE(t.dim() == 2 && t.stride(1) == 1, "expected a 2-D tensor with contiguous rows");
+  TORCH_CHECK_VALUE(t.device() == x.device(), "a saved tensor came back on another device: ", t.device(), ", not ", x.device());
+  return desc(t, dtype_code(t.scalar_type()));
+}
+
 // rows as the library takes them (the same test as the Python node's)
 at::Tensor rows(const at::Tensor& t, int64_t cols) {
   at::Tensor r = t.reshape({-1, cols});
@@ -119,8 +127,10 @@ struct LoRANode : public torch::autograd::Function<LoRANode> {
   static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, torch::autograd::variable_list grads) {
     const auto vars = ctx->get_saved_variables();
     const at::Tensor &W = vars[1], &A = vars[2], &B = vars[3];
+    TORCH_CHECK_VALUE(vars[0].is_cuda(), "the saved input came back on ", vars[0].device());
+    const rl_tensor_t dw = saved_desc(W, vars[0]), da = saved_desc(A, vars[0]), db = saved_desc(B, vars[0]);
     const int64_t i = W.size(0), o = W.size(1), r = A.size(1);
-    const at::Tensor x2 = rows(vars[0], i);  // (a saved-tensor hook may have laid it out anew)
+    const at::Tensor x2 = rows(vars[0], i);
     const int64_t n = x2.size(0);
     const int code = dtype_code(x2.scalar_type());
     const c10::OptionalDeviceGuard guard(x2.device());
@@ -143,14 +153,14 @@ struct LoRANode : public torch::autograd::Function<LoRANode> {
     at::Tensor dx, dA, dB;
     rl_tensor_t tx{}, ta{}, tb{};
     if (ctx->needs_input_grad(0)) { dx = at::empty({n, i}, x2.options()); tx = desc(dx, code); }
-    if (ctx->needs_input_grad(2)) { dA = at::empty_like(A); ta = desc(dA, code); }
-    if (ctx->needs_input_grad(3)) { dB = at::empty_like(B); tb = desc(dB, code); }
+    if (ctx->needs_input_grad(2)) { dA = at::empty_like(A); ta = desc(dA, da.dtype); }
+    if (ctx->needs_input_grad(3)) { dB = at::empty_like(B); tb = desc(dB, db.dtype); }
     const at::Tensor ws = scratch(p_workspace_bytes(-1, bwd, n, i, o, r, code), x2);
     rl_opts_t opts{};
     opts.stream = c10::hip::getCurrentHIPStream(x2.device().index()).stream();
     opts.workspace = ws.data_ptr();
     opts.workspace_bytes = (size_t)ws.numel();
-    const rl_tensor_t ddy = desc(dy2, dtype_code(dy2.scalar_type())), dw = desc(W, code), da = desc(A, code), db = desc(B, code);
+    const rl_tensor_t ddy = desc(dy2, dtype_code(dy2.scalar_type()));
     check(p_backward(bwd, &ddy, &saved, &dw, &da, &db, dx.defined() ? &tx : nullptr, dA.defined() ? &ta : nullptr,
                      dB.defined() ? &tb : nullptr, &opts));
     if (dx.defined()) dx = dx.view(ctx->saved_data["x_shape"].toIntVector());

@@ -127,7 +127,7 @@ def under_hooks(fn, unpack, x, W, A, B, dy, extra):
     return grads
 
 
-@pytest.mark.parametrize("node", ["python"])
+@pytest.mark.parametrize("node", ["native", "python"])
 def test_saved_tensors_that_come_back_changed(node):
     """What a saved-tensor hook returns is what the backward reads: moved to the host and back, or laid out anew, it gives the
     plain pass's bits; a type, layout or device that the forward would refuse is refused."""
