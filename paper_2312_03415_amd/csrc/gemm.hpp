@@ -86,10 +86,15 @@ struct GemmPlan {
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg = -1,
                    int force_splits = 0, bool b_int4 = false);
 
-// Modelled time in us of one launch of the middle-sized kernel (CFG_MT*) or of CFG_MC4: `wgs` workgroups (output tiles x
-// K slices) of `ktiles` K tiles each.
-double mt_time_us(int cfg, int64_t wgs, int64_t ktiles);
-// ... and of the partials' round trip and the reduce pass behind a contraction split `splits` ways.
+// Modelled time in us of one launch of a 16-bit tile GEMM (CFG_MT*, CFG_MC4, and the generic engine's 128x128, 128x64 and
+// 64x128 tiles): nbm x nbn output tiles x K slices of `ktiles` K tiles each; odd = odd_lines of the product.
+double launch_time_us(int cfg, int64_t nbm, int64_t nbn, int splits, int64_t ktiles, double odd);
+// Share of a 16-bit product's operands whose rows are not whole 128-byte lines, as far as its sizes tell (rows of K and of N
+// elements).
+inline double odd_lines(int64_t N, int64_t K) { return 0.5 * (K % 64 != 0) + 0.5 * (N % 64 != 0); }
+// Modelled time of a plan for a 16-bit product with dense operands (its tail launch and reduce passes included).
+double plan_time_us(const GemmPlan& p, int64_t M, int64_t N, int64_t K0, int64_t K1);
+// Modelled time of the partials' round trip and the reduce pass behind a contraction split `splits` ways.
 double split_time_us(int64_t M, int64_t N, int splits);
 
 // Plan for the one-pass LoRA forward (GemmDesc::fuse_t): a tile shape of the generic engine, the contraction whole.

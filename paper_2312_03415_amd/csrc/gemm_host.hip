@@ -31,57 +31,73 @@ static int pick_splits(int64_t tiles, int64_t K, int smin) {
   return best;
 }
 
-// What a launch takes, from sweeps over 32 .. 2048 workgroups and K = 512 .. 4096 (bf16, N(0,1) operands, NN and NT, in
-// us): `full` = one K tile of every resident workgroup, `half` = the same with at most one workgroup per compute unit,
-// `round` = prologue and epilogue of a round of workgroups, `fix` = the launch.  E.g. 256 tiles of 128x128 at K = 4096:
-// 35.8 (128x128, 4 stages) against 46 (2 stages), 59.1 (generic engine, two K slices) and 47.5 (256x256, three slices);
-// 512 of them: 67.6, 60.1, and 60.3 as 256 tiles of 256x128.
-struct LaunchModel { int slots; double full, half, round, fix; };
+// What a launch of a 16-bit tile GEMM takes, in us, fitted to one sweep of tile shapes and K splits (534 products: M 33 .. 8192,
+// N 40 .. 11008, K 512 .. 11008, NN / NT / TN; 17 800 timings with W from HBM, as in a model): `one` and `full` = one K tile
+// with at most one workgroup on a compute unit and with all its slots taken, `fix` = launch, prologue and epilogue, `round` =
+// every further round of workgroups, `store` = a million outputs, `split_lines` = what a K tile takes longer where rows are not
+// whole 128-byte lines (a row's piece then touches two), `fabric` = KB per us that reach an XCD's L2 from outside it.
+// One standard deviation is 7-11 %.  The plan these choose takes 2 % longer on average than the best one timed (26 % at worst),
+// and for none of the 534 more than 2 % longer than the plan by tile counts in gemm_plan.  Constants from operands that the
+// caches held, without the last three terms, lost 8 % on average, up to 22 % against that plan, and 48 % at 4096 x 2056 x 5464
+// (182-201 us on 64x128 tiles, 123-137 on 256x256).
+struct LaunchModel { int slots; double fix, one, full, round, store, split_lines, fabric; };
 static LaunchModel launch_model(int cfg) {
   switch (cfg) {
-    case CFG_MT128: return {512, 0.80, 0.63, 4.8, 4.0};
-    case CFG_MT128D: return {256, 0.44, 0.44, 4.5, 3.6};
-    case CFG_MT256: return {256, 0.755, 0.755, 8.8, 3.5};
-    case CFG_MTN64: return {512, 0.53, 0.25, 2.3, 5.2};
-    case CFG_MTM64: return {512, 0.51, 0.26, 2.3, 5.2};
-    default: return {256, 1.40, 1.40, 1.7, 10.5};  // CFG_MC4: persistent, the next tile's loads run during an epilogue
+    case CFG_MID: return {512, 3.8, 1.04, 1.26, 0.0, 0.51, 0.05, 1360};
+    case CFG_TALL64: return {768, 2.7, 0.78, 1.13, 0.0, 0.59, 0.0, 1240};
+    case CFG_WIDE64: return {768, 3.7, 0.89, 1.19, 2.8, 4.01, 0.09, 860};
+    case CFG_MT128: return {512, 3.5, 0.66, 0.89, 0.0, 0.42, 0.18, 1130};
+    case CFG_MT128D: return {256, 5.2, 0.42, 0.51, 1.8, 0.43, 0.15, 1380};
+    case CFG_MT256: return {256, 6.2, 0.69, 0.81, 1.5, 0.69, 0.16, 1510};
+    case CFG_MTN64: return {512, 3.8, 0.297, 0.637, 0.0, 0.26, 0.14, 1230};
+    case CFG_MTM64: return {512, 4.1, 0.29, 0.586, 0.0, 0.35, 0.15, 1160};
+    default: return {256, 5.0, 1.2, 1.32, 0.0, 0.48, 0.26, 1900};  // CFG_MC4: persistent, the next tile's loads run during an epilogue
   }
 }
 
-double mt_time_us(int cfg, int64_t wgs, int64_t ktiles) {
+double launch_time_us(int cfg, int64_t nbm, int64_t nbn, int splits, int64_t ktiles, double odd) {
   const LaunchModel m = launch_model(cfg);
-  const int64_t rounds = wgs / m.slots, rest = wgs % m.slots;
-  double us = m.fix + (double)rounds * (m.round + (double)ktiles * m.full);
-  if (rest > 0) {
-    // a round that leaves compute units idle runs up to a sixth faster (clock, cache)
-    const double fill = rest >= 256 ? 1.0 : 0.84 + 0.16 * (double)rest / 256.0;
-    us += m.round + (double)ktiles * (rest <= 256 ? m.half : m.full) * fill;
-  }
-  return us;
+  const int64_t tiles = nbm * nbn, wgs = tiles * splits, rounds = wgs / m.slots, rest = wgs % m.slots;
+  // operand bytes of a K tile that an XCD's resident workgroups want, each once: they hold a run of tiles in bands of eight
+  // tile rows (per K slice), of which those in a row share A and those in a column share B
+  auto kb = [&](int64_t run) {
+    const int64_t band = nbm < 8 ? nbm : 8, rows = run < band ? run : band, cols = (run + rows - 1) / rows;
+    return (double)(rows * kTileBM[cfg] + cols * kTileBN[cfg]) * 0.128;
+  };
+  const int64_t per_xcd = (tiles + 7) / 8, most = m.slots / 8, resident = (wgs + 7) / 8 < most ? (wgs + 7) / 8 : most;
+  const double bytes = resident >= per_xcd ? (double)resident / (double)per_xcd * kb(per_xcd) : kb(resident);
+  const double feed = bytes * (1.0 + odd) / m.fabric;
+  auto tile = [&](double t) { t += m.split_lines * odd; return t > feed ? t : feed; };
+  double per_k = (double)rounds * tile(m.full);
+  if (rest > 0) per_k += tile(rest <= 256 ? m.one : m.full);
+  const double outs = splits > 1 ? 0.0 : (double)(tiles * kTileBM[cfg] * kTileBN[cfg]);
+  return m.fix + (double)ktiles * per_k + m.round * (double)(rounds + (rest > 0 ? 1 : 0) - 1) + m.store * outs / 1e6;
 }
 
-// partials written, read back and reduced: 3 us and ~7.5 TB/s (measured 10 while they fit the caches, 6 beyond)
+// partials written, read back and reduced: 3 us, 5.5 TB/s, and 0.36 us for every slice beyond 16 (a thread of the reduce pass
+// walks them one after the other)
 double split_time_us(int64_t M, int64_t N, int splits) {
-  return splits > 1 ? 3.0 + (double)M * (double)N * (8.0 * splits + 2.0) / 7.5e6 : 0.0;
+  return splits > 1 ? 3.0 + (double)M * (double)N * (8.0 * splits + 2.0) / 5.5e6 + 0.36 * (splits > 16 ? splits - 16 : 0) : 0.0;
 }
 
 // Tile shape and K split of a 16-bit product on the matrix-core kernels: the smallest modelled time among 256x256 (whole
 // rounds with cut-off tail columns included), 256x128, 128x128 (two ways), 128x64 and 64x128, each with the contraction
-// in 1 .. 16 slices of at least four K tiles.  cap = scratch bytes the plan may use for partials.
+// in 1 .. 64 slices of at least four K tiles.  cap = scratch bytes the plan may use for partials.
 static bool mt_plan(GemmPlan* out, double* out_us, int64_t M, int64_t N, int64_t K0, int64_t K1, size_t cap, bool tail_ok) {
   static const int cfgs[] = {CFG_MC4, CFG_MT256, CFG_MT128, CFG_MT128D, CFG_MTN64, CFG_MTM64};
   const int64_t kt = (K0 + 63) / 64 + (K1 + 63) / 64;
+  const double odd = odd_lines(N, K0);
   double best = 1e30;
   for (int cfg : cfgs) {
     const int64_t nbm = (M + kTileBM[cfg] - 1) / kTileBM[cfg], nbn = (N + kTileBN[cfg] - 1) / kTileBN[cfg], tiles = nbm * nbn;
     if (tiles > (1 << 30)) continue;
-    for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+    for (int s = 1; s <= 64 && (s == 1 || kt / s >= 4); ++s) {
       const int64_t per = (kt + s - 1) / s;
       const int used = (int)((kt + per - 1) / per);  // no empty slice
       if (used != s) continue;
       const size_t bytes = s > 1 ? (size_t)s * (size_t)M * (size_t)N * sizeof(float) : 0;
       if (bytes > cap) break;
-      const double us = mt_time_us(cfg, tiles * s, per) + split_time_us(M, N, s);
+      const double us = launch_time_us(cfg, nbm, nbn, s, per, odd) + split_time_us(M, N, s);
       if (us < best) {
         best = us;
         *out = GemmPlan{};
@@ -103,7 +119,7 @@ static bool mt_plan(GemmPlan* out, double* out_us, int64_t M, int64_t N, int64_t
         GemmPlan tp;
         double tus = 0;
         if (!mt_plan(&tp, &tus, M, N - t * 256, K0, K1, cap, false)) break;
-        const double us = mt_time_us(CFG_MC4, nbm * t, kt) + tus;
+        const double us = launch_time_us(CFG_MC4, nbm, t, 1, kt, odd) + tus;
         if (us < best) {
           best = us;
           *out = GemmPlan{};
@@ -202,13 +218,13 @@ GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int 
       break;
     }
   }
-  // 16-bit products with more than 32 rows and columns run on the matrix-core kernels, with no more scratch than the plan
-  // above, whose need stays the one that is reported: the size of a workspace that callers keep is a matter of the
-  // product, not of the kernel it runs on.
+  // 16-bit products with more than 32 rows and columns run on the matrix-core kernels where those are modelled faster than
+  // the plan above (256x256 tiles are among theirs), with no more scratch than it takes: its need stays the one that is
+  // reported, the size of a workspace that callers keep is a matter of the product, not of the kernel it runs on.
   if (dtype != DT_F32 && !b_int4 && force_cfg < 0 && force_splits <= 0 && M > 32 && N > 32) {
     GemmPlan q;
     double us = 0;
-    if (mt_plan(&q, &us, M, N, K0, K1, p.partial_bytes, true)) {
+    if (mt_plan(&q, &us, M, N, K0, K1, p.partial_bytes, true) && (p.cfg == CFG_MC4 || us < plan_time_us(p, M, N, K0, K1))) {
       q.partial_bytes = p.partial_bytes;
       return q;
     }
@@ -218,6 +234,16 @@ GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int 
 
 GemmPlan gemm_tail_plan(const GemmPlan& main, int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1) {
   return gemm_plan(dtype, M, N - main.tail_n0, K0, K1, main.tail_cfg, main.tail_splits);
+}
+
+double plan_time_us(const GemmPlan& p, int64_t M, int64_t N, int64_t K0, int64_t K1) {
+  if (p.tail_n0 > 0) {
+    GemmPlan main = p;
+    main.tail_n0 = 0;
+    return plan_time_us(main, M, p.tail_n0, K0, K1) + plan_time_us(gemm_tail_plan(p, DT_BF16, M, N, K0, K1), M, N - p.tail_n0, K0, K1);
+  }
+  const int64_t kt = p.splits > 1 ? p.tiles_per_split : (K0 + 63) / 64 + (K1 + 63) / 64;
+  return launch_time_us(p.cfg, p.nbm, p.nbn, p.splits, kt, odd_lines(N, K0)) + split_time_us(M, N, p.splits);
 }
 
 GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1) {
@@ -463,13 +489,13 @@ hipError_t splitk_reduce_launch(int dtype, const float* partial, int splits, int
 FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_bytes) {
   FewPlan best;
   if (n < 1 || n > kFewMaxRows || r > kFewMaxR || n > (1LL << 30)) return best;
-  const int64_t nbm = (n + 63) / 64, tiles = nbm * ((o + 127) / 128 + (r + 127) / 128);
+  const int64_t nbm = (n + 63) / 64, nbn = (o + 127) / 128 + (r + 127) / 128;
   const int64_t kt = (i + 63) / 64;
   for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
     const int64_t per = (kt + s - 1) / s;
     if ((kt + per - 1) / per != s) continue;  // no empty slice
     if ((size_t)s * (size_t)n * (size_t)(o + r) * sizeof(float) > scratch_bytes) break;
-    const double us = mt_time_us(CFG_MTM64, tiles * s, per) + 3.0 + (double)n * (double)(o + r) * (8.0 * s + 2.0) / 7.5e6;
+    const double us = launch_time_us(CFG_MTM64, nbm, nbn, s, per, odd_lines(o, i)) + 3.0 + (double)n * (double)(o + r) * (8.0 * s + 2.0) / 7.5e6;
     if (best.splits == 0 || us < best.us) {
       best.splits = s;
       best.tiles_per_split = (int)per;

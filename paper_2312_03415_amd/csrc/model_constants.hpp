@@ -14,7 +14,7 @@ struct TileModel {
 };
 
 struct ModelConstants {
-  TileModel tile[2][CFG_STREAM];  // [0] = bf16/fp16, [1] = fp32 (the middle-sized kernel's: mt_time_us, gemm.hpp)
+  TileModel tile[2][CFG_STREAM];  // [0] = bf16/fp16, [1] = fp32 (the middle-sized kernel's: launch_time_us, gemm.hpp)
   double stream_tbps[2];         // streaming kernel, big operand row-major / stored [K,M]
   double stream_fix_us;          // its fixed cost per launch
   double reduce_tbps;            // second stage of a split contraction: rate over the partials' round trip

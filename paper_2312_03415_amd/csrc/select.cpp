@@ -53,7 +53,8 @@ static double gemm_time_us(const GemmDesc& d, const GemmPlan& p) {
   }
   if (cfg_is_mt(p.cfg)) {
     const int64_t kt = (d.K[0] + p.bk - 1) / p.bk + (d.nseg > 1 ? (d.K[1] + p.bk - 1) / p.bk : 0);
-    return mt_time_us(p.cfg, (int64_t)p.nbm * p.nbn * p.splits, p.splits > 1 ? p.tiles_per_split : kt) + split_time_us(d.M, d.N, p.splits);
+    return launch_time_us(p.cfg, p.nbm, p.nbn, p.splits, p.splits > 1 ? p.tiles_per_split : kt, odd_lines(d.N, d.K[0])) +
+           split_time_us(d.M, d.N, p.splits);
   }
   const TileModel& tm = mc.tile[d.dtype == DT_F32 ? 1 : 0][p.cfg];
   const int lay = d.a_strided ? 2 : (d.b_kcontig ? 1 : 0);

@@ -1,0 +1,45 @@
+"""Host-side checks of the plans the library makes for its launches (no GPU): what is taken is never modelled slower than what it
+stands in for."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB_DIR = os.path.join(HERE, "..", "paper_2312_03415_amd")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plans") / "plan_probe")
+    p = subprocess.run([HIPCC, "-std=c++17", "-O1", "--offload-arch=gfx950", os.path.join(HERE, "plan_probe.cpp"), "-o", exe,
+                        "-L" + LIB_DIR, "-lrunlora", "-Wl,-rpath," + os.path.abspath(LIB_DIR)], capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr[-2000:]
+
+    def ask(kind, rows):
+        text = "".join(kind + " " + " ".join(str(v) for v in r) + "\n" for r in rows)
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.strip().split("\n")
+        assert len(out) == len(rows)
+        return [[float(v) for v in line.split()] for line in out]
+    return ask
+
+
+def products():
+    rng = np.random.default_rng(5)
+    dims = lambda hi: int(np.exp(rng.uniform(np.log(40), np.log(hi)))) // 8 * 8
+    return [(int(np.exp(rng.uniform(np.log(33), np.log(8192)))), dims(12000), dims(12000), int(rng.choice([0, 8, 32, 128]))) for _ in range(400)]
+
+
+def test_a_products_plan_is_not_modelled_slower_than_the_generic_engines(probe):
+    rows = products()
+    for r, (cfg, splits, tail, part, us, gcfg, gus) in zip(rows, probe("product", rows)):
+        assert us <= gus * (1 + 1e-9), (r, cfg, splits, us, gcfg, gus)
+
+
+def test_rows_that_split_lines_are_priced(probe):
+    """4096 x 2056 x 5464: rows of 5464 and 2056 elements are no whole 128-byte lines, and narrow tiles pay most for them
+    (64x128 tiles 182-201 us, 256x256 123-137); short contractions of many tiles stay on the middle-sized kernel."""
+    wide, narrow = probe("product", [(4096, 2056, 5464, 0), (1024, 768, 768, 0)])
+    assert wide[0] == 7 and narrow[0] >= 12
