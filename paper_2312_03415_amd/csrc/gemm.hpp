@@ -140,6 +140,8 @@ struct FewPlan {
   double us = 0;   // modelled time
 };
 constexpr int64_t kFewMaxRows = 256, kFewMaxR = 128;
+// us per MB of operands that few rows read from HBM, beyond launch_time_us (in FewPlan::us; to be added to what it is compared with)
+constexpr double kColdUsPerMB = 0.09;
 // scratch_bytes: what the call has for partials whatever route it takes
 FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_bytes);
 hipError_t few_run(int dtype, const FewDesc& d, const FewPlan& plan, float* scratch, hipStream_t stream);
@@ -170,7 +172,7 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
 // ---- rank-r products with r > 32 on the middle-sized matrix-core kernel, 16-bit types, no mask ------------------
 // One product (gemm_run with the plan) or two in one launch (mt_pair_run); `cap` = scratch bytes the plan may use.  False
 // where the streaming kernel is modelled faster.
-bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan);
+bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us = nullptr);
 GemmDesc rank_desc(int dtype, const SkinnyDesc& d);  // the product as gemm_run takes it
 struct MtPairPlan {
   int cfg[2] = {0, 0}, splits[2] = {1, 1}, tiles_per_split[2] = {0, 0};

@@ -45,6 +45,7 @@ static LaunchModel launch_model(int cfg) {
   switch (cfg) {
     case CFG_MID: return {512, 3.8, 1.04, 1.26, 0.0, 0.51, 0.05, 1360};
     case CFG_TALL64: return {768, 2.7, 0.78, 1.13, 0.0, 0.59, 0.0, 1240};
+    case CFG_WIDE32: return {768, 3.6, 0.35, 0.6, 0.0, 0.5, 0.09, 860};  // (priced for few_forward only)
     case CFG_WIDE64: return {768, 3.7, 0.89, 1.19, 2.8, 4.01, 0.09, 860};
     case CFG_MT128: return {512, 3.5, 0.66, 0.89, 0.0, 0.42, 0.18, 1130};
     case CFG_MT128D: return {256, 5.2, 0.42, 0.51, 1.8, 0.43, 0.15, 1380};
@@ -55,17 +56,21 @@ static LaunchModel launch_model(int cfg) {
   }
 }
 
-double launch_time_us(int cfg, int64_t nbm, int64_t nbn, int splits, int64_t ktiles, double odd) {
-  const LaunchModel m = launch_model(cfg);
-  const int64_t tiles = nbm * nbn, wgs = tiles * splits, rounds = wgs / m.slots, rest = wgs % m.slots;
-  // operand bytes of a K tile that an XCD's resident workgroups want, each once: they hold a run of tiles in bands of eight
-  // tile rows (per K slice), of which those in a row share A and those in a column share B
+// Operand KB of a K tile that an XCD's resident workgroups want, each once: they hold a run of tiles in bands of eight tile rows
+// (per K slice), of which those in a row share A and those in a column share B.
+static double xcd_kbytes(int cfg, int64_t nbm, int64_t nbn, int64_t wgs, int64_t slots) {
   auto kb = [&](int64_t run) {
     const int64_t band = nbm < 8 ? nbm : 8, rows = run < band ? run : band, cols = (run + rows - 1) / rows;
     return (double)(rows * kTileBM[cfg] + cols * kTileBN[cfg]) * 0.128;
   };
-  const int64_t per_xcd = (tiles + 7) / 8, most = m.slots / 8, resident = (wgs + 7) / 8 < most ? (wgs + 7) / 8 : most;
-  const double bytes = resident >= per_xcd ? (double)resident / (double)per_xcd * kb(per_xcd) : kb(resident);
+  const int64_t per_xcd = (nbm * nbn + 7) / 8, most = slots / 8, resident = (wgs + 7) / 8 < most ? (wgs + 7) / 8 : most;
+  return resident >= per_xcd ? (double)resident / (double)per_xcd * kb(per_xcd) : kb(resident);
+}
+
+double launch_time_us(int cfg, int64_t nbm, int64_t nbn, int splits, int64_t ktiles, double odd) {
+  const LaunchModel m = launch_model(cfg);
+  const int64_t tiles = nbm * nbn, wgs = tiles * splits, rounds = wgs / m.slots, rest = wgs % m.slots;
+  const double bytes = xcd_kbytes(cfg, nbm, nbn, wgs, m.slots);
   const double feed = bytes * (1.0 + odd) / m.fabric;
   auto tile = [&](double t) { t += m.split_lines * odd; return t > feed ? t : feed; };
   double per_k = (double)rounds * tile(m.full);
@@ -484,18 +489,36 @@ hipError_t splitk_reduce_launch(int dtype, const float* partial, int splits, int
 
 // ---- few-token forward ---------------------------------------------------------------------------------
 
-// Two launches where [X|T] [W;B] after T = X A takes three or four: taken whenever the scratch the call has anyway holds
-// the partials of at least one slicing.  Up to 256 rows; beyond, the rows fill the chip without a split.
+// What few_run's two launches take, us, fitted to the kernel times of 396 layers (n 1 .. 256, 512 .. 11008 wide, r 8 .. 128, W
+// from HBM) in every slicing.  The first: as launch_time_us, with the operands' bytes (few rows share W), the fp32 partials, and
+// what a second workgroup on some of the compute units costs while the others wait (64 x 8192 -> 8192: 195 workgroups 29 us, 260
+// 40, 455 32).  The second (lora_finish.hpp): a thread walks the rank's rows of B, a workgroup's threads form its rows of T from
+// all slices (four loads in flight), and T B is n o r products on the vector units: 3.9 us at r 8, 23 with 16 slices at 64 x 8192
+// -> 1024, r 128, 35 at 256 x 4096 -> 11008, r 128.  The slicing chosen costs 2 % more than the best on average (25 % at worst).
+static double few_time_us(int64_t n, int64_t i, int64_t o, int64_t r, int splits, int64_t ktiles) {
+  const int64_t nbm = (n + 63) / 64, nbn = (o + 127) / 128 + (r + 127) / 128, wgs = nbm * nbn * splits, rounds = wgs / 512, rest = wgs % 512;
+  const double feed = xcd_kbytes(CFG_MTM64, nbm, nbn, wgs, 512) / 2080;
+  const double uneven = wgs > 256 && wgs < 512 ? (double)(512 - wgs) / 256.0 : 0.0;
+  const double per_k = (double)rounds * (feed > 0.35 ? feed : 0.35) + (rest == 0 ? 0.0 : (feed > (rest <= 256 ? 0.25 : 0.35) ? feed : (rest <= 256 ? 0.25 : 0.35)));
+  const double first = 2.9 + 2e-6 * (double)(n * i + i * o + i * r) * (kColdUsPerMB + 0.02 * uneven) + (double)ktiles * (per_k + 0.065 * uneven) +
+                       1.5e-6 * (double)n * (double)(o + r) * splits;
+  int64_t ry = 1;
+  while (ry < 32 && ry < n) ry *= 2;  // rows and column chunks of a workgroup, as it is launched
+  const int64_t cx = 64 / ry > 8 ? 64 / ry : 8, loads = (r + cx - 1) / cx * (splits / 4 + splits % 4);
+  const double second = 3.7 + 0.05 * (double)(r > 32 ? r - 32 : 0) + 0.17 * (double)loads + (double)n * (double)o * (3.6e-8 * (double)r + 2.1e-7 * splits);
+  return first + second;
+}
+
+// The slicing of the first launch whose partials fit the scratch the call has anyway.
 FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_bytes) {
   FewPlan best;
   if (n < 1 || n > kFewMaxRows || r > kFewMaxR || n > (1LL << 30)) return best;
-  const int64_t nbm = (n + 63) / 64, nbn = (o + 127) / 128 + (r + 127) / 128;
   const int64_t kt = (i + 63) / 64;
   for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
     const int64_t per = (kt + s - 1) / s;
     if ((kt + per - 1) / per != s) continue;  // no empty slice
     if ((size_t)s * (size_t)n * (size_t)(o + r) * sizeof(float) > scratch_bytes) break;
-    const double us = launch_time_us(CFG_MTM64, nbm, nbn, s, per, odd_lines(o, i)) + 3.0 + (double)n * (double)(o + r) * (8.0 * s + 2.0) / 7.5e6;
+    const double us = few_time_us(n, i, o, r, s, per);
     if (best.splits == 0 || us < best.us) {
       best.splits = s;
       best.tiles_per_split = (int)per;
@@ -581,7 +604,15 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
   }
   double rate = plan.rt == 1 ? (d[0].a_strided ? 4.4 : 4.8) : (plan.rt == 2 ? 2.8 : 2.1);
   if (nprob == 1) rate *= plan.rt == 1 ? 0.65 : 0.8;
-  return (plan.rt == 1 || nprob == 1 ? 5.0 : 9.0) + bytes / (rate * 1e6) + (plan.splits > 1 ? 3.0 + outs * 8.0 * plan.splits / 7.5e6 : 0.0);
+  double us = (plan.rt == 1 || nprob == 1 ? 5.0 : 9.0) + bytes / (rate * 1e6);
+  if (nprob == 1 && dtype != DT_F32 && !d[0].a_strided) {
+    // few rows: a workgroup's four waves walk their K tiles one after the other, 0.35 / 0.62 / 1.27 us each with up to 32 / 64 /
+    // 128 columns (T of 1 .. 256 rows: 4.7 / 5.7 / 7.7 us at K 512, 6.6 / 9.9 / 15.4 at 2048)
+    const double tiles = (double)(((d[0].K + 63) / 64 + 4 * plan.splits - 1) / (4 * plan.splits));
+    const double chain = plan.rt == 1 ? 4.4 + 0.35 * tiles : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles);
+    if (chain > us) us = chain;
+  }
+  return us + (plan.splits > 1 ? 4.0 + outs * 8.0 * plan.splits / 7.5e6 : 0.0);
 }
 
 // ---- rank-r products with r > 32 on the middle-sized kernel ------------------------------------------------------
@@ -621,7 +652,7 @@ static bool rank_shape_ok(int dtype, const SkinnyDesc& d) {
   return dtype != DT_F32 && d.N > 32 && d.M > 32 && d.drop_thr == 0;
 }
 
-bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan) {
+bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us) {
   if (!rank_shape_ok(dtype, d)) return false;
   const GemmDesc g = rank_desc(dtype, d);
   const int cfg = g.N == d.N ? CFG_MTN64 : CFG_MTM64;
@@ -650,6 +681,7 @@ bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan) {
     plan->tiles_per_split = (int)per;
     plan->partial_bytes = part;
   }
+  if (found && plan_us != nullptr) *plan_us = best;
   return found;
 }
 

@@ -201,24 +201,32 @@ struct Builder {
     }
     out->steps.push_back(s);
   }
-  // forward1 for a few tokens in two launches; false where it does not apply.  The scratch is what forward1's launches
-  // would take, so that a call's workspace does not depend on the route.
+  // forward1 for a few tokens in two launches; false where it does not apply or is modelled slower than forward1's launches
+  // (few rows or a low rank: 48 x 4096 -> 11008, r 32 takes 24 us so and 33 by T = X A and [X|T] [W;B]; at 256 rows, r 128 it
+  // would be 87 and 55).  The scratch is what forward1's launches would take, so that a call's workspace does not depend on
+  // the route.
   bool few_forward(const char* what, Mat X, Mat W, Mat A, Mat B, Mat Y, Mat T, bool keep_T, const void* bias) {
     if (L.dtype == DT_F32 || L.w_int4 || L.drop_thr || L.n > kFewMaxRows || L.r > kFewMaxR) return false;
     // gemm_mt.hpp addresses its operands with 31-bit byte offsets
     if (L.n * X.ld >= (1LL << 30) || L.i * W.ld >= (1LL << 30) || L.i * A.ld >= (1LL << 30)) return false;
     const SkinnyDesc sd = to_skinny({0, 0, L.n, L.r, L.i, X, A, T, true});
-    size_t bytes = skinny_plan(L.dtype, 1, &sd).partial_bytes;
-    const size_t gemm_bytes = gemm_plan(L.dtype, L.n, L.o, L.i, L.r).partial_bytes;
-    if (gemm_bytes > bytes) bytes = gemm_bytes;
+    const SkinnyPlan skp = skinny_plan(L.dtype, 1, &sd);
+    const GemmPlan gp = gemm_plan(L.dtype, L.n, L.o, L.i, L.r);
+    const size_t bytes = skp.partial_bytes > gp.partial_bytes ? skp.partial_bytes : gp.partial_bytes;
     const FewPlan plan = rl::few_plan(L.n, L.i, L.o, L.r, bytes);
     if (plan.splits == 0) return false;
+    GemmPlan rank;
+    double t_us = 0;
+    if (!rank_plan(L.dtype, sd, bytes, &rank, &t_us)) t_us = skinny_time_us(L.dtype, 1, &sd, skp);
+    const double cold_us = kColdUsPerMB * 2e-6 * (double)(L.n * L.i + L.i * L.o);
+    if (plan.us >= t_us + plan_time_us(gp, L.n, L.o, L.i, L.r) + cold_us) return false;
     if (bytes > max_partial) max_partial = bytes;
     Step s;
     s.what = what;
     s.is_few = true;
     s.d.dtype = L.dtype;
     s.few_plan = plan;
+    s.few_plan.us -= cold_us;  // (the selector prices the other forwards without it)
     FewDesc& f = s.few;
     f.X = X.ptr; f.ldx = X.ld; f.W = W.ptr; f.ldw = W.ld; f.A = A.ptr; f.lda = A.ld; f.B = B.ptr; f.ldb = B.ld;
     f.Y = const_cast<void*>(Y.ptr); f.ldy = Y.ld;

@@ -3,7 +3,7 @@
 #include <cstdio>
 #include <cstring>
 
-#include "../paper_2312_03415_amd/csrc/gemm.hpp"
+#include "../paper_2312_03415_amd/csrc/schedule.hpp"
 
 using namespace rl;
 
@@ -16,6 +16,20 @@ int main() {
       const GemmPlan f = gemm_plan(DT_F32, M, N, K0, K1);  // (the rule by tile counts names its shape for fp32 too)
       const GemmPlan g = gemm_plan(DT_BF16, M, N, K0, K1, f.cfg == CFG_BIG ? CFG_MC4 : f.cfg);
       std::printf("%d %d %ld %zu %.3f %d %.3f\n", p.cfg, p.splits, (long)p.tail_n0, p.partial_bytes, plan_time_us(p, M, N, K0, K1), g.cfg, plan_time_us(g, M, N, K0, K1));
+    } else if (std::strcmp(kind, "few") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: the few-token route's price and taken or not
+      SkinnyDesc d;
+      d.M = M; d.N = K1; d.K = N;
+      const GemmPlan g = gemm_plan(DT_BF16, M, K0, N, K1);
+      const SkinnyPlan t = skinny_plan(DT_BF16, 1, &d);
+      const size_t bytes = t.partial_bytes > g.partial_bytes ? t.partial_bytes : g.partial_bytes;
+      const FewPlan f = few_plan(M, N, K0, K1, bytes);
+      GemmPlan rank;
+      double t_us = 0;
+      if (!rank_plan(DT_BF16, d, bytes, &rank, &t_us)) t_us = skinny_time_us(DT_BF16, 1, &d, t);
+      Schedule sch;
+      const bool ok = build_forward(1, LayerDims{M, N, K0, K1, DT_BF16}, FwdOperands{}, nullptr, &sch);
+      std::printf("%d %d %.3f %.3f %zu\n", ok && sch.steps[0].is_few ? 1 : 0, f.splits, f.us,
+                  t_us + plan_time_us(g, M, K0, N, K1) + kColdUsPerMB * 2e-6 * (double)(M * N + N * K0), sch.workspace_bytes);
     }
   }
   return 0;

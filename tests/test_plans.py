@@ -18,7 +18,7 @@ def probe(tmp_path_factory):
                         "-L" + LIB_DIR, "-lrunlora", "-Wl,-rpath," + os.path.abspath(LIB_DIR)], capture_output=True, text=True)
     assert p.returncode == 0, p.stderr[-2000:]
 
-    def ask(kind, rows):
+    def ask(kind, rows):  # product: M, N, K, K of a second segment; few: tokens, d_in, d_out, r
         text = "".join(kind + " " + " ".join(str(v) for v in r) + "\n" for r in rows)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.strip().split("\n")
         assert len(out) == len(rows)
@@ -43,3 +43,18 @@ def test_rows_that_split_lines_are_priced(probe):
     (64x128 tiles 182-201 us, 256x256 123-137); short contractions of many tiles stay on the middle-sized kernel."""
     wide, narrow = probe("product", [(4096, 2056, 5464, 0), (1024, 768, 768, 0)])
     assert wide[0] == 7 and narrow[0] >= 12
+
+
+def test_the_few_token_route_is_taken_where_it_is_modelled_faster(probe):
+    """Two launches with the partials of [X W | X A] against T = X A and [X|T] [W;B]: a matter of rows and rank (256 x 4096 -> 11008,
+    r 128: 87 us and 55; 48 rows, r 32: 24 and 33), and the workspace is the same either way."""
+    rng = np.random.default_rng(6)
+    rows = [(int(np.exp(rng.uniform(0, np.log(256)))), int(rng.integers(64, 1376)) * 8, int(rng.integers(64, 1376)) * 8, int(rng.choice([8, 32, 64, 128])))
+            for _ in range(300)]
+    taken = 0
+    for r, (few, splits, us, other, ws) in zip(rows, probe("few", [(n, i, o, k) for n, i, o, k in rows])):
+        assert bool(few) == (splits > 0 and us < other), (r, splits, us, other)
+        taken += int(few)
+    assert 150 < taken < 300
+    wide, small, one = probe("few", [(256, 4096, 11008, 128), (48, 4096, 11008, 32), (1, 4096, 4096, 16)])
+    assert not wide[0] and small[0] and one[0]
