@@ -189,17 +189,21 @@ extern "C" int runlora_select_by(int criterion, int64_t n, int64_t i, int64_t o,
   L.w_int4 = int4;
   int bf = 1, bb = 1;
   double cf = 0, cb = 0;
-  // Modelled times closer than the model's own error (3 %, or 2.5 us of a short layer) are a tie: the lower id rounds fewer
-  // intermediates to 16 bits (forward1 no W + AB, Algorithm 1 no X^T dY and no W + AB).  fp32 has nothing to lose.
+  // 16-bit layers: a graph that rounds more intermediates than the one picked so far (forward2 and Algorithms 4, 5: W + AB,
+  // Algorithms 2, 3: X^T dY, the default chain: XW) has to be modelled more than 3 % and more than 2.5 us faster, the model's own
+  // error: 12 layers of 28-50 us where a merged graph was modelled 2-2.5 us faster all ran 1-14 % slower on it.  Forward 3 rounds
+  // what forward1 rounds and takes one launch less (64 x 80: 4.4 us and 8.1): no margin.  fp32 has nothing to lose.
   const bool strict = criterion == 0 || dt == DT_F32;
-  const double tie = strict ? 1.0 : 0.97, gap = strict ? 0.0 : 2.5;
+  auto beats = [&](double c, double current, bool rounds_more) {
+    return strict || !rounds_more ? c < current : c < 0.97 * current && c < current - 2.5;  // strict '<': ties go to the lower id
+  };
   for (int v = 1; v <= fmax; ++v) {
     double c = criterion == 0 ? (double)table1_flops(0, v, n, i, o, r) : model_time_us(0, v, L);
-    if (v == 1 || (c < tie * cf && c < cf - gap)) { cf = c; bf = v; }  // strict '<': ties go to the lower id
+    if (v == 1 || beats(c, cf, v != 3)) { cf = c; bf = v; }
   }
   for (int v = 1; v <= bmax; ++v) {
     double c = criterion == 0 ? (double)table1_flops(1, v, n, i, o, r) : model_time_us(1, v, L);
-    if (v == 1 || (c < tie * cb && c < cb - gap)) { cb = c; bb = v; }
+    if (v == 1 || beats(c, cb, true)) { cb = c; bb = v; }
   }
   // The default chain (keeps XA, no fusion) is a legal pair too; under the time criterion it is
   // returned when the model says it beats the best RunLoRA pair (large r at few tokens, where the
@@ -212,7 +216,7 @@ extern "C" int runlora_select_by(int criterion, int64_t n, int64_t i, int64_t o,
       const double f2 = model_time_us(0, 2, L);
       for (int v = 4; v <= 5; ++v) {
         const double c = f2 + model_time_us(1, v, L, true);
-        if (c < cf + cb) { cf = f2; cb = c - f2; bf = 2; bb = v; }
+        if (beats(c, cf + cb, true)) { cf = f2; cb = c - f2; bf = 2; bb = v; }
       }
     }
     // Criterion 3, for callers that let forward1 keep T = XA (n r elements): forward1 paired with the backwards that
@@ -221,11 +225,11 @@ extern "C" int runlora_select_by(int criterion, int64_t n, int64_t i, int64_t o,
       const double f1 = model_time_us(0, 1, L);
       for (int v = 1; v <= bmax; v += 4) {  // Algorithms 1 and 5
         const double c = f1 + model_time_us(1, v, L, false, true);
-        if (c < cf + cb) { cf = f1; cb = c - f1; bf = 1; bb = v; }
+        if (beats(c, cf + cb, v != 1)) { cf = f1; cb = c - f1; bf = 1; bb = v; }
       }
     }
     const double c0 = model_time_us(0, 0, L) + model_time_us(1, 0, L);
-    if (c0 < cf + cb) { bf = 0; bb = 0; }
+    if (beats(c0, cf + cb, true)) { bf = 0; bb = 0; }
   }
   *fwd = bf;
   *bwd = bb;
