@@ -9,7 +9,7 @@ Cache does not serve them, on problems long enough that the GPU and not the call
 sets the time.  Per tile shape and operand layout two contraction lengths give the
 time per K tile and the fixed cost of a round of workgroups; a third run with an addend gives the
 fixed cost with D; the streaming kernel is timed on both orientations of the big operand; the
-W + AB kernel on two sizes through the merged forward's own step timing; a tiny problem gives the
+W + AB kernel on its own duration in the merged forward, with W from HBM; a tiny problem gives the
 launch cost.
 """
 import argparse
@@ -103,26 +103,32 @@ def main():
             tiles[fam][cfg] = dict(tk=tk, fix=sum(fix) / 3.0, fix_d=fix_d)
             print(fam, NAMES[cfg], [round(v, 3) for v in tk], round(tiles[fam][cfg]["fix"], 2), round(fix_d, 2), flush=True)
 
-    # W + AB kernel: per-step event times of the merged forward on two sizes -> rate and fixed cost
-    def merge_time(i, o, r=32, n=256, sets=4):
-        X = torch.randn(n, i, device="cuda").to(bf)
-        As = [torch.randn(i, r, device="cuda").to(bf) for _ in range(sets)]
-        Bs = [torch.randn(r, o, device="cuda").to(bf) for _ in range(sets)]
-        Ws = [torch.randn(i, o, device="cuda").to(bf) for _ in range(sets)]
+    # W + AB kernel: its own duration in the merged forward.  Fixed cost: a small W in the caches; rate: a large one, each call
+    # behind a 512 MB fill (in a model the caches hold other layers' results by then, which its reads evict); and what r 64 and
+    # 128 add to a 4096 x 4096 W
+    flush = torch.empty(1 << 29, dtype=torch.uint8, device="cuda")
+
+    def merge_time(i, o, r=32, cold=True, n=256, reps=20):
+        X, W = torch.randn(n, i, device="cuda").to(bf), torch.randn(i, o, device="cuda").to(bf)
+        A, B = torch.randn(i, r, device="cuda").to(bf), torch.randn(r, o, device="cuda").to(bf)
         Yb = torch.empty(n, o, device="cuda", dtype=bf)
-        wss = [rl.new_workspace(2, -1, n, i, o, r, rl.RL_BF16) for _ in range(sets)]
+        ws = rl.new_workspace(2, -1, n, i, o, r, rl.RL_BF16)
         rl.runlora_profile_enable(4096)
-        for k in range(20):
-            rl.runlora_forward(2, X, Ws[k % sets], As[k % sets], Bs[k % sets], Yb, rl.new_saved(), workspace=wss[k % sets])
+        rl.runlora_profile_kernel_times(True)
+        for k in range(reps):
+            if cold:
+                flush.fill_(k)
+            rl.runlora_forward(2, X, W, A, B, Yb, rl.new_saved(), workspace=ws)
         torch.cuda.synchronize()
         rec = rl.runlora_profile_collect(4096)
+        rl.runlora_profile_kernel_times(False)
         rl.runlora_profile_disable()
-        m = sorted(x["us"] for x in rec[8:] if "W + A B" in x["what"])
+        m = sorted(x["main_us"] for x in rec[8:] if "W + A B" in x["what"])
         return m[len(m) // 2]
-    tm_b, tm_s = merge_time(8192, 8192), merge_time(4096, 4096)
-    merge_tbps = 2.0 * 2.0 * (8192.0 * 8192 - 4096.0 * 4096) / (tm_b - tm_s) / 1e6
-    merge_fix = max(tm_s - 2.0 * 2.0 * 4096 * 4096 / merge_tbps / 1e6 - launch, 0.0)
-    print("merge_tbps", round(merge_tbps, 2), "fix", round(merge_fix, 2), flush=True)
+    merge_fix = merge_time(512, 512, cold=False)
+    merge_tbps = 2.0 * 2.0 * 8192.0 * 8192 / (merge_time(8192, 8192) - merge_fix) / 1e6
+    merge_rank = [max(merge_time(4096, 4096, r) - merge_time(4096, 4096), 0.0) for r in (64, 128)]
+    print("merge_tbps", round(merge_tbps, 2), "fix", round(merge_fix, 2), "r 64, 128", [round(v, 2) for v in merge_rank], flush=True)
 
     # streaming kernel: two sizes per orientation -> rate and fixed cost
     def stream(layout, M, K, sets):
@@ -175,12 +181,14 @@ def main():
       %.2f,
       %.2f,
       %.2f,
+      %.2f,
+      %.2f,
   };
   return c;
 }
 
 }  // namespace rl
-""" % (body, rates[0], rates[1], sum(fixes) / 2.0, reduce_tbps, reduce_fix, launch, merge_tbps, merge_fix)
+""" % (body, rates[0], rates[1], sum(fixes) / 2.0, reduce_tbps, reduce_fix, launch, merge_tbps, merge_fix, *merge_rank)
     with open(args.out, "w") as fh:
         fh.write(out)
     print("wrote", args.out)

@@ -1,6 +1,9 @@
 // Constants of the selector's time model, measured on one MI355X with this library's own kernels.
-// GENERATED by `python -m paper_2312_03415_amd.calibrate` (run on the GPU); regenerate after
-// changing a kernel.  Times in microseconds, rates in TB/s.
+// The values below are GENERATED by `python -m paper_2312_03415_amd.calibrate` (run on the GPU); regenerate after
+// changing a kernel.  Times in microseconds, rates in TB/s.  Not among them: the launch models that choose tile shapes, K splits
+// and routes (launch_model, few_time_us, skinny_time_us, rank_time_us, split_time_us, int4_direct_us in gemm_host.hip), fitted by
+// hand to the sweeps that their comments describe.  The 256x256 kernel has a price in both: here at the power-limited rate of
+// long runs, for comparing graphs, there for one product, for comparing tile shapes.
 #pragma once
 #include "gemm.hpp"
 
@@ -20,8 +23,9 @@ struct ModelConstants {
   double reduce_tbps;            // second stage of a split contraction: rate over the partials' round trip
   double reduce_fix_us;          // its fixed cost beyond the launch
   double launch_us;              // fixed cost per kernel launch seen by the caller
-  double merge_tbps;             // M = W + A B kernel: rate over 2 i o e bytes
+  double merge_tbps;             // M = W + A B kernel: rate over 2 i o e bytes, W from HBM behind dirty caches, as in a model
   double merge_fix_us;           // its fixed cost
+  double merge_r64_us, merge_r128_us;  // what it takes longer at r 64 and 128 than at 32 (4096 x 4096)
 };
 
 inline const ModelConstants& model_constants() {
@@ -52,8 +56,10 @@ inline const ModelConstants& model_constants() {
       5.58,
       2.75,
       6.44,
-      3.60,  // (W from HBM, as in a model; 4.95 while the Infinity Cache holds part of it)
-      2.52,
+      3.96,
+      5.48,
+      11.04,
+      8.04,
   };
   return c;
 }

@@ -53,8 +53,10 @@ static double gemm_time_us(const GemmDesc& d, const GemmPlan& p) {
   }
   if (cfg_is_mt(p.cfg)) {
     const int64_t kt = (d.K[0] + p.bk - 1) / p.bk + (d.nseg > 1 ? (d.K[1] + p.bk - 1) / p.bk : 0);
+    // an addend is read in the epilogue, nothing hides it: W + A B at r 256, 2048 x 8192: 35 us, 18 by the products alone
+    const double addend = d.has_addend || d.D != nullptr ? e * (double)d.M * (double)d.N / 2.0e6 : 0.0;
     return launch_time_us(p.cfg, p.nbm, p.nbn, p.splits, p.splits > 1 ? p.tiles_per_split : kt, odd_lines(d.N, d.K[0])) +
-           split_time_us(d.M, d.N, p.splits);
+           split_time_us(d.M, d.N, p.splits) + addend;
   }
   const TileModel& tm = mc.tile[d.dtype == DT_F32 ? 1 : 0][p.cfg];
   const int lay = d.a_strided ? 2 : (d.b_kcontig ? 1 : 0);
@@ -106,8 +108,13 @@ static double step_time_us(const Step& s) {
   const double e = (double)dtype_size(s.d.dtype);
   if (s.is_few) return s.few_plan.us;
   if (s.is_panel) return s.panel.us;
-  if (s.is_merge)
-    return e * 2.0 * (double)s.mg.I * (double)s.mg.O / (mc.merge_tbps * 1e12) * 1e6 + mc.merge_fix_us;
+  if (s.is_merge) {
+    // beyond r = 32 a block's A B takes longer than its share of W; less so while W is small (2048 x 2048: 4.0 and 2.8 us more
+    // at r 64 and 128, 4096 x 4096 10.6 and 7.4)
+    const double outs = (double)s.mg.I * (double)s.mg.O;
+    const double rank = (s.mg.R <= 32 ? 0.0 : (s.mg.R <= 64 ? mc.merge_r64_us : mc.merge_r128_us)) * (outs > 4.2e6 ? 1.0 : 0.4);
+    return e * 2.0 * outs / (mc.merge_tbps * 1e12) * 1e6 + mc.merge_fix_us + rank;
+  }
   if (s.is_mtpair) return s.mtpair.us;
   if (s.nsk > 0 && s.d.dtype != DT_F32 && s.skplan.rt > 1) return skinny_time_us(s.d.dtype, s.nsk, s.sk, s.skplan);
   if (s.nsk > 0) {

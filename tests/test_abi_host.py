@@ -131,6 +131,16 @@ def test_select_ties_of_modelled_times():
     assert rl.runlora_select(6, 64, 80, 8, rl.RL_BF16)[0] == 3    # one launch: 4.4 us against 8.1
 
 
+def test_model_constants_have_the_generators_form():
+    """csrc/model_constants.hpp holds what calibrate.py writes: as many values behind the tile tables as its template has, and
+    none annotated by hand (the next calibration would drop the note and the value with it)."""
+    pkg = os.path.join(ROOT, "paper_2312_03415_amd")
+    values = open(os.path.join(pkg, "csrc", "model_constants.hpp")).read().split("       }},\n")[1].split("  };")[0].rstrip("\n").split("\n")
+    assert all(re.fullmatch(r"      (\{\d+\.\d\d, \d+\.\d\d\}|\d+\.\d\d),", v) for v in values), values
+    template = open(os.path.join(pkg, "calibrate.py")).read().split("%s},\n")[1].split("  };")[0].rstrip("\n").split("\n")
+    assert len(template) == len(values)
+
+
 def test_select_with_kept_merged_weight():
     """Criterion 2 prices forward2 + backward4/5 without the second W + AB pass: it may only move the
     choice towards such a pair, never to a slower one under the plain model."""
