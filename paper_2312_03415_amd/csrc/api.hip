@@ -890,7 +890,7 @@ static int check_gemm(const rl_gemm_t* g, GemmDesc* d, GemmPlan* plan) {
     if (g->tile_cfg == CFG_STREAM) return RL_ERR_UNSUPPORTED;  // the streaming kernel has no bias path
     d->bias = g->bias;
   }
-  if (g->tile_cfg != CFG_STREAM) *plan = gemm_plan(dt, g->M, g->N, g->K, g->K2, g->tile_cfg, g->splits);
+  if (g->tile_cfg != CFG_STREAM) *plan = gemm_plan(dt, g->M, g->N, g->K, g->K2, g->tile_cfg, g->splits, false, long_operand(*d));
   return RL_OK;
 }
 

@@ -83,8 +83,12 @@ struct GemmPlan {
 // Tile shape and K split for a problem; depends on shapes and dtype only (never on pointers), so
 // the same plan sizes the workspace and drives the launch.  force_cfg / force_splits (>= 0 / > 0)
 // override the heuristics (used by the tuning sweeps and tests).
+// long_operand: see long_operand below.
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg = -1,
-                   int force_splits = 0, bool b_int4 = false);
+                   int force_splits = 0, bool b_int4 = false, bool long_operand = false);
+// An operand beyond what the middle-sized kernel addresses (31-bit byte offsets; the 256x256 kernel takes twice that): the
+// product keeps the plan by tile counts (same scratch).
+bool long_operand(const GemmDesc& d);
 
 // Modelled time in us of one launch of a 16-bit tile GEMM (CFG_MT*, CFG_MC4, and the generic engine's 128x128, 128x64 and
 // 64x128 tiles): nbm x nbn output tiles x K slices of `ktiles` K tiles each; odd = odd_lines of the product.
@@ -176,6 +180,7 @@ bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, doubl
 GemmDesc rank_desc(int dtype, const SkinnyDesc& d);  // the product as gemm_run takes it
 struct MtPairPlan {
   int cfg[2] = {0, 0}, splits[2] = {1, 1}, tiles_per_split[2] = {0, 0};
+  size_t partial_bytes = 0;
   double us = 0;
 };
 bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan);

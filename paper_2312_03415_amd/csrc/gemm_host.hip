@@ -147,8 +147,18 @@ static bool mt_plan(GemmPlan* out, double* out_us, int64_t M, int64_t N, int64_t
   return best < 1e30;
 }
 
+bool long_operand(const GemmDesc& d) {
+  for (int s = 0; s < d.nseg; ++s) {
+    const int64_t a_rows = d.a_strided ? d.K[s] : d.M, b_rows = d.b_kcontig ? d.N : d.K[s];
+    const int64_t a_cols = d.a_strided ? d.M : d.K[s], b_cols = d.b_kcontig ? d.K[s] : d.N;  // (planned without operands: ld 0)
+    if (a_rows * (d.lda[s] > a_cols ? d.lda[s] : a_cols) >= (1LL << 30)) return true;
+    if (!(s == 0 && d.b_int4) && b_rows * (d.ldb[s] > b_cols ? d.ldb[s] : b_cols) >= (1LL << 30)) return true;
+  }
+  return false;
+}
+
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg,
-                   int force_splits, bool b_int4) {
+                   int force_splits, bool b_int4, bool long_operand) {
   GemmPlan p;
   int cfg;
   if (b_int4 && force_cfg < 0) {
@@ -226,7 +236,7 @@ GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int 
   // 16-bit products with more than 32 rows and columns run on the matrix-core kernels where those are modelled faster than
   // the plan above (256x256 tiles are among theirs), with no more scratch than it takes: its need stays the one that is
   // reported, the size of a workspace that callers keep is a matter of the product, not of the kernel it runs on.
-  if (dtype != DT_F32 && !b_int4 && force_cfg < 0 && force_splits <= 0 && M > 32 && N > 32) {
+  if (dtype != DT_F32 && !b_int4 && !long_operand && force_cfg < 0 && force_splits <= 0 && M > 32 && N > 32) {
     GemmPlan q;
     double us = 0;
     if (mt_plan(&q, &us, M, N, K0, K1, p.partial_bytes, true) && (p.cfg == CFG_MC4 || us < plan_time_us(p, M, N, K0, K1))) {
@@ -399,13 +409,9 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   }
   int nbm = plan.nbm, nbn = plan.nbn;
   if (cfg_is_mt(cfg)) {
-    // gemm_mt.hpp addresses each operand with 31-bit byte offsets; larger ones run on the generic engine (same K tile)
-    bool ok = d.dtype != DT_F32 && plan.bk == 64;
-    for (int s = 0; s < d.nseg; ++s) {
-      const int64_t a_rows = d.a_strided ? d.K[s] : d.M, b_rows = d.b_kcontig ? d.N : d.K[s];
-      if (a_rows * d.lda[s] >= (1LL << 30) || b_rows * d.ldb[s] >= (1LL << 30)) ok = false;
-    }
-    if (!ok) {
+    // gemm_mt.hpp addresses each operand with 31-bit byte offsets; a forced id with a larger one runs on the generic engine
+    // (same K tile)
+    if (d.dtype == DT_F32 || plan.bk != 64 || long_operand(d)) {
       cfg = CFG_MID;
       nbm = (int)((d.M + kTileBM[cfg] - 1) / kTileBM[cfg]);
       nbn = (int)((d.N + kTileBN[cfg] - 1) / kTileBN[cfg]);
@@ -721,6 +727,7 @@ bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan) 
     us += rank_time_us(d[0].a_strided != 0, wgs, per, bytes) + (part > 0 ? 3.0 : 0.0);
     if (us < best) {
       best = us;
+      plan->partial_bytes = part;
       for (int w = 0; w < 2; ++w) { plan->splits[w] = (int)sp[w]; plan->tiles_per_split[w] = (int)tps[w]; }
     }
   }

@@ -25,10 +25,15 @@ struct Builder {
   // workspace larger.
   size_t spare() const { return later_partial > max_partial ? later_partial : max_partial; }
   // the product [M, K0 + K1] x [K0 + K1, N] comes after the rank-r products and brings its own scratch
-  void expect_gemm(int64_t M, int64_t N, int64_t K0, int64_t K1, bool b_is_w) {
+  void expect_gemm(int64_t M, int64_t N, int64_t K0, int64_t K1, bool b_is_w, int64_t lda) {
     const GemmPlan p = b_is_w && L.w_int4 ? gemm_plan_int4(L.dtype, M, N, K0, K1) : gemm_plan(L.dtype, M, N, K0, K1);
     if (p.partial_bytes > later_partial) later_partial = p.partial_bytes;
-    if (b_is_w && L.w_int4 && L.int4_panels) {
+    GemmDesc d;  // (the test gemm() makes before it takes panels)
+    d.M = M; d.N = N; d.K[0] = K0; d.K[1] = K1;
+    d.nseg = K1 > 0 ? 2 : 1;
+    d.lda[0] = lda;
+    d.b_int4 = true;
+    if (b_is_w && L.w_int4 && L.int4_panels && !long_operand(d)) {
       const size_t panel = int4_panel_plan(L.dtype, M, N, K0, K1).scratch_bytes;
       if (panel > later_partial) later_partial = panel;
     }
@@ -89,13 +94,13 @@ struct Builder {
       d.Bscale = B.scales;
       d.ldbs = B.lds;
       s.plan = gemm_plan_int4(L.dtype, M, N, K, K2);
-      if (L.int4_panels && !D && !a_strided && !mask_out) s.panel = int4_panel_plan(L.dtype, M, N, K, K2);
+      if (L.int4_panels && !D && !a_strided && !mask_out && !long_operand(d)) s.panel = int4_panel_plan(L.dtype, M, N, K, K2);
       if (s.panel.width > 0) {
         s.is_panel = true;
         if (s.panel.scratch_bytes > max_partial) max_partial = s.panel.scratch_bytes;
       }
     } else {
-      s.plan = gemm_plan(L.dtype, M, N, K, K2);
+      s.plan = gemm_plan(L.dtype, M, N, K, K2, -1, 0, false, long_operand(d));
     }
     if (s.plan.partial_bytes > max_partial) max_partial = s.plan.partial_bytes;
     out->steps.push_back(s);
@@ -198,6 +203,7 @@ struct Builder {
       s.nsk = 0;
       s.d = rank_desc(L.dtype, s.sk[0]);
       s.plan = mp;
+      if (mp.partial_bytes > max_partial) max_partial = mp.partial_bytes;  // (spare() holds it: never more than the call has)
     }
     out->steps.push_back(s);
   }
@@ -263,6 +269,7 @@ struct Builder {
     s.skplan = skinny_plan(L.dtype, 2, s.sk);
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
     s.is_mtpair = mt_pair_plan(L.dtype, s.sk, spare(), &s.mtpair);  // r > 32
+    if (s.is_mtpair && s.mtpair.partial_bytes > max_partial) max_partial = s.mtpair.partial_bytes;
     out->steps.push_back(s);
   }
 
@@ -317,7 +324,7 @@ bool build_forward(int variant, const LayerDims& L, const FwdOperands& op, void*
     case 1: {  // forward1: (XW) + ((XA)B), the sum folded into one contraction over [X|T]
       Mat T = op.keep_T ? op.T : b.scratch(n, r);
       if (b.few_forward("Y = X [W|A] ; Y += T B", op.X, op.W, op.A, op.B, op.Y, T, op.keep_T, op.bias)) break;
-      if (r > 32) b.expect_gemm(n, o, i, r, true);
+      if (r > 32) b.expect_gemm(n, o, i, r, true, op.X.ld);
       b.skinny("T = X A", {0, 0, n, r, i, op.X, op.A, T, true, true});
       b.gemm("Y = [X|T] [W;B]", 0, 0, n, o, i, op.X, op.W, op.Y, nullptr, r, &T, &op.B, true, 1.f, op.bias);
       break;
@@ -359,7 +366,7 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
     }
     case 1: {  // Algorithm 1
       Mat Z1 = b.scratch(n, r), Z2 = op.have_T ? op.T : b.scratch(n, r);
-      if (dX && !L.drop_thr && r > 32) b.expect_gemm(n, i, o, r, true);
+      if (dX && !L.drop_thr && r > 32) b.expect_gemm(n, i, o, r, true, op.dY.ld);
       rank_r_pass(b, op, n, i, o, r, Z1, Z2, dA || dX, dB && !op.have_T, dA, dB);
       if (dX && L.drop_thr) {  // the mask sits between the two products: no concatenated contraction
         b.gemm("dX = dY W^T", 0, 1, n, i, o, op.dY, op.W, op.dX, nullptr, 0, nullptr, nullptr, true);
@@ -402,7 +409,7 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
       if (L.w_int4) return false;
       Mat Z1 = b.scratch(n, r), Z2 = op.have_T ? op.T : b.scratch(n, r), Z3 = op.have_M ? op.M : b.scratch(i, o);
       if (dX && !op.have_M) b.merge("Z3 = W + A B", op.A, op.B, op.W, Z3);
-      if (dX && r > 32) b.expect_gemm(n, i, o, 0, false);
+      if (dX && r > 32) b.expect_gemm(n, i, o, 0, false, op.dY.ld);
       rank_r_pass(b, op, n, i, o, r, Z1, Z2, dA, dB && !op.have_T, dA, dB);
       if (dX) b.gemm("dX = dY Z3^T", 0, 1, n, i, o, op.dY, Z3, op.dX);
       break;

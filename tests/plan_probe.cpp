@@ -16,6 +16,12 @@ int main() {
       const GemmPlan f = gemm_plan(DT_F32, M, N, K0, K1);  // (the rule by tile counts names its shape for fp32 too)
       const GemmPlan g = gemm_plan(DT_BF16, M, N, K0, K1, f.cfg == CFG_BIG ? CFG_MC4 : f.cfg);
       std::printf("%d %d %ld %zu %.3f %d %.3f\n", p.cfg, p.splits, (long)p.tail_n0, p.partial_bytes, plan_time_us(p, M, N, K0, K1), g.cfg, plan_time_us(g, M, N, K0, K1));
+    } else if (std::strcmp(kind, "padded") == 0) {  // K1 = leading dimension of A [M, K0]: the plan gemm_run gets, and the scratch reported for the shape
+      GemmDesc d;
+      d.dtype = DT_BF16;
+      d.M = M; d.N = N; d.K[0] = K0; d.lda[0] = K1;
+      const GemmPlan p = gemm_plan(DT_BF16, M, N, K0, 0, -1, 0, false, long_operand(d));
+      std::printf("%d %d %zu %zu\n", p.cfg, p.tail_n0 > 0 ? p.tail_cfg : p.cfg, p.partial_bytes, gemm_plan(DT_BF16, M, N, K0, 0).partial_bytes);
     } else if (std::strcmp(kind, "few") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: the few-token route's price and taken or not
       SkinnyDesc d;
       d.M = M; d.N = K1; d.K = N;

@@ -18,7 +18,7 @@ def probe(tmp_path_factory):
                         "-L" + LIB_DIR, "-lrunlora", "-Wl,-rpath," + os.path.abspath(LIB_DIR)], capture_output=True, text=True)
     assert p.returncode == 0, p.stderr[-2000:]
 
-    def ask(kind, rows):  # product: M, N, K, K of a second segment; few: tokens, d_in, d_out, r
+    def ask(kind, rows):  # product: M, N, K, K of a second segment; few: tokens, d_in, d_out, r; padded: M, N, K, ld of A
         text = "".join(kind + " " + " ".join(str(v) for v in r) + "\n" for r in rows)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.strip().split("\n")
         assert len(out) == len(rows)
@@ -43,6 +43,18 @@ def test_rows_that_split_lines_are_priced(probe):
     (64x128 tiles 182-201 us, 256x256 123-137); short contractions of many tiles stay on the middle-sized kernel."""
     wide, narrow = probe("product", [(4096, 2056, 5464, 0), (1024, 768, 768, 0)])
     assert wide[0] == 7 and narrow[0] >= 12
+
+
+def test_operands_beyond_two_gib_stay_on_kernels_that_address_them(probe):
+    """The middle-sized kernel addresses 2^30 elements of an operand, the 256x256 kernel twice that.  A product with a longer one
+    (by its sizes or by its rows' distance) keeps the plan by tile counts, in the scratch reported for its sizes, instead of
+    falling back from a middle-sized tile to the generic engine's 128x128."""
+    rows = [(262144, 256, 4096, 4096), (262144, 2056, 4104, 4104), (200000, 1024, 2048, 8192), (524288, 264, 2056, 2056), (40000, 768, 768, 30000)]
+    for r, (cfg, tail, part, reported) in zip(rows, probe("padded", rows)):
+        assert cfg == 7 and tail == 7, (r, cfg, tail)
+        assert part == reported, r
+    short = probe("padded", [(r[0] // 8, r[1], r[2], r[2]) for r in rows])
+    assert any(p[0] >= 12 or p[1] >= 12 for p in short)   # the same products with fewer rows do run on its tiles
 
 
 def test_the_few_token_route_is_taken_where_it_is_modelled_faster(probe):
