@@ -93,7 +93,7 @@ struct Mc64Tile {
 //   3: the same with a bias and / or ragged M, N: the bias is added to the accumulators, stores are guarded;
 //   2: a split contraction, M and N multiples of the tile: every tile writes fp32 partials;
 //   4: the same with ragged M, N: stores are guarded;
-//   0: everything else (general epilogue).
+//   0: everything else that writes C whole (general epilogue).
 // Bound by the pattern and number of its store instructions: the general epilogue stores 8 bytes per lane, two rows of
 // 256 bytes per instruction, behind its options' branches; 3 stores 16 bytes per lane like 1.  Y = X W + bias at
 // 4096 x 2048 -> 8192 (two tiles per compute unit): 148 us with the general epilogue, 126 with 3 (118 without a bias).
@@ -515,13 +515,13 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
         }
       });
     } else {
-      // fp32 partials of a split contraction (PLAIN == 2, 4), or the general epilogue (ragged tiles, addend, bias, scale,
-      // mask, partials of a ragged split).  One row block (16 rows x 128 fp32 columns of this wave = 8 KB) at a time
-      // passes through the wave's LDS area, row r at r * 512 bytes: 16-byte pieces in the accumulator layout in (piece
-      // 4 b + grp of 32, rotated by the row against bank conflicts), two rows x 512 bytes per instruction out, so that
-      // a lane owns four consecutive columns of one row: the unit of every option (one mask group, 8 bytes of
-      // addend / bias / output, 16 bytes of partials), and a store instruction covers 2 rows x 256 bytes (512 of
-      // partials).  Arithmetic and its order are store_block's: alpha, mask, + addend, + bias, one rounding.
+      // fp32 partials of a split contraction (PLAIN == 2, 4), or the general epilogue (addend, scale, mask; PLAIN == 0).  One
+      // row block (16 rows x 128 fp32 columns of this wave = 8 KB) at a time passes through the wave's LDS area, row r at
+      // r * 512 bytes: 16-byte pieces in the accumulator layout in (piece 4 b + grp of 32, rotated by the row against bank
+      // conflicts), two rows x 512 bytes per instruction out, so that a lane owns four consecutive columns of one row: the
+      // unit of every option (one mask group, 8 bytes of addend / bias / output, 16 bytes of partials), and a store
+      // instruction covers 2 rows x 256 bytes (512 of partials).  Arithmetic and its order are store_block's: alpha, mask,
+      // + addend, + bias, one rounding.
       const Epilogue ep{g.C, g.ldc, g.D, g.ldd, g.partial, g.M, g.N, split, g.alpha, g.bias, g.drop_thr, g.drop_key, g.drop_cpr};
       unsigned char* const stg = smem + P::LDS_BYTES + wave * 8192;
       const uint32_t stg_base = (uint32_t)(uintptr_t)((mc_lds_void_t*)stg);
@@ -531,7 +531,7 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
       const bool n_ok = n < g.N;
       [[maybe_unused]] f32x4 bias4 = {0.f, 0.f, 0.f, 0.f};
       if constexpr (PLAIN == 0) {
-        if (g.bias != nullptr && g.partial == nullptr && n_ok) {
+        if (g.bias != nullptr && n_ok) {
           T b4[4];
           *reinterpret_cast<i32x2*>(b4) = *reinterpret_cast<const i32x2*>(static_cast<const T*>(g.bias) + n);
 #pragma unroll
@@ -563,7 +563,7 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
         // wait out a trip to memory)
         [[maybe_unused]] i32x2 dq[8];
         if constexpr (PLAIN == 0) {
-          if (g.D != nullptr && g.partial == nullptr) {
+          if (g.D != nullptr) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
               const int m = m0 + wm * 128 + a * 16 + 2 * k + rr;
@@ -583,20 +583,16 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
             *reinterpret_cast<f32x4*>(g.partial + ((int64_t)split * g.M + m) * g.N + n) = o[k];
           } else {
             if (m < g.M && n_ok) {
-              if (g.partial != nullptr) {
-                *reinterpret_cast<f32x4*>(g.partial + ((int64_t)split * g.M + m) * g.N + n) = o[k];
-              } else {
-                f32x4 v = epilogue_scale(ep, o[k], m, n);
-                if (g.D != nullptr) {
-                  T d4[4];
-                  *reinterpret_cast<i32x2*>(d4) = dq[k];
+              f32x4 v = epilogue_scale(ep, o[k], m, n);
+              if (g.D != nullptr) {
+                T d4[4];
+                *reinterpret_cast<i32x2*>(d4) = dq[k];
 #pragma unroll
-                  for (int e = 0; e < 4; ++e) v[e] += (float)d4[e];
-                }
-                if (g.bias != nullptr) v += bias4;
-                T o4[4] = {from_f32<T>(v[0]), from_f32<T>(v[1]), from_f32<T>(v[2]), from_f32<T>(v[3])};
-                *reinterpret_cast<i32x2*>(static_cast<T*>(g.C) + (int64_t)m * g.ldc + n) = *reinterpret_cast<const i32x2*>(o4);
+                for (int e = 0; e < 4; ++e) v[e] += (float)d4[e];
               }
+              if (g.bias != nullptr) v += bias4;
+              T o4[4] = {from_f32<T>(v[0]), from_f32<T>(v[1]), from_f32<T>(v[2]), from_f32<T>(v[3])};
+              *reinterpret_cast<i32x2*>(static_cast<T*>(g.C) + (int64_t)m * g.ldc + n) = *reinterpret_cast<const i32x2*>(o4);
             }
           }
           __builtin_amdgcn_sched_barrier(0);
