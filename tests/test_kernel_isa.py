@@ -4,7 +4,8 @@ The kernel's speed rests on three properties of its K loop that a harmless-looki
 silently break, with results staying correct: (1) no full wait for outstanding loads (`s_waitcnt
 vmcnt(0)`) inside a K step, which would serialise the LDS ring; (2) no per-lane loop around a load (the
 compiler wraps a load whose scalar offset it cannot prove uniform in a `s_cbranch_execnz` loop);
-(3) no register spills.  Both the dense and the int4 route are checked, in the NN and NT layouts.
+(3) no register spills.  Both the dense and the int4 route are checked, in the NN and NT layouts; the K-tile-64 kernel and
+the middle-sized one, every build, by the same properties.
 """
 import os
 import re
@@ -101,3 +102,41 @@ def test_k_loop_of_the_matrix_core_kernel_with_k_tile_64(asm, al, bl, plain):
     for b in blocks(text):
         if b and b[-1].startswith("s_cbranch_execnz"):
             assert not any(i.startswith(("buffer_load", "global_load")) for i in b), "a load sits in a per-lane (waterfall) loop"
+
+
+MT_BUILDS = [(al, bl, bm, bn, ns, 0) for al, bl in ((0, 0), (0, 1), (1, 0)) for bm, bn, ns in ((128, 128, 2), (128, 128, 4), (256, 128, 3), (128, 64, 3), (64, 128, 3))]
+
+
+@pytest.mark.parametrize("al,bl,bm,bn,ns,xa", MT_BUILDS + [(0, 0, 64, 128, 3, 1), ("pair", 1, 0, 0, 0, 0), ("pair", 0, 0, 0, 0, 0)])
+def test_k_loop_of_the_middle_sized_kernel(asm, al, bl, bm, bn, ns, xa):
+    """gemm_mt_kernel: a K tile's two K steps are one straight-line block (its hand-issued LDS reads are in flight across the whole
+    of it: a branch would let the compiler copy what has not arrived) with all its products, one wait for loads that leaves
+    the younger ring stages in flight, and nothing spilled or moved between the register files."""
+    if al == "pair":   # (bl = 1: Z1 = dY B^T ; Z2 = X A, else dA = X^T Z1 ; dB = Z2^T dY)
+        name = "_ZN2rl19gemm_mt_pair_kernelIDF16bLi0ELi1ELi0ELi128ELi64ELi128ELi64EEEvNS_8GemmArgsES1_" if bl else \
+            "_ZN2rl19gemm_mt_pair_kernelIDF16bLi1ELi0ELi0ELi128ELi64ELi64ELi128EEEvNS_8GemmArgsES1_"
+        bodies, bm, bn, ns = 2, 128, 64, 3
+    else:
+        name = f"_ZN2rl14gemm_mt_kernelIDF16bLi{al}ELi{bl}ELi{bm}ELi{bn}ELi{ns}ELb{xa}EEEvNS_8GemmArgsE"
+        bodies = 1
+    start = asm.index("\n" + name + ":")
+    text = asm[start:asm.index(".Lfunc_end", start)]
+    meta = asm[asm.index(".name:           " + name):]
+    meta = meta[:meta.index(".wavefront_size")]
+    assert re.search(r"\.vgpr_spill_count:\s+0\b", meta), "the kernel spills vector registers"
+    per_tile = 2 * (bm // 32) * (bn // 32)           # products of a wave, both K steps
+    loads = (bm + bn) * 128 // 4096                  # of a wave and K tile
+    ksteps = [b for b in blocks(text) if any(i.startswith("v_mfma") for i in b)]
+    assert len(ksteps) == bodies, "a K tile is cut into several blocks"
+    for b in ksteps:
+        at = [k for k, i in enumerate(b) if i.startswith("v_mfma")]
+        assert len(at) == per_tile and all("16x16x32" in b[k] for k in at)
+        body = b[at[0]:at[-1] + 1]
+        assert not any(i.startswith(("scratch_", "v_accvgpr")) for i in body), "spill or accumulator copies inside a K step"
+        waits = [i for i in body if re.match(r"s_waitcnt.*vmcnt", i)]
+        assert len(waits) == 1 and f"vmcnt({(ns - 2) * loads})" in waits[0], waits
+        assert sum(i.startswith("s_barrier") for i in body) == 1
+        assert len(body) <= 2 * per_tile + 66, "too many instructions between the products of a K tile"
+    for b in blocks(text):   # (a per-lane loop reads one lane's offset at a time)
+        assert not (any(i.startswith("v_readfirstlane") for i in b) and any(i.startswith(("buffer_load", "global_load")) for i in b)), \
+            "a load sits in a per-lane (waterfall) loop"
