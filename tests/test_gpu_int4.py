@@ -44,6 +44,27 @@ def run_pair(L, dev, fwd, bwd):
     return {"Y": to_f64(Y), "dX": to_f64(dX), "dA": to_f64(dA), "dB": to_f64(dB)}
 
 
+def direct_workspace(dev, L, fwd, bwd=None):
+    """A workspace of what the call needs without dequantised panels of W: the figure in its refusal of a smaller one."""
+    import re
+
+    import torch
+    td = torch_dtype(L.dtype)
+    tiny = torch.empty(256, dtype=torch.uint8, device="cuda")
+    Y = torch.empty((L.n, L.o), dtype=td, device="cuda")
+    saved = rl.new_saved()
+    with pytest.raises(rl.RunLoRAError) as e:
+        if bwd is None:
+            rl.runlora_forward(fwd, dev["X"], dev["W"], dev["A"], dev["B"], Y, saved, workspace=tiny)
+        else:
+            full = rl.new_workspace(fwd, bwd, L.n, L.i, L.o, L.r, rl.dtype_from_name(L.dtype), w_dtype=rl.RL_INT4_G64)
+            rl.runlora_forward(fwd, dev["X"], dev["W"], dev["A"], dev["B"], Y, saved, workspace=full)
+            rl.runlora_backward(bwd, dev["dY"], saved, dev["W"], dev["A"], dev["B"], torch.empty_like(dev["X"]), torch.empty_like(dev["A"]),
+                                torch.empty_like(dev["B"]), workspace=tiny)
+    assert e.value.code == rl.RL_ERR_WORKSPACE
+    return torch.empty(int(re.search(r"(\d+) bytes", str(e.value)).group(1)), dtype=torch.uint8, device="cuda")
+
+
 def reference(host):
     Y = oracle.reference_forward(host["X"], host["W"], host["A"], host["B"])
     dX, dA, dB = oracle.reference_backward(host["X"], host["W"], host["A"], host["B"], host["dY"])
@@ -126,8 +147,8 @@ def test_int4_config_shape_sampled_rows():
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_int4_matrix_core_route_ragged(dtype):
-    """Large enough for the matrix-core kernel's int4 route (>= 160 tiles of 256x256) and ragged in
-    every direction: n not a multiple of the tile, d_in = 32*64 + 8 (a partial last K tile and a
+    """Panels of W on the dense kernels (the workspace is the one runlora_workspace_bytes_w names; the same layer on the
+    matrix-core kernel's int4 route: test_int4_direct_route_with_real_scales), ragged in every direction: n not a multiple of the tile, d_in = 32*64 + 8 (a partial last K tile and a
     partial last scale group for X W), d_out = 32*112 + 8 (the same for dY W^T), r = 24 (a partial K
     tile in the dense second segment).  Y and dX on sampled rows (first and last row of every tile
     row, plus random ones), dA and dB in full; also the default chain, whose dX GEMM has no second
@@ -149,7 +170,7 @@ def test_int4_matrix_core_route_ragged(dtype):
 
 
 def test_int4_matrix_core_route_with_scale_and_bias():
-    """The int4 route's epilogue and the dense second segment with a LoRA scale and a bias."""
+    """The panels' epilogue and the dense second segment with a LoRA scale and a bias."""
     import torch
     L = synth.Layer("int4mcs", 3001, 2056, 3592, 24, "bf16", 13)
     dev, host = make_layer(L)
@@ -175,6 +196,45 @@ def test_int4_matrix_core_route_with_scale_and_bias():
     assert relerr(to_f64(gB), oracle.matmul(Tm, host["dY"], ta=True)) < TOL["bf16"]
 
 
+# the tile ids (rl_step_time_t.tile_cfg) of X W and dY W^T: 6 = matrix-core kernel and 1 = generic engine, each dequantising W on
+# its way to LDS; panels run on the dense kernels (7, 12-16)
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r,cfg_y,cfg_dx", [(3001, 3592, 3592, 24, 6, 6),   # ragged in every direction, partial last scale group
+                                                  (333, 264, 328, 24, 1, 1),      # generic engine
+                                                  (65, 200, 40, 8, 1, 1)])        # one tile, most of it outside
+def test_int4_direct_route_with_real_scales(n, i, o, r, cfg_y, cfg_dx, dtype):
+    """The kernels that dequantise on their way to LDS, forced by a workspace of only their need (with the one
+    runlora_workspace_bytes_w names, all of these shapes multiply dequantised panels): scales that differ per group and column,
+    LoRA scale and bias, Y and dX on sampled rows, dA and dB in full.  (Shapes whose direct plan splits its contraction or cuts
+    columns off take more scratch that way than in panels: no workspace forces it.)"""
+    import torch
+    L = synth.Layer("int4direct", n, i, o, r, dtype, 14)
+    dev, host = make_layer(L)
+    td = torch_dtype(dtype)
+    bst = synth.store(synth.normal(synth.BASE_SEED, 99, (o,)), dtype)
+    rows = np.unique(np.concatenate([np.arange(0, n, 256), np.arange(255, n, 256), [n - 1], np.random.default_rng(8).integers(0, n, 24)]))
+    Yr, dXr = oracle.scaled_rows(host["X"][rows], host["dY"][rows], host["W"], host["A"], host["B"], 0.5, synth.widen(bst, dtype))
+    Z1, Tm = 0.5 * oracle.matmul(host["dY"], host["B"], tb=True), 0.5 * oracle.matmul(host["X"], host["A"])
+    dAw, dBw = oracle.matmul(host["X"], Z1, ta=True), oracle.matmul(Tm, host["dY"], ta=True)
+    full = rl.new_workspace(1, 1, n, i, o, r, rl.dtype_from_name(dtype), w_dtype=rl.RL_INT4_G64)
+    for ws_f, ws_b, direct in ((direct_workspace(dev, L, 1), direct_workspace(dev, L, 1, 1), True), (full, full, False)):
+        print(f"case int4 {n} {i}->{o} r={r} {dtype} {'direct' if direct else 'panels'}", flush=True)
+        Y, gX = (torch.full(s, float("nan"), dtype=td, device="cuda") for s in ((n, o), (n, i)))
+        gA, gB = (torch.full(s, float("nan"), dtype=td, device="cuda") for s in ((i, r), (r, o)))
+        saved = rl.new_saved()
+        rl.runlora_profile_enable(32)
+        rl.runlora_forward(1, dev["X"], dev["W"], dev["A"], dev["B"], Y, saved, workspace=ws_f, scale=0.5, bias=to_device(bst, dtype))
+        rl.runlora_backward(1, dev["dY"], saved, dev["W"], dev["A"], dev["B"], gX, gA, gB, workspace=ws_b)
+        torch.cuda.synchronize()
+        cfg = {s["what"].split(" ")[0]: s["tile_cfg"] for s in rl.runlora_profile_collect(32) if "W" in s["what"]}
+        rl.runlora_profile_disable()
+        if direct:
+            assert cfg == {"Y": cfg_y, "dX": cfg_dx}
+        else:
+            assert all(c == 7 or 12 <= c <= 16 for c in cfg.values()), cfg
+        assert relerr(to_f64(Y)[rows], Yr) < TOL[dtype] and relerr(to_f64(gX)[rows], dXr) < TOL[dtype]
+        assert relerr(to_f64(gA), dAw) < TOL[dtype] and relerr(to_f64(gB), dBw) < TOL[dtype]
+
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("n,i,o,r", [(300, 1096, 1000, 16),    # one panel, rows and columns that end inside a scale group / a tile
@@ -183,15 +243,16 @@ def test_int4_matrix_core_route_with_scale_and_bias():
 def test_int4_panels_and_direct_route_agree(n, i, o, r, dtype):
     """A call with the workspace that runlora_workspace_bytes_w names multiplies dequantised panels of W; one with only what
     the direct route needs (the figure in the error text) still runs, on the kernels that dequantise on their way to LDS.
-    Unit scales and integer values: both give the same bits, every option included."""
+    Scales of 1 and 2 that differ per group and column, integer values: both give the same bits, every option included."""
     import re
 
     import torch
     rng = np.random.default_rng(n)
     td = torch_dtype(dtype)
     pick = lambda shape, p: to_device(synth.store((rng.random(shape) < p) * rng.choice([-1.0, 1.0], size=shape), dtype), dtype)
-    q = (rng.integers(-7, 8, size=(i, o)) * (rng.random((i, o)) < 0.05)).astype(np.int8)
-    W = rl.Int4Weight.from_host(q, np.ones(((i + 63) // 64, o), dtype=np.float16))
+    q = (rng.integers(-4, 5, size=(i, o)) * (rng.random((i, o)) < 0.05)).astype(np.int8)
+    scales = rng.integers(1, 3, size=((i + 63) // 64, o)).astype(np.float16)
+    W = rl.Int4Weight.from_host(q, scales)
     X, A, B, dY = pick((n, i), 0.05), pick((i, r), 0.01), pick((r, o), 0.05), pick((n, o), 0.05)
     bias = pick((o,), 0.5)
     code = rl.dtype_from_name(dtype)
@@ -227,7 +288,7 @@ def test_int4_panels_and_direct_route_agree(n, i, o, r, dtype):
     if n > 1000:  # (the short layers' direct route splits its contraction and takes more scratch than their panels)
         assert small_f.numel() < full.numel() and small_b.numel() < full.numel()
         assert direct != panels, "both calls took the same route"
-    Wq = q.astype(np.float64)
+    Wq = q.astype(np.float64) * np.repeat(scales.astype(np.float64), 64, axis=0)[:i]
     want = to_f64(X) @ Wq + 2.0 * (to_f64(X) @ to_f64(A)) @ to_f64(B) + to_f64(bias)
     want_dX = to_f64(dY) @ Wq.T + 2.0 * (to_f64(dY) @ to_f64(B).T) @ to_f64(A).T
     assert np.abs(want).max() <= 256 and np.abs(want_dX).max() <= 256   # integers bf16 holds
