@@ -265,8 +265,11 @@ GemmPlan gemm_plan_int4(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1)
   return gemm_plan(dtype, M, N, K0, K1, -1, 0, true);
 }
 
-// What the kernels that dequantise on the way to LDS take, in us (bf16, 4096 x 5120 x 13824: 557 us for three rounds of 256
-// tiles and 162 K tiles of 32, 492 for one of 434; 128x128 tiles of the generic engine as on dense operands).
+// What the kernels that dequantise on the way to LDS take, in us (bf16; 4096 x 5120 x 13824: 557 us for three rounds of 256 tiles
+// and 162 K tiles of 32, 492 for one of 434; 128x128 tiles of the generic engine, two to a compute unit: 247 us at 672 x 3208 x
+// 12960 in four slices, 310 at 491 x 7408 x 11744 in three).  Layers timed on both routes, forward, r 16-64, us (direct / panels):
+// 512 x 2048 -> 2048 38.8 / 30.7, 1024 x 4096 -> 4096 171 / 62.6, 2048 x 4096 -> 4096 124 / 92.6, 672 x 12960 -> 3208 266 / 183;
+// 913 x 6240 -> 6232 135 / 159, 3748 x 12720 -> 7888 838 / 1156 (panels on the tiles chosen at the time).
 static double int4_direct_us(const GemmPlan& p, int64_t M, int64_t N, int64_t K0, int64_t K1) {
   if (p.tail_n0 > 0) {
     GemmPlan main = p;
@@ -277,11 +280,13 @@ static double int4_direct_us(const GemmPlan& p, int64_t M, int64_t N, int64_t K0
   const double wgs = (double)p.nbm * p.nbn * p.splits;
   const int64_t kt = (K0 + p.bk - 1) / p.bk + (K1 + p.bk - 1) / p.bk;
   const double per = p.splits > 1 ? (double)p.tiles_per_split : (double)kt;
-  const bool mc = p.cfg == CFG_MC3;
-  const double slots = mc ? 256.0 : 512.0;
-  const double rounds = wgs <= slots ? 1.0 : (double)(int64_t)(wgs / slots + 0.999);
-  const double tk = mc ? 1.14 : (wgs <= 256.0 ? 1.0 : 1.6);
-  return 10.0 + rounds * (per * tk + 6.0) + split_time_us(M, N, p.splits);
+  if (p.cfg == CFG_MC3) {
+    const double rounds = wgs <= 256.0 ? 1.0 : (double)(int64_t)(wgs / 256.0 + 0.999);
+    return 10.0 + rounds * (per * 1.14 + 6.0) + split_time_us(M, N, p.splits);
+  }
+  // a K tile takes 1 us alone, 2.2 where two share a compute unit; a few workgroups of a last round take as long as a whole one
+  const double rounds = wgs <= 512.0 ? 1.0 : (double)(int64_t)(wgs / 512.0 + 0.999);
+  return 8.0 + rounds * (per * (wgs <= 256.0 ? 1.0 : 2.2) + 1.0) + split_time_us(M, N, p.splits);
 }
 
 Int4PanelPlan int4_panel_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1) {

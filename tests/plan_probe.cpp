@@ -22,6 +22,8 @@ int main() {
       d.M = M; d.N = N; d.K[0] = K0; d.lda[0] = K1;
       const GemmPlan p = gemm_plan(DT_BF16, M, N, K0, 0, -1, 0, false, long_operand(d));
       std::printf("%d %d %zu %zu\n", p.cfg, p.tail_n0 > 0 ? p.tail_cfg : p.cfg, p.partial_bytes, gemm_plan(DT_BF16, M, N, K0, 0).partial_bytes);
+    } else if (std::strcmp(kind, "int4") == 0) {  // panels or not, and the direct kernel's id
+      std::printf("%d %d\n", int4_panel_plan(DT_BF16, M, N, K0, K1).width > 0 ? 1 : 0, gemm_plan_int4(DT_BF16, M, N, K0, K1).cfg);
     } else if (std::strcmp(kind, "few") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: the few-token route's price and taken or not
       SkinnyDesc d;
       d.M = M; d.N = K1; d.K = N;

@@ -18,7 +18,7 @@ def probe(tmp_path_factory):
                         "-L" + LIB_DIR, "-lrunlora", "-Wl,-rpath," + os.path.abspath(LIB_DIR)], capture_output=True, text=True)
     assert p.returncode == 0, p.stderr[-2000:]
 
-    def ask(kind, rows):  # product: M, N, K, K of a second segment; few: tokens, d_in, d_out, r; padded: M, N, K, ld of A
+    def ask(kind, rows):  # product: M, N, K, K of a second segment; few: tokens, d_in, d_out, r; padded: M, N, K, ld of A; int4: M, N, K, r
         text = "".join(kind + " " + " ".join(str(v) for v in r) + "\n" for r in rows)
         out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.strip().split("\n")
         assert len(out) == len(rows)
@@ -70,3 +70,13 @@ def test_the_few_token_route_is_taken_where_it_is_modelled_faster(probe):
     assert 150 < taken < 300
     wide, small, one = probe("few", [(256, 4096, 11008, 128), (48, 4096, 11008, 32), (1, 4096, 4096, 16)])
     assert not wide[0] and small[0] and one[0]
+
+
+def test_int4_products_take_the_faster_route(probe):
+    """Layers timed on both routes: panels of W on the dense kernels (512 x 2048 -> 2048 30.7 us against 38.8, 672 x 12960 -> 3208
+    183 against 266, 4096 x 5120 -> 13824) and the kernels that dequantise on their way to LDS (913 x 6240 -> 6232 135 against 159,
+    3748 x 12720 -> 7888 838 against 1156, 1062 x 8680 -> 7768 229 against 313)."""
+    panels = [(512, 2048, 2048, 32), (672, 3208, 12960, 16), (4096, 13824, 5120, 64), (1024, 4096, 4096, 64)]
+    direct = [(913, 6232, 6240, 16), (3748, 7888, 12720, 16), (1062, 7768, 8680, 16)]
+    assert [p[0] for p in probe("int4", panels)] == [1] * 4
+    assert [p[0] for p in probe("int4", direct)] == [0] * 3
