@@ -36,6 +36,20 @@ def _compile(src):
     return obj
 
 
+def _ext_abi():
+    """What _autograd.so is built against; it is rebuilt when one of them changes."""
+    import torch
+    return f"python {sys.implementation.cache_tag} torch {torch.__version__}"
+
+
+def _ext_is_current():
+    try:
+        with open(EXT + ".abi") as fh:
+            return fh.read() == _ext_abi()
+    except OSError:
+        return False
+
+
 def _compile_ext():
     """_autograd.so: a CPython extension against torch's headers; librunlora's entry points are handed to it at run time."""
     import sysconfig
@@ -51,10 +65,12 @@ def _compile_ext():
     p = subprocess.run(cmd, capture_output=True, text=True)
     if p.returncode != 0:
         raise RuntimeError(f"g++ failed on autograd.cpp:\n{p.stderr}")
+    with open(EXT + ".abi", "w") as fh:
+        fh.write(_ext_abi())
 
 
 def build(force=False):
-    if not force and all(os.path.exists(f) and all(os.path.getmtime(f) >= os.path.getmtime(d) for d in _deps()) for f in (LIB, EXT)):
+    if not force and _ext_is_current() and all(os.path.exists(f) and all(os.path.getmtime(f) >= os.path.getmtime(d) for d in _deps()) for f in (LIB, EXT)):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:

@@ -42,6 +42,9 @@ def _native():
     global _native_module
     if _native_module is None:
         lib = rl.lib()
+        from . import build
+        if not build._ext_is_current():  # (loading it against another torch would fail later, or worse)
+            raise ImportError(f"_autograd.so was not built for {build._ext_abi()}: run `python -m paper_2312_03415_amd.build`")
         from . import _autograd
         address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
         _autograd.init(address(lib.runlora_forward), address(lib.runlora_backward), address(lib.runlora_workspace_bytes), rl._check)
