@@ -37,15 +37,15 @@ def _compile(src):
 
 
 def _ext_abi():
-    """What _autograd.so is built against; it is rebuilt when one of them changes."""
+    """What _autograd.so is built against (it carries this text); it is rebuilt when one of them changes."""
     import torch
     return f"python {sys.implementation.cache_tag} torch {torch.__version__}"
 
 
 def _ext_is_current():
     try:
-        with open(EXT + ".abi") as fh:
-            return fh.read() == _ext_abi()
+        with open(EXT, "rb") as fh:
+            return f"built for [{_ext_abi()}]".encode() in fh.read()
     except OSError:
         return False
 
@@ -57,7 +57,7 @@ def _compile_ext():
     import torch
     root = os.path.dirname(torch.__file__)
     inc = os.path.join(root, "include")
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f'-DRL_BUILT_FOR="{_ext_abi()}"',
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", inc,
            "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
            "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "autograd.cpp"), "-o", EXT,
@@ -65,8 +65,6 @@ def _compile_ext():
     p = subprocess.run(cmd, capture_output=True, text=True)
     if p.returncode != 0:
         raise RuntimeError(f"g++ failed on autograd.cpp:\n{p.stderr}")
-    with open(EXT + ".abi", "w") as fh:
-        fh.write(_ext_abi())
 
 
 def build(force=False):

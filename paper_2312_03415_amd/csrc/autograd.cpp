@@ -245,6 +245,9 @@ PyMethodDef methods[] = {{"lora", reinterpret_cast<PyCFunction>(reinterpret_cast
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_autograd", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
+// read by build.py without loading the library
+[[gnu::used]] const char built_for[] = "built for [" RL_BUILT_FOR "]";
+
 }  // namespace
 
 PyMODINIT_FUNC PyInit__autograd(void) { return PyModule_Create(&module_def); }

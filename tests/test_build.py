@@ -6,8 +6,9 @@ from paper_2312_03415_amd import build, module
 
 
 def test_a_change_of_torch_rebuilds_the_native_node(monkeypatch):
-    if not build._ext_is_current():   # (built before the record existed)
+    if not build._ext_is_current():   # (built for another torch)
         build.build()
+    assert build._ext_is_current()    # the library itself says what it was built for: no second file to lose
     calls = []
     monkeypatch.setattr(build, "_compile", lambda src: calls.append(src) or src)
     monkeypatch.setattr(build, "_compile_ext", lambda: calls.append("ext"))
