@@ -197,12 +197,17 @@ extern "C" int runlora_select_by(int criterion, int64_t n, int64_t i, int64_t o,
   int bf = 1, bb = 1;
   double cf = 0, cb = 0;
   // 16-bit layers: a graph that rounds more intermediates than the one picked so far (forward2 and Algorithms 4, 5: W + AB,
-  // Algorithms 2, 3: X^T dY, the default chain: XW) has to be modelled more than 3 % and more than 2.5 us faster, the model's own
-  // error: 12 layers of 28-50 us where a merged graph was modelled 2-2.5 us faster all ran 1-14 % slower on it.  Forward 3 rounds
+  // Algorithms 2, 3: X^T dY, the default chain: XW) has to be modelled faster by more than the model's own error: 3 %, at least
+  // 2.5 us (12 layers of 28-50 us where a merged graph was modelled 2-2.5 us faster all ran 1-14 % slower on it) and at most 8.
+  // Layers in rotation, forward + backward, (2, 1) against (1, 1): of 26 forwards modelled up to 8 us faster 14 ran
+  // slower (all: 1.0 % slower on average), of 12 between 8 us and 3 % 10 ran faster (all: 1.4 %; 25099 x 6320 -> 5176, r 8: 3681 ->
+  // 3606 us); Algorithm 5 against 1 within 1.5 % either way.  Forward 3 rounds
   // what forward1 rounds and takes one launch less (64 x 80: 4.4 us and 8.1): no margin.  fp32 has nothing to lose.
   const bool strict = criterion == 0 || dt == DT_F32;
   auto beats = [&](double c, double current, bool rounds_more) {
-    return strict || !rounds_more ? c < current : c < 0.97 * current && c < current - 2.5;  // strict '<': ties go to the lower id
+    if (strict || !rounds_more) return c < current;  // strict '<': ties go to the lower id
+    const double margin = 0.03 * current;
+    return c < current - (margin < 2.5 ? 2.5 : (margin > 8.0 ? 8.0 : margin));
   };
   for (int v = 1; v <= fmax; ++v) {
     double c = criterion == 0 ? (double)table1_flops(0, v, n, i, o, r) : model_time_us(0, v, L);

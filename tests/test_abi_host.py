@@ -105,8 +105,8 @@ def test_select_honours_the_debugging_overrides(monkeypatch):
 
 
 def test_select_ties_of_modelled_times():
-    """16-bit layers: a graph that rounds more intermediates is returned only where it is modelled more than 3 % and more than
-    2.5 us faster; forward 3, which rounds what forward1 rounds, wherever it is modelled faster; fp32: the smallest time."""
+    """16-bit layers: a graph that rounds more intermediates is returned only where it is modelled more than 3 % faster, at least
+    2.5 us and at most 8; forward 3, which rounds what forward1 rounds, wherever it is modelled faster; fp32: the smallest time."""
     rng = np.random.default_rng(11)
     merged_forwards = thirds = 0
     for _ in range(300):
@@ -115,7 +115,7 @@ def test_select_ties_of_modelled_times():
         time = lambda bwd, v, dt=rl.RL_BF16: rl.runlora_model_time_us(bwd, v, n, i, o, r, dt)
         f, b = rl.runlora_select(n, i, o, r, rl.RL_BF16, criterion=1)
         fwd, bwd = {v: time(0, v) for v in (0, 1, 2, 3)}, {v: time(1, v) for v in range(6)}
-        clear = lambda c, current: c < 0.97 * current and c < current - 2.5
+        clear = lambda c, current: c < current - min(max(0.03 * current, 2.5), 8.0)
         if (f, b) == (0, 0):
             assert clear(fwd[0] + bwd[0], min(fwd[1], fwd[3]) + bwd[1]), (n, i, o, r)
             continue
@@ -129,6 +129,8 @@ def test_select_ties_of_modelled_times():
         assert total <= min(time(0, v, rl.RL_F32) for v in (1, 2, 3)) + min(time(1, v, rl.RL_F32) for v in range(1, 6)) + 1e-9
     assert merged_forwards > 5 and thirds > 5
     assert rl.runlora_select(6, 64, 80, 8, rl.RL_BF16)[0] == 3    # one launch: 4.4 us against 8.1
+    for r in (8, 32):   # 3 % of a long layer is no error of the model: 945 us a pass on (1, 1), 920 on (2, 1)
+        assert rl.runlora_select(16384, 4096, 4096, r, rl.RL_BF16) == (2, 1)
 
 
 def test_model_constants_have_the_generators_form():
