@@ -21,17 +21,11 @@ from torch import nn
 
 from . import binding as rl
 
-# one scratch buffer per device, shared by every layer (calls on a device are ordered on its current
-# stream and nothing lives in the workspace between two calls)
-_workspaces = {}
-
 
 def _workspace(device, nbytes):
-    ws = _workspaces.get(device)
-    if ws is None or ws.numel() < nbytes:
-        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
-        _workspaces[device] = ws
-    return ws
+    """Scratch of one call, given back to the caching allocator behind it (stream-ordered like every tensor): calls on other
+    streams or from other threads may run at the same time."""
+    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
 _native_module = None

@@ -507,3 +507,13 @@ def test_gemm_call_rejects_bad_arguments():
     g.tile_cfg = -1
     g.C = None
     assert L.runlora_gemm(ctypes.byref(g), None) == rl.RL_ERR_NULL
+
+
+def test_calls_of_the_python_nodes_share_no_scratch():
+    """Two calls may run at once, on two streams or from two threads: each holds a workspace of its own (on the CPU here)."""
+    torch = pytest.importorskip("torch")
+    from paper_2312_03415_amd import module
+    cpu = torch.device("cpu")
+    first, second = module._workspace(cpu, 1000), module._workspace(cpu, 1000)
+    assert first.numel() >= 1000 and second.numel() >= 1000 and first.data_ptr() != second.data_ptr()
+    assert module._workspace(cpu, 0).numel() >= 256

@@ -204,3 +204,49 @@ def test_native_node_on_streams_and_threads():
     assert not errors, errors
     for k in range(4):
         assert all(torch.equal(a, b) for a, b in zip(out[k], alone[k])), k
+
+
+@pytest.mark.parametrize("kind", ["lora", "vera", "dora"])
+def test_python_nodes_on_streams_and_threads(kind):
+    """The same for the nodes in Python, DoRA and VeRA among them."""
+    import threading
+
+    import torch
+    from paper_2312_03415_amd.module import RunDoRALinear, RunVeRALinear
+    jobs = []
+    for k in range(4):
+        x, W, A, B, bias, dy = layer(torch.bfloat16, 300 + 40 * k, 520, 776, 16, seed=k)
+        if kind == "lora":
+            jobs.append(lambda x=x, W=W, A=A, B=B, dy=dy: run(python_node, x, W, A, B, dy, (None, 1.0, (1, 1), False))[0])
+            continue
+        mod = RunVeRALinear(W, A, B, bias) if kind == "vera" else RunDoRALinear(W, 16, bias=bias)
+        with torch.no_grad():
+            mod.vera_b.copy_(bias) if kind == "vera" else (mod.lora_A.copy_(A), mod.lora_B.copy_(B))
+
+        def job(mod=mod, x=x, dy=dy):
+            xs = x.detach().requires_grad_(True)
+            y = mod(xs)
+            return [y.detach(), *torch.autograd.grad(y, [xs, *(p for p in mod.parameters() if p.requires_grad)], dy)]
+        jobs.append(job)
+    alone = [job() for job in jobs]
+    torch.cuda.synchronize()
+    out, errors = {}, []
+
+    def work(k):
+        try:
+            s = torch.cuda.Stream()
+            s.wait_stream(torch.cuda.default_stream())
+            with torch.cuda.stream(s):
+                for rep in range(8):
+                    out[k] = jobs[k]()
+            s.synchronize()
+        except Exception as e:   # noqa: BLE001 - reported by the main thread
+            errors.append(e)
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k in range(4):
+        assert all(torch.equal(a, b) for a, b in zip(out[k], alone[k])), (kind, k)
