@@ -572,28 +572,51 @@ hipError_t few_run(int dtype, const FewDesc& d, const FewPlan& plan, float* scra
 SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d) {
   SkinnyPlan p;
   const int bk = dtype == DT_F32 ? 32 : 64;
-  int64_t blocks = 0, min_ktiles = 1 << 30, outs = 0, maxn = 0;
+  int64_t min_ktiles = 1 << 30, outs = 0, maxn = 0;
   for (int w = 0; w < nprob; ++w)
     if (d[w].N > maxn) maxn = d[w].N;
   p.rt = maxn <= 32 ? 1 : (maxn <= 64 ? 2 : 4);
-  // see skinny.hpp; a masked problem (LoRA dropout) is bound by its waves' mask arithmetic, which 32-row workgroups
-  // spread over twice as many waves
   const bool masked = d[0].drop_thr != 0 || (nprob == 2 && d[1].drop_thr != 0);
-  p.mr = (nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2 && !masked) ? 2 : 1;
-  const int mb = 32 * p.mr;
+  auto count = [&](int mb) {
+    int64_t b = 0;
+    for (int w = 0; w < nprob; ++w) b += (d[w].M + mb - 1) / mb;
+    return b;
+  };
   for (int w = 0; w < nprob; ++w) {
-    blocks += (d[w].M + mb - 1) / mb;
     const int64_t kt = (d[w].K + bk - 1) / bk;
     if (kt < min_ktiles) min_ktiles = kt;
     outs += d[w].M * d[w].N;
   }
-  // split K over workgroups only when there are fewer workgroups than compute units, and keep >= 8 K tiles
-  // per wave and slice.  (64-row workgroups: 128-160 of them without a split beat twice as many plus the
-  // reduce pass, measured on the paired dA / dB launches.)
+  // 64-row workgroups (see skinny.hpp) where they fill more than half of the compute units, or where the contraction can be
+  // split over them.  dA, dB in us, 64 rows / 32 rows: 2048 x (2048 + 2048) 12.4 / 8.9, 2048 x (4096 + 4096) 13.4 / 10.3, 4096
+  // x (4096 + 4096) 18.8 / 15.6, 8192 x (4096 + 4096) 34 / 30.6, 8192 x (1024 + 4096) 27.7 (four slices) / 22.9; with more
+  // blocks 2048 x (2048 + 8192) 15.1 / 16.6, 4096 x (2048 + 8192) 21.1 / 25.4, 8192 x (4096 + 6144) 33 / 48; with few and a long
+  // contraction 8192 x (768 + 3072) 21.4 (four slices) / 24.0.
+  if (nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2 && !masked) {
+    const int64_t b64 = count(64);
+    if (b64 > 128 || (b64 <= 64 && min_ktiles >= 64)) p.mr = 2;
+  }
+  const int64_t blocks = count(32 * p.mr);
+  // 16 waves for a masked problem of the [M,K] orientation with at least 24 K tiles (T of 8192 x 768, 12 tiles of 64: 10.1 us
+  // on 16 waves, 9.0 on 4; 2048 x 2048, 32 tiles: 9.3 and 13.4).  Next to an unmasked problem that streams better on 4 waves
+  // (4096 x 2048 -> 8192: 27.8 and 23.6) only while the launch leaves its masked part half a compute unit or more and that
+  // part is no shorter than half of the other (4096 x (4096 + 4096): 17.3 and 22.5; 8192 x (4096 + 4096): 38.5 and 37.4).
+  if (masked && !d[0].a_strided && p.rt == 1) {
+    const SkinnyDesc& m = d[0].drop_thr != 0 ? d[0] : d[1];
+    const bool alone = nprob == 1 || (blocks <= 256 && 2 * m.K >= (d[0].drop_thr != 0 ? d[1] : d[0]).K);
+    if (alone && (m.K + bk - 1) / bk >= 24) p.nwv = 16;
+  }
+  // Split K over workgroups only when there are fewer workgroups than compute units, and keep >= 8 K tiles per wave and slice
+  // (12 where 32 or more blocks of up to 32 columns share the work: T of 2048 x 4096 12.2 us in two slices with their reduce
+  // pass, 12.0 whole, 5000 x 5464 23.5 and 18.3, 4096 x 8192 18.2 and 20.4).
+  // (64-row workgroups: 128-160 of them without a split beat twice as many plus the reduce pass, and so do 32-row ones of a
+  // pair that 64-row blocks do not fill.)
   int64_t splits = 1;
-  if (blocks < (p.mr == 2 ? 128 : 224)) {
+  const bool half = nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2 && !masked;
+  if (blocks < (half ? 128 : 224)) {
     splits = (256 + blocks - 1) / blocks;
-    int64_t cap = min_ktiles / 32;
+    const int64_t per_wave = p.nwv == 16 ? 4 : (!d[0].a_strided && p.rt == 1 && blocks >= 32 ? 12 : 8);
+    int64_t cap = min_ktiles / (p.nwv * per_wave);
     if (cap < 1) cap = 1;
     if (splits > cap) splits = cap;
     if (splits > 16) splits = 16;
@@ -746,6 +769,7 @@ hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, f
   SkinnyArgs r{};
   r.nprob = 2;
   r.mr = 1;
+  r.nwv = 4;
   float* part = scratch;
   unsigned grid = 0;
   int al = 0, bl[2] = {0, 0};
@@ -793,6 +817,7 @@ hipError_t skinny_run(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
   SkinnyArgs a{};
   a.nprob = nprob;
   a.mr = plan.mr;
+  a.nwv = plan.nwv;
   if (plan.mr != 1 && !(plan.mr == 2 && nprob == 2 && d[0].a_strided && d[1].a_strided && plan.rt <= 2)) return hipErrorInvalidValue;
   float* part = scratch;
   for (int w = 0; w < nprob; ++w) {

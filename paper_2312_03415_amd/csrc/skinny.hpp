@@ -6,16 +6,20 @@
 // operand is used for only ~r FLOPs, so the kernel is HBM-bandwidth bound and is built for bytes in
 // flight rather than for MFMA occupancy.
 //
-//  - One workgroup = NWV (4) wavefronts that share a block of 32 * MR output rows and split the
-//    workgroup's K range between them.  MR = 2 (64 rows) is used by paired launches whose A operands are
-//    stored [K,M] (N <= 64, no LoRA dropout mask: a masked problem is bound by its waves' mask arithmetic): a block's rows are then columns of A, a 32-column strip is 64 bytes per
-//    row of A, half a 128-byte line, and the other half has to come from the neighbouring workgroup's
-//    fetch staying in L2; with 128-byte strips the paired dA / dB launch runs 20 % faster (OPT shapes:
-//    25.6 -> 20.5 us).  Single launches keep 32 rows: halving their workgroup count costs more than the
-//    strips gain (dB of OPT fc1 alone: 18.8 -> 23.4 us).  (The workgroup's K range is split between the waves as wave w taking K tiles w, w+NWV, ...; 8 or 16 wavefronts per
-//    workgroup measured slower.)  Every wavefront runs its own
-//    global -> register -> LDS -> MFMA pipeline on a private LDS region: no workgroup barrier in the
-//    loop, the next tile's loads are in flight while the current one is multiplied.
+//  - One workgroup = NWV wavefronts that share a block of 32 * MR output rows and split the workgroup's K range between
+//    them: wave w takes K tiles w, w+NWV, ...  Every wavefront runs its own global -> register -> LDS -> MFMA pipeline on a
+//    private LDS region: no workgroup barrier in the loop, the next tile's loads are in flight while the current one is
+//    multiplied.
+//  - MR = 2 (64 rows) is used by paired launches whose A operands are stored [K,M] (N <= 64, no LoRA dropout mask), where the
+//    64-row blocks fill more than half of the compute units: a block's rows are then columns of A, a 32-column strip is 64
+//    bytes per row of A, half a 128-byte line, and the other half has to come from the neighbouring workgroup's fetch staying
+//    in L2.  With 128-byte strips dA, dB of 4096 x (2048 + 8192) r 16 take 21.4 us, 25.0 without; with fewer blocks the chip's
+//    idle units cost more (skinny_plan).  Single launches keep 32 rows (dB of 4096 x 8192 alone: 18.8 -> 23.4 us).
+//  - NWV = 4 where loads bind: 8 or 16 waves make no plain launch faster (a compute unit fetches 50-60 bytes a ns, operand
+//    B's share included, whatever the number of waves).  A masked problem (LoRA dropout) in the [M,K] orientation is bound by
+//    its waves' mask arithmetic, one chain of instructions per wave: 16 waves (two tiles of loads in flight each) take 22.7
+//    us against 30.5 for T = (X o m) A of 4096 x 8192 r 16 (two K slices), 25.8 against 37.2 for {Z1, Z2} of 4096 x 8192 ->
+//    2048.
 //  - The waves' partial accumulators are summed through LDS in wave order and written once.  A grid
 //    that also splits K over workgroups (gridDim.y) writes fp32 partials that a second kernel sums
 //    in slice order.  No atomics: results are identical from run to run.
@@ -47,7 +51,8 @@ struct SkinnyProblem {
 struct SkinnyArgs {
   SkinnyProblem p[2];
   int nprob;
-  int mr;  // 32-row blocks per workgroup (1 or 2): selects the build
+  int mr;   // 32-row blocks per workgroup (1 or 2): selects the build
+  int nwv;  // wavefronts per workgroup (4, or 16 for a masked launch in the [M,K] orientation): selects the build
 };
 
 template <typename T, int RT, int NWV, int MR>
@@ -108,7 +113,8 @@ __device__ __forceinline__ void skinny_body(const SkinnyProblem& P, int bx, unsi
   constexpr int B_PER = 4 * RT;  // BK x NB/VE... = 256*RT chunks over 64 lanes
   // register stages: the loads of DEPTH tiles are in flight per wave (a streaming kernel lives on
   // bytes in flight, not on occupancy)
-  constexpr int DEPTH = MR * RT == 1 ? 4 : (MR * RT == 2 ? 3 : 2);  // (6 stages at RT = 1 measured 7-28 % slower)
+  constexpr int DEPTH = NWV == 16 ? 2 : (MR * RT == 1 ? 4 : (MR * RT == 2 ? 3 : 2));  // (6 stages at RT = 1 measured 7-28 % slower)
+  static_assert(NWV == 4 || (NWV == 16 && MR * RT == 1), "16 waves: two stages of a 32x32 block fit their registers and LDS");
   i32x4 ra[DEPTH][A_PER], rb[DEPTH][B_PER];
 
   // Loads go through buffer descriptors: a lane whose chunk lies outside the matrix (or whose tile
