@@ -36,6 +36,10 @@ struct GemmDesc {
   // LoRA dropout (drop_thr != 0): zero output element (m, n) of alpha * (the products) where the mask
   // drops element (m, n) of X; key and threshold as in gemm_engine.hpp, drop_cpr = columns of X / 4
   uint32_t drop_thr = 0, drop_key = 0, drop_cpr = 0;
+  // the mask applies to segment 0's product alone, C = mask o (A[0] B[0]) + A[1] B[1] (GemmArgs::mask_seg0), with drop_n4 =
+  // (first column of C in X) / 4; where masked_segment_ok holds
+  bool mask_seg0 = false;
+  uint32_t drop_n4 = 0;
   // One-pass LoRA forward, C = A[0] B[0] + round(t_alpha A[0] LA) B[1] in one kernel: nseg = 2, A[1] unused,
   // K[1] = R <= kFuseMaxR, LA stored [K[0], R] row-major; A [M,K], B [K,N], dense B, no addend, no K split
   // (plan with gemm_plan_fused).  fuse_t is also set when only shapes are modelled and LA is null.
@@ -89,6 +93,8 @@ GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int 
 // An operand beyond what the middle-sized kernel addresses (31-bit byte offsets; the 256x256 kernel takes twice that): the
 // product keeps the plan by tile counts (same scratch).
 bool long_operand(const GemmDesc& d);
+// A plan whose kernels are built with a masked first segment: dense 16-bit operands, A [M,K], B [N,K], no addend, scale or bias.
+bool masked_segment_ok(const GemmDesc& d, const GemmPlan& p);
 
 // Modelled time in us of one launch of a 16-bit tile GEMM (CFG_MT*, CFG_MC4, and the generic engine's 128x128, 128x64 and
 // 64x128 tiles): nbm x nbn output tiles x K slices of `ktiles` K tiles each; odd = odd_lines of the product.

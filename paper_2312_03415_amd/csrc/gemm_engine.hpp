@@ -56,6 +56,10 @@ struct GemmArgs {
   // drop_thr != 0: output element (m, n) of alpha * (the products) is zeroed where the dropout mask
   // drops element (m, n) of X (the adapter's share of dX); drop_cpr = groups of four columns per row
   uint32_t drop_thr, drop_key, drop_cpr;
+  // != 0 (gemm_mc64.hpp, gemm_mt.hpp; A [M,K], B [N,K]): the mask applies to segment 0's product alone, which is complete
+  // before segment 1's is added to it: C = mask o (A[0] B[0]) + A[1] B[1].  drop_n4 = first column of C in X / 4.
+  int mask_seg0;
+  uint32_t drop_n4;
   // One-pass LoRA forward (gemm_kernel's FUSE build, Y = X W + (s X A) B of Section 2's forward 1 in one kernel):
   // LA = the adapter's A [K[0], R] row-major (R <= 32), t_alpha = s.  The kernel then forms T = t_alpha * A[0] LA
   // for its own rows next to the main product, rounds it to T's type and contracts it with B[1] ([R, N]) as one more
@@ -122,6 +126,17 @@ __device__ __forceinline__ void drop_keep4(uint32_t g, uint32_t key, uint32_t th
   const uint32_t f = drop_ge_bytes(drop_mix(g ^ key), thr);
 #pragma unroll
   for (int k = 0; k < 4; ++k) keep[k] = (uint32_t)((int32_t)(f << (24 - 8 * k)) >> 31);
+}
+// four accumulators of columns 4 g .. + 3 with the dropped ones zeroed
+__device__ __forceinline__ f32x4 drop_acc4(f32x4 v, uint32_t g, uint32_t key, uint32_t thr) {
+  uint32_t keep[4];
+  drop_keep4(g, key, thr, keep);
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float x = v[k];  // (a bit cast of a vector's element itself reads element 0)
+    v[k] = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & keep[k]);
+  }
+  return v;
 }
 // a 16-byte chunk of X whose first column belongs to group g (8 columns = groups g, g+1 for 16-bit
 // types; 4 columns = group g for fp32) with the dropped elements zeroed

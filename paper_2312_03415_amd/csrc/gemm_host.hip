@@ -157,6 +157,12 @@ bool long_operand(const GemmDesc& d) {
   return false;
 }
 
+bool masked_segment_ok(const GemmDesc& d, const GemmPlan& p) {
+  auto built = [&](int cfg, int splits) { return cfg_is_mt(cfg) || (cfg == CFG_MC4 && splits <= 1 && d.K[0] <= 32); };
+  return d.dtype != DT_F32 && d.nseg == 2 && !d.a_strided && d.b_kcontig && !d.b_int4 && d.Bscale == nullptr && !d.has_addend && d.D == nullptr &&
+         d.bias == nullptr && d.alpha == 1.f && !d.fuse_t && !long_operand(d) && built(p.cfg, p.splits) && (p.tail_n0 == 0 || built(p.tail_cfg, p.tail_splits));
+}
+
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg,
                    int force_splits, bool b_int4, bool long_operand) {
   GemmPlan p;
@@ -359,7 +365,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   if (plan.tail_n0 > 0) {
     // columns [0, tail_n0) with this plan, columns [tail_n0, N) as their own problem
     if (plan.tail_n0 >= d.N) return hipErrorInvalidValue;
-    if (d.drop_thr != 0) return hipErrorInvalidValue;  // the mask is indexed by the full product's columns (K = r: never cut)
+    if (d.drop_thr != 0 && !d.mask_seg0) return hipErrorInvalidValue;  // the mask is indexed by the full product's columns (K = r: never cut)
     const size_t esz = d.dtype == DT_F32 ? 4 : 2;
     GemmDesc dm = d, dt = d;
     GemmPlan pm = plan;
@@ -367,6 +373,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
     pm.partial_bytes = 0;
     dm.N = plan.tail_n0;
     dt.N = d.N - plan.tail_n0;
+    dt.drop_n4 = d.drop_n4 + (uint32_t)(plan.tail_n0 / 4);
     for (int s = 0; s < d.nseg; ++s) {
       const int64_t off = d.b_kcontig ? plan.tail_n0 * d.ldb[s] : plan.tail_n0;
       if (s == 0 && d.Bscale != nullptr) {
@@ -389,6 +396,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
     return gemm_run(dt, pt, pt.splits > 1 ? scratch : nullptr, stream);
   }
   if (plan.splits > 1 && scratch == nullptr) return hipErrorInvalidValue;
+  if (d.mask_seg0 && (d.drop_thr == 0 || !masked_segment_ok(d, plan))) return hipErrorInvalidValue;
   if (d.fuse_t) {
     const bool ok = d.LA != nullptr && d.nseg == 2 && d.K[1] >= 1 && d.K[1] <= kFuseMaxR && d.K[0] >= 1 && !d.a_strided &&
                     !d.b_kcontig && plan.splits == 1 && d.D == nullptr && d.Bscale == nullptr && d.drop_thr == 0 &&
@@ -449,6 +457,8 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   a.drop_thr = d.drop_thr;
   a.drop_key = d.drop_key;
   a.drop_cpr = d.drop_cpr;
+  a.mask_seg0 = d.mask_seg0 ? 1 : 0;
+  a.drop_n4 = d.drop_n4;
   a.rotate = d.rotate;
   a.LA = d.fuse_t ? d.LA : nullptr;
   a.ldla = d.ldla;
@@ -466,7 +476,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   if (e != hipSuccess) return e;
   if (plan.splits > 1)
     e = splitk_reduce_launch(d.dtype, scratch, plan.splits, (int)d.M, (int)d.N, d.C, d.ldc, d.D, d.ldd, d.alpha,
-                             d.bias, DropMask{d.drop_thr, d.drop_key, d.drop_cpr}, stream);
+                             d.bias, d.mask_seg0 ? DropMask{} : DropMask{d.drop_thr, d.drop_key, d.drop_cpr}, stream);
   return e;
 }
 

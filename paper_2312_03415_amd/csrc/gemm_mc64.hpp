@@ -66,10 +66,16 @@ template <> struct Elem16<__bf16> {
   static __device__ __forceinline__ void mma(f32x4& acc, i32x4 rowop, i32x4 colop) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(rowop), "v"(colop));
   }
+  static __device__ __forceinline__ void mma0(f32x4& out, i32x4 rowop, i32x4 colop) {  // out = rowop * colop, in vector registers
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(out) : "v"(rowop), "v"(colop));
+  }
 };
 template <> struct Elem16<_Float16> {
   static __device__ __forceinline__ void mma(f32x4& acc, i32x4 rowop, i32x4 colop) {
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(rowop), "v"(colop));
+  }
+  static __device__ __forceinline__ void mma0(f32x4& out, i32x4 rowop, i32x4 colop) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=&v"(out) : "v"(rowop), "v"(colop));
   }
 };
 
@@ -97,8 +103,16 @@ struct Mc64Tile {
 // Bound by the pattern and number of its store instructions: the general epilogue stores 8 bytes per lane, two rows of
 // 256 bytes per instruction, behind its options' branches; 3 stores 16 bytes per lane like 1.  Y = X W + bias at
 // 4096 x 2048 -> 8192 (two tiles per compute unit): 148 us with the general epilogue, 126 with 3 (118 without a bias).
-template <typename T, int AL, int BL, int PLAIN>
+//
+// SEGMASK (with PLAIN 3, no bias): dX = dY W^T + m o (Z1 A^T) of a layer with LoRA dropout in one launch, r <= 32.  The masked
+// product cannot share the accumulators with the other (masking those in the K loop has the compiler move all 256), so it is
+// formed in the epilogue, a row block at a time: one MFMA a block out of fragments of Z1 (g.A[1], [M, R]) and A (g.B[1], [N,
+// R]) that come straight from memory, then one hash per four accumulators (a lane holds four consecutive columns of a row).
+// ~35 vector instructions a block, 5 us a tile, where an update of dX in a pass of its own reads and writes all of it: 4096 x
+// 8192, r 16: 33 us.
+template <typename T, int AL, int BL, int PLAIN, bool SEGMASK = false>
 __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
+  static_assert(!SEGMASK || (PLAIN == 3 && AL == 0 && BL == 1), "the epilogue and layout the masked product is built with");
   using P = Mc64Tile<AL, BL>;
   constexpr int BM = P::BM, BN = P::BN, BK = P::BK, IPW = P::IPW;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -415,7 +429,7 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
     // PLAIN 3: this lane's bias (columns 16 b + 4 grp .. + 3 of the wave's 128), requested ahead of the K loop so that
     // the epilogue does not wait for it; columns beyond N read the last four in range and are never stored
     [[maybe_unused]] i32x2 bias2[8];
-    if constexpr (PLAIN == 3) {
+    if constexpr (PLAIN == 3 && !SEGMASK) {
 #pragma unroll
       for (int b = 0; b < 8; ++b) {
         int n = n0 + wn * 128 + 16 * b + 4 * grp;
@@ -472,10 +486,34 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
       [[maybe_unused]] const bool n_ok = n0 + wn * 128 + rc * 8 < g.N;  // N is a multiple of 8: valid together
       typedef float f32x2_t __attribute__((ext_vector_type(2)));
       typedef T tx2_t __attribute__((ext_vector_type(2)));
+      // SEGMASK: this wave's fragments of Z1 and A (lane l: row l % 16 of a block, k 8 (l / 16) .. + 7; zero beyond M, N, R)
+      [[maybe_unused]] i32x4 fz[8], fr[8];
+      [[maybe_unused]] f32x4 upd[8];
+      [[maybe_unused]] uint32_t group = 0;
+      if constexpr (SEGMASK) {
+        const bool k_ok = 8 * grp < g.R;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+          const int n = n0 + wn * 128 + 16 * b + s16;
+          fr[b] = k_ok && n < g.N ? *reinterpret_cast<const i32x4*>(segB1 + (int64_t)n * ldb1 + 8 * grp) : i32x4{0, 0, 0, 0};
+        }
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+          const int m = m0 + wm * 128 + 16 * a + s16;
+          fz[a] = k_ok && m < g.M ? *reinterpret_cast<const i32x4*>(segA1 + (int64_t)m * lda1 + 8 * grp) : i32x4{0, 0, 0, 0};
+        }
+        group = (uint32_t)(m0 + wm * 128 + s16) * g.drop_cpr + g.drop_n4 + (uint32_t)((n0 + wn * 128) >> 2) + (uint32_t)grp;
+      }
       static_for<4>([&](auto a2c) {
         constexpr int a2 = decltype(a2c)::value;
         static_for<16>([&](auto ec) {
           constexpr int ah = decltype(ec)::value >> 3, b = decltype(ec)::value & 7, a = 2 * a2 + ah;
+          if constexpr (SEGMASK && b == 0) {
+            asm volatile("s_nop 4");  // (the fragments may just have been written)
+            static_for<8>([&](auto bc) { Elem16<T>::mma0(upd[decltype(bc)::value], fr[decltype(bc)::value], fz[a]); });
+            asm volatile("s_nop 7\n\ts_nop 7");  // the results are read by instructions the compiler does not see behind an MFMA
+            __builtin_amdgcn_sched_barrier(0);
+          }
           const uint32_t row = (uint32_t)(16 * ah + s16);
           const uint32_t wr = stg_base + row * 256u;
           const uint32_t wsw = 2u * (row & 15u);
@@ -484,7 +522,14 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
           asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x1) : "a"(acc[a][b][1]));
           asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x2) : "a"(acc[a][b][2]));
           asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x3) : "a"(acc[a][b][3]));
-          if constexpr (PLAIN == 3) {
+          if constexpr (SEGMASK) {
+            const f32x4 v = drop_acc4(upd[b], group + 4 * b, g.drop_key, g.drop_thr);
+            x0 += v[0]; x1 += v[1]; x2 += v[2]; x3 += v[3];
+            if constexpr (b == 7) {
+              group += 16u * g.drop_cpr;
+              asm volatile("" : "+v"(group));  // (nothing to prepare ahead)
+            }
+          } else if constexpr (PLAIN == 3) {
             T b4[4];
             *reinterpret_cast<i32x2*>(b4) = bias2[b];
             x0 += (float)b4[0]; x1 += (float)b4[1]; x2 += (float)b4[2]; x3 += (float)b4[3];
@@ -609,6 +654,10 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
 template <typename T, int AL, int BL, int PLAIN>
 __global__ __launch_bounds__(256, 1) void gemm_mc64_kernel(GemmArgs g) {
   gemm_mc64_body<T, AL, BL, PLAIN>(g);
+}
+template <typename T>
+__global__ __launch_bounds__(256, 1) void gemm_mc64_segmask_kernel(GemmArgs g) {
+  gemm_mc64_body<T, 0, 1, 3, true>(g);
 }
 
 }  // namespace rl

@@ -92,7 +92,10 @@ template <> struct MtFrag<true> {
   __device__ __forceinline__ void touch() { asm volatile("" : "+v"(lo), "+v"(hi)); }
 };
 
-template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA>
+// SEGMASK: dX = m o (Z1 A^T) + dY W^T of a layer with LoRA dropout in one launch.  Segment 0 is the rank-r one; behind its last K
+// tile (of this K slice) the dropped accumulators are zeroed (a lane holds four consecutive columns of a row: one hash), and
+// the other segment is added to what is left.
+template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA, bool SEGMASK = false>
 __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, const int by) {
   static_assert(!XA || (AL == 0 && BL == 0), "X [M,K], W and A [K,.]");
   using P = MtTile<AL, BL, BM, BN, NS>;
@@ -352,6 +355,26 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
       wait_frags(I0{});
       MT_FENCE();
       cursor_advance();
+      if constexpr (SEGMASK) {
+        if (u < nt0 && (u == nt0 - 1 || u == u1 - 1)) {  // wave-uniform: the last tile of segment 0 in this slice
+          if constexpr (TM * TN > 16) asm volatile("s_nop 7\n\ts_nop 7");
+          MT_FENCE();
+          // (opaque: nothing of this is worth keeping in registers around the K loop)
+          uint32_t group = (uint32_t)(m0 + wm * P::WTM + s16) * g.drop_cpr + g.drop_n4 + (uint32_t)((n0 + wn * P::WTN) >> 2) + (uint32_t)grp;
+          asm volatile("" : "+v"(group));
+          static_for<TM * TN>([&](auto e) {
+            constexpr int a = decltype(e)::value / TN, b = decltype(e)::value % TN;
+            acc[a][b] = drop_acc4(acc[a][b], group + 4 * b, g.drop_key, g.drop_thr);
+            if constexpr (b == TN - 1) {
+              group += 16u * g.drop_cpr;
+              asm volatile("" : "+v"(group));
+            }
+            MT_FENCE();
+          });
+          if constexpr (TM * TN > 16) asm volatile("s_nop 7");
+          MT_FENCE();
+        }
+      }
       st = stn;
     }
   }
@@ -398,7 +421,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
           *reinterpret_cast<f32x4*>(dst + 4) = v1;
         } else {
           if (g.alpha != 1.f) { v0 *= g.alpha; v1 *= g.alpha; }
-          if (g.drop_thr != 0u) {
+          if (!SEGMASK && g.drop_thr != 0u) {
             uint32_t k0[4], k1[4];
             const uint32_t grp4 = (uint32_t)m * g.drop_cpr + (uint32_t)(n >> 2);
             drop_keep4(grp4, g.drop_key, g.drop_thr, k0);
@@ -427,6 +450,11 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
 template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA = false>
 __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_kernel(GemmArgs g) {
   gemm_mt_body<T, AL, BL, BM, BN, NS, XA>(g, (int)blockIdx.x, (int)blockIdx.y);
+}
+
+template <typename T, int AL, int BL, int BM, int BN, int NS>
+__global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_segmask_kernel(GemmArgs g) {
+  gemm_mt_body<T, AL, BL, BM, BN, NS, false, true>(g, (int)blockIdx.x, (int)blockIdx.y);
 }
 
 // Two products in one launch (Z1 = dY B^T with Z2 = X A, dA = X^T Z1 with dB = Z2^T dY; r > 32): each fills a part of the

@@ -106,6 +106,32 @@ struct Builder {
     out->steps.push_back(s);
   }
 
+  // dX = m o (Z1 A^T) + dY W^T under LoRA dropout in one launch, the mask between the two products of the contraction; false
+  // where the plan's kernels are not built for it (fp32, an int4 W, a few rows or columns).  The plan, and with it the scratch,
+  // is that of the layer without dropout.
+  bool masked_update(const char* what, Mat dY, Mat W, Mat Z1, Mat A, Mat dX) {
+    Step s;
+    s.what = what;
+    GemmDesc& d = s.d;
+    d.dtype = L.dtype;
+    d.b_kcontig = 1;
+    d.M = L.n;
+    d.N = L.i;
+    d.nseg = 2;
+    d.A[0] = Z1.ptr; d.lda[0] = Z1.ld; d.B[0] = A.ptr; d.ldb[0] = A.ld; d.K[0] = L.r;
+    d.A[1] = dY.ptr; d.lda[1] = dY.ld; d.B[1] = W.ptr; d.ldb[1] = W.ld; d.K[1] = L.o;
+    d.C = const_cast<void*>(dX.ptr);
+    d.ldc = dX.ld;
+    d.mask_seg0 = true;
+    d.drop_thr = L.drop_thr; d.drop_key = L.drop_key; d.drop_cpr = drop_cpr();
+    if (L.w_int4) return false;
+    s.plan = gemm_plan(L.dtype, L.n, L.i, L.o, L.r, -1, 0, false, long_operand(d));
+    if (!masked_segment_ok(d, s.plan)) return false;
+    if (s.plan.partial_bytes > max_partial) max_partial = s.plan.partial_bytes;
+    out->steps.push_back(s);
+    return true;
+  }
+
   // Y = X W + (s X A) B (+ bias) in one launch of the tile GEMM's one-pass build: X is read once, T = s X A lives
   // in the kernel only
   void fused_forward(const char* what, Mat X, Mat W, Mat A, Mat B, Mat Y, const void* bias) {
@@ -368,7 +394,8 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
       Mat Z1 = b.scratch(n, r), Z2 = op.have_T ? op.T : b.scratch(n, r);
       if (dX && !L.drop_thr && r > 32) b.expect_gemm(n, i, o, r, true, op.dY.ld);
       rank_r_pass(b, op, n, i, o, r, Z1, Z2, dA || dX, dB && !op.have_T, dA, dB);
-      if (dX && L.drop_thr) {  // the mask sits between the two products: no concatenated contraction
+      if (dX && L.drop_thr && b.masked_update("dX = m o (Z1 A^T) + dY W^T", op.dY, op.W, Z1, op.A, op.dX)) {
+      } else if (dX && L.drop_thr) {  // no concatenated contraction: the mask sits between the two products
         b.gemm("dX = dY W^T", 0, 1, n, i, o, op.dY, op.W, op.dX, nullptr, 0, nullptr, nullptr, true);
         b.gemm("dX += Z1 A^T", 0, 1, n, i, r, Z1, op.A, op.dX, &op.dX, 0, nullptr, nullptr, false, 1.f, nullptr, true);
       } else if (dX) {
