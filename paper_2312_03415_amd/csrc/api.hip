@@ -809,17 +809,21 @@ extern "C" size_t runlora_workspace_bytes_w(int fwd, int bwd, int64_t n, int64_t
   size_t need = 0;
   Schedule sch;
   // dense rows (ld = columns): which kernel a rank-r product runs on, and with it the scratch, depends on the
-  // operands' extents; a call on tensors with padded rows may need more and says how much (RL_ERR_WORKSPACE)
-  if (fwd >= 0) {
-    FwdOperands op;
-    op.X.ld = i; op.W.ld = o; op.A.ld = r; op.B.ld = o; op.Y.ld = o; op.T.ld = r; op.M.ld = o;
-    if (build_forward(fwd, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
-  }
-  if (bwd >= 0) {
-    BwdOperands op;
-    op.dY.ld = o; op.X.ld = i; op.W.ld = o; op.A.ld = r; op.B.ld = o; op.T.ld = r; op.dX.ld = i; op.dA.ld = r; op.dB.ld = o;
-    op.M.ld = o;
-    if (build_backward(bwd, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
+  // operands' extents; a call on tensors with padded rows may need more and says how much (RL_ERR_WORKSPACE).  With and
+  // without LoRA dropout, which variants 0 and 1 exist with: masked products have plans of their own.
+  for (const uint32_t thr : {0u, 1u}) {
+    L.drop_thr = thr;
+    if (fwd >= 0 && (thr == 0 || fwd <= 1)) {
+      FwdOperands op;
+      op.X.ld = i; op.W.ld = o; op.A.ld = r; op.B.ld = o; op.Y.ld = o; op.T.ld = r; op.M.ld = o;
+      if (build_forward(fwd, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
+    }
+    if (bwd >= 0 && (thr == 0 || bwd <= 1)) {
+      BwdOperands op;
+      op.dY.ld = o; op.X.ld = i; op.W.ld = o; op.A.ld = r; op.B.ld = o; op.T.ld = r; op.dX.ld = i; op.dA.ld = r; op.dB.ld = o;
+      op.M.ld = o;
+      if (build_backward(bwd, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
+    }
   }
   return need;
 }

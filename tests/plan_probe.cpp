@@ -24,6 +24,12 @@ int main() {
       std::printf("%d %d %zu %zu\n", p.cfg, p.tail_n0 > 0 ? p.tail_cfg : p.cfg, p.partial_bytes, gemm_plan(DT_BF16, M, N, K0, 0).partial_bytes);
     } else if (std::strcmp(kind, "int4") == 0) {  // panels or not, and the direct kernel's id
       std::printf("%d %d\n", int4_panel_plan(DT_BF16, M, N, K0, K1).width > 0 ? 1 : 0, gemm_plan_int4(DT_BF16, M, N, K0, K1).cfg);
+    } else if (std::strncmp(kind, "drop", 4) == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: scratch of forward 1 and backward 1 with dropout
+      LayerDims L{M, N, K0, K1, kind[4] == '3' ? DT_F32 : DT_BF16};
+      L.drop_thr = 26;
+      Schedule f, b;
+      if (!build_forward(1, L, FwdOperands{}, nullptr, &f) || !build_backward(1, L, BwdOperands{}, nullptr, &b)) return 1;
+      std::printf("%zu %zu\n", f.workspace_bytes, b.workspace_bytes);
     } else if (std::strcmp(kind, "few") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: the few-token route's price and taken or not
       SkinnyDesc d;
       d.M = M; d.N = K1; d.K = N;

@@ -80,3 +80,16 @@ def test_int4_products_take_the_faster_route(probe):
     direct = [(913, 6232, 6240, 16), (3748, 7888, 12720, 16), (1062, 7768, 8680, 16)]
     assert [p[0] for p in probe("int4", panels)] == [1] * 4
     assert [p[0] for p in probe("int4", direct)] == [0] * 3
+
+
+def test_the_workspace_query_covers_lora_dropout(probe):
+    """A masked product has a plan of its own (256 x 768 -> 768, fp32: dY W^T in six slices, [dY|Z1] [W^T;A^T] in five): the bytes that
+    runlora_workspace_bytes names are enough with dropout too."""
+    from paper_2312_03415_amd import binding as rl
+    rng = np.random.default_rng(7)
+    rows = [(256, 768, 768, 8), (512, 176, 5872, 24), (5653, 2216, 2720, 8)]
+    rows += [(int(np.exp(rng.uniform(0, np.log(9000)))), int(rng.integers(8, 1000)) * 8, int(rng.integers(8, 1000)) * 8, int(rng.choice([8, 24, 64, 128]))) for _ in range(300)]
+    for kind, code in (("drop32", rl.RL_F32), ("drop16", rl.RL_BF16)):
+        for (n, i, o, r), need in zip(rows, probe(kind, rows)):
+            assert rl.runlora_workspace_bytes(1, -1, n, i, o, r, code) >= need[0], (kind, n, i, o, r)
+            assert rl.runlora_workspace_bytes(-1, 1, n, i, o, r, code) >= need[1], (kind, n, i, o, r)
