@@ -895,6 +895,7 @@ static int check_gemm(const rl_gemm_t* g, GemmDesc* d, GemmPlan* plan) {
     d->bias = g->bias;
   }
   if (g->tile_cfg != CFG_STREAM) *plan = gemm_plan(dt, g->M, g->N, g->K, g->K2, g->tile_cfg, g->splits, false, long_operand(*d));
+  if (dt == DT_F32 && g->tile_cfg < 0 && g->splits <= 0) gemm_plan_f32(plan, g->M, g->N, g->K, g->K2);
   return RL_OK;
 }
 

@@ -90,6 +90,9 @@ struct GemmPlan {
 // long_operand: see long_operand below.
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg = -1,
                    int force_splits = 0, bool b_int4 = false, bool long_operand = false);
+// For fp32 gemm_plan goes by tile counts (forward 3 takes its shape from there); a product of its own runs on the tile shape and
+// K split that this picks by modelled time, in the scratch of that plan.
+void gemm_plan_f32(GemmPlan* plan, int64_t M, int64_t N, int64_t K0, int64_t K1);
 // An operand beyond what the middle-sized kernel addresses (31-bit byte offsets; the 256x256 kernel takes twice that): the
 // product keeps the plan by tile counts (same scratch).
 bool long_operand(const GemmDesc& d);

@@ -163,6 +163,48 @@ bool masked_segment_ok(const GemmDesc& d, const GemmPlan& p) {
          d.bias == nullptr && d.alpha == 1.f && !d.fuse_t && !long_operand(d) && built(p.cfg, p.splits) && (p.tail_n0 == 0 || built(p.tail_cfg, p.tail_splits));
 }
 
+// What a launch of an fp32 tile GEMM takes, in us: a K tile of 32 takes a workgroup `one` alone on its compute unit, c workgroups on
+// a unit c `sat` together, whatever runs next to what (128x128 512 GFLOP/s a unit, narrower tiles less: their operands are read
+// more often).  Fitted to 16 products (200 .. 4096 rows, 512 .. 3000 columns, K 512 .. 4000), every tile and 1 .. 10 slices: within
+// 10 % but for a few with many short slices.
+static double f32_launch_us(int cfg, int64_t tiles, int splits, int64_t ktiles) {
+  struct { double one, sat; } static const m[6] = {{8.1, 8.1}, {2.56, 2.26}, {1.02, 0.76}, {1.55, 1.2}, {1.02, 0.78}, {1.55, 1.25}};
+  const double per = m[cfg].sat * (double)((tiles * splits + 255) / 256);
+  return 4.0 + (double)ktiles * (per > m[cfg].one ? per : m[cfg].one);
+}
+
+// Tile shape and K split of an fp32 product (more than 32 rows and columns) by that model, in the scratch of the plan by tile
+// counts that comes in, which takes 128x128 tiles and as many slices as fill the chip: 256 x 768 x 768 21.8 us against 12.8 on 48 tiles of
+// 32x128 in five slices, 4096 x 512 x 512 39.8 against 33 unsplit on 128x64, 1000 x 1024 x 1024 38 against 34.6, 300 x 2000 x 4000
+// 102 against 67, 500 x 2048 x 2048 57 against 55.5.  Larger products keep the plan by tile counts: several workgroups of narrow
+// tiles on every unit feed each other less than the model says (2000 x 768 x 3072 123 against 133, 3000 x 1800 x 1800 264 against
+// 278, 950 x 3000 x 3000 235 against 243).
+void gemm_plan_f32(GemmPlan* p, int64_t M, int64_t N, int64_t K0, int64_t K1) {
+  if (M <= 32 || N <= 32 || (double)M * (double)N * (double)(K0 + K1) > 4e9) return;
+  const int64_t kt = (K0 + p->bk - 1) / p->bk + (K1 + p->bk - 1) / p->bk;
+  const size_t cap = p->partial_bytes;  // the scratch stays what is reported
+  double best = 1e30;
+  for (int cfg = CFG_BIG; cfg <= CFG_WIDE64; ++cfg) {
+    const int64_t nbm = (M + kTileBM[cfg] - 1) / kTileBM[cfg], nbn = (N + kTileBN[cfg] - 1) / kTileBN[cfg];
+    if (nbm * nbn > (1 << 24)) continue;
+    for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+      const int64_t per = (kt + s - 1) / s;
+      if ((kt + per - 1) / per != s) continue;  // no empty slice
+      if (s > 1 && (size_t)s * (size_t)M * (size_t)N * sizeof(float) > cap) break;
+      const double us = f32_launch_us(cfg, nbm * nbn, s, per) + (s > 1 ? 4.0 + (double)M * (double)N * (8.0 * s + 4.0) / 5.5e6 : 0.0);
+      if (us >= best) continue;
+      best = us;
+      p->cfg = cfg;
+      p->bm = kTileBM[cfg];
+      p->bn = kTileBN[cfg];
+      p->nbm = (int)nbm;
+      p->nbn = (int)nbn;
+      p->splits = s;
+      p->tiles_per_split = (int)per;
+    }
+  }
+}
+
 GemmPlan gemm_plan(int dtype, int64_t M, int64_t N, int64_t K0, int64_t K1, int force_cfg,
                    int force_splits, bool b_int4, bool long_operand) {
   GemmPlan p;
@@ -617,15 +659,16 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d) {
     if (alone && (m.K + bk - 1) / bk >= 24) p.nwv = 16;
   }
   // Split K over workgroups only when there are fewer workgroups than compute units, and keep >= 8 K tiles per wave and slice
-  // (12 where 32 or more blocks of up to 32 columns share the work: T of 2048 x 4096 12.2 us in two slices with their reduce
-  // pass, 12.0 whole, 5000 x 5464 23.5 and 18.3, 4096 x 8192 18.2 and 20.4).
+  // (12 where 32 or more blocks of up to 32 columns of a 16-bit product share the work: T of 2048 x 4096 12.2 us in two slices
+  // with their reduce pass, 12.0 whole, 5000 x 5464 23.5 and 18.3, 4096 x 8192 18.2 and 20.4; {Z1, T} of 950 x (3000 + 3000)
+  // in fp32 17.3 and 22.7).
   // (64-row workgroups: 128-160 of them without a split beat twice as many plus the reduce pass, and so do 32-row ones of a
   // pair that 64-row blocks do not fill.)
   int64_t splits = 1;
   const bool half = nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2 && !masked;
   if (blocks < (half ? 128 : 224)) {
     splits = (256 + blocks - 1) / blocks;
-    const int64_t per_wave = p.nwv == 16 ? 4 : (!d[0].a_strided && p.rt == 1 && blocks >= 32 ? 12 : 8);
+    const int64_t per_wave = p.nwv == 16 ? 4 : (!d[0].a_strided && dtype != DT_F32 && p.rt == 1 && blocks >= 32 ? 12 : 8);
     int64_t cap = min_ktiles / (p.nwv * per_wave);
     if (cap < 1) cap = 1;
     if (splits > cap) splits = cap;

@@ -101,6 +101,7 @@ struct Builder {
       }
     } else {
       s.plan = gemm_plan(L.dtype, M, N, K, K2, -1, 0, false, long_operand(d));
+      if (L.dtype == DT_F32) gemm_plan_f32(&s.plan, M, N, K, K2);
     }
     if (s.plan.partial_bytes > max_partial) max_partial = s.plan.partial_bytes;
     out->steps.push_back(s);
