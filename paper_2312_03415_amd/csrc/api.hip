@@ -352,6 +352,10 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
   if (use_static) {
     // size the schedule first (no HIP call yet), then lay it out in the fixed array
     if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
+    if (sch.workspace_bytes > kStaticScratchBytes) {  // without scratch for the rank-r products the call may fit
+      L.rank_scratch = false;
+      if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
+    }
     if (w_int4 && sch.workspace_bytes > kStaticScratchBytes) {  // without panels of W the call may fit
       L.int4_panels = false;
       if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
@@ -370,6 +374,10 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
     if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
   } else {
     if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+    if (check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough without splits of the rank-r products?
+      L.rank_scratch = false;
+      if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+    }
     if (w_int4 && check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough for the direct route?
       L.int4_panels = false;
       if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
@@ -491,6 +499,10 @@ extern "C" int runlora_backward(int variant, const rl_tensor_t* dY, const rl_sav
   Schedule sch;
   char* ws = opts ? static_cast<char*>(opts->workspace) : nullptr;
   if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+  if (check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough without splits of the rank-r products?
+    L.rank_scratch = false;
+    if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+  }
   if (w_int4 && check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough for the direct route?
     L.int4_panels = false;
     if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;

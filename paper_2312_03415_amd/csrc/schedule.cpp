@@ -21,9 +21,13 @@ struct Builder {
   float scale() const { return L.drop_thr ? L.scale * 256.f / (256.f - (float)L.drop_thr) : L.scale; }
   uint32_t drop_cpr() const { return (uint32_t)(L.i / 4); }
 
-  // Scratch for partials that the call has anyway: a rank-r product may split its contraction into it, but never makes the
-  // workspace larger.
-  size_t spare() const { return later_partial > max_partial ? later_partial : max_partial; }
+  // Scratch for partials that the call has anyway, or a few MB: a rank-r product with r > 32 may split its contraction into it.
+  // Without a split a short batch runs on a handful of workgroups (1024 x 4096, r 64: T on 64 of the streaming kernel 15.7 us, {Z1,
+  // Z2} 14.5).
+  size_t spare() const {
+    const size_t have = later_partial > max_partial ? later_partial : max_partial;
+    return L.rank_scratch && have < kRankScratch ? kRankScratch : have;
+  }
   // the product [M, K0 + K1] x [K0 + K1, N] comes after the rank-r products and brings its own scratch
   void expect_gemm(int64_t M, int64_t N, int64_t K0, int64_t K1, bool b_is_w, int64_t lda) {
     const GemmPlan p = b_is_w && L.w_int4 ? gemm_plan_int4(L.dtype, M, N, K0, K1) : gemm_plan(L.dtype, M, N, K0, K1);
@@ -230,7 +234,7 @@ struct Builder {
       s.nsk = 0;
       s.d = rank_desc(L.dtype, s.sk[0]);
       s.plan = mp;
-      if (mp.partial_bytes > max_partial) max_partial = mp.partial_bytes;  // (spare() holds it: never more than the call has)
+      if (mp.partial_bytes > max_partial) max_partial = mp.partial_bytes;
     }
     out->steps.push_back(s);
   }

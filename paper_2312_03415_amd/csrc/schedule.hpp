@@ -38,7 +38,11 @@ struct LayerDims {
   // an int4 W's products may dequantise panels of it into scratch; false for calls whose scratch holds only what the
   // direct route takes
   bool int4_panels = true;
+  // rank-r products with r > 32 may ask for up to kRankScratch bytes to split their contraction into; false for calls whose scratch
+  // holds only what the other launches take
+  bool rank_scratch = true;
 };
+constexpr size_t kRankScratch = 8u << 20;
 
 struct Step {
   bool is_merge = false;  // M = W + A B on the merge kernel (mg); otherwise see nsk

@@ -49,3 +49,47 @@ def test_gradients_in_32_and_64_row_blocks(n, i, o, r, dtype):
     print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
     for name, err in gradients(L, 0.0, 0):
         assert err < TOL[dtype], (name, err)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r", [(520, 2056, 2120, 64), (1032, 4104, 1096, 40), (300, 1000, 3000, 128), (2056, 264, 4104, 72)])
+def test_rank_products_with_and_without_scratch_for_splits(n, i, o, r, dtype):
+    """r > 32: with the workspace that the query names, a rank-r product may split its contraction into a few MB of it; a call whose
+    workspace holds only what the other launches take (the figure in the error text) still runs, unsplit.  Integers: the same bits."""
+    import re
+
+    import torch
+    rng = np.random.default_rng(n)
+    td, code = torch_dtype(dtype), rl.dtype_from_name(dtype)
+    pick = lambda shape, p: torch.from_numpy((rng.random(shape) < p) * rng.choice([-1.0, 1.0], size=shape)).to(td).cuda()
+    X, W, A, B, dY = pick((n, i), 0.05), pick((i, o), 0.02), pick((i, r), 0.02), pick((r, o), 0.02), pick((n, o), 0.02)
+    print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
+
+    def run(wf, wb):
+        outs = [torch.full(s, float("nan"), dtype=td, device="cuda") for s in ((n, o), (n, i), (i, r), (r, o))]
+        saved = rl.new_saved()
+        rl.runlora_forward(1, X, W, A, B, outs[0], saved, workspace=wf)
+        rl.runlora_backward(1, dY, saved, W, A, B, *outs[1:], workspace=wb)
+        torch.cuda.synchronize()
+        return outs
+
+    def least(call):
+        with pytest.raises(rl.RunLoRAError) as e:
+            call(torch.empty(256, dtype=torch.uint8, device="cuda"))
+        assert e.value.code == rl.RL_ERR_WORKSPACE
+        return torch.full((int(re.search(r"(\d+) bytes", str(e.value)).group(1)),), 0xFF, dtype=torch.uint8, device="cuda")
+
+    full = torch.full((rl.runlora_workspace_bytes(1, 1, n, i, o, r, code),), 0xFF, dtype=torch.uint8, device="cuda")
+    outs = run(full, full)
+    saved = rl.new_saved()
+    rl.runlora_forward(1, X, W, A, B, torch.empty_like(dY), saved, workspace=full)
+    small_f = least(lambda w: rl.runlora_forward(1, X, W, A, B, torch.empty_like(dY), rl.new_saved(), workspace=w))
+    small_b = least(lambda w: rl.runlora_backward(1, dY, saved, W, A, B, torch.empty_like(X), torch.empty_like(A), torch.empty_like(B), workspace=w))
+    assert min(small_f.numel(), small_b.numel()) < full.numel()
+    for a, b in zip(outs, run(small_f, small_b)):
+        assert torch.equal(a, b)
+    h = [to_f64(t) for t in (X, W, A, B, dY)]
+    T, Z = h[0] @ h[2], h[4] @ h[3].T
+    want = (h[0] @ h[1] + T @ h[3], h[4] @ h[1].T + Z @ h[2].T, h[0].T @ Z, T.T @ h[4])
+    for got, w in zip(outs, want):
+        assert np.abs(w).max() <= 256 and np.array_equal(to_f64(got), w)   # integers bf16 holds
