@@ -707,10 +707,10 @@ extern "C" int runlora_dora_forward(int variant, const rl_tensor_t* X, const rl_
       if (overlap(rc_, in)) return RL_ERR_ALIAS;
   }
   WCol hook(v.g);
+  rl_saved_t checked = *saved;
   {
     DryRun dry;  // every check of the layer call, before the first launch
-    rl_saved_t probe = *saved;
-    if ((rc = runlora_forward(variant, X, W, A, &v.Bt, Y, &probe, &v.inner)) != RL_OK) return rc;
+    if ((rc = runlora_forward(variant, X, W, A, &v.Bt, Y, &checked, &v.inner)) != RL_OK) return rc;
   }
   hipStream_t stream = static_cast<hipStream_t>(opts->stream);
   MergeDesc nd;
@@ -719,6 +719,43 @@ extern "C" int runlora_dora_forward(int variant, const rl_tensor_t* X, const rl_
   nd.I = i; nd.O = o; nd.R = r;
   nd.alpha = opts->scale != 0.f ? opts->scale : 1.f;
   nd.sq_partial = v.partial;
+  // V and its column sums in one pass, Y = X V with its columns scaled.  V lies where the layer call's schedule has M = V diag(g);
+  // an M that the caller keeps is formed there afterwards, as the backward would form it.
+  const bool keep = saved->M != nullptr;
+  Step form, product;
+  form.what = "V = W + A B";
+  form.is_merge = true;
+  form.d.dtype = dt;
+  form.mg = nd;
+  form.mg.M = keep ? saved->M : v.inner.workspace;
+  form.mg.ldm = keep ? saved->ldm : o;
+  product.what = "Y = X V diag(g)";
+  GemmDesc& d = product.d;
+  d.dtype = dt;
+  d.M = X->rows; d.N = o;
+  d.A[0] = X->data; d.lda[0] = X->ld; d.B[0] = form.mg.M; d.ldb[0] = form.mg.ldm; d.K[0] = i;
+  d.C = Y->data; d.ldc = Y->ld;
+  d.bias = opts->bias;
+  d.cscale = v.g;
+  product.plan = gemm_plan(dt, X->rows, o, i, 0, -1, 0, false, long_operand(d));
+  if (column_scale_ok(d, product.plan)) {
+    Schedule first, then;
+    first.steps.push_back(form);
+    then.steps.push_back(product);
+    if (keep) {
+      form.what = "M = V diag(g)";
+      form.mg.sq_partial = nullptr;
+      form.mg.B = v.Bt.data; form.mg.ldb = v.Bt.ld;
+      form.mg.wcol = v.g;
+      then.steps.push_back(form);
+    }
+    if ((rc = run_schedule(first, nullptr, stream)) != RL_OK) return rc;
+    const hipError_t se = dora_scale_run(dt, v.partial, v.norm_rows, m, c, v.g, keep ? B->data : nullptr, B->ld, v.Bt.data, v.Bt.ld, r, o, stream);
+    if (se != hipSuccess) return set_hip_error(se, "c, g = m / c");
+    if ((rc = run_schedule(then, nullptr, stream)) != RL_OK) return rc;
+    *saved = checked;
+    return RL_OK;
+  }
   hipError_t e = merge_run(dt, nd, stream);
   if (e != hipSuccess) return set_hip_error(e, "column sums of (W + s A B)^2");
   if ((e = dora_scale_run(dt, v.partial, v.norm_rows, m, c, v.g, B->data, B->ld, v.Bt.data, v.Bt.ld, r, o, stream)) != hipSuccess)
@@ -781,10 +818,14 @@ extern "C" int runlora_dora_backward(int variant, const rl_tensor_t* dY, const r
   hipError_t e = dora_scale_run(dt, nullptr, 0, m, const_cast<float*>(c), v.g, B->data, B->ld, v.Bt.data, v.Bt.ld, r, o, stream);  // (c is only read)
   if (e != hipSuccess) return set_hip_error(e, "g = m / c, B~ = B diag(g)");
   if ((rc = runlora_backward(variant, dY, saved, W, A, &v.Bt, dX, dA, dBt, &v.inner)) != RL_OK) return rc;
-  if (dB && (e = dora_colscale_run(dt, v.dBt.data, v.dBt.ld, v.g, dB->data, dB->ld, r, o, stream)) != hipSuccess)
+  ColScale b;
+  if (dB) b = ColScale{v.dBt.data, v.dBt.ld, v.g, dB->data, dB->ld, r};
+  if (dm) {  // and dB = dB~ diag(g) with its second launch
+    if ((e = dora_dm_run(dt, dY->data, dY->ld, Y->data, Y->ld, opts->bias, m, v.partial, dm, n, o, b, stream)) != hipSuccess)
+      return set_hip_error(e, "dm");
+  } else if (dB && (e = dora_colscale_run(dt, b.in, b.ldi, b.g, b.out, b.ldo, r, o, stream)) != hipSuccess) {
     return set_hip_error(e, "dB = dB~ diag(g)");
-  if (dm && (e = dora_dm_run(dt, dY->data, dY->ld, Y->data, Y->ld, opts->bias, m, v.partial, dm, n, o, stream)) != hipSuccess)
-    return set_hip_error(e, "dm");
+  }
   return RL_OK;
 }
 

@@ -37,6 +37,7 @@ __global__ __launch_bounds__(kThreads) void dora_scale_kernel(const float* __res
   if (j >= O) return;
   const float gj = (float)m[j] / cj;
   if (q == 0) g[j] = gj;
+  if (in == nullptr) return;
 #pragma unroll 4
   for (int k = q; k < R; k += 4) out[(int64_t)k * ldo + j] = (T)((float)in[(int64_t)k * ldi + j] * gj);
 }
@@ -103,10 +104,13 @@ __global__ __launch_bounds__(kThreads) void dora_dm_partial_kernel(const T* __re
   }
 }
 
-// dm[j] = the column's slices / m[j]: 64 columns per workgroup, slices q, q + 4, ... per group of 64 threads, groups in order
+// dm[j] = the column's slices / m[j]: 64 columns per workgroup, slices q, q + 4, ... per group of 64 threads, groups in order.
+// With R > 0 also out = in diag(g) for the R rows of dB~, the groups sharing them (as a launch of its own 4.8 us next to this one's
+// 4.2, both of them latency).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void dora_dm_finish_kernel(const float* __restrict__ partial, int rows,
-                                                                  const T* __restrict__ m, T* __restrict__ dm, int O) {
+                                                                  const T* __restrict__ m, T* __restrict__ dm, int O, const T* in,
+                                                                  int64_t ldi, const float* __restrict__ g, T* out, int64_t ldo, int R) {
   __shared__ float part[4][64];
   const int jj = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int j = blockIdx.x * 64 + jj;
@@ -116,6 +120,11 @@ __global__ __launch_bounds__(kThreads) void dora_dm_finish_kernel(const float* _
     for (int y = q; y < rows; y += 4) sum += partial[(int64_t)y * O + j];
   }
   part[q][jj] = sum;
+  if (R > 0 && j < O) {
+    const float gj = g[j];
+#pragma unroll 4
+    for (int k = q; k < R; k += 4) out[(int64_t)k * ldo + j] = (T)((float)in[(int64_t)k * ldi + j] * gj);
+  }
   __syncthreads();
   if (q == 0 && j < O) dm[j] = (T)((((part[0][jj] + part[1][jj]) + part[2][jj]) + part[3][jj]) / (float)m[j]);
 }
@@ -132,7 +141,7 @@ int rows_per_slice(int64_t n, int64_t o) {
 
 template <typename T>
 hipError_t dm_t(const void* dY, int64_t lddy, const void* Y, int64_t ldy, const void* bias, const void* m, float* partial,
-                void* dm, int64_t n, int64_t o, hipStream_t s) {
+                void* dm, int64_t n, int64_t o, const ColScale& b, hipStream_t s) {
   const int rows = rows_per_slice(n, o), slices = dora_dm_slices(n, o);
   hipLaunchKernelGGL(dora_dm_partial_kernel<T>, dim3((unsigned)((o + 127) / 128), (unsigned)slices), dim3(kThreads), 0, s,
                      static_cast<const T*>(dY), lddy, static_cast<const T*>(Y), ldy, static_cast<const T*>(bias), partial,
@@ -140,7 +149,8 @@ hipError_t dm_t(const void* dY, int64_t lddy, const void* Y, int64_t ldy, const 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(dora_dm_finish_kernel<T>, dim3((unsigned)((o + 63) / 64)), dim3(kThreads), 0, s, partial,
-                     slices, static_cast<const T*>(m), static_cast<T*>(dm), (int)o);
+                     slices, static_cast<const T*>(m), static_cast<T*>(dm), (int)o, static_cast<const T*>(b.in), b.ldi, b.g,
+                     static_cast<T*>(b.out), b.ldo, b.out != nullptr ? (int)b.R : 0);
   return hipGetLastError();
 }
 
@@ -181,9 +191,9 @@ hipError_t dora_colscale_run(int dtype, const void* in, int64_t ldi, const float
 }
 
 hipError_t dora_dm_run(int dtype, const void* dY, int64_t lddy, const void* Y, int64_t ldy, const void* bias, const void* m,
-                       float* partial, void* dm, int64_t n, int64_t o, hipStream_t stream) {
-  if (dtype == DT_F16) return dm_t<_Float16>(dY, lddy, Y, ldy, bias, m, partial, dm, n, o, stream);
-  if (dtype == DT_BF16) return dm_t<__bf16>(dY, lddy, Y, ldy, bias, m, partial, dm, n, o, stream);
+                       float* partial, void* dm, int64_t n, int64_t o, const ColScale& b, hipStream_t stream) {
+  if (dtype == DT_F16) return dm_t<_Float16>(dY, lddy, Y, ldy, bias, m, partial, dm, n, o, b, stream);
+  if (dtype == DT_BF16) return dm_t<__bf16>(dY, lddy, Y, ldy, bias, m, partial, dm, n, o, b, stream);
   return hipErrorInvalidValue;
 }
 

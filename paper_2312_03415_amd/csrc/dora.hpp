@@ -4,8 +4,10 @@
 // detaches it).  With c fixed the layer is the LoRA layer on (W diag(g), A, B diag(g)), and in forward2 and in
 // backward 4 / 5 / 7 / 8 the frozen weight enters only through M = W + s A B, which the merge kernel forms with
 // W's columns scaled on the way: W diag(g) is never written.  What DoRA adds per step:
-//   - one more pass of the merge kernel over W that stores nothing and sums (W + s A B)^2 per column
-//     (merge.hpp, sq_partial), finished here into c and g;
+//   - the column sums of (W + s A B)^2 (merge.hpp, sq_partial), finished here into c and g.  The forward takes them from the
+//     pass that forms V, multiplies by V and scales the product's columns by g in its epilogue (4096 x 2048 -> 8192: a pass over
+//     W of 16 us less than one for the sums and another for M); where the product's kernel is not built for that the sums are a
+//     pass that stores nothing;
 //   - B~ = B diag(g) and dB = dB~ diag(g): r x o elements each;
 //   - dm[j] = sum_t dY[t,j] (Y[t,j] - bias[j]) / m[j]: one pass over dY and the forward's output.
 // All sums are fp32 in a fixed order.  Internal to the library; 16-bit types only.
@@ -16,7 +18,7 @@
 
 namespace rl {
 
-// g[j] = m[j] / c[j] and out[k,j] = in[k,j] * g[j] (product in fp32, rounded once); c[j] = sqrt(sum over the `rows` rows of
+// g[j] = m[j] / c[j] and, unless `in` is null, out[k,j] = in[k,j] * g[j] (product in fp32, rounded once); c[j] = sqrt(sum over the `rows` rows of
 // partial[.][j]) is formed first unless partial is null
 hipError_t dora_scale_run(int dtype, const float* partial, int rows, const void* m, float* c, float* g, const void* in, int64_t ldi,
                           void* out, int64_t ldo, int64_t R, int64_t O, hipStream_t stream);
@@ -25,8 +27,16 @@ hipError_t dora_colscale_run(int dtype, const void* in, int64_t ldi, const float
                              int64_t O, hipStream_t stream);
 // row slices of the dm pass (rows of `partial`, o floats each)
 int dora_dm_slices(int64_t n, int64_t o);
+// what dora_colscale_run takes, for dora_dm_run to do along the way (out null: nothing)
+struct ColScale {
+  const void* in = nullptr;
+  int64_t ldi = 0;
+  const float* g = nullptr;
+  void* out = nullptr;
+  int64_t ldo = 0, R = 0;
+};
 // dm[j] = (sum_t dY[t,j] (Y[t,j] - bias[j])) / m[j]; bias may be null; partial: dora_dm_slices(n, o) * o floats
 hipError_t dora_dm_run(int dtype, const void* dY, int64_t lddy, const void* Y, int64_t ldy, const void* bias, const void* m,
-                       float* partial, void* dm, int64_t n, int64_t o, hipStream_t stream);
+                       float* partial, void* dm, int64_t n, int64_t o, const ColScale& b, hipStream_t stream);
 
 }  // namespace rl

@@ -40,6 +40,8 @@ struct GemmDesc {
   // (first column of C in X) / 4; where masked_segment_ok holds
   bool mask_seg0 = false;
   uint32_t drop_n4 = 0;
+  // optional [N] (16-byte aligned): C = (the products) diag(cscale) + bias; where column_scale_ok holds
+  const float* cscale = nullptr;
   // One-pass LoRA forward, C = A[0] B[0] + round(t_alpha A[0] LA) B[1] in one kernel: nseg = 2, A[1] unused,
   // K[1] = R <= kFuseMaxR, LA stored [K[0], R] row-major; A [M,K], B [K,N], dense B, no addend, no K split
   // (plan with gemm_plan_fused).  fuse_t is also set when only shapes are modelled and LA is null.
@@ -98,6 +100,8 @@ void gemm_plan_f32(GemmPlan* plan, int64_t M, int64_t N, int64_t K0, int64_t K1)
 bool long_operand(const GemmDesc& d);
 // A plan whose kernels are built with a masked first segment: dense 16-bit operands, A [M,K], B [N,K], no addend, scale or bias.
 bool masked_segment_ok(const GemmDesc& d, const GemmPlan& p);
+// A plan whose kernels are built with a column scale: dense 16-bit operands, A [M,K], B [K,N], no addend, scale or mask, no split.
+bool column_scale_ok(const GemmDesc& d, const GemmPlan& p);
 
 // Modelled time in us of one launch of a 16-bit tile GEMM (CFG_MT*, CFG_MC4, and the generic engine's 128x128, 128x64 and
 // 64x128 tiles): nbm x nbn output tiles x K slices of `ktiles` K tiles each; odd = odd_lines of the product.

@@ -157,6 +157,12 @@ bool long_operand(const GemmDesc& d) {
   return false;
 }
 
+bool column_scale_ok(const GemmDesc& d, const GemmPlan& p) {
+  auto built = [](int cfg, int splits) { return splits <= 1 && (cfg_is_mt(cfg) || cfg == CFG_MC4); };
+  return d.dtype != DT_F32 && d.nseg == 1 && !d.a_strided && !d.b_kcontig && !d.b_int4 && d.Bscale == nullptr && !d.has_addend && d.D == nullptr &&
+         d.alpha == 1.f && d.drop_thr == 0 && !d.fuse_t && !long_operand(d) && built(p.cfg, p.splits) && (p.tail_n0 == 0 || built(p.tail_cfg, p.tail_splits));
+}
+
 bool masked_segment_ok(const GemmDesc& d, const GemmPlan& p) {
   auto built = [&](int cfg, int splits) { return cfg_is_mt(cfg) || (cfg == CFG_MC4 && splits <= 1 && d.K[0] <= 32); };
   return d.dtype != DT_F32 && d.nseg == 2 && !d.a_strided && d.b_kcontig && !d.b_int4 && d.Bscale == nullptr && !d.has_addend && d.D == nullptr &&
@@ -431,6 +437,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
     dt.C = static_cast<char*>(d.C) + (size_t)plan.tail_n0 * esz;
     if (d.D) dt.D = static_cast<const char*>(d.D) + (size_t)plan.tail_n0 * esz;
     if (d.bias) dt.bias = static_cast<const char*>(d.bias) + (size_t)plan.tail_n0 * esz;
+    if (d.cscale) dt.cscale = d.cscale + plan.tail_n0;
     hipError_t e = gemm_run(dm, pm, nullptr, stream);
     if (e != hipSuccess) return e;
     const GemmPlan pt = gemm_tail_plan(plan, d.dtype, d.M, d.N, d.K[0], d.nseg > 1 ? d.K[1] : 0);
@@ -438,6 +445,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
     return gemm_run(dt, pt, pt.splits > 1 ? scratch : nullptr, stream);
   }
   if (plan.splits > 1 && scratch == nullptr) return hipErrorInvalidValue;
+  if (d.cscale != nullptr && !column_scale_ok(d, plan)) return hipErrorInvalidValue;
   if (d.mask_seg0 && (d.drop_thr == 0 || !masked_segment_ok(d, plan))) return hipErrorInvalidValue;
   if (d.fuse_t) {
     const bool ok = d.LA != nullptr && d.nseg == 2 && d.K[1] >= 1 && d.K[1] <= kFuseMaxR && d.K[0] >= 1 && !d.a_strided &&
@@ -501,6 +509,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   a.drop_cpr = d.drop_cpr;
   a.mask_seg0 = d.mask_seg0 ? 1 : 0;
   a.drop_n4 = d.drop_n4;
+  a.cscale = d.cscale;
   a.rotate = d.rotate;
   a.LA = d.fuse_t ? d.LA : nullptr;
   a.ldla = d.ldla;

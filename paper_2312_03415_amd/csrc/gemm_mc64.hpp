@@ -110,9 +110,12 @@ struct Mc64Tile {
 // R]) that come straight from memory, then one hash per four accumulators (a lane holds four consecutive columns of a row).
 // ~35 vector instructions a block, 5 us a tile, where an update of dX in a pass of its own reads and writes all of it: 4096 x
 // 8192, r 16: 33 us.
-template <typename T, int AL, int BL, int PLAIN, bool SEGMASK = false>
+// COLSCALE (with PLAIN 1, 3): the accumulators are scaled per column before the bias (Y = X V diag(g) + bias of a DoRA layer, whose V is
+// formed in the pass that gives its column norms).
+template <typename T, int AL, int BL, int PLAIN, bool SEGMASK = false, bool COLSCALE = false>
 __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
   static_assert(!SEGMASK || (PLAIN == 3 && AL == 0 && BL == 1), "the epilogue and layout the masked product is built with");
+  static_assert(!COLSCALE || ((PLAIN == 1 || PLAIN == 3) && AL == 0 && BL == 0 && !SEGMASK), "the epilogue and layout the column scale is built with");
   using P = Mc64Tile<AL, BL>;
   constexpr int BM = P::BM, BN = P::BN, BK = P::BK, IPW = P::IPW;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -437,6 +440,15 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
         bias2[b] = g.bias != nullptr ? *reinterpret_cast<const i32x2*>(static_cast<const T*>(g.bias) + n) : i32x2{0, 0};
       }
     }
+    [[maybe_unused]] f32x4 scale4[8];  // COLSCALE: likewise
+    if constexpr (COLSCALE) {
+#pragma unroll
+      for (int b = 0; b < 8; ++b) {
+        int n = n0 + wn * 128 + 16 * b + 4 * grp;
+        n = n < g.N ? n : g.N - 4;
+        scale4[b] = *reinterpret_cast<const f32x4*>(g.cscale + n);
+      }
+    }
     static_for<64>([&](auto e) { acc[decltype(e)::value >> 3][decltype(e)::value & 7] = f32x4{0.f, 0.f, 0.f, 0.f}; });
 
     for (int u = u0; u < u1; ++u) {
@@ -529,7 +541,9 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
               group += 16u * g.drop_cpr;
               asm volatile("" : "+v"(group));  // (nothing to prepare ahead)
             }
-          } else if constexpr (PLAIN == 3) {
+          }
+          if constexpr (COLSCALE) { x0 *= scale4[b][0]; x1 *= scale4[b][1]; x2 *= scale4[b][2]; x3 *= scale4[b][3]; }
+          if constexpr (PLAIN == 3 && !SEGMASK) {
             T b4[4];
             *reinterpret_cast<i32x2*>(b4) = bias2[b];
             x0 += (float)b4[0]; x1 += (float)b4[1]; x2 += (float)b4[2]; x3 += (float)b4[3];
@@ -654,6 +668,10 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
 template <typename T, int AL, int BL, int PLAIN>
 __global__ __launch_bounds__(256, 1) void gemm_mc64_kernel(GemmArgs g) {
   gemm_mc64_body<T, AL, BL, PLAIN>(g);
+}
+template <typename T, int PLAIN>
+__global__ __launch_bounds__(256, 1) void gemm_mc64_colscale_kernel(GemmArgs g) {
+  gemm_mc64_body<T, 0, 0, PLAIN, false, true>(g);
 }
 template <typename T>
 __global__ __launch_bounds__(256, 1) void gemm_mc64_segmask_kernel(GemmArgs g) {

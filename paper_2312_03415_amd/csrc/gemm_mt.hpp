@@ -95,7 +95,8 @@ template <> struct MtFrag<true> {
 // SEGMASK: dX = m o (Z1 A^T) + dY W^T of a layer with LoRA dropout in one launch.  Segment 0 is the rank-r one; behind its last K
 // tile (of this K slice) the dropped accumulators are zeroed (a lane holds four consecutive columns of a row: one hash), and
 // the other segment is added to what is left.
-template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA, bool SEGMASK = false>
+// COLSCALE: C = (the products) diag(cscale) + bias, see gemm_mc64.hpp
+template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA, bool SEGMASK = false, bool COLSCALE = false>
 __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, const int by) {
   static_assert(!XA || (AL == 0 && BL == 0), "X [M,K], W and A [K,.]");
   using P = MtTile<AL, BL, BM, BN, NS>;
@@ -404,6 +405,14 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
 #pragma unroll
     for (int e = 0; e < 8; ++e) b8[e] = (float)t8[e];
   }
+  [[maybe_unused]] f32x4 c8[2];
+  if constexpr (COLSCALE) {
+    c8[0] = c8[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (n_ok) {
+      c8[0] = *reinterpret_cast<const f32x4*>(g.cscale + n);
+      c8[1] = *reinterpret_cast<const f32x4*>(g.cscale + n + 4);
+    }
+  }
 #pragma unroll
   for (int a = 0; a < TM; ++a) {
 #pragma unroll
@@ -420,6 +429,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
           *reinterpret_cast<f32x4*>(dst) = v0;
           *reinterpret_cast<f32x4*>(dst + 4) = v1;
         } else {
+          if constexpr (COLSCALE) { v0 *= c8[0]; v1 *= c8[1]; }
           if (g.alpha != 1.f) { v0 *= g.alpha; v1 *= g.alpha; }
           if (!SEGMASK && g.drop_thr != 0u) {
             uint32_t k0[4], k1[4];
@@ -452,6 +462,10 @@ __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_k
   gemm_mt_body<T, AL, BL, BM, BN, NS, XA>(g, (int)blockIdx.x, (int)blockIdx.y);
 }
 
+template <typename T, int AL, int BL, int BM, int BN, int NS>
+__global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_colscale_kernel(GemmArgs g) {
+  gemm_mt_body<T, AL, BL, BM, BN, NS, false, false, true>(g, (int)blockIdx.x, (int)blockIdx.y);
+}
 template <typename T, int AL, int BL, int BM, int BN, int NS>
 __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_segmask_kernel(GemmArgs g) {
   gemm_mt_body<T, AL, BL, BM, BN, NS, false, true>(g, (int)blockIdx.x, (int)blockIdx.y);

@@ -28,8 +28,8 @@ struct MergeArgs {
   float alpha;        // the layer's LoRA scale (1 for the paper's layer)
   int b_trans;        // 1: B is stored [O, R] (the r values of a column contiguous), as A^T of dX += Z1 A^T is
   const float* wcol;  // optional [O]: M = W diag(wcol) + alpha A B (the column-scaled frozen weight of DoRA)
-  // optional [gridDim.y][O]: nothing is stored to M; each workgroup writes, per column, the sum over its
-  // rows of (W + alpha A B)^2 in fp32 (the squared column norms, summed over gridDim.y by the caller)
+  // optional [gridDim.y][O]: each workgroup writes, per column, the sum over its rows of (W + alpha A B)^2 in fp32, before any
+  // rounding (the squared column norms, summed over gridDim.y by the caller); without M nothing else is stored
   float* sq_partial;
   // drop_thr != 0: the product is masked before it is added, M = W + mask o (alpha A B), with the LoRA dropout
   // keep-mask of element (row, column) of M (drop_keep4, gemm_engine.hpp; drop_cpr = groups of four columns per row)
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
           sq[e] += v0 * v0;
           sq[4 + e] += v1 * v1;
         }
-        continue;
+        if (Mp == nullptr) continue;
       }
       T o8[8];
 #pragma unroll

@@ -188,3 +188,36 @@ def test_dora_full_size_opt_fc1():
     Yr = oracle.dora_forward(host["X"][rows], host["W"], host["A"], host["B"], m, s, bias)
     dXr = oracle.matmul(dU[rows], V, tb=True)
     assert relerr(got["Y"][rows], Yr) < TOL["bf16"] and relerr(got["dX"][rows], dXr) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r,scaled", [(4104, 520, 2568, 16, True),   # 256x256 tiles, ragged
+                                            (8192, 264, 4360, 8, True),    # 256x256 with a column of tiles cut off
+                                            (1240, 1096, 5464, 24, True), (520, 264, 1000, 128, True), (70, 136, 264, 8, True),
+                                            (300, 4104, 264, 16, False),   # contraction split: M is formed as before
+                                            (24, 264, 520, 8, False)])     # few rows: the generic engine
+def test_dora_forward_with_scaled_columns(n, i, o, r, scaled, dtype):
+    """Y = X V diag(g) on every kernel that scales its product's columns, and the route without one, against the oracle."""
+    import torch
+    L = synth.Layer("doracs", n, i, o, r, dtype, 55)
+    dev, host = layer_on_device(L)
+    vec = vectors(L)
+    print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
+    rows = np.unique(np.concatenate([np.arange(0, n, 253), [n - 1]]))
+    V = host["W"] + 0.5 * host["A"] @ host["B"]
+    c = np.sqrt((V * V).sum(axis=0))
+    want = host["X"][rows] @ V * (vec["m"][1] / c)[None, :] + vec["bias"][1][None, :]
+    buf = torch.full((n + 2, o + 16), 7.0, dtype=torch_dtype(dtype), device="cuda")
+    Y = buf[1:n + 1, 8:o + 8]
+    cd = torch.empty((o,), dtype=torch.float32, device="cuda")
+    ws = torch.full((rl.runlora_dora_workspace_bytes(2, -1, n, i, o, r, rl.dtype_from_name(dtype)),), 0xFF, dtype=torch.uint8, device="cuda")
+    rl.runlora_profile_enable(8)
+    rl.runlora_dora_forward(2, dev["X"], dev["W"], dev["A"], dev["B"], vec["m"][0], Y, rl.new_saved(), cd, ws, scale=0.5, bias=vec["bias"][0])
+    torch.cuda.synchronize()
+    steps = [s["what"] for s in rl.runlora_profile_collect(8)]
+    rl.runlora_profile_disable()
+    assert ("Y = X V diag(g)" in steps) == scaled, steps
+    assert relerr(to_f64(cd), c) < 1e-5 and relerr(to_f64(Y)[rows], want) < TOL[dtype]
+    edge = buf.float()
+    edge[1:n + 1, 8:o + 8] = 7.0
+    assert bool((edge == 7.0).all())
