@@ -8,10 +8,14 @@
 // the bias: 1 x 4096 -> 4096, r 16: 21.9 us on the GPU in four launches, 13.2 in two (of which this one 4.7); 48 x 4096 ->
 // 11008, r 32: 41.5 and 23.7 (6.0).
 //
-// Bound by latency: a thread owns 16 bytes of a row of Y; a workgroup is cx column chunks by ry rows (ry covers the rows up
+// Bound by latency, that is by the number of trips to memory one behind the other: the slices are summed in blocks of two, four or
+// eight whose loads are in flight together (slices beyond the last read the last one and add zero: as a rolled remainder the
+// last three of seven took a trip each), T's columns of a thread four at a time, sixteen rows of B ahead of T.  A thread owns 16 bytes of a row of Y; a workgroup is cx column chunks by ry rows (ry covers the rows up
 // to 32, so that one row still spreads over 64 threads), with its rows of T in LDS.
 #pragma once
 #include "gemm_engine.hpp"
+
+#include <type_traits>
 
 namespace rl {
 
@@ -35,31 +39,85 @@ __global__ __launch_bounds__(256) void lora_finish_kernel(FinishArgs g) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
   const T* const b = static_cast<const T*>(g.B) + n;
-  i32x4 first[8];  // the first eight rows of B (R is a multiple of 8), on their way while T is formed
+  i32x4 first[16];  // the first sixteen rows of B (R is a multiple of 8), on their way while T is formed
+  const bool second = g.R > 8;  // uniform
   if (ok) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) first[k] = *reinterpret_cast<const i32x4*>(b + (int64_t)k * g.ldb);
-    const float* src = g.partial + (int64_t)m * g.N + n;
-#pragma unroll 4
-    for (int z = 0; z < g.splits; ++z) {
-      const f32x4 p0 = *reinterpret_cast<const f32x4*>(src + (int64_t)z * g.M * g.N);
-      const f32x4 p1 = *reinterpret_cast<const f32x4*>(src + (int64_t)z * g.M * g.N + 4);
+    if (second) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) { acc[e] += p0[e]; acc[4 + e] += p1[e]; }
+      for (int k = 8; k < 16; ++k) first[k] = *reinterpret_cast<const i32x4*>(b + (int64_t)k * g.ldb);
     }
   }
-  // this workgroup's rows of T (a row per threadIdx.y, its columns over threadIdx.x)
-  for (int k = (int)threadIdx.x; k < g.R; k += (int)blockDim.x) {
-    float t = 0.f;
+  // the slices in blocks of U, in slice order
+  auto sum_y = [&](auto u_c) {
+    constexpr int U = decltype(u_c)::value;
+    const float* const src = g.partial + (int64_t)m * g.N + n;
+    for (int z0 = 0; z0 < g.splits; z0 += U) {
+      f32x4 p[U][2];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int z = z0 + u < g.splits ? z0 + u : g.splits - 1;
+        p[u][0] = *reinterpret_cast<const f32x4*>(src + (int64_t)z * g.M * g.N);
+        p[u][1] = *reinterpret_cast<const f32x4*>(src + (int64_t)z * g.M * g.N + 4);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (z0 + u < g.splits) {  // uniform
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { acc[e] += p[u][0][e]; acc[4 + e] += p[u][1][e]; }
+        }
+    }
+  };
+  // Q columns of this thread's row of T, k0, k0 + blockDim.x, ...
+  auto sum_t = [&](auto u_c, auto q_c, int k0) {
+    constexpr int U = decltype(u_c)::value, Q = decltype(q_c)::value;
+    float t[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) t[q] = 0.f;
     if (m < g.M) {
-      const float* src = g.partial_t + (int64_t)m * g.R + k;
-#pragma unroll 4
-      for (int z = 0; z < g.splits; ++z) t += src[(int64_t)z * g.M * g.R];
+      const float* const src = g.partial_t + (int64_t)m * g.R;
+      for (int z0 = 0; z0 < g.splits; z0 += U) {
+        float p[U][Q];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int z = z0 + u < g.splits ? z0 + u : g.splits - 1;
+#pragma unroll
+          for (int q = 0; q < Q; ++q) {
+            const int k = k0 + q * (int)blockDim.x;
+            p[u][q] = src[(int64_t)z * g.M * g.R + (k < g.R ? k : k0)];
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (z0 + u < g.splits) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) t[q] += p[u][q];
+          }
+      }
     }
-    const T tr = from_f32<T>(g.t_alpha * t);
-    sT[(int)threadIdx.y * g.R + k] = (float)tr;
-    if (g.T != nullptr && blockIdx.x == 0 && m < g.M) static_cast<T*>(g.T)[(int64_t)m * g.ldt + k] = tr;
-  }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int k = k0 + q * (int)blockDim.x;
+      if (k < g.R) {
+        const T tr = from_f32<T>(g.t_alpha * t[q]);
+        sT[(int)threadIdx.y * g.R + k] = (float)tr;
+        if (g.T != nullptr && blockIdx.x == 0 && m < g.M) static_cast<T*>(g.T)[(int64_t)m * g.ldt + k] = tr;
+      }
+    }
+  };
+  auto sums = [&](auto u_c) {
+    if (ok) sum_y(u_c);
+    // this workgroup's rows of T (a row per threadIdx.y, its columns over threadIdx.x)
+    if (g.R <= (int)blockDim.x) {
+      if ((int)threadIdx.x < g.R) sum_t(u_c, std::integral_constant<int, 1>{}, (int)threadIdx.x);
+    } else {
+      for (int k0 = (int)threadIdx.x; k0 < g.R; k0 += 4 * (int)blockDim.x) sum_t(u_c, std::integral_constant<int, 4>{}, k0);
+    }
+  };
+  if (g.splits <= 2) sums(std::integral_constant<int, 2>{});
+  else if (g.splits <= 4) sums(std::integral_constant<int, 4>{});
+  else sums(std::integral_constant<int, 8>{});
   __syncthreads();
   if (!ok) return;
   const float* const tr = sT + (int)threadIdx.y * g.R;
@@ -70,8 +128,29 @@ __global__ __launch_bounds__(256) void lora_finish_kernel(FinishArgs g) {
   };
 #pragma unroll
   for (int k = 0; k < 8; ++k) add(first[k], tr[k]);
-#pragma unroll 8
-  for (int k = 8; k < g.R; ++k) add(*reinterpret_cast<const i32x4*>(b + (int64_t)k * g.ldb), tr[k]);
+  if (second) {
+#pragma unroll
+    for (int k = 8; k < 16; ++k) add(first[k], tr[k]);
+  }
+  // the others in blocks of eight, the next one on its way while a block is multiplied
+  if (g.R > 16) {
+    i32x4 rows[2][8];
+    auto fetch = [&](i32x4 (&to)[8], int k0) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) to[u] = *reinterpret_cast<const i32x4*>(b + (int64_t)((k0 < g.R ? k0 : 16) + u) * g.ldb);
+    };
+    fetch(rows[0], 16);
+    for (int k0 = 16; k0 < g.R; k0 += 16) {
+      fetch(rows[1], k0 + 8);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) add(rows[0][u], tr[k0 + u]);
+      fetch(rows[0], k0 + 16);
+      if (k0 + 8 < g.R) {  // uniform
+#pragma unroll
+        for (int u = 0; u < 8; ++u) add(rows[1][u], tr[k0 + 8 + u]);
+      }
+    }
+  }
   if (g.bias != nullptr) {
     const i32x4 v = *reinterpret_cast<const i32x4*>(static_cast<const T*>(g.bias) + n);
     const T* v8 = reinterpret_cast<const T*>(&v);
