@@ -37,37 +37,37 @@ __global__ __launch_bounds__(kThreads) void vera_scale_kernel(const T* __restric
   v.store(Bt + (int64_t)k * ldt + j);
 }
 
-// a workgroup owns 32 columns; thread (c, g) sums the rows k = g, g + 8, g + 16, ... of column c in that
-// order, then the eight partial sums of a column are added in the order of g
+// Both gradients in one launch (two of 5.3 and 4.0 us at 256 x 8192, each of them latency): workgroups [0, db_wgs) sum columns, the
+// others rows.  Either part may be absent.
+// db: a workgroup owns 32 columns; thread (c, g) sums the rows k = g, g + 8, g + 16, ... of column c in that order, then the eight
+// partial sums of a column are added in the order of g.
+// dd: one workgroup per row k: every thread sums its 16-byte chunks tid, tid + 256, ... in order, then a fixed binary tree over the
+// 256 partial sums (256 x 8192: 12 us with two bytes per load, 4.8 so).
 template <typename T>
-__global__ __launch_bounds__(kThreads) void vera_db_kernel(const T* __restrict__ G, int64_t ldg, const T* __restrict__ B,
-                                                           int64_t ldb, const T* __restrict__ d, T* __restrict__ db, int R, int O) {
-  __shared__ float part[8][32];
-  const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
-  const int j = blockIdx.x * 32 + c;
-  float acc = 0.f;
-  if (j < O) {
-#pragma unroll 4
-    for (int k = g; k < R; k += 8) acc += (float)G[(int64_t)k * ldg + j] * ((float)d[k] * (float)B[(int64_t)k * ldb + j]);
-  }
-  part[g][c] = acc;
-  __syncthreads();
-  if (g == 0 && j < O) {
-    float sum = part[0][c];
-#pragma unroll
-    for (int q = 1; q < 8; ++q) sum += part[q][c];
-    db[j] = (T)sum;
-  }
-}
-
-// one workgroup per row k: every thread sums its 16-byte chunks tid, tid + 256, ... in order, then a fixed binary tree over
-// the 256 partial sums (256 x 8192: 12 us with two bytes per load, 4.8 so)
-template <typename T>
-__global__ __launch_bounds__(kThreads) void vera_dd_kernel(const T* __restrict__ G, int64_t ldg, const T* __restrict__ B,
-                                                           int64_t ldb, const T* __restrict__ b, T* __restrict__ dd, int R, int O) {
-  constexpr int VE = Chunk<T>::VE;
+__global__ __launch_bounds__(kThreads) void vera_grad_kernel(const T* __restrict__ G, int64_t ldg, const T* __restrict__ B, int64_t ldb,
+                                                             const T* __restrict__ d, const T* __restrict__ b, T* __restrict__ dd,
+                                                             T* __restrict__ db, int R, int O, int db_wgs) {
   __shared__ float part[kThreads];
-  const int k = blockIdx.x;
+  if ((int)blockIdx.x < db_wgs) {
+    const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const int j = blockIdx.x * 32 + c;
+    float acc = 0.f;
+    if (j < O) {
+#pragma unroll 4
+      for (int k = g; k < R; k += 8) acc += (float)G[(int64_t)k * ldg + j] * ((float)d[k] * (float)B[(int64_t)k * ldb + j]);
+    }
+    part[threadIdx.x] = acc;
+    __syncthreads();
+    if (g == 0 && j < O) {
+      float sum = part[c];
+#pragma unroll
+      for (int q = 1; q < 8; ++q) sum += part[32 * q + c];
+      db[j] = (T)sum;
+    }
+    return;
+  }
+  constexpr int VE = Chunk<T>::VE;
+  const int k = (int)blockIdx.x - db_wgs;
   float acc = 0.f;
 #pragma unroll 4
   for (int j = (int)threadIdx.x * VE; j < O; j += kThreads * VE) {
@@ -105,20 +105,12 @@ hipError_t scale_t(const void* B, int64_t ldb, const void* d, const void* b, voi
 template <typename T>
 hipError_t grad_t(const void* G, int64_t ldg, const void* B, int64_t ldb, const void* d, const void* b, void* dd, void* db,
                   int64_t R, int64_t O, hipStream_t s) {
-  if (db) {
-    hipLaunchKernelGGL(vera_db_kernel<T>, dim3((unsigned)((O + 31) / 32)), dim3(kThreads), 0, s,
-                       static_cast<const T*>(G), ldg, static_cast<const T*>(B), ldb, static_cast<const T*>(d),
-                       static_cast<T*>(db), (int)R, (int)O);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (dd) {
-    hipLaunchKernelGGL(vera_dd_kernel<T>, dim3((unsigned)R), dim3(kThreads), 0, s, static_cast<const T*>(G), ldg,
-                       static_cast<const T*>(B), ldb, static_cast<const T*>(b), static_cast<T*>(dd), (int)R, (int)O);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  const int64_t db_wgs = db ? (O + 31) / 32 : 0, dd_wgs = dd ? R : 0;
+  if (db_wgs + dd_wgs == 0) return hipSuccess;
+  hipLaunchKernelGGL(vera_grad_kernel<T>, dim3((unsigned)(db_wgs + dd_wgs)), dim3(kThreads), 0, s, static_cast<const T*>(G), ldg,
+                     static_cast<const T*>(B), ldb, static_cast<const T*>(d), static_cast<const T*>(b), static_cast<T*>(dd),
+                     static_cast<T*>(db), (int)R, (int)O, (int)db_wgs);
+  return hipGetLastError();
 }
 
 }  // namespace
