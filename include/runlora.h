@@ -404,7 +404,8 @@ size_t runlora_gemm_workspace_bytes(const rl_gemm_t* g);
  * how many were timed; us then also holds the handling of those events.  Otherwise kernel_us = main_us = us
  * and kernels = 0.
  * tile_cfg names the kernel that ran the step: 0..7 and 12..16 as in rl_gemm_t, 8 / 9 / 10 = the streaming kernel with up to
- * 32 / 64 / 128 output columns, 11 = the W + alpha A B kernel (also the default chain's rank-r updates).
+ * 32 / 64 / 128 output columns, 11 = the W + alpha A B kernel (also the default chain's rank-r updates).  Two rank-r products in one
+ * launch of the middle-sized kernel report 15 or 16, whatever its tiles.
  * Events are host objects created at enable and destroyed at disable; no device memory.
  */
 typedef struct {

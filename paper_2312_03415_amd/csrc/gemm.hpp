@@ -193,11 +193,14 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
 bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us = nullptr);
 GemmDesc rank_desc(int dtype, const SkinnyDesc& d);  // the product as gemm_run takes it
 struct MtPairPlan {
-  int cfg[2] = {0, 0}, splits[2] = {1, 1}, tiles_per_split[2] = {0, 0};
+  int cfg[2] = {0, 0};  // CFG_MTN64 / CFG_MTM64
+  bool wide = false;    // 128x128 tiles for both instead
+  int splits[2] = {1, 1}, tiles_per_split[2] = {0, 0};
   size_t partial_bytes = 0;
   double us = 0;
 };
-bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan);
+// alone_us: what the two take otherwise (0: a launch of the streaming kernel)
+bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, double alone_us = 0.0);
 hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, float* scratch, hipStream_t stream);
 hipError_t skinny_run(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan, float* scratch,
                       hipStream_t stream);
@@ -265,8 +268,8 @@ hipError_t merge_launch_f16(const MergeArgs& a, hipStream_t s);
 struct GemmArgs;
 struct FinishArgs;
 struct SkinnyArgs;
-hipError_t mt_pair_launch_bf16(int al, int bl0, int bl1, const GemmArgs& g0, const GemmArgs& g1, unsigned grid, hipStream_t s);
-hipError_t mt_pair_launch_f16(int al, int bl0, int bl1, const GemmArgs& g0, const GemmArgs& g1, unsigned grid, hipStream_t s);
+hipError_t mt_pair_launch_bf16(int al, int bl0, int bl1, bool wide, const GemmArgs& g0, const GemmArgs& g1, unsigned grid, hipStream_t s);
+hipError_t mt_pair_launch_f16(int al, int bl0, int bl1, bool wide, const GemmArgs& g0, const GemmArgs& g1, unsigned grid, hipStream_t s);
 hipError_t skinny_reduce_launch_bf16(const SkinnyArgs& a, int splits0, int splits1, hipStream_t s);
 hipError_t skinny_reduce_launch_f16(const SkinnyArgs& a, int splits0, int splits1, hipStream_t s);
 hipError_t finish_launch_bf16(const FinishArgs& a, hipStream_t s);

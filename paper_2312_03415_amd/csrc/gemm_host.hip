@@ -744,6 +744,14 @@ static double rank_time_us(bool a_strided, int64_t wgs, int64_t ktiles, double b
   return us > floor_us ? us : floor_us;
 }
 
+// The same for a pair on 128x128 tiles, one workgroup to a compute unit: they read the long operand once where 128x64 ones read it for every 64
+// columns.  A K tile is 32 KB, 0.65 us at the 50 bytes a ns that a unit fetches (0.45 from the caches).
+static double wide_rank_us(bool a_strided, int64_t wgs, int64_t ktiles, double bytes) {
+  const double tk = bytes < 32e6 ? 0.45 : (a_strided ? 0.6 : 0.65);
+  const double us = 7.5 + (double)((wgs + 255) / 256) * (double)ktiles * tk, floor_us = 5.0 + bytes / 4.8e6;
+  return us > floor_us ? us : floor_us;
+}
+
 static bool rank_shape_ok(int dtype, const SkinnyDesc& d) {
   return dtype != DT_F32 && d.N > 32 && d.M > 32 && d.drop_thr == 0;
 }
@@ -781,7 +789,7 @@ bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, doubl
   return found;
 }
 
-bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan) {
+bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, double alone_us) {
   if (!rank_shape_ok(dtype, d[0]) || !rank_shape_ok(dtype, d[1])) return false;
   int64_t tiles[2], kt[2];
   double bytes = 0, best = 1e30;
@@ -821,8 +829,41 @@ bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan) 
       for (int w = 0; w < 2; ++w) { plan->splits[w] = (int)sp[w]; plan->tiles_per_split[w] = (int)tps[w]; }
     }
   }
+  // r > 64: 128x128 tiles, each product cut into about as many slices as make its workgroups equally long: {Z1, Z2} of 8192 x (11008 +
+  // 4096) r 128 96.5 us on 128x64 tiles, 74.4 so; 4096 x (2048 + 8192) 36.7 and 33.7; dA, dB of 8192 x (4096 + 4096) 41.6 and 35.6.
+  // (A lone product gains nothing: T of 8192 x 4096 27.8 and 28.7, of 8192 x 11008 62.2 and 61.6.)
+  if (d[0].N > 64 && d[1].N > 64) {
+    int64_t wide[2];
+    for (int w = 0; w < 2; ++w) wide[w] = ((d[w].M + 127) / 128) * ((d[w].N + 127) / 128);
+    for (int s = 1; s <= 16 && (s == 1 || longest / s >= 8); ++s) {
+      const int64_t per = (longest + s - 1) / s;
+      int64_t sp[2], tps[2], wgs = 0, most = 0;
+      size_t part = 0;
+      double us = 0;
+      for (int w = 0; w < 2; ++w) {
+        sp[w] = (kt[w] + per / 2) / per;
+        if (sp[w] < 1) sp[w] = 1;
+        tps[w] = (kt[w] + sp[w] - 1) / sp[w];
+        sp[w] = (kt[w] + tps[w] - 1) / tps[w];  // no empty slice
+        wgs += wide[w] * sp[w];
+        if (tps[w] > most) most = tps[w];
+        if (sp[w] > 1) {
+          part += (size_t)sp[w] * (size_t)d[w].M * (size_t)d[w].N * sizeof(float);
+          us += (double)d[w].M * (double)d[w].N * (8.0 * sp[w] + 2.0) / 7.5e6;
+        }
+      }
+      if (part > cap) break;
+      us += wide_rank_us(d[0].a_strided != 0, wgs, most, bytes) + (part > 0 ? 3.0 : 0.0);
+      if (us < best) {
+        best = us;
+        plan->wide = true;
+        plan->partial_bytes = part;
+        for (int w = 0; w < 2; ++w) { plan->splits[w] = (int)sp[w]; plan->tiles_per_split[w] = (int)tps[w]; }
+      }
+    }
+  }
   plan->us = best;
-  return best < skinny_time_us(dtype, 2, d, skinny_plan(dtype, 2, d));
+  return best < (alone_us > 0.0 ? alone_us : skinny_time_us(dtype, 2, d, skinny_plan(dtype, 2, d)));
 }
 
 hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, float* scratch, hipStream_t stream) {
@@ -848,8 +889,9 @@ hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, f
     a[w].rotate = g.a_strided ? 0 : 5;
     a[w].splits = plan.splits[w];
     a[w].tiles_per_split = plan.tiles_per_split[w];
-    a[w].nbm = (int)((g.M + kTileBM[plan.cfg[w]] - 1) / kTileBM[plan.cfg[w]]);
-    a[w].nbn = (int)((g.N + kTileBN[plan.cfg[w]] - 1) / kTileBN[plan.cfg[w]]);
+    const int64_t bm = plan.wide ? 128 : kTileBM[plan.cfg[w]], bn = plan.wide ? 128 : kTileBN[plan.cfg[w]];
+    a[w].nbm = (int)((g.M + bm - 1) / bm);
+    a[w].nbn = (int)((g.N + bn - 1) / bn);
     al = g.a_strided;
     bl[w] = g.b_kcontig;
     grid += (unsigned)(a[w].nbm * a[w].nbn * a[w].splits);
@@ -864,8 +906,8 @@ hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, f
       part += (size_t)plan.splits[w] * (size_t)g.M * (size_t)g.N;
     }
   }
-  hipError_t e = dtype == DT_BF16 ? mt_pair_launch_bf16(al, bl[0], bl[1], a[0], a[1], grid, stream)
-                                  : mt_pair_launch_f16(al, bl[0], bl[1], a[0], a[1], grid, stream);
+  hipError_t e = dtype == DT_BF16 ? mt_pair_launch_bf16(al, bl[0], bl[1], plan.wide, a[0], a[1], grid, stream)
+                                  : mt_pair_launch_f16(al, bl[0], bl[1], plan.wide, a[0], a[1], grid, stream);
   if (e != hipSuccess || (plan.splits[0] <= 1 && plan.splits[1] <= 1)) return e;
   return dtype == DT_BF16 ? skinny_reduce_launch_bf16(r, plan.splits[0], plan.splits[1], stream)
                           : skinny_reduce_launch_f16(r, plan.splits[0], plan.splits[1], stream);

@@ -473,7 +473,8 @@ __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_s
 
 // Two products in one launch (Z1 = dY B^T with Z2 = X A, dA = X^T Z1 with dB = Z2^T dY; r > 32): each fills a part of the
 // chip only, so they run side by side.  Workgroups [0, tiles0 splits0) belong to the first.  Tiles of 128x64 for a
-// product with r columns, 64x128 for one with r rows.  Bound by what a compute unit fetches from HBM: ~45 bytes a ns
+// product with r columns, 64x128 for one with r rows; beyond r = 64 also 128x128 for both (mt_pair_plan), which fetch the long
+// operand once.  Bound by what a compute unit fetches from HBM: ~45 bytes a ns
 // however many stages are in flight (three and six measure the same), so that a K tile's 24 KB take 0.53 us.  The streaming
 // kernel (skinny.hpp), whose waves re-read the short operand for every 32 rows, against this one: dA, dB of 8192 x (4096 +
 // 11008) r 128 129 / 61 us, Z1, Z2 120 / 97; dA, dB of 4096 x (5120 + 13824) r 64 59 / 29, of 1024 x 4096 r 64 17.5 / 9.7.

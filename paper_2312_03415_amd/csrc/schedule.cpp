@@ -274,6 +274,34 @@ struct Builder {
     out->steps.push_back(s);
     return true;
   }
+  // 128 < r <= 256: the streaming kernel's columns end at 128, but two products may still share a launch of the middle-sized kernel.
+  // In us, two launches / one: {Z1, Z2} and {dA, dB} of 1024 x (2048 + 2048) r 256 22.2 / 13.2 and 16.9 / 9.4, of 2048 x (4096 + 4096)
+  // 29.8 / 26.2 and 27.7 / 16.3, of 8192 x (4096 + 4096) 62.6 / 47.9 and 71.3 / 54.4; {Z1, Z2} of 8192 x (768 + 3072) 35.1 / 41.0.  The
+  // model of a lone product knows nothing of the other's launch behind it and too little of cold operands: a quarter more.
+  bool wide_pair(const char* what, const Sk& g1, const Sk& g2) {
+    if (L.dtype == DT_F32 || L.drop_thr != 0 || L.r <= 128 || L.r > 256) return false;
+    SkinnyDesc d[2] = {to_skinny(g1), to_skinny(g2)};
+    if (d[0].a_strided != d[1].a_strided) return false;
+    if (d[0].b_kcontig == 0 && d[1].b_kcontig == 1) { SkinnyDesc t = d[0]; d[0] = d[1]; d[1] = t; }
+    double alone_us = 0;
+    for (const SkinnyDesc& k : d) {
+      const int64_t a_rows = k.a_strided ? k.K : k.M, b_rows = k.b_kcontig ? k.N : k.K;
+      if (k.N != L.r || a_rows * k.lda >= (1LL << 30) || b_rows * k.ldb >= (1LL << 30)) return false;
+      const GemmDesc g = rank_desc(L.dtype, k);
+      alone_us += plan_time_us(gemm_plan(L.dtype, g.M, g.N, g.K[0], 0), g.M, g.N, g.K[0], 0);
+    }
+    Step s;
+    s.what = what;
+    s.nsk = 2;
+    s.d.dtype = L.dtype;
+    s.sk[0] = d[0];
+    s.sk[1] = d[1];
+    s.is_mtpair = mt_pair_plan(L.dtype, s.sk, spare(), &s.mtpair, 1.25 * alone_us);
+    if (!s.is_mtpair) return false;
+    if (s.mtpair.partial_bytes > max_partial) max_partial = s.mtpair.partial_bytes;
+    out->steps.push_back(s);
+    return true;
+  }
   void skinny2(const char* what, const char* what1, const Sk& g1, const char* what2, const Sk& g2) {
     bool pair = sk_ok(g1) && sk_ok(g2);
     SkinnyDesc d1, d2;
@@ -286,6 +314,7 @@ struct Builder {
       else if (d1.b_kcontig == 0 && d2.b_kcontig == 1) { SkinnyDesc t = d1; d1 = d2; d2 = t; }
       if (pair && d1.a_strided == 1 && (d1.b_kcontig || d2.b_kcontig)) pair = false;
     }
+    if (!pair && wide_pair(what, g1, g2)) return;
     if (!pair) {
       skinny(what1, g1);
       skinny(what2, g2);

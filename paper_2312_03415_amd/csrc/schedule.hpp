@@ -42,7 +42,7 @@ struct LayerDims {
   // holds only what the other launches take
   bool rank_scratch = true;
 };
-constexpr size_t kRankScratch = 8u << 20;
+constexpr size_t kRankScratch = 16u << 20;
 
 struct Step {
   bool is_merge = false;  // M = W + A B on the merge kernel (mg); otherwise see nsk

@@ -52,7 +52,9 @@ def test_gradients_in_32_and_64_row_blocks(n, i, o, r, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("n,i,o,r", [(520, 2056, 2120, 64), (1032, 4104, 1096, 40), (300, 1000, 3000, 128), (2056, 264, 4104, 72)])
+@pytest.mark.parametrize("n,i,o,r", [(520, 2056, 2120, 64), (1032, 4104, 1096, 40), (300, 1000, 3000, 128), (2056, 264, 4104, 72),
+                                     (4104, 520, 2056, 128), (1032, 4104, 1096, 256), (2056, 1096, 4104, 136), (200, 392, 264, 200),
+                                     (520, 1032, 1096, 264)])
 def test_rank_products_with_and_without_scratch_for_splits(n, i, o, r, dtype):
     """r > 32: with the workspace that the query names, a rank-r product may split its contraction into a few MB of it; a call whose
     workspace holds only what the other launches take (the figure in the error text) still runs, unsplit.  Integers: the same bits."""
