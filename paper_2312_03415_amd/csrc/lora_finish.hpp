@@ -5,13 +5,16 @@
 // spent more time on being launched and on waiting for each other than on W.  Here the first launch (gemm_mt.hpp, XA
 // build) forms the fp32 partials of X W and of X A side by side, K split over enough workgroups to fill the chip, and this
 // one sums them in slice order, rounds T = s X A to the storage type as the stored T is everywhere else, and adds T B and
-// the bias: 1 x 4096 -> 4096, r 16: 21.9 us on the GPU in four launches, 13.2 in two (of which this one 4.7); 48 x 4096 ->
-// 11008, r 32: 41.5 and 23.7 (6.0).
+// the bias: 1 x 4096 -> 4096, r 16: 21.9 us on the GPU in four launches, 12.2 in two (of which this one 4.1); 48 x 4096 ->
+// 11008, r 32: 41.5 and 21.5 (5.2).
 //
-// Bound by latency, that is by the number of trips to memory one behind the other: the slices are summed in blocks of two, four or
-// eight whose loads are in flight together (slices beyond the last read the last one and add zero: as a rolled remainder the
-// last three of seven took a trip each), T's columns of a thread four at a time, sixteen rows of B ahead of T.  A thread owns 16 bytes of a row of Y; a workgroup is cx column chunks by ry rows (ry covers the rows up
-// to 32, so that one row still spreads over 64 threads), with its rows of T in LDS.
+// Bound by latency, that is by the number of trips to memory one behind the other: the slices are summed four at a time, and what
+// is left of them together (as a rolled remainder the last three of seven took a trip each), T's columns of a thread four at a
+// time, sixteen rows of B ahead of T and the others a block of eight ahead.  Together 9.0 -> 5.9 us at 3 x 8192 -> 8192 r 48, 13.6
+// -> 12.2 at 16 x 4096 -> 4096 r 128, 5.7 -> 5.2 at 48 x 4096 -> 11008 r 32.  (Eight slices at a time, padded or each count
+// unrolled, cost registers and instruction fetches: 94 x 9568 -> 1024 in twelve slices 5.0 -> 6.3.)  A thread owns 16 bytes of a
+// row of Y; a workgroup is cx column chunks by ry rows (ry covers the rows up to 32, so that one row still spreads over 64
+// threads), with its rows of T in LDS.
 #pragma once
 #include "gemm_engine.hpp"
 
@@ -49,52 +52,56 @@ __global__ __launch_bounds__(256) void lora_finish_kernel(FinishArgs g) {
       for (int k = 8; k < 16; ++k) first[k] = *reinterpret_cast<const i32x4*>(b + (int64_t)k * g.ldb);
     }
   }
-  // the slices in blocks of U, in slice order
-  auto sum_y = [&](auto u_c) {
-    constexpr int U = decltype(u_c)::value;
+  // f(first slice, how many: a constant up to four) over all slices in order
+  auto slices = [&](auto f) {
+    int z = 0;
+    for (; z + 4 <= g.splits; z += 4) f(z, std::integral_constant<int, 4>{});
+    switch (g.splits - z) {
+      case 1: f(z, std::integral_constant<int, 1>{}); break;
+      case 2: f(z, std::integral_constant<int, 2>{}); break;
+      case 3: f(z, std::integral_constant<int, 3>{}); break;
+      default: break;
+    }
+  };
+  if (ok) {
     const float* const src = g.partial + (int64_t)m * g.N + n;
-    for (int z0 = 0; z0 < g.splits; z0 += U) {
+    slices([&](int z, auto u_c) {
+      constexpr int U = decltype(u_c)::value;
       f32x4 p[U][2];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int z = z0 + u < g.splits ? z0 + u : g.splits - 1;
-        p[u][0] = *reinterpret_cast<const f32x4*>(src + (int64_t)z * g.M * g.N);
-        p[u][1] = *reinterpret_cast<const f32x4*>(src + (int64_t)z * g.M * g.N + 4);
+        p[u][0] = *reinterpret_cast<const f32x4*>(src + (int64_t)(z + u) * g.M * g.N);
+        p[u][1] = *reinterpret_cast<const f32x4*>(src + (int64_t)(z + u) * g.M * g.N + 4);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (z0 + u < g.splits) {  // uniform
 #pragma unroll
-          for (int e = 0; e < 4; ++e) { acc[e] += p[u][0][e]; acc[4 + e] += p[u][1][e]; }
-        }
-    }
-  };
-  // Q columns of this thread's row of T, k0, k0 + blockDim.x, ...
-  auto sum_t = [&](auto u_c, auto q_c, int k0) {
-    constexpr int U = decltype(u_c)::value, Q = decltype(q_c)::value;
+        for (int e = 0; e < 4; ++e) { acc[e] += p[u][0][e]; acc[4 + e] += p[u][1][e]; }
+    });
+  }
+  // this workgroup's rows of T (a row per threadIdx.y, its columns over threadIdx.x: Q of them a thread at a time)
+  auto sum_t = [&](auto q_c, int k0) {
+    constexpr int Q = decltype(q_c)::value;
     float t[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) t[q] = 0.f;
     if (m < g.M) {
       const float* const src = g.partial_t + (int64_t)m * g.R;
-      for (int z0 = 0; z0 < g.splits; z0 += U) {
+      slices([&](int z, auto u_c) {
+        constexpr int U = decltype(u_c)::value;
         float p[U][Q];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int z = z0 + u < g.splits ? z0 + u : g.splits - 1;
+        for (int u = 0; u < U; ++u)
 #pragma unroll
           for (int q = 0; q < Q; ++q) {
             const int k = k0 + q * (int)blockDim.x;
-            p[u][q] = src[(int64_t)z * g.M * g.R + (k < g.R ? k : k0)];
+            p[u][q] = src[(int64_t)(z + u) * g.M * g.R + (k < g.R ? k : k0)];
           }
-        }
 #pragma unroll
         for (int u = 0; u < U; ++u)
-          if (z0 + u < g.splits) {
 #pragma unroll
-            for (int q = 0; q < Q; ++q) t[q] += p[u][q];
-          }
-      }
+          for (int q = 0; q < Q; ++q) t[q] += p[u][q];
+      });
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -106,18 +113,11 @@ __global__ __launch_bounds__(256) void lora_finish_kernel(FinishArgs g) {
       }
     }
   };
-  auto sums = [&](auto u_c) {
-    if (ok) sum_y(u_c);
-    // this workgroup's rows of T (a row per threadIdx.y, its columns over threadIdx.x)
-    if (g.R <= (int)blockDim.x) {
-      if ((int)threadIdx.x < g.R) sum_t(u_c, std::integral_constant<int, 1>{}, (int)threadIdx.x);
-    } else {
-      for (int k0 = (int)threadIdx.x; k0 < g.R; k0 += 4 * (int)blockDim.x) sum_t(u_c, std::integral_constant<int, 4>{}, k0);
-    }
-  };
-  if (g.splits <= 2) sums(std::integral_constant<int, 2>{});
-  else if (g.splits <= 4) sums(std::integral_constant<int, 4>{});
-  else sums(std::integral_constant<int, 8>{});
+  if (g.R <= (int)blockDim.x) {
+    if ((int)threadIdx.x < g.R) sum_t(std::integral_constant<int, 1>{}, (int)threadIdx.x);
+  } else {
+    for (int k0 = (int)threadIdx.x; k0 < g.R; k0 += 4 * (int)blockDim.x) sum_t(std::integral_constant<int, 4>{}, k0);
+  }
   __syncthreads();
   if (!ok) return;
   const float* const tr = sT + (int)threadIdx.y * g.R;
