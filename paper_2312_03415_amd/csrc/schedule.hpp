@@ -29,11 +29,12 @@ struct LayerDims {
   // LoRA dropout on the adapter's input (drop_thr = round(256 p), 0 = none): Y = XW + s' ((X o m) A) B with
   // the keep-mask m of gemm_engine.hpp and s' = scale / (1 - drop_thr / 256) in place of scale.  Only the
   // graphs that never merge AB into W and never form X^T dY exist with it: forward 0/1, backward 0/1, the
-  // latter with dX = dY W^T followed by dX += m o (Z1 A^T) instead of the concatenated contraction.
+  // latter with dX = m o (Z1 A^T) + dY W^T in one launch where masked_segment_ok, else dX = dY W^T followed by
+  // dX += m o (Z1 A^T), instead of the concatenated contraction.
   uint32_t drop_thr = 0, drop_key = 0;
   // DoRA: the frozen weight is W diag(wcol) (device, o floats).  It is never formed: only the graphs in which
   // W enters through M = W + s AB alone exist with it (forward2, backward 4 / 5 / 7 / 8), where the merge kernel
-  // scales W's columns on the way; 16-bit types, r <= 128.
+  // scales W's columns on the way, or the forward's product the columns of X M; 16-bit types, r <= 128.
   const float* wcol = nullptr;
   // an int4 W's products may dequantise panels of it into scratch; false for calls whose scratch holds only what the
   // direct route takes
