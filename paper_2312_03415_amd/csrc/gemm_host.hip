@@ -157,9 +157,11 @@ bool long_operand(const GemmDesc& d) {
   return false;
 }
 
+// bf16 only: V = W + s A B rounded to f16 may overflow, or lose bits as a subnormal, where V diag(g), rounded after the scaling, does
+// neither; in bf16 the two have the same range.
 bool column_scale_ok(const GemmDesc& d, const GemmPlan& p) {
   auto built = [](int cfg, int splits) { return splits <= 1 && (cfg_is_mt(cfg) || cfg == CFG_MC4); };
-  return d.dtype != DT_F32 && d.nseg == 1 && !d.a_strided && !d.b_kcontig && !d.b_int4 && d.Bscale == nullptr && !d.has_addend && d.D == nullptr &&
+  return d.dtype == DT_BF16 && d.nseg == 1 && !d.a_strided && !d.b_kcontig && !d.b_int4 && d.Bscale == nullptr && !d.has_addend && d.D == nullptr &&
          d.alpha == 1.f && d.drop_thr == 0 && !d.fuse_t && !long_operand(d) && built(p.cfg, p.splits) && (p.tail_n0 == 0 || built(p.tail_cfg, p.tail_splits));
 }
 

@@ -216,8 +216,25 @@ def test_dora_forward_with_scaled_columns(n, i, o, r, scaled, dtype):
     torch.cuda.synchronize()
     steps = [s["what"] for s in rl.runlora_profile_collect(8)]
     rl.runlora_profile_disable()
-    assert ("Y = X V diag(g)" in steps) == scaled, steps
+    assert ("Y = X V diag(g)" in steps) == (scaled and dtype == "bf16"), steps
     assert relerr(to_f64(cd), c) < 1e-5 and relerr(to_f64(Y)[rows], want) < TOL[dtype]
     edge = buf.float()
     edge[1:n + 1, 8:o + 8] = 7.0
     assert bool((edge == 7.0).all())
+
+
+def test_dora_f16_weight_sum_beyond_the_type():
+    """W + s A B may leave the range of f16 (70000 here) where its scaled columns do not: nothing is rounded in between."""
+    import torch
+    n, i, o, r = 520, 264, 1000, 8
+    g = torch.Generator().manual_seed(3)
+    X = torch.randn(n, i, generator=g).to(torch.float16)
+    full = lambda a, b, v: torch.full((a, b), v, dtype=torch.float16, device="cuda")
+    W, A, B, m = full(i, o, 60000.0), full(i, r, 50.0), full(r, o, 50.0), full(1, o, 30.0)[0]
+    Y, cd = full(n, o, 0.0), torch.empty((o,), dtype=torch.float32, device="cuda")
+    ws = torch.empty((rl.runlora_dora_workspace_bytes(2, -1, n, i, o, r, rl.RL_F16),), dtype=torch.uint8, device="cuda")
+    rl.runlora_dora_forward(2, X.cuda(), W, A, B, m, Y, rl.new_saved(), cd, ws, scale=0.5)
+    torch.cuda.synchronize()
+    want = np.repeat(X.double().numpy().sum(axis=1, keepdims=True) * (30.0 / np.sqrt(i)), o, axis=1)  # c = 70000 sqrt(i) in every column
+    assert relerr(to_f64(cd), np.full((o,), 70000.0 * np.sqrt(i))) < 1e-5
+    assert relerr(to_f64(Y), want) < TOL["f16"]
