@@ -334,7 +334,9 @@ double runlora_model_time_us(int is_bwd, int variant, int64_t n, int64_t i, int6
 size_t runlora_saved_bytes(int fwd, int64_t n, int64_t i, int64_t o, int64_t r, int dtype, int keep_merged);
 
 /* Scratch bytes needed by a forward variant (bwd < 0), a backward variant (fwd < 0), or the
- * larger of the two, for a dense W of the layer dtype and tensors with dense rows (ld = columns).
+ * larger of the two, for a dense W of the layer dtype and tensors with dense rows (ld = columns):
+ * the most that any call takes, whatever it keeps (T, M), whichever gradients it wants, with and
+ * without LoRA dropout (RL_FWD3: where it applies; otherwise what RL_FWD1 needs).
  * Which kernel a rank-r product runs on depends on its operands' extents in memory, so a call on
  * tensors with padded rows whose extent reaches 2 GiB may need more: it then returns
  * RL_ERR_WORKSPACE and runlora_last_hip_error() names the size.  0 for an unknown variant or dtype. */

@@ -620,7 +620,9 @@ extern "C" size_t runlora_vera_workspace_bytes(int fwd, int bwd, int64_t n, int6
   const int dt = internal_dtype(dtype);
   if (dt < 0 || n < 1 || i < 1 || o < 1 || r < 1) return 0;
   if (fwd > RL_FWD3 || bwd > RL_BWD8 || (fwd < 0 && bwd < 0)) return 0;
-  return 2 * align256((size_t)r * (size_t)o * dtype_size(dt)) + runlora_workspace_bytes(fwd, bwd, n, i, o, r, dtype);
+  const LayerDims L{n, i, o, r, dt};
+  const size_t f = fwd >= 0 ? forward_workspace(fwd, L) : 0, b = bwd >= 0 ? backward_workspace(bwd, L, true) : 0;  // (A is frozen)
+  return 2 * align256((size_t)r * (size_t)o * dtype_size(dt)) + (f > b ? f : b);
 }
 
 // ---- DoRA: the merged-weight graphs on (W diag(g), A, B diag(g)), g = m / c, see dora.hpp ----------------
@@ -860,23 +862,12 @@ extern "C" size_t runlora_workspace_bytes_w(int fwd, int bwd, int64_t n, int64_t
   if (w_dtype != dtype && w_dtype != RL_INT4_G64) return 0;
   LayerDims L{n, i, o, r, dt, w_dtype == RL_INT4_G64};
   size_t need = 0;
-  Schedule sch;
-  // dense rows (ld = columns): which kernel a rank-r product runs on, and with it the scratch, depends on the
-  // operands' extents; a call on tensors with padded rows may need more and says how much (RL_ERR_WORKSPACE).  With and
-  // without LoRA dropout, which variants 0 and 1 exist with: masked products have plans of their own.
-  for (const uint32_t thr : {0u, 1u}) {
-    L.drop_thr = thr;
-    if (fwd >= 0 && (thr == 0 || fwd <= 1)) {
-      FwdOperands op;
-      op.X.ld = i; op.W.ld = o; op.A.ld = r; op.B.ld = o; op.Y.ld = o; op.T.ld = r; op.M.ld = o;
-      if (build_forward(fwd, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
-    }
-    if (bwd >= 0 && (thr == 0 || bwd <= 1)) {
-      BwdOperands op;
-      op.dY.ld = o; op.X.ld = i; op.W.ld = o; op.A.ld = r; op.B.ld = o; op.T.ld = r; op.dX.ld = i; op.dA.ld = r; op.dB.ld = o;
-      op.M.ld = o;
-      if (build_backward(bwd, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
-    }
+  // on dense rows: which kernel a rank-r product runs on, and with it the scratch, depends on the operands' extents; a call on tensors
+  // with padded rows may need more and says how much (RL_ERR_WORKSPACE)
+  if (fwd >= 0) need = forward_workspace(fwd, L);
+  if (bwd >= 0) {
+    const size_t b = backward_workspace(bwd, L);
+    if (b > need) need = b;
   }
   return need;
 }

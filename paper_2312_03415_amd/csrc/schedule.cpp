@@ -28,9 +28,20 @@ struct Builder {
     const size_t have = later_partial > max_partial ? later_partial : max_partial;
     return L.rank_scratch && have < kRankScratch ? kRankScratch : have;
   }
+  GemmPlan dense_plan(int64_t M, int64_t N, int64_t K0, int64_t K1, bool long_op = false) const {
+    if (L.memo != nullptr)
+      for (int k = 0; k < L.memo->used; ++k) {
+        const PlanMemo::Entry& e = L.memo->entry[k];
+        if (e.M == M && e.N == N && e.K0 == K0 && e.K1 == K1 && e.long_operand == long_op) return e.plan;
+      }
+    GemmPlan p = gemm_plan(L.dtype, M, N, K0, K1, -1, 0, false, long_op);
+    if (L.dtype == DT_F32) gemm_plan_f32(&p, M, N, K0, K1);
+    if (L.memo != nullptr && L.memo->used < 8) L.memo->entry[L.memo->used++] = {M, N, K0, K1, long_op, p};
+    return p;
+  }
   // the product [M, K0 + K1] x [K0 + K1, N] comes after the rank-r products and brings its own scratch
   void expect_gemm(int64_t M, int64_t N, int64_t K0, int64_t K1, bool b_is_w, int64_t lda) {
-    const GemmPlan p = b_is_w && L.w_int4 ? gemm_plan_int4(L.dtype, M, N, K0, K1) : gemm_plan(L.dtype, M, N, K0, K1);
+    const GemmPlan p = b_is_w && L.w_int4 ? gemm_plan_int4(L.dtype, M, N, K0, K1) : dense_plan(M, N, K0, K1);
     if (p.partial_bytes > later_partial) later_partial = p.partial_bytes;
     GemmDesc d;  // (the test gemm() makes before it takes panels)
     d.M = M; d.N = N; d.K[0] = K0; d.K[1] = K1;
@@ -104,8 +115,7 @@ struct Builder {
         if (s.panel.scratch_bytes > max_partial) max_partial = s.panel.scratch_bytes;
       }
     } else {
-      s.plan = gemm_plan(L.dtype, M, N, K, K2, -1, 0, false, long_operand(d));
-      if (L.dtype == DT_F32) gemm_plan_f32(&s.plan, M, N, K, K2);
+      s.plan = dense_plan(M, N, K, K2, long_operand(d));
     }
     if (s.plan.partial_bytes > max_partial) max_partial = s.plan.partial_bytes;
     out->steps.push_back(s);
@@ -130,7 +140,7 @@ struct Builder {
     d.mask_seg0 = true;
     d.drop_thr = L.drop_thr; d.drop_key = L.drop_key; d.drop_cpr = drop_cpr();
     if (L.w_int4) return false;
-    s.plan = gemm_plan(L.dtype, L.n, L.i, L.o, L.r, -1, 0, false, long_operand(d));
+    s.plan = dense_plan(L.n, L.i, L.o, L.r, long_operand(d));
     if (!masked_segment_ok(d, s.plan)) return false;
     if (s.plan.partial_bytes > max_partial) max_partial = s.plan.partial_bytes;
     out->steps.push_back(s);
@@ -248,7 +258,7 @@ struct Builder {
     if (L.n * X.ld >= (1LL << 30) || L.i * W.ld >= (1LL << 30) || L.i * A.ld >= (1LL << 30)) return false;
     const SkinnyDesc sd = to_skinny({0, 0, L.n, L.r, L.i, X, A, T, true});
     const SkinnyPlan skp = skinny_plan(L.dtype, 1, &sd);
-    const GemmPlan gp = gemm_plan(L.dtype, L.n, L.o, L.i, L.r);
+    const GemmPlan gp = dense_plan(L.n, L.o, L.i, L.r);
     const size_t bytes = skp.partial_bytes > gp.partial_bytes ? skp.partial_bytes : gp.partial_bytes;
     const FewPlan plan = rl::few_plan(L.n, L.i, L.o, L.r, bytes);
     if (plan.splits == 0) return false;
@@ -288,7 +298,7 @@ struct Builder {
       const int64_t a_rows = k.a_strided ? k.K : k.M, b_rows = k.b_kcontig ? k.N : k.K;
       if (k.N != L.r || a_rows * k.lda >= (1LL << 30) || b_rows * k.ldb >= (1LL << 30)) return false;
       const GemmDesc g = rank_desc(L.dtype, k);
-      alone_us += plan_time_us(gemm_plan(L.dtype, g.M, g.N, g.K[0], 0), g.M, g.N, g.K[0], 0);
+      alone_us += plan_time_us(dense_plan(g.M, g.N, g.K[0], 0), g.M, g.N, g.K[0], 0);
     }
     Step s;
     s.what = what;
@@ -520,6 +530,47 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
   }
   b.finish();
   return !b.failed;
+}
+
+size_t forward_workspace(int variant, LayerDims L) {
+  PlanMemo memo;
+  L.memo = &memo;
+  FwdOperands op;  // (T or M kept: the same launches and less scratch)
+  op.X.ld = L.i; op.W.ld = L.o; op.A.ld = L.r; op.B.ld = L.o; op.Y.ld = L.o; op.T.ld = L.r; op.M.ld = L.o;
+  size_t need = 0;
+  Schedule sch;
+  for (const uint32_t thr : {0u, 1u}) {
+    if (thr != 0 && variant > 1) continue;  // variants 0 and 1 exist with dropout; masked products have plans of their own
+    L.drop_thr = thr;
+    if (build_forward(variant, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
+  }
+  return need;
+}
+
+size_t backward_workspace(int variant, LayerDims L, bool never_dA) {
+  PlanMemo memo;
+  L.memo = &memo;
+  BwdOperands op;
+  op.dY.ld = L.o; op.X.ld = L.i; op.W.ld = L.o; op.A.ld = L.r; op.B.ld = L.o; op.T.ld = L.r; op.dX.ld = L.i; op.dA.ld = L.r; op.dB.ld = L.o;
+  op.M.ld = L.o;
+  // Gradients (dX 4, dA 2, dB 1) such that both products of every pair are planned together and each alone: Z1 and dA alone, Z1 as
+  // with T kept (6), dB alone (5), X A alone (1).  A call that wants less, or has T or M kept, plans each of its launches as one of
+  // these does and holds no more.
+  const bool forms_xa = variant == 1 || variant == 5 || variant == 6;
+  size_t need = 0;
+  Schedule sch;
+  for (const uint32_t thr : {0u, 1u}) {
+    if (thr != 0 && variant > 1) continue;
+    L.drop_thr = thr;
+    for (const int want : {7, 6, 5, 1}) {
+      if ((want == 1 && !forms_xa) || (want == 7 && never_dA)) continue;
+      op.want_dX = (want & 4) != 0;
+      op.want_dA = (want & 2) != 0 && !never_dA;
+      op.want_dB = (want & 1) != 0;
+      if (build_backward(variant, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
+    }
+  }
+  return need;
 }
 
 }  // namespace rl

@@ -18,6 +18,15 @@ struct Mat {  // device matrix view; ptr may be null when only shapes are needed
   int64_t lds = 0;
 };
 
+constexpr size_t kRankScratch = 16u << 20;
+
+// Plans already made for the dense tile GEMMs of one layer: sizing a workspace builds its schedule for every choice that a call has, in
+// which the large products repeat.
+struct PlanMemo {
+  struct Entry { int64_t M, N, K0, K1; bool long_operand; GemmPlan plan; } entry[8];
+  int used = 0;
+};
+
 struct LayerDims {
   int64_t n = 0, i = 0, o = 0, r = 0;
   int dtype = DT_BF16;
@@ -42,8 +51,8 @@ struct LayerDims {
   // rank-r products with r > 32 may ask for up to kRankScratch bytes to split their contraction into; false for calls whose scratch
   // holds only what the other launches take
   bool rank_scratch = true;
+  PlanMemo* memo = nullptr;  // shared by builds of one shape
 };
-constexpr size_t kRankScratch = 16u << 20;
 
 struct Step {
   bool is_merge = false;  // M = W + A B on the merge kernel (mg); otherwise see nsk
@@ -88,6 +97,12 @@ struct BwdOperands {
 // ws_base may be null (sizing / modelling).  Returns false for an unknown variant.
 bool build_forward(int variant, const LayerDims& L, const FwdOperands& op, void* ws_base, Schedule* out);
 bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void* ws_base, Schedule* out);
+
+// Workspace of calls on dense rows (ld = columns): the most that any of them takes, with T and M kept or not, with and without LoRA
+// dropout (L.drop_thr is not looked at), whichever gradients are wanted; never_dA: none for A.  A rank-r product alone may need more than
+// the launch that serves it and another (backward 1 of 4096 x 4096 -> 4096, r 256, bf16: 20 MB with all gradients, 34 with T kept).
+size_t forward_workspace(int variant, LayerDims L);
+size_t backward_workspace(int variant, LayerDims L, bool never_dA = false);
 
 inline size_t dtype_size(int dtype) { return dtype == DT_F32 ? 4 : 2; }
 

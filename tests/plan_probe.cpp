@@ -3,9 +3,39 @@
 #include <cstdio>
 #include <cstring>
 
+#include "../include/runlora.h"
 #include "../paper_2312_03415_amd/csrc/schedule.hpp"
 
 using namespace rl;
+
+// every forward (T or M kept or not) and backward (T and M kept or not, each choice of gradients) of a layer, with and without dropout: f(is
+// a backward, variant, dA wanted, the schedule it runs)
+template <typename F>
+static void each_call(LayerDims L, F f) {
+  Schedule s;
+  FwdOperands a;
+  a.X.ld = L.i; a.W.ld = L.o; a.A.ld = L.r; a.B.ld = L.o; a.Y.ld = L.o; a.T.ld = L.r; a.M.ld = L.o;
+  BwdOperands b;
+  b.dY.ld = L.o; b.X.ld = L.i; b.W.ld = L.o; b.A.ld = L.r; b.B.ld = L.o; b.T.ld = L.r; b.dX.ld = L.i; b.dA.ld = L.r; b.dB.ld = L.o; b.M.ld = L.o;
+  for (unsigned thr : {0u, 26u}) {
+    L.drop_thr = thr;
+    for (int v = 0; v <= 3; ++v)
+      for (int keep = 0; keep <= (v == 1 || v == 2 ? 1 : 0); ++keep) {
+        if (v == 3 && thr != 0) continue;  // (runs as variant 1, and needs what that needs)
+        a.keep_T = v == 1 && keep != 0;
+        a.keep_M = v == 2 && keep != 0;
+        if (build_forward(v, L, a, nullptr, &s)) f(false, v, true, s);
+      }
+    for (int v = 0; v <= 8; ++v)
+      for (int keep = 0; keep < 4; ++keep)
+        for (int want = 1; want < 8; ++want) {
+          b.have_T = (keep & 1) != 0 && (v == 1 || v == 5 || v == 6 || v == 7);
+          b.have_M = (keep & 2) != 0 && (v == 4 || v == 5 || v == 7 || v == 8);
+          b.want_dX = (want & 4) != 0; b.want_dA = (want & 2) != 0; b.want_dB = (want & 1) != 0;
+          if (build_backward(v, L, b, nullptr, &s)) f(true, v, b.want_dA, s);
+        }
+  }
+}
 
 int main() {
   char kind[16];
@@ -30,6 +60,17 @@ int main() {
       Schedule f, b;
       if (!build_forward(1, L, FwdOperands{}, nullptr, &f) || !build_backward(1, L, BwdOperands{}, nullptr, &b)) return 1;
       std::printf("%zu %zu\n", f.workspace_bytes, b.workspace_bytes);
+    } else if (std::strncmp(kind, "calls", 5) == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: calls that need more than the query names
+      const int dt = kind[5] == '3' ? DT_F32 : DT_BF16, code = kind[5] == '3' ? RL_F32 : RL_BF16;
+      const bool int4 = kind[5] == '4';
+      const size_t factors = 2 * (((size_t)K1 * (size_t)K0 * dtype_size(dt) + 255) / 256 * 256);
+      int beyond = 0, beyond_vera = 0, first = -1;
+      each_call(LayerDims{M, N, K0, K1, dt, int4}, [&](bool bwd, int v, bool dA, const Schedule& s) {
+        const size_t have = runlora_workspace_bytes_w(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code, int4 ? RL_INT4_G64 : code);
+        if (s.workspace_bytes > have && beyond++ == 0) first = v;
+        if (!int4 && !(bwd && dA) && factors + s.workspace_bytes > runlora_vera_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code)) ++beyond_vera;
+      });
+      std::printf("%d %d %d\n", beyond, beyond_vera, first);
     } else if (std::strcmp(kind, "few") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: the few-token route's price and taken or not
       SkinnyDesc d;
       d.M = M; d.N = K1; d.K = N;

@@ -98,6 +98,38 @@ def test_rank_products_with_and_without_scratch_for_splits(n, i, o, r, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r", [(4096, 4096, 4096, 256), (2056, 1096, 4104, 192), (520, 1032, 1096, 264), (4104, 520, 2056, 136), (6577, 2824, 8496, 72),
+                                     (1032, 4104, 1096, 40)])
+def test_rank_products_with_T_kept_and_with_fewer_gradients(n, i, o, r, dtype):
+    """Algorithm 1 in exactly the bytes that the query names, with T = X A kept or not, for every choice of gradients (a VeRA layer never wants
+    dA): Z1, X A, dA and dB then run alone or in pairs, each with splits of its own.  Integers: the same bits every time."""
+    import torch
+    rng = np.random.default_rng(n + r)
+    td, code = torch_dtype(dtype), rl.dtype_from_name(dtype)
+    pick = lambda shape, p: torch.from_numpy((rng.random(shape, dtype=np.float32) < p) * rng.choice(np.float32([-1.0, 1.0]), size=shape)).to(td).cuda()
+    X, W, A, B, dY = pick((n, i), 0.02), pick((i, o), 0.01), pick((i, r), 0.01), pick((r, o), 0.01), pick((n, o), 0.01)
+    print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
+    f32 = lambda t: t.float().contiguous()
+    Z, T = (f32(dY) @ f32(B.t())).to(td), (f32(X) @ f32(A)).to(td)   # (sums of integers below 2^24: exact in fp32; below 257 in bf16)
+    want = {"dX": f32(dY) @ f32(W.t()) + f32(Z) @ f32(A.t()), "dA": f32(X.t()) @ f32(Z), "dB": f32(T.t()) @ f32(dY)}
+    assert max(float(v.abs().max()) for v in (Z, T, *want.values())) <= 256
+    wb = torch.empty((rl.runlora_workspace_bytes(-1, 1, n, i, o, r, code),), dtype=torch.uint8, device="cuda")
+    wf = torch.empty((rl.runlora_workspace_bytes(1, -1, n, i, o, r, code),), dtype=torch.uint8, device="cuda")
+    for keep in (False, True):
+        wf.fill_(0xFF)
+        kept = torch.full((n, r), float("nan"), dtype=td, device="cuda") if keep else None
+        saved = rl.new_saved(kept)
+        rl.runlora_forward(1, X, W, A, B, torch.empty_like(dY), saved, workspace=wf)
+        for names in (("dX", "dA", "dB"), ("dX", "dA"), ("dX", "dB"), ("dA", "dB"), ("dX",), ("dA",), ("dB",)):
+            out = {k: torch.full(s, float("nan"), dtype=td, device="cuda") if k in names else None for k, s in (("dX", (n, i)), ("dA", (i, r)), ("dB", (r, o)))}
+            wb.fill_(0xFF)
+            rl.runlora_backward(1, dY, saved, W, A, B, *out.values(), workspace=wb)
+            torch.cuda.synchronize()
+            for k in names:
+                assert torch.equal(out[k].float(), want[k]), (keep, names, k)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_few_tokens_in_every_number_of_slices(dtype):
     """lora_finish_kernel sums two, four or eight slices at a time and takes B's rows in blocks of eight: 1 to 16 slices, ranks on both
     sides of 8, 16, 24 and of its threads' share of T, bit for bit on integers."""

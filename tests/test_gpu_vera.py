@@ -136,3 +136,28 @@ def test_vera_full_size_opt_fc1_rank256():
     Yr = oracle.vera_forward(host["X"][rows], host["W"], host["A"], host["B"], d, b, 0.25, bias)
     dXr = oracle.matmul(host["dY"][rows], host["W"], tb=True) + oracle.matmul(dU[rows] * d[None, :], host["A"], tb=True)
     assert relerr(got["Y"][rows], Yr) < TOL["bf16"] and relerr(got["dX"][rows], dXr) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("r", [192, 256])
+def test_vera_module_beyond_rank_128(r):
+    """RunVeRALinear at 4096 x 4096 -> 4096, bf16: its backward forms no dA, so that Z1 and X A share a launch and dB runs alone, in the workspace
+    that the module asks for.  All of dd and db, sampled rows of dX, in fp32 from the same operands."""
+    import torch
+    from paper_2312_03415_amd.module import RunVeRALinear
+    n, i, o = 4096, 4096, 4096
+    L = synth.Layer("vera_module", n, i, o, r, "bf16", 45)
+    dev, _ = layer_on_device(L)
+    vec = vectors(L)
+    layer = RunVeRALinear(dev["W"], dev["A"], dev["B"], scale=0.25, pair=(1, 1))
+    with torch.no_grad():
+        layer.vera_d.copy_(vec["d"][0])
+        layer.vera_b.copy_(vec["b"][0])
+    x = dev["X"].clone().requires_grad_()
+    layer(x).backward(dev["dY"])
+    torch.cuda.synchronize()
+    X, A, B, dY, d, b = (t.detach().float() for t in (dev["X"], dev["A"], dev["B"], dev["dY"], layer.vera_d, layer.vera_b))
+    T, U = X @ A, 0.25 * (dY * b) @ B.t().contiguous()
+    rows = torch.arange(0, n, 61, device="cuda")
+    dX = dY[rows] @ dev["W"].float().t().contiguous() + (U[rows] * d) @ A.t().contiguous()
+    for got, want in ((layer.vera_d.grad, (T * U).sum(0)), (layer.vera_b.grad, 0.25 * (dY * ((T * d) @ B)).sum(0)), (x.grad[rows], dX)):
+        assert relerr(to_f64(got), to_f64(want)) < TOL["bf16"]

@@ -93,3 +93,16 @@ def test_the_workspace_query_covers_lora_dropout(probe):
         for (n, i, o, r), need in zip(rows, probe(kind, rows)):
             assert rl.runlora_workspace_bytes(1, -1, n, i, o, r, code) >= need[0], (kind, n, i, o, r)
             assert rl.runlora_workspace_bytes(-1, 1, n, i, o, r, code) >= need[1], (kind, n, i, o, r)
+
+
+def test_the_workspace_query_covers_every_call(probe):
+    """Whatever a call keeps or leaves out, the bytes that runlora_workspace_bytes (runlora_vera_workspace_bytes) names for its variant are
+    enough for the schedule it runs without a look at its workspace: Z1 alone of 4096 x 4096, r 256, takes more partials than Z1 and X A
+    in one launch, and so does a product with r <= 128 whose pair is not split."""
+    rng = np.random.default_rng(11)
+    rows = [(4096, 4096, 4096, 256), (8192, 4096, 4096, 256), (8192, 2048, 2048, 256), (4096, 4096, 4096, 192), (6577, 2824, 8496, 72), (1032, 4104, 1096, 40)]
+    dims = lambda: int(np.exp(rng.uniform(0, np.log(1200)))) * 8
+    rows += [(int(np.exp(rng.uniform(0, np.log(9000)))), dims(), dims(), int(rng.choice([8, 24, 40, 64, 104, 128, 136, 192, 256, 264, 384]))) for _ in range(120)]
+    for kind in ("calls16", "calls32", "calls4"):
+        for row, (beyond, beyond_vera, first) in zip(rows, probe(kind, rows)):
+            assert beyond == 0 and beyond_vera == 0, (kind, row, beyond, beyond_vera, first)
