@@ -264,6 +264,8 @@ int static_scratch(void** out) {
   return RL_OK;
 }
 
+size_t brought(const rl_opts_t* opts) { return opts && opts->workspace ? opts->workspace_bytes : 0; }
+
 int check_workspace(const Schedule& sch, const rl_opts_t* opts) {
   if (sch.workspace_bytes == 0) return RL_OK;
   if (!opts || !opts->workspace || opts->workspace_bytes < sch.workspace_bytes) {
@@ -351,15 +353,7 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
   char* ws = opts ? static_cast<char*>(opts->workspace) : nullptr;
   if (use_static) {
     // size the schedule first (no HIP call yet), then lay it out in the fixed array
-    if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
-    if (sch.workspace_bytes > kStaticScratchBytes) {  // without scratch for the rank-r products the call may fit
-      L.rank_scratch = false;
-      if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
-    }
-    if (w_int4 && sch.workspace_bytes > kStaticScratchBytes) {  // without panels of W the call may fit
-      L.int4_panels = false;
-      if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
-    }
+    if (!fit_forward(variant, L, op, nullptr, kStaticScratchBytes, &sch)) return RL_ERR_VARIANT;
     if (sch.workspace_bytes > kStaticScratchBytes) {
       std::snprintf(g_hip_error, sizeof(g_hip_error), "runlora_forward_static: this call needs %zu bytes of scratch, the fixed array holds %zu",
                     sch.workspace_bytes, kStaticScratchBytes);
@@ -371,17 +365,9 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
       if ((rc = static_scratch(&p)) != RL_OK) return rc;
       ws = static_cast<char*>(p);
     }
-    if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
+    if (!fit_forward(variant, L, op, ws, kStaticScratchBytes, &sch)) return RL_ERR_VARIANT;
   } else {
-    if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
-    if (check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough without splits of the rank-r products?
-      L.rank_scratch = false;
-      if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
-    }
-    if (w_int4 && check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough for the direct route?
-      L.int4_panels = false;
-      if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
-    }
+    if (!fit_forward(variant, L, op, ws, brought(opts), &sch)) return RL_ERR_VARIANT;
     if ((rc = check_workspace(sch, opts)) != RL_OK) return rc;
   }
 
@@ -498,15 +484,7 @@ extern "C" int runlora_backward(int variant, const rl_tensor_t* dY, const rl_sav
   if (dB) op.dB = mat(dB);
   Schedule sch;
   char* ws = opts ? static_cast<char*>(opts->workspace) : nullptr;
-  if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
-  if (check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough without splits of the rank-r products?
-    L.rank_scratch = false;
-    if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
-  }
-  if (w_int4 && check_workspace(sch, opts) == RL_ERR_WORKSPACE) {  // enough for the direct route?
-    L.int4_panels = false;
-    if (!build_backward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
-  }
+  if (!fit_backward(variant, L, op, ws, brought(opts), &sch)) return RL_ERR_VARIANT;
   if ((rc = check_workspace(sch, opts)) != RL_OK) return rc;
   hipStream_t stream = opts ? static_cast<hipStream_t>(opts->stream) : nullptr;
   return run_schedule(sch, ws, stream);

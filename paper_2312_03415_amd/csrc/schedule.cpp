@@ -13,9 +13,10 @@ struct Builder {
   size_t max_partial = 0;
   Schedule* out;
   size_t later_partial = 0;  // scratch for partials that a step still to come provides for
+  size_t rank_bytes;         // see LayerDims
   bool failed = false;  // a step this build cannot run (masking X inside the tile GEMM)
 
-  Builder(const LayerDims& l, void* ws, Schedule* o) : L(l), base(static_cast<char*>(ws)), out(o) {}
+  Builder(const LayerDims& l, void* ws, Schedule* o) : L(l), base(static_cast<char*>(ws)), out(o), rank_bytes(l.rank_bytes) {}
 
   // the LoRA scale as the kernels apply it: under dropout the kept inputs are scaled by 1 / (1 - p)
   float scale() const { return L.drop_thr ? L.scale * 256.f / (256.f - (float)L.drop_thr) : L.scale; }
@@ -26,7 +27,7 @@ struct Builder {
   // Z2} 14.5).
   size_t spare() const {
     const size_t have = later_partial > max_partial ? later_partial : max_partial;
-    return L.rank_scratch && have < kRankScratch ? kRankScratch : have;
+    return have < rank_bytes ? rank_bytes : have;
   }
   GemmPlan dense_plan(int64_t M, int64_t N, int64_t K0, int64_t K1, bool long_op = false) const {
     if (L.memo != nullptr)
@@ -530,6 +531,36 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
   }
   b.finish();
   return !b.failed;
+}
+
+bool fit_forward(int variant, const LayerDims& L, const FwdOperands& op, void* ws_base, size_t bytes, Schedule* out) {
+  if (!build_forward(variant, L, op, ws_base, out)) return false;
+  LayerDims l = L;
+  const size_t left = bytes > out->partial_offset ? (bytes - out->partial_offset) / kAlign * kAlign : 0;
+  if (out->workspace_bytes > bytes && left < l.rank_bytes) {
+    l.rank_bytes = left;
+    if (!build_forward(variant, l, op, ws_base, out)) return false;
+  }
+  if (out->workspace_bytes > bytes && l.w_int4) {
+    l.int4_panels = false;
+    if (!build_forward(variant, l, op, ws_base, out)) return false;
+  }
+  return true;
+}
+
+bool fit_backward(int variant, const LayerDims& L, const BwdOperands& op, void* ws_base, size_t bytes, Schedule* out) {
+  if (!build_backward(variant, L, op, ws_base, out)) return false;
+  LayerDims l = L;
+  const size_t left = bytes > out->partial_offset ? (bytes - out->partial_offset) / kAlign * kAlign : 0;
+  if (out->workspace_bytes > bytes && left < l.rank_bytes) {
+    l.rank_bytes = left;
+    if (!build_backward(variant, l, op, ws_base, out)) return false;
+  }
+  if (out->workspace_bytes > bytes && l.w_int4) {
+    l.int4_panels = false;
+    if (!build_backward(variant, l, op, ws_base, out)) return false;
+  }
+  return true;
 }
 
 size_t forward_workspace(int variant, LayerDims L) {

@@ -48,9 +48,9 @@ struct LayerDims {
   // an int4 W's products may dequantise panels of it into scratch; false for calls whose scratch holds only what the
   // direct route takes
   bool int4_panels = true;
-  // rank-r products with r > 32 may ask for up to kRankScratch bytes to split their contraction into; false for calls whose scratch
-  // holds only what the other launches take
-  bool rank_scratch = true;
+  // rank-r products with r > 32 may split their contraction into this many bytes of partials (or into what the other launches take);
+  // less for a call that brings less
+  size_t rank_bytes = kRankScratch;
   PlanMemo* memo = nullptr;  // shared by builds of one shape
 };
 
@@ -97,6 +97,11 @@ struct BwdOperands {
 // ws_base may be null (sizing / modelling).  Returns false for an unknown variant.
 bool build_forward(int variant, const LayerDims& L, const FwdOperands& op, void* ws_base, Schedule* out);
 bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void* ws_base, Schedule* out);
+
+// The schedule that a call takes which brings `bytes` of workspace: the one above where it fits, else with what the rank-r products
+// may ask for reduced to what there is, then without panels of an int4 W.  Where nothing fits, workspace_bytes > bytes.
+bool fit_forward(int variant, const LayerDims& L, const FwdOperands& op, void* ws_base, size_t bytes, Schedule* out);
+bool fit_backward(int variant, const LayerDims& L, const BwdOperands& op, void* ws_base, size_t bytes, Schedule* out);
 
 // Workspace of calls on dense rows (ld = columns): the most that any of them takes, with T and M kept or not, with and without LoRA
 // dropout (L.drop_thr is not looked at), whichever gradients are wanted; never_dA: none for A.  A rank-r product alone may need more than

@@ -1,6 +1,7 @@
 // Prints what the library's host code plans for the products and layers named on stdin (tests/test_plans.py); links librunlora.so,
 // runs nothing on a GPU.
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 
 #include "../include/runlora.h"
@@ -71,6 +72,25 @@ int main() {
         if (!int4 && !(bwd && dA) && factors + s.workspace_bytes > runlora_vera_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code)) ++beyond_vera;
       });
       std::printf("%d %d %d\n", beyond, beyond_vera, first);
+    } else if (std::strncmp(kind, "fit", 3) == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: forward 1 and backward 1 in full, in nothing, and in seven
+      // amounts between: how often the schedule is beyond what was brought, and how often beyond its need with nothing
+      LayerDims L{M, N, K0, K1, DT_BF16, kind[3] == '4'};
+      int beyond = 0, uses_it = 0;
+      for (int bwd = 0; bwd < 2; ++bwd) {
+        Schedule s;
+        auto fit = [&](size_t bytes) {
+          if (bwd ? !fit_backward(1, L, BwdOperands{}, nullptr, bytes, &s) : !fit_forward(1, L, FwdOperands{}, nullptr, bytes, &s)) std::exit(1);
+          return s.workspace_bytes;
+        };
+        const size_t full = fit((size_t)1 << 50), least = fit(0);
+        for (int k = 0; k <= 8; ++k) {
+          const size_t bytes = least + (full - least) * (size_t)k / 8;
+          const size_t need = fit(bytes);
+          if (full >= least && need > bytes) ++beyond;
+          if (need > least) ++uses_it;
+        }
+      }
+      std::printf("%d %d\n", beyond, uses_it);
     } else if (std::strcmp(kind, "few") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: the few-token route's price and taken or not
       SkinnyDesc d;
       d.M = M; d.N = K1; d.K = N;

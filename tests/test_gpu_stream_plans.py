@@ -129,6 +129,40 @@ def test_rank_products_with_T_kept_and_with_fewer_gradients(n, i, o, r, dtype):
                 assert torch.equal(out[k].float(), want[k]), (keep, names, k)
 
 
+@pytest.mark.parametrize("int4", [False, True])
+def test_rank_products_split_into_the_workspace_that_is_there(int4):
+    """1024 x 4096 -> 4096, r 64, in its least workspace, in 60 % of the way to what the rank-r products take, and (int4) in too little for panels of
+    W: they split as far as it goes, and integers come out the same."""
+    import torch
+    n, i, o, r, td = 1024, 4096, 4096, 64, torch.bfloat16
+    rng = np.random.default_rng(3)
+    pick = lambda shape, p: torch.from_numpy((rng.random(shape, dtype=np.float32) < p) * rng.choice(np.float32([-1.0, 1.0]), size=shape)).to(td).cuda()
+    X, A, B, dY = pick((n, i), 0.02), pick((i, r), 0.01), pick((r, o), 0.01), pick((n, o), 0.01)
+    if int4:
+        W = rl.Int4Weight(torch.randint(0, 256, (i, o // 2), dtype=torch.uint8, device="cuda"), torch.full((i // 64, o), 0.125, dtype=torch.float16, device="cuda"), i, o)
+    else:
+        W = pick((i, o), 0.01)
+    outs, splits = [], []
+    # (the whole of it is 2.75 MB: T of 128 KB, partials of up to ten slices of 256 KB; 2.88: Z1 and X A, five slices each)
+    for wf, wb in ((655360, 1310720), (1900000, 2300000), (2752512, 2883584)):
+        Y, dX, dA, dB = (torch.full(s, float("nan"), dtype=td, device="cuda") for s in ((n, o), (n, i), (i, r), (r, o)))
+        wsf, wsb = (torch.full((b,), 0xFF, dtype=torch.uint8, device="cuda") for b in (wf, wb))
+        saved = rl.new_saved()
+        print(f"case int4={int4} {wf} {wb}", flush=True)
+        rl.runlora_profile_enable(16)
+        rl.runlora_forward(1, X, W, A, B, Y, saved, workspace=wsf)
+        rl.runlora_backward(1, dY, saved, W, A, B, dX, dA, dB, workspace=wsb)
+        torch.cuda.synchronize()
+        steps = {s["what"]: s["splits"] for s in rl.runlora_profile_collect(16)}
+        rl.runlora_profile_disable()
+        splits.append((steps["T = X A"], steps["Z1 = dY B^T ; Z2 = X A"]))
+        outs.append((Y, dX, dA, dB))
+    assert splits[0][0] < splits[1][0] < splits[2][0] and splits[0][1] < splits[1][1] < splits[2][1], splits
+    for k in (1, 2):
+        for a, b in zip(outs[0], outs[k]):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_few_tokens_in_every_number_of_slices(dtype):
     """lora_finish_kernel sums two, four or eight slices at a time and takes B's rows in blocks of eight: 1 to 16 slices, ranks on both

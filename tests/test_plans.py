@@ -106,3 +106,16 @@ def test_the_workspace_query_covers_every_call(probe):
     for kind in ("calls16", "calls32", "calls4"):
         for row, (beyond, beyond_vera, first) in zip(rows, probe(kind, rows)):
             assert beyond == 0 and beyond_vera == 0, (kind, row, beyond, beyond_vera, first)
+
+
+def test_a_call_runs_in_what_it_brings(probe):
+    """Between the least workspace a layer runs in and the most it makes use of, its schedule takes no more than is there, and some of it:
+    the rank-r products split their contraction as far as it goes, also next to an int4 W whose panels do not fit."""
+    rng = np.random.default_rng(12)
+    dims = lambda: int(np.exp(rng.uniform(np.log(8), np.log(1200)))) * 8
+    rows = [(1024, 4096, 4096, 64), (1032, 4104, 1096, 40)]
+    rows += [(int(np.exp(rng.uniform(0, np.log(9000)))), dims(), dims(), int(rng.choice([8, 40, 64, 128, 192, 256, 264]))) for _ in range(300)]
+    for kind in ("fit16", "fit4"):
+        got = probe(kind, rows)
+        assert all(beyond == 0 for beyond, _ in got), [r for r, g in zip(rows, got) if g[0]]
+        assert got[0][1] >= 14, got[0]   # (forward and backward: all but the first of nine)
