@@ -394,6 +394,10 @@ bool build_forward(int variant, const LayerDims& L, const FwdOperands& op, void*
       [[fallthrough]];
     case 1: {  // forward1: (XW) + ((XA)B), the sum folded into one contraction over [X|T]
       Mat T = op.keep_T ? op.T : b.scratch(n, r);
+      // T and these partials together fit the array of runlora_forward_static, so that it takes the plans of runlora_forward
+      const size_t t_bytes = ((size_t)n * (size_t)r * dtype_size(L.dtype) + kAlign - 1) / kAlign * kAlign;
+      const size_t left = t_bytes < kRankScratch ? kRankScratch - t_bytes : 0;
+      if (b.rank_bytes > left) b.rank_bytes = left;
       if (b.few_forward("Y = X [W|A] ; Y += T B", op.X, op.W, op.A, op.B, op.Y, T, op.keep_T, op.bias)) break;
       if (r > 32) b.expect_gemm(n, o, i, r, true, op.X.ld);
       b.skinny("T = X A", {0, 0, n, r, i, op.X, op.A, T, true, true});

@@ -72,6 +72,13 @@ int main() {
         if (!int4 && !(bwd && dA) && factors + s.workspace_bytes > runlora_vera_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code)) ++beyond_vera;
       });
       std::printf("%d %d %d\n", beyond, beyond_vera, first);
+    } else if (std::strcmp(kind, "static") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: forward 1 with splits of its rank-r product and without
+      LayerDims L{M, N, K0, K1, DT_BF16};
+      Schedule s, t;
+      if (!build_forward(1, L, FwdOperands{}, nullptr, &s)) return 1;
+      L.rank_bytes = 0;
+      if (!build_forward(1, L, FwdOperands{}, nullptr, &t)) return 1;
+      std::printf("%zu %zu\n", s.workspace_bytes, t.workspace_bytes);
     } else if (std::strncmp(kind, "fit", 3) == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: forward 1 and backward 1 in full, in nothing, and in seven
       // amounts between: how often the schedule is beyond what was brought, and how often beyond its need with nothing
       LayerDims L{M, N, K0, K1, DT_BF16, kind[3] == '4'};

@@ -119,3 +119,14 @@ def test_a_call_runs_in_what_it_brings(probe):
         got = probe(kind, rows)
         assert all(beyond == 0 for beyond, _ in got), [r for r, g in zip(rows, got) if g[0]]
         assert got[0][1] >= 14, got[0]   # (forward and backward: all but the first of nine)
+
+
+def test_splits_of_T_fit_the_static_scratch(probe):
+    """runlora_forward_static runs what runlora_forward runs: where its array holds T, it holds the partials that T is split into as well."""
+    from paper_2312_03415_amd import binding as rl
+    rng = np.random.default_rng(13)
+    dims = lambda: int(np.exp(rng.uniform(0, np.log(1500)))) * 8
+    rows = [(18292, 5640, 2520, 104), (21656, 9080, 8, 80), (24317, 3760, 3392, 80)]
+    rows += [(int(np.exp(rng.uniform(0, np.log(40000)))), dims(), dims(), 8 * int(rng.integers(5, 64))) for _ in range(2000)]
+    for row, (whole, least) in zip(rows, probe("static", rows)):
+        assert whole <= rl.STATIC_SCRATCH_BYTES or least > rl.STATIC_SCRATCH_BYTES, (row, whole, least)

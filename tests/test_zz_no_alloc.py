@@ -58,3 +58,20 @@ def test_static_scratch_refuses_what_does_not_fit():
     assert e.value.code == rl.RL_ERR_WORKSPACE
     torch.cuda.synchronize()
     assert not Y.any()   # nothing was enqueued
+
+
+def test_static_scratch_forward_splits_as_workspace_forward():
+    """24317 x 3760 -> 3392, r 80: T = X A runs in slices whose partials fill what T leaves of 16 MB.  Bit for bit the same result means the same
+    slices."""
+    import torch
+    n, i, o, r = 24317, 3760, 3392, 80
+    g = torch.Generator(device="cuda").manual_seed(2)
+    mk = lambda *s: torch.randn(*s, device="cuda", generator=g).to(torch.bfloat16)
+    dev = {"X": mk(n, i), "W": mk(i, o) * 0.02, "A": mk(i, r) * 0.02, "B": mk(r, o)}
+    assert rl.runlora_workspace_bytes(1, -1, n, i, o, r, rl.RL_BF16) <= rl.STATIC_SCRATCH_BYTES
+    rl.runlora_profile_enable(8)
+    Y0, Y1 = forward_both(synth.Layer("static_split", n, i, o, r, "bf16", 24), 1, dev)
+    steps = [(s["what"], s["tile_cfg"], s["splits"]) for s in rl.runlora_profile_collect(8)]
+    rl.runlora_profile_disable()
+    assert len(steps) == 4 and steps[:2] == steps[2:], steps
+    assert torch.equal(Y0, Y1)
