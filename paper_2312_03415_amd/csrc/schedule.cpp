@@ -140,7 +140,7 @@ struct Builder {
     d.ldc = dX.ld;
     d.mask_seg0 = true;
     d.drop_thr = L.drop_thr; d.drop_key = L.drop_key; d.drop_cpr = drop_cpr();
-    if (L.w_int4) return false;
+    if (L.w_int4 || !L.masked_product) return false;
     s.plan = dense_plan(L.n, L.i, L.o, L.r, long_operand(d));
     if (!masked_segment_ok(d, s.plan)) return false;
     if (s.plan.partial_bytes > max_partial) max_partial = s.plan.partial_bytes;
@@ -562,6 +562,10 @@ bool fit_backward(int variant, const LayerDims& L, const BwdOperands& op, void* 
   }
   if (out->workspace_bytes > bytes && l.w_int4) {
     l.int4_panels = false;
+    if (!build_backward(variant, l, op, ws_base, out)) return false;
+  }
+  if (out->workspace_bytes > bytes && l.drop_thr) {
+    l.masked_product = false;
     if (!build_backward(variant, l, op, ws_base, out)) return false;
   }
   return true;

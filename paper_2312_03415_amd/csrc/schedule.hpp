@@ -51,6 +51,9 @@ struct LayerDims {
   // rank-r products with r > 32 may split their contraction into this many bytes of partials (or into what the other launches take);
   // less for a call that brings less
   size_t rank_bytes = kRankScratch;
+  // dX under LoRA dropout in one launch where that is built; false for calls whose scratch holds only what two launches take (492 x 104
+  // -> 9568, r 48, bf16: 6.44 and 6.23 MB)
+  bool masked_product = true;
   PlanMemo* memo = nullptr;  // shared by builds of one shape
 };
 
@@ -99,7 +102,7 @@ bool build_forward(int variant, const LayerDims& L, const FwdOperands& op, void*
 bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void* ws_base, Schedule* out);
 
 // The schedule that a call takes which brings `bytes` of workspace: the one above where it fits, else with what the rank-r products
-// may ask for reduced to what there is, then without panels of an int4 W.  Where nothing fits, workspace_bytes > bytes.
+// may ask for reduced to what there is, then without panels of an int4 W, or with dX under dropout in two launches.  Where nothing fits, workspace_bytes > bytes.
 bool fit_forward(int variant, const LayerDims& L, const FwdOperands& op, void* ws_base, size_t bytes, Schedule* out);
 bool fit_backward(int variant, const LayerDims& L, const BwdOperands& op, void* ws_base, size_t bytes, Schedule* out);
 

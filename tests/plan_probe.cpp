@@ -72,6 +72,17 @@ int main() {
         if (!int4 && !(bwd && dA) && factors + s.workspace_bytes > runlora_vera_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code)) ++beyond_vera;
       });
       std::printf("%d %d %d\n", beyond, beyond_vera, first);
+    } else if (std::strcmp(kind, "masked") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: backward 1 with dropout, dX = dY W^T and its masked update
+      // as launches of their own: what they take, and what the call takes that brings so much
+      LayerDims L{M, N, K0, K1, DT_BF16};
+      L.drop_thr = 26;
+      Schedule one, two, got;
+      if (!build_backward(1, L, BwdOperands{}, nullptr, &one)) return 1;
+      L.masked_product = false;
+      if (!build_backward(1, L, BwdOperands{}, nullptr, &two)) return 1;
+      L.masked_product = true;
+      if (!fit_backward(1, L, BwdOperands{}, nullptr, two.workspace_bytes, &got)) return 1;
+      std::printf("%zu %zu %zu %zu\n", one.workspace_bytes, two.workspace_bytes, got.workspace_bytes, got.steps.size());
     } else if (std::strcmp(kind, "static") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: forward 1 with splits of its rank-r product and without
       LayerDims L{M, N, K0, K1, DT_BF16};
       Schedule s, t;

@@ -1,5 +1,7 @@
 """GPU: dX = dY W^T + m o (Z1 A^T) of a layer with LoRA dropout, in one launch where the product's plan is built for it, in two
 otherwise, on every kernel that serves it, against the oracle."""
+import re
+
 import numpy as np
 import pytest
 
@@ -49,3 +51,33 @@ def test_masked_update_of_dX(n, i, o, r, fused, dtype):
     edge = buf.float()
     edge[1:n + 1, 8:i + 8] = 7.0
     assert bool((edge == 7.0).all())   # nothing beyond dX is written
+
+
+@pytest.mark.parametrize("n,i,o,r", [(492, 104, 9568, 48), (706, 1384, 1112, 128)])
+def test_masked_update_in_the_workspace_of_two_launches(n, i, o, r):
+    """A call that brings what dX = dY W^T and its masked update take, less than their one launch does, runs those."""
+    import torch
+    L = synth.Layer("masktwo", n, i, o, r, "bf16", 62)
+    dev, host = layer_on_device(L)
+    p, seed, scale = 0.4, 99, 0.5
+    print(f"case {n} {i}->{o} r={r}", flush=True)
+    Y, dX = (torch.full(s, float("nan"), dtype=torch.bfloat16, device="cuda") for s in ((n, o), (n, i)))
+    full = rl.runlora_workspace_bytes(1, 1, n, i, o, r, rl.RL_BF16)
+    saved = rl.new_saved()
+    rl.runlora_forward(1, dev["X"], dev["W"], dev["A"], dev["B"], Y, saved, workspace=torch.empty(full, dtype=torch.uint8, device="cuda"),
+                       scale=scale, dropout_p=p, dropout_seed=seed)
+    back = lambda ws: rl.runlora_backward(1, dev["dY"], saved, dev["W"], dev["A"], dev["B"], dX, None, None, workspace=ws)
+    with pytest.raises(rl.RunLoRAError) as e:
+        back(torch.empty(256, dtype=torch.uint8, device="cuda"))
+    assert e.value.code == rl.RL_ERR_WORKSPACE
+    least = int(re.search(r"(\d+) bytes", str(e.value)).group(1))
+    rl.runlora_profile_enable(16)
+    back(torch.full((least,), 0xFF, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    steps = [s["what"] for s in rl.runlora_profile_collect(16)]
+    rl.runlora_profile_disable()
+    assert steps[-2:] == ["dX = dY W^T", "dX += Z1 A^T"], steps
+    mask, pq = oracle.dropout_mask(n, i, p, seed)
+    Z1 = scale / (1.0 - pq) * oracle.matmul(host["dY"], host["B"], tb=True)
+    want = oracle.matmul(host["dY"], host["W"], tb=True) + mask * oracle.matmul(Z1, host["A"], tb=True)
+    assert relerr(to_f64(dX), want) < TOL["bf16"] and elem_excess(to_f64(dX), want, "bf16", roundings=2) < 1.0

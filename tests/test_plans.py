@@ -130,3 +130,16 @@ def test_splits_of_T_fit_the_static_scratch(probe):
     rows += [(int(np.exp(rng.uniform(0, np.log(40000)))), dims(), dims(), 8 * int(rng.integers(5, 64))) for _ in range(2000)]
     for row, (whole, least) in zip(rows, probe("static", rows)):
         assert whole <= rl.STATIC_SCRATCH_BYTES or least > rl.STATIC_SCRATCH_BYTES, (row, whole, least)
+
+
+def test_masked_product_falls_back_where_the_workspace_is_that_of_two_launches(probe):
+    """dX under LoRA dropout in one launch may split into more partials than dX = dY W^T and the masked update behind it: a call that brings
+    what those take still runs."""
+    rng = np.random.default_rng(14)
+    dims = lambda: int(np.exp(rng.uniform(np.log(4), np.log(1200)))) * 8
+    rows = [(492, 104, 9568, 48), (706, 1384, 1112, 128), (99, 168, 7856, 32)]
+    rows += [(int(np.exp(rng.uniform(np.log(33), np.log(9000)))), dims(), dims(), int(rng.choice([8, 24, 48, 72, 128]))) for _ in range(600)]
+    got = probe("masked", rows)
+    for row, (one, two, need, steps) in zip(rows, got):
+        assert need <= two, (row, one, two, need)
+    assert all(one > two and steps == 4 for one, two, _, steps in got[:3]), got[:3]   # ({Z1, Z2}, {dA, dB}, dX, its update)
