@@ -345,6 +345,13 @@ size_t runlora_workspace_bytes(int fwd, int bwd, int64_t n, int64_t i, int64_t o
 /* Same with W's dtype explicit: w_dtype = dtype (dense) or RL_INT4_G64. */
 size_t runlora_workspace_bytes_w(int fwd, int bwd, int64_t n, int64_t i, int64_t o, int64_t r,
                                  int dtype, int w_dtype);
+/* Same for one call whose choices are known (dense W; dense rows), never more than the above: a bit set of
+ *   RL_CALL_T        forward1 keeps T / the backward reads a kept T (rl_saved_t.T)
+ *   RL_CALL_M        forward2 keeps M / the backward reads a kept M (rl_saved_t.M)
+ *   RL_CALL_DROPOUT  LoRA dropout
+ *   RL_CALL_NO_DX, RL_CALL_NO_DA, RL_CALL_NO_DB   gradients that the backward is not asked for */
+enum { RL_CALL_T = 1, RL_CALL_M = 2, RL_CALL_DROPOUT = 4, RL_CALL_NO_DX = 8, RL_CALL_NO_DA = 16, RL_CALL_NO_DB = 32 };
+size_t runlora_call_workspace_bytes(int fwd, int bwd, int64_t n, int64_t i, int64_t o, int64_t r, int dtype, int choices);
 
 /*
  * The building block every step above is made of, exposed for tests, tuning and calibration of

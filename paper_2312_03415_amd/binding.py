@@ -30,7 +30,7 @@ RL_ERR_ALIGN, RL_ERR_ALIAS, RL_ERR_WORKSPACE, RL_ERR_UNSUPPORTED, RL_ERR_HIP = -
 
 EXPORTS = (
     "runlora_forward", "runlora_forward_static", "runlora_backward", "runlora_select", "runlora_select_by", "runlora_flops",
-    "runlora_model_time_us", "runlora_workspace_bytes", "runlora_workspace_bytes_w", "runlora_saved_bytes",
+    "runlora_model_time_us", "runlora_workspace_bytes", "runlora_workspace_bytes_w", "runlora_call_workspace_bytes", "runlora_saved_bytes",
     "runlora_strerror", "runlora_last_hip_error",
     "runlora_version", "runlora_gemm", "runlora_gemm_workspace_bytes",
     "runlora_profile_enable", "runlora_profile_collect", "runlora_profile_disable", "runlora_profile_kernel_times",
@@ -134,6 +134,8 @@ def lib():
     L.runlora_workspace_bytes.restype = ctypes.c_size_t
     L.runlora_workspace_bytes_w.argtypes = [ci, ci, i64, i64, i64, i64, ci, ci]
     L.runlora_workspace_bytes_w.restype = ctypes.c_size_t
+    L.runlora_call_workspace_bytes.argtypes = [ci, ci, i64, i64, i64, i64, ci, ci]
+    L.runlora_call_workspace_bytes.restype = ctypes.c_size_t
     L.runlora_saved_bytes.argtypes = [ci, i64, i64, i64, i64, ci, ci]
     L.runlora_saved_bytes.restype = ctypes.c_size_t
     L.runlora_strerror.argtypes = [ci]
@@ -388,6 +390,12 @@ def runlora_workspace_bytes(fwd, bwd, n, i, o, r, dtype, w_dtype=None):
     if w_dtype is None:
         return int(lib().runlora_workspace_bytes(fwd, bwd, n, i, o, r, dtype))
     return int(lib().runlora_workspace_bytes_w(fwd, bwd, n, i, o, r, dtype, w_dtype))
+
+
+def runlora_call_workspace_bytes(fwd, bwd, n, i, o, r, dtype, keep_t=False, keep_merged=False, dropout=False, dx=True, da=True, db=True):
+    """runlora_workspace_bytes for one call whose choices are known."""
+    choices = (keep_t and 1) | (keep_merged and 2) | (dropout and 4) | (0 if dx else 8) | (0 if da else 16) | (0 if db else 32)
+    return int(lib().runlora_call_workspace_bytes(fwd, bwd, n, i, o, r, dtype, choices))
 
 
 def runlora_saved_bytes(fwd, n, i, o, r, dtype, keep_merged=False, keep_t=False):

@@ -850,6 +850,31 @@ extern "C" size_t runlora_workspace_bytes_w(int fwd, int bwd, int64_t n, int64_t
   return need;
 }
 
+extern "C" size_t runlora_call_workspace_bytes(int fwd, int bwd, int64_t n, int64_t i, int64_t o, int64_t r, int dtype, int choices) {
+  const int dt = internal_dtype(dtype);
+  if (dt < 0 || n < 1 || i < 1 || o < 1 || r < 1) return 0;
+  LayerDims L{n, i, o, r, dt};
+  L.drop_thr = (choices & RL_CALL_DROPOUT) ? 1 : 0;
+  size_t need = 0;
+  Schedule sch;
+  if (fwd >= 0) {
+    FwdOperands op = dense_forward(L);
+    op.keep_T = (choices & RL_CALL_T) != 0 && (fwd == RL_FWD1 || fwd == RL_FWD3);
+    op.keep_M = (choices & RL_CALL_M) != 0 && fwd == RL_FWD2;
+    if (build_forward(fwd, L, op, nullptr, &sch)) need = sch.workspace_bytes;
+  }
+  if (bwd >= 0) {
+    BwdOperands op = dense_backward(L);
+    op.have_T = (choices & RL_CALL_T) != 0 && (bwd == RL_BWD1 || bwd == RL_BWD5 || bwd == RL_BWD6 || bwd == RL_BWD7);
+    op.have_M = (choices & RL_CALL_M) != 0 && (bwd == RL_BWD4 || bwd == RL_BWD5 || bwd == RL_BWD7 || bwd == RL_BWD8);
+    op.want_dX = (choices & RL_CALL_NO_DX) == 0;
+    op.want_dA = (choices & RL_CALL_NO_DA) == 0;
+    op.want_dB = (choices & RL_CALL_NO_DB) == 0;
+    if (build_backward(bwd, L, op, nullptr, &sch) && sch.workspace_bytes > need) need = sch.workspace_bytes;
+  }
+  return need;
+}
+
 extern "C" const char* runlora_strerror(int code) {
   switch (code) {
     case RL_OK: return "ok";

@@ -33,7 +33,7 @@ namespace {
 // entry points of librunlora (already loaded by binding.py, which hands over the addresses) and binding._check
 decltype(&runlora_forward) p_forward = nullptr;
 decltype(&runlora_backward) p_backward = nullptr;
-decltype(&runlora_workspace_bytes) p_workspace_bytes = nullptr;
+decltype(&runlora_call_workspace_bytes) p_workspace_bytes = nullptr;
 PyObject* g_check = nullptr;
 
 void check(int rc) {
@@ -98,7 +98,8 @@ struct LoRANode : public torch::autograd::Function<LoRANode> {
       saved.M = M.data_ptr();
       saved.ldm = o;
     }
-    const at::Tensor ws = scratch(p_workspace_bytes((int)fwd, -1, n, i, o, r, code), x);
+    const int choices = (T.defined() ? RL_CALL_T : 0) | (M.defined() ? RL_CALL_M : 0) | ((float)dropout_p != 0.f ? RL_CALL_DROPOUT : 0);
+    const at::Tensor ws = scratch(p_workspace_bytes((int)fwd, -1, n, i, o, r, code, choices), x);
     rl_opts_t opts{};
     opts.stream = c10::hip::getCurrentHIPStream(x.device().index()).stream();
     opts.workspace = ws.data_ptr();
@@ -155,7 +156,9 @@ struct LoRANode : public torch::autograd::Function<LoRANode> {
     if (ctx->needs_input_grad(0)) { dx = at::empty({n, i}, x2.options()); tx = desc(dx, code); }
     if (ctx->needs_input_grad(2)) { dA = at::empty_like(A); ta = desc(dA, da.dtype); }
     if (ctx->needs_input_grad(3)) { dB = at::empty_like(B); tb = desc(dB, db.dtype); }
-    const at::Tensor ws = scratch(p_workspace_bytes(-1, bwd, n, i, o, r, code), x2);
+    const int choices = (T.defined() ? RL_CALL_T : 0) | (M.defined() ? RL_CALL_M : 0) | (saved.dropout_thr != 0 ? RL_CALL_DROPOUT : 0) |
+                        (dx.defined() ? 0 : RL_CALL_NO_DX) | (dA.defined() ? 0 : RL_CALL_NO_DA) | (dB.defined() ? 0 : RL_CALL_NO_DB);
+    const at::Tensor ws = scratch(p_workspace_bytes(-1, bwd, n, i, o, r, code, choices), x2);
     rl_opts_t opts{};
     opts.stream = c10::hip::getCurrentHIPStream(x2.device().index()).stream();
     opts.workspace = ws.data_ptr();
@@ -226,7 +229,7 @@ PyObject* py_lora(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   END_HANDLE_TH_ERRORS
 }
 
-// init(forward, backward, workspace_bytes addresses, check)
+// init(forward, backward, call_workspace_bytes addresses, check)
 PyObject* py_init(PyObject*, PyObject* args) {
   unsigned long long a, b, c;
   PyObject* chk;

@@ -571,11 +571,23 @@ bool fit_backward(int variant, const LayerDims& L, const BwdOperands& op, void* 
   return true;
 }
 
+FwdOperands dense_forward(const LayerDims& L) {
+  FwdOperands op;
+  op.X.ld = L.i; op.W.ld = L.o; op.A.ld = L.r; op.B.ld = L.o; op.Y.ld = L.o; op.T.ld = L.r; op.M.ld = L.o;
+  return op;
+}
+
+BwdOperands dense_backward(const LayerDims& L) {
+  BwdOperands op;
+  op.dY.ld = L.o; op.X.ld = L.i; op.W.ld = L.o; op.A.ld = L.r; op.B.ld = L.o; op.T.ld = L.r; op.dX.ld = L.i; op.dA.ld = L.r; op.dB.ld = L.o;
+  op.M.ld = L.o;
+  return op;
+}
+
 size_t forward_workspace(int variant, LayerDims L) {
   PlanMemo memo;
   L.memo = &memo;
-  FwdOperands op;  // (T or M kept: the same launches and less scratch)
-  op.X.ld = L.i; op.W.ld = L.o; op.A.ld = L.r; op.B.ld = L.o; op.Y.ld = L.o; op.T.ld = L.r; op.M.ld = L.o;
+  const FwdOperands op = dense_forward(L);  // (T or M kept: the same launches and less scratch)
   size_t need = 0;
   Schedule sch;
   for (const uint32_t thr : {0u, 1u}) {
@@ -589,9 +601,7 @@ size_t forward_workspace(int variant, LayerDims L) {
 size_t backward_workspace(int variant, LayerDims L, bool never_dA) {
   PlanMemo memo;
   L.memo = &memo;
-  BwdOperands op;
-  op.dY.ld = L.o; op.X.ld = L.i; op.W.ld = L.o; op.A.ld = L.r; op.B.ld = L.o; op.T.ld = L.r; op.dX.ld = L.i; op.dA.ld = L.r; op.dB.ld = L.o;
-  op.M.ld = L.o;
+  BwdOperands op = dense_backward(L);
   // Gradients (dX 4, dA 2, dB 1) such that both products of every pair are planned together and each alone: Z1 and dA alone, Z1 as
   // with T kept (6), dB alone (5), X A alone (1).  A call that wants less, or has T or M kept, plans each of its launches as one of
   // these does and holds no more.

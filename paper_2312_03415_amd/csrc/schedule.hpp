@@ -106,6 +106,10 @@ bool build_backward(int variant, const LayerDims& L, const BwdOperands& op, void
 bool fit_forward(int variant, const LayerDims& L, const FwdOperands& op, void* ws_base, size_t bytes, Schedule* out);
 bool fit_backward(int variant, const LayerDims& L, const BwdOperands& op, void* ws_base, size_t bytes, Schedule* out);
 
+// operands with dense rows (ld = columns) and no pointers
+FwdOperands dense_forward(const LayerDims& L);
+BwdOperands dense_backward(const LayerDims& L);
+
 // Workspace of calls on dense rows (ld = columns): the most that any of them takes, with T and M kept or not, with and without LoRA
 // dropout (L.drop_thr is not looked at), whichever gradients are wanted; never_dA: none for A.  A rank-r product alone may need more than
 // the launch that serves it and another (backward 1 of 4096 x 4096 -> 4096, r 256, bf16: 20 MB with all gradients, 34 with T kept).

@@ -41,7 +41,7 @@ def _native():
             raise ImportError(f"_autograd.so was not built for {build._ext_abi()}: run `python -m paper_2312_03415_amd.build`")
         from . import _autograd
         address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
-        _autograd.init(address(lib.runlora_forward), address(lib.runlora_backward), address(lib.runlora_workspace_bytes), rl._check)
+        _autograd.init(address(lib.runlora_forward), address(lib.runlora_backward), address(lib.runlora_call_workspace_bytes), rl._check)
         _native_module = _autograd
     return _native_module
 
@@ -97,8 +97,8 @@ class RunLoRAFunction(torch.autograd.Function):
         if keep_merged and fwd == rl.FWD2 and bwd in rl.BWD_MERGED:
             M = torch.empty((i, o), dtype=x.dtype, device=x.device)
         saved = rl.new_saved(T, M)
-        ws = _workspace(x.device, rl.runlora_workspace_bytes(fwd, bwd, n, i, o, r, code))
         p, seed = dropout if dropout else (None, 0)
+        ws = _workspace(x.device, rl.runlora_call_workspace_bytes(fwd, -1, n, i, o, r, code, keep_t=T is not None, keep_merged=M is not None, dropout=bool(p)))
         rl.runlora_forward(fwd, x2, W, A, B, y, saved, workspace=ws, scale=scale, bias=bias, dropout_p=p, dropout_seed=seed)
         ctx.saved = saved
         ctx.bwd = bwd
@@ -122,7 +122,8 @@ class RunLoRAFunction(torch.autograd.Function):
         dA = torch.empty_like(A) if need_a else None
         dB = torch.empty_like(B) if need_b else None
         code = rl.dtype_code(dy.dtype)
-        ws = _workspace(dy.device, rl.runlora_workspace_bytes(-1, ctx.bwd, n, i, o, r, code))
+        ws = _workspace(dy.device, rl.runlora_call_workspace_bytes(-1, ctx.bwd, n, i, o, r, code, keep_t=ctx.keep[0] is not None, keep_merged=ctx.keep[1] is not None,
+                                                                   dropout=saved.dropout_thr != 0, dx=need_x, da=need_a, db=need_b))
         rl.runlora_backward(ctx.bwd, dy2, saved, W, A, B, dx, dA, dB, workspace=ws)
         if dx is not None:
             dx = dx.view(ctx.x_shape)
@@ -204,7 +205,7 @@ class RunVeRAFunction(torch.autograd.Function):
         y = torch.empty((n, o), dtype=x.dtype, device=x.device)
         T = torch.empty((n, r), dtype=x.dtype, device=x.device) if fwd == rl.FWD_DEFAULT else None
         saved = rl.new_saved(T)
-        ws = _workspace(x.device, rl.runlora_vera_workspace_bytes(fwd, bwd, n, i, o, r, code))
+        ws = _workspace(x.device, rl.runlora_vera_workspace_bytes(fwd, -1, n, i, o, r, code))
         rl.runlora_vera_forward(fwd, x2, W, A, B, d, b, y, saved, ws, scale=scale, bias=bias)
         ctx.saved = saved
         ctx.bwd = bwd
@@ -289,7 +290,7 @@ class RunDoRAFunction(torch.autograd.Function):
         y = torch.empty((n, o), dtype=x.dtype, device=x.device)
         c = torch.empty((o,), dtype=torch.float32, device=x.device)
         saved = rl.new_saved(None)
-        ws = _workspace(x.device, rl.runlora_dora_workspace_bytes(rl.FWD2, bwd, n, i, o, r, code))
+        ws = _workspace(x.device, rl.runlora_dora_workspace_bytes(rl.FWD2, -1, n, i, o, r, code))
         rl.runlora_dora_forward(rl.FWD2, x2, W, A, B, m, y, saved, c, ws, scale=scale, bias=bias)
         ctx.saved = saved
         ctx.bwd = bwd

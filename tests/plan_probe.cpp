@@ -10,7 +10,7 @@
 using namespace rl;
 
 // every forward (T or M kept or not) and backward (T and M kept or not, each choice of gradients) of a layer, with and without dropout: f(is
-// a backward, variant, dA wanted, the schedule it runs)
+// a backward, variant, dA wanted, the schedule it runs, the call's choices)
 template <typename F>
 static void each_call(LayerDims L, F f) {
   Schedule s;
@@ -25,7 +25,7 @@ static void each_call(LayerDims L, F f) {
         if (v == 3 && thr != 0) continue;  // (runs as variant 1, and needs what that needs)
         a.keep_T = v == 1 && keep != 0;
         a.keep_M = v == 2 && keep != 0;
-        if (build_forward(v, L, a, nullptr, &s)) f(false, v, true, s);
+        if (build_forward(v, L, a, nullptr, &s)) f(false, v, true, s, (a.keep_T ? RL_CALL_T : 0) | (a.keep_M ? RL_CALL_M : 0) | (thr ? RL_CALL_DROPOUT : 0));
       }
     for (int v = 0; v <= 8; ++v)
       for (int keep = 0; keep < 4; ++keep)
@@ -33,7 +33,9 @@ static void each_call(LayerDims L, F f) {
           b.have_T = (keep & 1) != 0 && (v == 1 || v == 5 || v == 6 || v == 7);
           b.have_M = (keep & 2) != 0 && (v == 4 || v == 5 || v == 7 || v == 8);
           b.want_dX = (want & 4) != 0; b.want_dA = (want & 2) != 0; b.want_dB = (want & 1) != 0;
-          if (build_backward(v, L, b, nullptr, &s)) f(true, v, b.want_dA, s);
+          const int choices = (b.have_T ? RL_CALL_T : 0) | (b.have_M ? RL_CALL_M : 0) | (thr ? RL_CALL_DROPOUT : 0) | (b.want_dX ? 0 : RL_CALL_NO_DX) |
+                              (b.want_dA ? 0 : RL_CALL_NO_DA) | (b.want_dB ? 0 : RL_CALL_NO_DB);
+          if (build_backward(v, L, b, nullptr, &s)) f(true, v, b.want_dA, s, choices);
         }
   }
 }
@@ -65,13 +67,14 @@ int main() {
       const int dt = kind[5] == '3' ? DT_F32 : DT_BF16, code = kind[5] == '3' ? RL_F32 : RL_BF16;
       const bool int4 = kind[5] == '4';
       const size_t factors = 2 * (((size_t)K1 * (size_t)K0 * dtype_size(dt) + 255) / 256 * 256);
-      int beyond = 0, beyond_vera = 0, first = -1;
-      each_call(LayerDims{M, N, K0, K1, dt, int4}, [&](bool bwd, int v, bool dA, const Schedule& s) {
+      int beyond = 0, beyond_vera = 0, first = -1, inexact = 0;
+      each_call(LayerDims{M, N, K0, K1, dt, int4}, [&](bool bwd, int v, bool dA, const Schedule& s, int choices) {
         const size_t have = runlora_workspace_bytes_w(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code, int4 ? RL_INT4_G64 : code);
         if (s.workspace_bytes > have && beyond++ == 0) first = v;
         if (!int4 && !(bwd && dA) && factors + s.workspace_bytes > runlora_vera_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code)) ++beyond_vera;
+        if (!int4 && s.workspace_bytes != runlora_call_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code, choices)) ++inexact;
       });
-      std::printf("%d %d %d\n", beyond, beyond_vera, first);
+      std::printf("%d %d %d %d\n", beyond, beyond_vera, inexact, first);
     } else if (std::strcmp(kind, "masked") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: backward 1 with dropout, dX = dY W^T and its masked update
       // as launches of their own: what they take, and what the call takes that brings so much
       LayerDims L{M, N, K0, K1, DT_BF16};

@@ -288,3 +288,22 @@ def test_dora_module_matches_oracle_and_starts_as_the_frozen_layer():
     assert relerr(to_f64(x.grad.reshape(-1, d_in)), dXw) < TOL["bf16"]
     assert relerr(to_f64(layer.lora_A.grad), dAw) < TOL["bf16"] and relerr(to_f64(layer.lora_B.grad), dBw) < TOL["bf16"]
     assert relerr(to_f64(layer.dora_m.grad), dmw) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_forward_3_with_T_kept_gets_the_workspace_of_forward_1(native):
+    """With T kept, forward 3 runs as forward 1, whose product is split here and needs scratch that forward 3 does not."""
+    import torch
+    from paper_2312_03415_amd.module import RunLoRAFunction
+    layer, host = make_layer(2056, 2120, 16, "bf16", 32, False, (3, 1), keep_t=True)
+    x = torch.randn(520, 2056, generator=torch.Generator().manual_seed(4)).to(torch.bfloat16).cuda().requires_grad_()
+    assert rl.runlora_call_workspace_bytes(1, -1, 520, 2056, 2120, 16, rl.RL_BF16, keep_t=True) > 256
+    if native:
+        y = layer(x)
+    else:
+        y = super(RunLoRAFunction, RunLoRAFunction).apply(x, layer.weight, layer.lora_A, layer.lora_B, layer.bias, layer.scale, (3, 1), False, None, True)
+    y.sum().backward()
+    torch.cuda.synchronize()
+    want = oracle.reference_forward(to_f64(x), to_f64(layer.weight), to_f64(layer.lora_A) * layer.scale, to_f64(layer.lora_B))
+    assert relerr(to_f64(y), want) < TOL["bf16"]
+    assert all(bool(t.grad.isfinite().all()) for t in (x, layer.lora_A, layer.lora_B))

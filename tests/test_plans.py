@@ -104,8 +104,9 @@ def test_the_workspace_query_covers_every_call(probe):
     dims = lambda: int(np.exp(rng.uniform(0, np.log(1200)))) * 8
     rows += [(int(np.exp(rng.uniform(0, np.log(9000)))), dims(), dims(), int(rng.choice([8, 24, 40, 64, 104, 128, 136, 192, 256, 264, 384]))) for _ in range(120)]
     for kind in ("calls16", "calls32", "calls4"):
-        for row, (beyond, beyond_vera, first) in zip(rows, probe(kind, rows)):
+        for row, (beyond, beyond_vera, inexact, first) in zip(rows, probe(kind, rows)):
             assert beyond == 0 and beyond_vera == 0, (kind, row, beyond, beyond_vera, first)
+            assert inexact == 0, (kind, row, inexact)   # (runlora_call_workspace_bytes: the schedule of that call)
 
 
 def test_a_call_runs_in_what_it_brings(probe):
