@@ -48,7 +48,11 @@ struct MergeTile {
   static constexpr int PASSES = 32 / RPP;
 };
 
-template <typename T, int KSTEPS, int CB>
+// BOTH: sums and M in one pass (V of a DoRA layer).  A build of its own: as one more choice of the other build it cost that one's passes
+// 3 us at 4096 x 4096, r 64 (forward 2 of 1024 tokens 72.1 -> 75.5 us, a DoRA layer in f16 102.3 -> 105.3), and a loop for each choice 4 us
+// more at r 32 and 128.  It tests for both at run time all the same: the branches keep a row pass's LDS reads and stores from being
+// gathered over all passes (with none, DoRA's forward took 130.4 us for 124.4 at 4096 x 2048 -> 8192, r 16).
+template <typename T, int KSTEPS, int CB, bool BOTH = false>
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
   using MT = MergeTile<KSTEPS, CB>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -172,7 +176,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
           sq[e] += v0 * v0;
           sq[4 + e] += v1 * v1;
         }
-        if (Mp == nullptr) continue;
+        if (!BOTH || Mp == nullptr) continue;
       }
       T o8[8];
 #pragma unroll
