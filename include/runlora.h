@@ -268,7 +268,9 @@ size_t runlora_vera_workspace_bytes(int fwd, int bwd, int64_t n, int64_t i, int6
  * RL_ERR_UNSUPPORTED), and there the kernel that forms W + s A B scales W's columns on the way.  16-bit dtypes,
  * r <= 128, no LoRA dropout (otherwise RL_ERR_UNSUPPORTED).  *saved and rl_opts_t mean what they mean for
  * runlora_forward / runlora_backward (scale, bias, stream; rl_saved_t.M keeps (W + s A B) diag(g), valid while
- * W, A, B and m are what the forward saw); a forward of one family may not be followed by a backward of another.
+ * W, A, B and m are what the forward saw; Y is then rounded from it, where a call that keeps nothing may multiply by
+ * the rounded W + s A B and scale the product's columns); a forward of one family may not be followed by a backward
+ * of another.
  *   m        device pointer, o elements of the activation dtype, 16-byte aligned; no element may be 0 if dm
  *            is asked for (dm divides by it; DoRA initialises m to the column norms of W)
  *   c        device pointer, o floats (fp32 whatever the dtype), 16-byte aligned: written by the forward (the

@@ -699,9 +699,13 @@ extern "C" int runlora_dora_forward(int variant, const rl_tensor_t* X, const rl_
   nd.I = i; nd.O = o; nd.R = r;
   nd.alpha = opts->scale != 0.f ? opts->scale : 1.f;
   nd.sq_partial = v.partial;
-  // V and its column sums in one pass, Y = X V with its columns scaled.  V lies where the layer call's schedule has M = V diag(g);
-  // an M that the caller keeps is formed there afterwards, as the backward would form it.
+  // V and its column sums in one pass, Y = X V with its columns scaled.  V lies where the layer call's schedule has M = V diag(g).  An
+  // M that the caller keeps has to be formed besides, as the backward would form it, which makes V one matrix more to write: sums
+  // alone, M and Y = X M take 139 us where V, Y and M take 147 (4096 x 2048 -> 8192, r 16), 103 and 117 (1024 x 4096 -> 4096, r 64), 24.6
+  // and 28.6 (1024 x 1024 -> 1024), 28.3 and 29.5 (300 x 128 -> 512, r 64).  For a small W and a low rank V is for nothing (512 x 256 ->
+  // 256, r 16: 23.8 and 21.7), and Y is bit for bit that of a call which keeps nothing.
   const bool keep = saved->M != nullptr;
+  const bool wants_v = !keep || (i * o <= (1 << 16) && r <= 16);
   Step form, product;
   form.what = "V = W + A B";
   form.is_merge = true;
@@ -718,7 +722,7 @@ extern "C" int runlora_dora_forward(int variant, const rl_tensor_t* X, const rl_
   d.bias = opts->bias;
   d.cscale = v.g;
   product.plan = gemm_plan(dt, X->rows, o, i, 0, -1, 0, false, long_operand(d));
-  if (column_scale_ok(d, product.plan)) {
+  if (wants_v && column_scale_ok(d, product.plan)) {
     Schedule first, then;
     first.steps.push_back(form);
     then.steps.push_back(product);

@@ -238,3 +238,31 @@ def test_dora_f16_weight_sum_beyond_the_type():
     want = np.repeat(X.double().numpy().sum(axis=1, keepdims=True) * (30.0 / np.sqrt(i)), o, axis=1)  # c = 70000 sqrt(i) in every column
     assert relerr(to_f64(cd), np.full((o,), 70000.0 * np.sqrt(i))) < 1e-5
     assert relerr(to_f64(Y), want) < TOL["f16"]
+
+
+@pytest.mark.parametrize("n,i,o,r,v", [(4104, 520, 2568, 16, False), (512, 256, 264, 16, False), (512, 256, 256, 24, False), (512, 256, 256, 16, True), (70, 136, 264, 8, True)])
+def test_dora_forward_that_keeps_its_merged_weight(n, i, o, r, v):
+    """A kept (W + s A B) diag(g) is what the product multiplies by; only where W is small and r low is V formed besides."""
+    import torch
+    L = synth.Layer("dorakeep", n, i, o, r, "bf16", 56)
+    dev, host = layer_on_device(L)
+    vec = vectors(L)
+    print(f"case {n} {i}->{o} r={r}", flush=True)
+    Y, M = (torch.full(s, float("nan"), dtype=torch.bfloat16, device="cuda") for s in ((n, o), (i, o)))
+    cd = torch.empty((o,), dtype=torch.float32, device="cuda")
+    ws = torch.full((rl.runlora_dora_workspace_bytes(2, -1, n, i, o, r, rl.RL_BF16),), 0xFF, dtype=torch.uint8, device="cuda")
+    rl.runlora_profile_enable(8)
+    rl.runlora_dora_forward(2, dev["X"], dev["W"], dev["A"], dev["B"], vec["m"][0], Y, rl.new_saved(None, M), cd, ws, scale=0.5, bias=vec["bias"][0])
+    torch.cuda.synchronize()
+    steps = [s["what"] for s in rl.runlora_profile_collect(8)]
+    rl.runlora_profile_disable()
+    assert steps == (["V = W + A B", "Y = X V diag(g)", "M = V diag(g)"] if v else ["M = W + A B", "Y = X M"])
+    V = host["W"] + 0.5 * host["A"] @ host["B"]
+    want = V * (vec["m"][1] / np.sqrt((V * V).sum(axis=0)))[None, :]
+    assert relerr(to_f64(M), want) < TOL["bf16"]
+    assert relerr(to_f64(Y), host["X"] @ want + vec["bias"][1][None, :]) < TOL["bf16"]
+    if not v:
+        Y2 = torch.empty_like(Y)
+        rl.runlora_gemm(dev["X"], M, Y2, bias=vec["bias"][0])
+        torch.cuda.synchronize()
+        assert torch.equal(Y, Y2)
