@@ -203,9 +203,11 @@ __device__ __forceinline__ void gemm_mc64_body(const GemmArgs& g) {
     rsB = seg ? rsB1 : rsB0;
     kA = (uint32_t)ts * stepA;
     kB = (uint32_t)ts * stepB;
+    int ln = lane;
+    if constexpr (SEGMASK) asm volatile("" : "+v"(ln));  // (what follows from the lane alone is not worth a register across the K loop)
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
-      const int p = (wave * IPW + j) * 64 + lane;   // 16-byte slot of the operand tile this lane fills
+      const int p = (wave * IPW + j) * 64 + ln;   // 16-byte slot of the operand tile this lane fills
       {
         const int row = P::A_STR ? (p >> 5) : (p >> 3);
         const int col = P::A_STR ? (((p & 31) ^ (4 * (row & 3))) << 3) : (((p & 7) ^ ((row >> 1) & 7)) << 3);

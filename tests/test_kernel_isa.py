@@ -5,7 +5,8 @@ silently break, with results staying correct: (1) no full wait for outstanding l
 vmcnt(0)`) inside a K step, which would serialise the LDS ring; (2) no per-lane loop around a load (the
 compiler wraps a load whose scalar offset it cannot prove uniform in a `s_cbranch_execnz` loop);
 (3) no register spills.  Both the dense and the int4 route are checked, in the NN and NT layouts; the K-tile-64 kernel and
-the middle-sized one, every build, by the same properties.
+the middle-sized one, every build (also those with a masked segment or a column scale), by the same properties.  No kernel of the
+file, whatever it is, spills vector registers.
 """
 import os
 import re
@@ -32,6 +33,13 @@ def kernel_text(asm, al, bl, ns, bq, plain=0):
     name = f"_ZN2rl14gemm_mc_kernelIDF16bLi{al}ELi{bl}ELi{ns}ELb{bq}ELi{plain}EEEvNS_8GemmArgsE"
     start = asm.index("\n" + name + ":")
     return name, asm[start:asm.index("s_endpgm", start)]
+
+
+def test_no_kernel_spills_vector_registers(asm):
+    names = re.findall(r"\.name:           (\S+)", asm)
+    spills = re.findall(r"\.vgpr_spill_count:\s+(\d+)", asm)
+    assert len(names) == len(spills) > 100
+    assert not [n for n, s in zip(names, spills) if s != "0"]
 
 
 def blocks(text):
@@ -68,12 +76,18 @@ def test_k_loop_of_the_matrix_core_kernel(asm, al, bl, ns, bq, plain):
             assert not any(i.startswith(("buffer_load", "global_load")) for i in b), "a load sits in a per-lane (waterfall) loop"
 
 
-@pytest.mark.parametrize("al,bl,plain", [(0, 0, 1), (0, 1, 1), (1, 0, 1), (0, 0, 0), (0, 1, 0), (0, 1, 2), (0, 0, 2)])
+@pytest.mark.parametrize("al,bl,plain", [(0, 0, 1), (0, 1, 1), (1, 0, 1), (0, 0, 0), (0, 1, 0), (0, 1, 2), (0, 0, 2),
+                                         (0, 1, "segmask"), (0, 0, "colscale 1"), (0, 0, "colscale 3")])
 def test_k_loop_of_the_matrix_core_kernel_with_k_tile_64(asm, al, bl, plain):
     """gemm_mc64_kernel: a K tile is two straight-line K steps of 64 MFMAs (16x16x32) with tied accumulators and nothing
     between them but the fragment reads, the 16 refill loads and, in the second, one wait + barrier; no spills, no
     accumulator traffic between the two register files, no load in a per-lane loop."""
-    name = f"_ZN2rl16gemm_mc64_kernelIDF16bLi{al}ELi{bl}ELi{plain}EEEvNS_8GemmArgsE"
+    if plain == "segmask":
+        name = "_ZN2rl24gemm_mc64_segmask_kernelIDF16bEEvNS_8GemmArgsE"
+    elif str(plain).startswith("colscale"):
+        name = f"_ZN2rl25gemm_mc64_colscale_kernelIDF16bLi{plain[-1]}EEEvNS_8GemmArgsE"
+    else:
+        name = f"_ZN2rl16gemm_mc64_kernelIDF16bLi{al}ELi{bl}ELi{plain}EEEvNS_8GemmArgsE"
     start = asm.index("\n" + name + ":")
     text = asm[start:asm.index("s_endpgm", start)]
     meta = asm[asm.index(".name:           " + name):]
@@ -107,7 +121,8 @@ def test_k_loop_of_the_matrix_core_kernel_with_k_tile_64(asm, al, bl, plain):
 MT_BUILDS = [(al, bl, bm, bn, ns, 0) for al, bl in ((0, 0), (0, 1), (1, 0)) for bm, bn, ns in ((128, 128, 2), (128, 128, 4), (256, 128, 3), (128, 64, 3), (64, 128, 3))]
 
 
-@pytest.mark.parametrize("al,bl,bm,bn,ns,xa", MT_BUILDS + [(0, 0, 64, 128, 3, 1), ("pair", 1, 0, 0, 0, 0), ("pair", 0, 0, 0, 0, 0)])
+@pytest.mark.parametrize("al,bl,bm,bn,ns,xa", MT_BUILDS + [(0, 0, 64, 128, 3, 1), ("pair", 1, 0, 0, 0, 0), ("pair", 0, 0, 0, 0, 0), ("wide", 1, 0, 0, 0, 0), ("wide", 0, 0, 0, 0, 0)]
+                         + [(al, bl, bm, bn, ns, opt) for al, bl, bm, bn, ns, _ in MT_BUILDS for opt in ("segmask", "colscale") if (al, bl) == ((0, 1) if opt == "segmask" else (0, 0))])
 def test_k_loop_of_the_middle_sized_kernel(asm, al, bl, bm, bn, ns, xa):
     """gemm_mt_kernel: a K tile's two K steps are one straight-line block (its hand-issued LDS reads are in flight across the whole
     of it: a branch would let the compiler copy what has not arrived) with all its products, one wait for loads that leaves
@@ -116,6 +131,12 @@ def test_k_loop_of_the_middle_sized_kernel(asm, al, bl, bm, bn, ns, xa):
         name = "_ZN2rl19gemm_mt_pair_kernelIDF16bLi0ELi1ELi0ELi128ELi64ELi128ELi64EEEvNS_8GemmArgsES1_" if bl else \
             "_ZN2rl19gemm_mt_pair_kernelIDF16bLi1ELi0ELi0ELi128ELi64ELi64ELi128EEEvNS_8GemmArgsES1_"
         bodies, bm, bn, ns = 2, 128, 64, 3
+    elif al == "wide":   # (the same on 128x128 tiles)
+        name = f"_ZN2rl19gemm_mt_pair_kernelIDF16bLi{1 - bl}ELi{bl}ELi0ELi128ELi128ELi128ELi128EEEvNS_8GemmArgsES1_"
+        bodies, bm, bn, ns = 2, 128, 128, 3
+    elif xa in ("segmask", "colscale"):
+        name = f"_ZN2rl{15 + len(xa)}gemm_mt_{xa}_kernelIDF16bLi{al}ELi{bl}ELi{bm}ELi{bn}ELi{ns}EEEvNS_8GemmArgsE"
+        bodies = 1
     else:
         name = f"_ZN2rl14gemm_mt_kernelIDF16bLi{al}ELi{bl}ELi{bm}ELi{bn}ELi{ns}ELb{xa}EEEvNS_8GemmArgsE"
         bodies = 1
