@@ -123,7 +123,11 @@ __global__ __launch_bounds__(kThreads) void dora_dm_finish_kernel(const float* _
   if (R > 0 && j < O) {
     const float gj = g[j];
 #pragma unroll 4
-    for (int k = q; k < R; k += 4) out[(int64_t)k * ldo + j] = (T)((float)in[(int64_t)k * ldi + j] * gj);
+    for (int k = q; k < R; k += 4) {
+      float v = (float)in[(int64_t)k * ldi + j] * gj;
+      asm("" : "+v"(v));  // rounded to fp32 and then to T, as by dora_colscale_kernel (f16: not by one instruction from the operands)
+      out[(int64_t)k * ldo + j] = (T)v;
+    }
   }
   __syncthreads();
   if (q == 0 && j < O) dm[j] = (T)((((part[0][jj] + part[1][jj]) + part[2][jj]) + part[3][jj]) / (float)m[j]);

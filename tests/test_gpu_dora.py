@@ -266,3 +266,13 @@ def test_dora_forward_that_keeps_its_merged_weight(n, i, o, r, v):
         rl.runlora_gemm(dev["X"], M, Y2, bias=vec["bias"][0])
         torch.cuda.synchronize()
         assert torch.equal(Y, Y2)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_dora_dB_does_not_depend_on_whether_dm_is_wanted(dtype):
+    """dB = dB~ diag(g) is formed by the launch that finishes dm, or by one of its own: half a million elements, the same bits."""
+    L = synth.Layer("doradb", 72, 64, 4096, 128, dtype, 57)
+    dev, _ = layer_on_device(L)
+    vec = vectors(L)
+    both, alone = (run_dora(L, dev, vec, 5, 0.7, None, want=w) for w in (("dB", "dm"), ("dB",)))
+    assert np.array_equal(both["dB"], alone["dB"])
