@@ -353,7 +353,11 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
   char* ws = opts ? static_cast<char*>(opts->workspace) : nullptr;
   if (use_static) {
     // size the schedule first (no HIP call yet), then lay it out in the fixed array
-    if (!fit_forward(variant, L, op, nullptr, kStaticScratchBytes, &sch)) return RL_ERR_VARIANT;
+    if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
+    if (w_int4 && sch.workspace_bytes > kStaticScratchBytes) {  // without panels of W the call may fit
+      L.int4_panels = false;
+      if (!build_forward(variant, L, op, nullptr, &sch)) return RL_ERR_VARIANT;
+    }
     if (sch.workspace_bytes > kStaticScratchBytes) {
       std::snprintf(g_hip_error, sizeof(g_hip_error), "runlora_forward_static: this call needs %zu bytes of scratch, the fixed array holds %zu",
                     sch.workspace_bytes, kStaticScratchBytes);
@@ -365,7 +369,7 @@ int forward_impl(int variant, const rl_tensor_t* X, const rl_tensor_t* W, const 
       if ((rc = static_scratch(&p)) != RL_OK) return rc;
       ws = static_cast<char*>(p);
     }
-    if (!fit_forward(variant, L, op, ws, kStaticScratchBytes, &sch)) return RL_ERR_VARIANT;
+    if (!build_forward(variant, L, op, ws, &sch)) return RL_ERR_VARIANT;
   } else {
     if (!fit_forward(variant, L, op, ws, brought(opts), &sch)) return RL_ERR_VARIANT;
     if ((rc = check_workspace(sch, opts)) != RL_OK) return rc;

@@ -183,7 +183,7 @@ struct SkinnyPlan {
   size_t partial_bytes = 0;
 };
 inline bool skinny_ok(int64_t N) { return N <= 128; }
-SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d);
+SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap = ~(size_t)0);  // cap: partials may take so much
 // modelled time of that launch (and its reduce pass) in us
 double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan);
 

@@ -632,7 +632,7 @@ hipError_t few_run(int dtype, const FewDesc& d, const FewPlan& plan, float* scra
 
 // ---- streaming kernel for the rank-r products -----------------------------------------------------
 
-SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d) {
+SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap) {
   SkinnyPlan p;
   const int bk = dtype == DT_F32 ? 32 : 64;
   int64_t min_ktiles = 1 << 30, outs = 0, maxn = 0;
@@ -669,22 +669,28 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d) {
     const bool alone = nprob == 1 || (blocks <= 256 && 2 * m.K >= (d[0].drop_thr != 0 ? d[1] : d[0]).K);
     if (alone && (m.K + bk - 1) / bk >= 24) p.nwv = 16;
   }
-  // Split K over workgroups only when there are fewer workgroups than compute units, and keep >= 8 K tiles per wave and slice
-  // (12 where 32 or more blocks of up to 32 columns of a 16-bit product share the work: T of 2048 x 4096 12.2 us in two slices
-  // with their reduce pass, 12.0 whole, 5000 x 5464 23.5 and 18.3, 4096 x 8192 18.2 and 20.4; {Z1, T} of 950 x (3000 + 3000)
-  // in fp32 17.3 and 22.7).
+  // Split K over workgroups only when there are fewer workgroups than compute units, and keep >= 8 K tiles per wave and slice; with
+  // 16 waves that many per four of them (T of 5 x 3744, fp32, masked: 20.9 us in three slices, 30.8 whole; 2048 x 8192, bf16, 18.3 in
+  // four and 21.8 in two), but twice as many for a pair that fills a quarter of the chip whole ({Z1, T} of 2048 x (4096 + 4096) 15.1
+  // in two slices, 14.2 whole).
   // (64-row workgroups: 128-160 of them without a split beat twice as many plus the reduce pass, and so do 32-row ones of a
   // pair that 64-row blocks do not fill.)
+  // In the [M,K] orientation a launch of 16-bit or 16-wave blocks of up to 32 columns takes no more slices than leave every workgroup a
+  // compute unit: T r 16 of 5000 x 5464 19.2 us whole, 22.7 in two, 3232 x 8192 16.1 in two, 21.6 in three, 2560 x 8192 15.5 in three, 18.2
+  // in four (in fp32 and with wider blocks a few beyond are no worse: {Z1, T} of 950 x (3000 + 3000), fp32, 17.3 in five, 22.7 whole).
+  // 32 and more of them on 4 waves stay whole up to 64 K tiles: T of 2048 x 4096 12.7 us, 13.2 in two slices, {Z1, T} 12.0 and 13.1;
+  // with more the reduce pass pays: Z1 of 1776 x 4536 19.3 us, 16.4 in two, T of 1240 x 5464 19.6 and 16.1, 2048 x 8192 18.4 in two, 16.9 in four.
   int64_t splits = 1;
   const bool half = nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2 && !masked;
   if (blocks < (half ? 128 : 224)) {
-    splits = (256 + blocks - 1) / blocks;
-    const int64_t per_wave = p.nwv == 16 ? 4 : (!d[0].a_strided && dtype != DT_F32 && p.rt == 1 && blocks >= 32 ? 12 : 8);
-    int64_t cap = min_ktiles / (p.nwv * per_wave);
-    if (cap < 1) cap = 1;
-    if (splits > cap) splits = cap;
+    const bool one_each = !d[0].a_strided && p.rt == 1 && (dtype != DT_F32 || p.nwv == 16);
+    splits = one_each ? 256 / blocks : (256 + blocks - 1) / blocks;
+    int64_t slice_max = min_ktiles / (p.nwv == 16 && nprob == 2 && blocks >= 64 ? 64 : 32);
+    if (slice_max < 1 || (one_each && p.nwv == 4 && blocks >= 32 && min_ktiles <= 64)) slice_max = 1;
+    if (splits > slice_max) splits = slice_max;
     if (splits > 16) splits = 16;
   }
+  while (splits > 1 && (size_t)splits * (size_t)outs * sizeof(float) > cap) --splits;
   p.splits = (int)splits;
   p.partial_bytes = splits > 1 ? (size_t)splits * (size_t)outs * sizeof(float) : 0;
   return p;

@@ -238,7 +238,7 @@ struct Builder {
     s.nsk = 1;
     s.d.dtype = L.dtype;
     s.sk[0] = to_skinny(g);
-    s.skplan = skinny_plan(L.dtype, 1, s.sk);
+    s.skplan = skinny_plan(L.dtype, 1, s.sk, L.stream_bytes);
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
     GemmPlan mp;
     if (rank_plan(L.dtype, s.sk[0], spare(), &mp)) {  // r > 32
@@ -258,7 +258,7 @@ struct Builder {
     // gemm_mt.hpp addresses its operands with 31-bit byte offsets
     if (L.n * X.ld >= (1LL << 30) || L.i * W.ld >= (1LL << 30) || L.i * A.ld >= (1LL << 30)) return false;
     const SkinnyDesc sd = to_skinny({0, 0, L.n, L.r, L.i, X, A, T, true});
-    const SkinnyPlan skp = skinny_plan(L.dtype, 1, &sd);
+    const SkinnyPlan skp = skinny_plan(L.dtype, 1, &sd, L.stream_bytes);
     const GemmPlan gp = dense_plan(L.n, L.o, L.i, L.r);
     const size_t bytes = skp.partial_bytes > gp.partial_bytes ? skp.partial_bytes : gp.partial_bytes;
     const FewPlan plan = rl::few_plan(L.n, L.i, L.o, L.r, bytes);
@@ -337,7 +337,7 @@ struct Builder {
     s.d.dtype = L.dtype;
     s.sk[0] = d1;
     s.sk[1] = d2;
-    s.skplan = skinny_plan(L.dtype, 2, s.sk);
+    s.skplan = skinny_plan(L.dtype, 2, s.sk, L.stream_bytes);
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
     s.is_mtpair = mt_pair_plan(L.dtype, s.sk, spare(), &s.mtpair);  // r > 32
     if (s.is_mtpair && s.mtpair.partial_bytes > max_partial) max_partial = s.mtpair.partial_bytes;
@@ -541,8 +541,9 @@ bool fit_forward(int variant, const LayerDims& L, const FwdOperands& op, void* w
   if (!build_forward(variant, L, op, ws_base, out)) return false;
   LayerDims l = L;
   const size_t left = bytes > out->partial_offset ? (bytes - out->partial_offset) / kAlign * kAlign : 0;
-  if (out->workspace_bytes > bytes && left < l.rank_bytes) {
-    l.rank_bytes = left;
+  if (out->workspace_bytes > bytes) {
+    l.stream_bytes = left;
+    if (left < l.rank_bytes) l.rank_bytes = left;
     if (!build_forward(variant, l, op, ws_base, out)) return false;
   }
   if (out->workspace_bytes > bytes && l.w_int4) {
@@ -556,8 +557,9 @@ bool fit_backward(int variant, const LayerDims& L, const BwdOperands& op, void* 
   if (!build_backward(variant, L, op, ws_base, out)) return false;
   LayerDims l = L;
   const size_t left = bytes > out->partial_offset ? (bytes - out->partial_offset) / kAlign * kAlign : 0;
-  if (out->workspace_bytes > bytes && left < l.rank_bytes) {
-    l.rank_bytes = left;
+  if (out->workspace_bytes > bytes) {
+    l.stream_bytes = left;
+    if (left < l.rank_bytes) l.rank_bytes = left;
     if (!build_backward(variant, l, op, ws_base, out)) return false;
   }
   if (out->workspace_bytes > bytes && l.w_int4) {

@@ -51,6 +51,7 @@ struct LayerDims {
   // rank-r products with r > 32 may split their contraction into this many bytes of partials (or into what the other launches take);
   // less for a call that brings less
   size_t rank_bytes = kRankScratch;
+  size_t stream_bytes = ~(size_t)0;  // likewise the products on the streaming kernel, which split by shape alone
   // dX under LoRA dropout in one launch where that is built; false for calls whose scratch holds only what two launches take (492 x 104
   // -> 9568, r 48, bf16: 6.44 and 6.23 MB)
   bool masked_product = true;

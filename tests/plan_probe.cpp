@@ -75,6 +75,12 @@ int main() {
         if (!int4 && s.workspace_bytes != runlora_call_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code, choices)) ++inexact;
       });
       std::printf("%d %d %d %d\n", beyond, beyond_vera, inexact, first);
+    } else if (std::strncmp(kind, "stream", 6) == 0) {  // M, N = r, K of T = X A, K1 = masked or not: slices, wavefronts, rows of a block
+      SkinnyDesc d;
+      d.M = M; d.N = N; d.K = K0;
+      d.drop_thr = K1 != 0 ? 26 : 0;
+      const SkinnyPlan p = skinny_plan(kind[6] == '3' ? DT_F32 : DT_BF16, 1, &d);
+      std::printf("%d %d %d\n", p.splits, p.nwv, p.mr);
     } else if (std::strcmp(kind, "masked") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: backward 1 with dropout, dX = dY W^T and its masked update
       // as launches of their own: what they take, and what the call takes that brings so much
       LayerDims L{M, N, K0, K1, DT_BF16};

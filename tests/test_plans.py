@@ -119,7 +119,7 @@ def test_a_call_runs_in_what_it_brings(probe):
     for kind in ("fit16", "fit4"):
         got = probe(kind, rows)
         assert all(beyond == 0 for beyond, _ in got), [r for r, g in zip(rows, got) if g[0]]
-        assert got[0][1] >= 14, got[0]   # (forward and backward: all but the first of nine)
+        assert got[0][1] >= 12, got[0]   # (of nine amounts each way: T takes ten slices, Z1 and X A five each, and fewer than two are none)
 
 
 def test_splits_of_T_fit_the_static_scratch(probe):
@@ -144,3 +144,19 @@ def test_masked_product_falls_back_where_the_workspace_is_that_of_two_launches(p
     for row, (one, two, need, steps) in zip(rows, got):
         assert need <= two, (row, one, two, need)
     assert all(one > two and steps == 4 for one, two, _, steps in got[:3]), got[:3]   # ({Z1, Z2}, {dA, dB}, dX, its update)
+
+
+def test_slices_of_streaming_launches(probe):
+    """T = X A, r <= 32: no more workgroups than compute units where it is split (16 bits), a masked product in no fewer slices than the same
+    product without a mask, unless that one's slices leave compute units with two workgroups."""
+    rows = [(n, r, k) for n in (1, 5, 18, 64, 200, 700, 1240, 2048, 3232, 4096, 5000, 7000) for r in (8, 32) for k in (1536, 2048, 3744, 4096, 5464, 8192, 11008)]
+    for kind in ("stream16", "stream32"):
+        plain, masked = (probe(kind, [(*row, m) for row in rows]) for m in (0, 1))
+        for (n, r, k), (s0, _, _), (s1, waves, _) in zip(rows, plain, masked):
+            blocks = -(-n // 32)
+            assert waves == 16 and (s1 == 1 or s1 * blocks <= 256), (n, r, k, s1)
+            if kind == "stream16":
+                assert s0 == 1 or s0 * blocks <= 256, (n, r, k, s0)
+            assert s1 >= s0 or s0 * blocks > 256, (kind, n, r, k, s0, s1)
+    assert [p[0] for p in probe("stream32", [(5, 16, 3744, 1)])] == [3]   # 20.9 us, 30.8 whole
+    assert [p[0] for p in probe("stream16", [(5000, 16, 5464, 0), (3232, 16, 5840, 0), (2048, 16, 4096, 0)])] == [1, 2, 1]
