@@ -81,6 +81,11 @@ int main() {
       d.drop_thr = K1 != 0 ? 26 : 0;
       const SkinnyPlan p = skinny_plan(kind[6] == '3' ? DT_F32 : DT_BF16, 1, &d);
       std::printf("%d %d %d\n", p.splits, p.nwv, p.mr);
+    } else if (std::strcmp(kind, "f32") == 0) {  // M, N, K: tile and slices by tile counts, and as the library runs the product
+      GemmPlan p = gemm_plan(DT_F32, M, N, K0, K1);
+      std::printf("%d %d ", p.cfg, p.splits);
+      gemm_plan_f32(&p, M, N, K0, K1);
+      std::printf("%d %d\n", p.cfg, p.splits);
     } else if (std::strcmp(kind, "masked") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: backward 1 with dropout, dX = dY W^T and its masked update
       // as launches of their own: what they take, and what the call takes that brings so much
       LayerDims L{M, N, K0, K1, DT_BF16};

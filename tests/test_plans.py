@@ -160,3 +160,10 @@ def test_slices_of_streaming_launches(probe):
             assert s1 >= s0 or s0 * blocks > 256, (kind, n, r, k, s0, s1)
     assert [p[0] for p in probe("stream32", [(5, 16, 3744, 1)])] == [3]   # 20.9 us, 30.8 whole
     assert [p[0] for p in probe("stream16", [(5000, 16, 5464, 0), (3232, 16, 5840, 0), (2048, 16, 4096, 0)])] == [1, 2, 1]
+
+
+def test_fp32_products_leave_the_plan_by_tile_counts_for_a_clear_gain(probe):
+    """Modelled within 5 % of each other, 204 x 4008 x 4060 and 212 x 3284 x 1944 run 10-11 % faster on 128x128 tiles."""
+    kept = probe("f32", [(204, 4008, 4060, 0), (212, 3284, 1944, 0)])
+    assert all(p[:2] == p[2:] for p in kept), kept
+    assert all(p[:2] != p[2:] for p in probe("f32", [(256, 768, 768, 8), (300, 2000, 4000, 0)]))
