@@ -251,8 +251,7 @@ struct Builder {
   }
   // forward1 for a few tokens in two launches; false where it does not apply or is modelled slower than forward1's launches
   // (few rows or a low rank: 48 x 4096 -> 11008, r 32 takes 24 us so and 33 by T = X A and [X|T] [W;B]; at 256 rows, r 128 it
-  // would be 87 and 55).  The scratch is what forward1's launches would take, so that a call's workspace does not depend on
-  // the route.
+  // would be 87 and 55).  The scratch is what forward1's launches take, but for what they split T with r > 32 into (spare()).
   bool few_forward(const char* what, Mat X, Mat W, Mat A, Mat B, Mat Y, Mat T, bool keep_T, const void* bias) {
     if (L.dtype == DT_F32 || L.w_int4 || L.drop_thr || L.n > kFewMaxRows || L.r > kFewMaxR) return false;
     // gemm_mt.hpp addresses its operands with 31-bit byte offsets
@@ -265,7 +264,9 @@ struct Builder {
     if (plan.splits == 0) return false;
     GemmPlan rank;
     double t_us = 0;
-    if (!rank_plan(L.dtype, sd, bytes, &rank, &t_us)) t_us = skinny_time_us(L.dtype, 1, &sd, skp);
+    // (T of the other route may split into more than these bytes)
+    const size_t t_cap = bytes > rank_bytes ? bytes : rank_bytes;
+    if (!rank_plan(L.dtype, sd, t_cap, &rank, &t_us)) t_us = skinny_time_us(L.dtype, 1, &sd, skp);
     const double cold_us = kColdUsPerMB * 2e-6 * (double)(L.n * L.i + L.i * L.o);
     if (plan.us >= t_us + plan_time_us(gp, L.n, L.o, L.i, L.r) + cold_us) return false;
     if (bytes > max_partial) max_partial = bytes;

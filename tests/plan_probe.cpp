@@ -132,7 +132,7 @@ int main() {
       const FewPlan f = few_plan(M, N, K0, K1, bytes);
       GemmPlan rank;
       double t_us = 0;
-      if (!rank_plan(DT_BF16, d, bytes, &rank, &t_us)) t_us = skinny_time_us(DT_BF16, 1, &d, t);
+      if (!rank_plan(DT_BF16, d, K1 > 32 && bytes < kRankScratch ? kRankScratch - ((size_t)M * (size_t)K1 * 2 + 255) / 256 * 256 : bytes, &rank, &t_us)) t_us = skinny_time_us(DT_BF16, 1, &d, t);
       Schedule sch;
       const bool ok = build_forward(1, LayerDims{M, N, K0, K1, DT_BF16}, FwdOperands{}, nullptr, &sch);
       std::printf("%d %d %.3f %.3f %zu\n", ok && sch.steps[0].is_few ? 1 : 0, f.splits, f.us,

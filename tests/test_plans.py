@@ -167,3 +167,10 @@ def test_fp32_products_leave_the_plan_by_tile_counts_for_a_clear_gain(probe):
     kept = probe("f32", [(204, 4008, 4060, 0), (212, 3284, 1944, 0)])
     assert all(p[:2] == p[2:] for p in kept), kept
     assert all(p[:2] != p[2:] for p in probe("f32", [(256, 768, 768, 8), (300, 2000, 4000, 0)]))
+
+
+def test_few_token_route_is_weighed_against_a_split_T(probe):
+    """T = X A may split into more than the bytes that the few-token route takes: [X|T] [W;B] behind it is then the faster one (67 x 2472 -> 72,
+    r 96: 23.7 us by the few-token route, 18.0; 46 x 1328 -> 72, r 128 27.0 and 15.2)."""
+    rows = [(67, 2472, 72, 96), (34, 1200, 80, 128), (132, 1272, 64, 128), (77, 1192, 64, 128), (46, 1328, 72, 128)]
+    assert [p[0] for p in probe("few", rows)] == [0] * 5
