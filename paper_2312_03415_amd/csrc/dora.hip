@@ -105,8 +105,8 @@ __global__ __launch_bounds__(kThreads) void dora_dm_partial_kernel(const T* __re
 }
 
 // dm[j] = the column's slices / m[j]: 64 columns per workgroup, slices q, q + 4, ... per group of 64 threads, groups in order.
-// With R > 0 also out = in diag(g) for the R rows of dB~, the groups sharing them (as a launch of its own 4.8 us next to this one's
-// 4.2, both of them latency).
+// With R > 0 also out = in diag(g): the workgroups beyond the first of a column group (blockIdx.y) scale 16 rows of dB~ each (as a launch
+// of its own 4.8 us next to this one's 4.2, both of them latency; by the first workgroup, behind its sums, 7 us more at r 128).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void dora_dm_finish_kernel(const float* __restrict__ partial, int rows,
                                                                   const T* __restrict__ m, T* __restrict__ dm, int O, const T* in,
@@ -114,21 +114,26 @@ __global__ __launch_bounds__(kThreads) void dora_dm_finish_kernel(const float* _
   __shared__ float part[4][64];
   const int jj = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int j = blockIdx.x * 64 + jj;
+  if (blockIdx.y > 0) {
+    if (j >= O) return;
+    const int k0 = ((int)blockIdx.y - 1) * 16 + q;
+    const float gj = g[j];
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = k0 + 4 * u < R ? (float)in[(int64_t)(k0 + 4 * u) * ldi + j] * gj : 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      asm("" : "+v"(v[u]));  // rounded to fp32 and then to T, as by dora_colscale_kernel (f16: not by one instruction from the operands)
+      if (k0 + 4 * u < R) out[(int64_t)(k0 + 4 * u) * ldo + j] = (T)v[u];
+    }
+    return;
+  }
   float sum = 0.f;
   if (j < O) {
 #pragma unroll 8
     for (int y = q; y < rows; y += 4) sum += partial[(int64_t)y * O + j];
   }
   part[q][jj] = sum;
-  if (R > 0 && j < O) {
-    const float gj = g[j];
-#pragma unroll 4
-    for (int k = q; k < R; k += 4) {
-      float v = (float)in[(int64_t)k * ldi + j] * gj;
-      asm("" : "+v"(v));  // rounded to fp32 and then to T, as by dora_colscale_kernel (f16: not by one instruction from the operands)
-      out[(int64_t)k * ldo + j] = (T)v;
-    }
-  }
   __syncthreads();
   if (q == 0 && j < O) dm[j] = (T)((((part[0][jj] + part[1][jj]) + part[2][jj]) + part[3][jj]) / (float)m[j]);
 }
@@ -152,7 +157,8 @@ hipError_t dm_t(const void* dY, int64_t lddy, const void* Y, int64_t ldy, const 
                      (int)n, (int)o, rows);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(dora_dm_finish_kernel<T>, dim3((unsigned)((o + 63) / 64)), dim3(kThreads), 0, s, partial,
+  const unsigned scalers = b.out != nullptr ? (unsigned)((b.R + 15) / 16) : 0u;
+  hipLaunchKernelGGL(dora_dm_finish_kernel<T>, dim3((unsigned)((o + 63) / 64), 1 + scalers), dim3(kThreads), 0, s, partial,
                      slices, static_cast<const T*>(m), static_cast<T*>(dm), (int)o, static_cast<const T*>(b.in), b.ldi, b.g,
                      static_cast<T*>(b.out), b.ldo, b.out != nullptr ? (int)b.R : 0);
   return hipGetLastError();
