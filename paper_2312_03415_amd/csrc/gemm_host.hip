@@ -190,17 +190,18 @@ static double f32_time_us(int cfg, int64_t tiles, int splits, int64_t ktiles, do
 // 32x128 in five slices, 4096 x 512 x 512 39.8 against 33 unsplit on 128x64, 1000 x 1024 x 1024 38 against 34.6, 300 x 2000 x 4000
 // 102 against 67, 500 x 2048 x 2048 57 against 55.5.  Larger products keep the plan by tile counts: several workgroups of narrow
 // tiles on every unit feed each other less than the model says (2000 x 768 x 3072 123 against 133, 3000 x 1800 x 1800 264 against
-// 278, 950 x 3000 x 3000 235 against 243).  A plan on 128x128 tiles in 2 .. 16 slices has to be modelled more than 5 % slower: of 283 products (68 ..
-// 6000 rows and columns, K 64 .. 6000) four are then slower than on the plan that comes in, by 2-8 %, where all take 0.76 of its time on
-// average; without the 5 %, two more by 10-11 % (204 x 4008 x 4060 83.3 against 94.1, 212 x 3284 x 1944 45.3 against 50.2).  Other
-// plans are never kept: whole ones and those in many slices are modelled too fast (296 x 7496 x 32 3 us slower, 52 x 344 x 5992 6).
+// 278, 950 x 3000 x 3000 235 against 243).  A plan on 128x128 tiles in 2 .. 16 slices has to be modelled more than 3 % slower: of 409 products (68 ..
+// 6000 rows and columns, K 64 .. 6000) six are then slower than on the plan that comes in, by 4-8 %, where all take 0.8 of its time on
+// average; without the 3 %, two more by 10 % (204 x 4008 x 4060 83.3 against 94.1, 212 x 3284 x 1944 45.3 against 50.2); with 5 %, none
+// fewer and five gains of 4-16 % are lost.  Other plans are never kept: whole ones and those in many slices are modelled too fast (296 x
+// 7496 x 32 3 us slower, 52 x 344 x 5992 6).
 void gemm_plan_f32(GemmPlan* p, int64_t M, int64_t N, int64_t K0, int64_t K1) {
   if (M <= 32 || N <= 32 || (double)M * (double)N * (double)(K0 + K1) > 4e9) return;
   const int64_t kt = (K0 + p->bk - 1) / p->bk + (K1 + p->bk - 1) / p->bk;
   const size_t cap = p->partial_bytes;  // the scratch stays what is reported
   const double outs = (double)M * (double)N;
   double best = 1e30;
-  if (p->cfg == CFG_MID && p->splits > 1 && p->splits <= 16) best = f32_time_us(p->cfg, (int64_t)p->nbm * p->nbn, p->splits, p->tiles_per_split, outs) / 1.05;
+  if (p->cfg == CFG_MID && p->splits > 1 && p->splits <= 16) best = f32_time_us(p->cfg, (int64_t)p->nbm * p->nbn, p->splits, p->tiles_per_split, outs) / 1.03;
   for (int cfg = CFG_BIG; cfg <= CFG_WIDE64; ++cfg) {
     const int64_t nbm = (M + kTileBM[cfg] - 1) / kTileBM[cfg], nbn = (N + kTileBN[cfg] - 1) / kTileBN[cfg];
     if (nbm * nbn > (1 << 24)) continue;

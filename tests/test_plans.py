@@ -163,11 +163,11 @@ def test_slices_of_streaming_launches(probe):
 
 
 def test_fp32_products_leave_the_plan_by_tile_counts_for_a_clear_gain(probe):
-    """Modelled within 5 % of each other, 204 x 4008 x 4060 and 212 x 3284 x 1944 run 10-11 % faster on 128x128 tiles in a few slices;
+    """Modelled within 3 % of each other, 204 x 4008 x 4060 and 212 x 3284 x 1944 run 10-11 % faster on 128x128 tiles in a few slices;
     whole plans and those in many slices are left (52 x 344 x 5992 41 us, 46 on its plan by tile counts; 296 x 7496 x 32 17 and 20)."""
     kept = probe("f32", [(204, 4008, 4060, 0), (212, 3284, 1944, 0)])
     assert all(p[:2] == p[2:] for p in kept), kept
-    assert all(p[:2] != p[2:] for p in probe("f32", [(256, 768, 768, 8), (300, 2000, 4000, 0), (52, 344, 5992, 192), (296, 7496, 32, 0)]))
+    assert all(p[:2] != p[2:] for p in probe("f32", [(256, 768, 768, 8), (300, 2000, 4000, 0), (52, 344, 5992, 192), (296, 7496, 32, 0), (2012, 240, 1044, 0), (233, 1304, 1552, 0)]))
 
 
 def test_few_token_route_is_weighed_against_a_split_T(probe):
