@@ -5,9 +5,9 @@
 // backward 4 / 5 / 7 / 8 the frozen weight enters only through M = W + s A B, which the merge kernel forms with
 // W's columns scaled on the way: W diag(g) is never written.  What DoRA adds per step:
 //   - the column sums of (W + s A B)^2 (merge.hpp, sq_partial), finished here into c and g.  The forward takes them from the
-//     pass that forms V, multiplies by V and scales the product's columns by g in its epilogue (4096 x 2048 -> 8192: a pass over
-//     W of 16 us less than one for the sums and another for M); where the product's kernel is not built for that (f16: the range of
-//     V is not that of V diag(g)) the sums are a pass that stores nothing;
+//     pass that forms V, multiplies by V and scales the product's columns by g in its epilogue (4096 x 2048 -> 8192, r 16: 124 us
+//     where sums and M in a pass each take 134); where the product's kernel is not built for that (f16: the range of V is not that
+//     of V diag(g)), and where the caller keeps M, the sums are a pass that stores nothing;
 //   - B~ = B diag(g) and dB = dB~ diag(g): r x o elements each;
 //   - dm[j] = sum_t dY[t,j] (Y[t,j] - bias[j]) / m[j]: one pass over dY and the forward's output.
 // All sums are fp32 in a fixed order.  Internal to the library; 16-bit types only.

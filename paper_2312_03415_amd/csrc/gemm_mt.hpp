@@ -5,10 +5,11 @@
 // What bounds it.  A 128x128 tile needs 32 KB of operands per K tile of 64 and 512 cycles of v_mfma_f32_16x16x32 per
 // wave: the compute unit's path from L1 to LDS (64 bytes a cycle) and its LDS reads (128 bytes a cycle) are then as busy
 // as the matrix cores, where the generic engine (gemm_engine.hpp) also passes every operand byte through registers,
-// issues half-size products and waits for memory once per K tile.  What a compute unit fetches decides: 44 bytes a cycle, so a
-// K tile of a 128x128 tile takes 0.31 .. 0.39 us against 0.21 of products, which is why 256x128 wins as soon as its tiles fill the
-// chip.  (Waves that split K instead of the tile read and write 64 KB of LDS per K tile instead of 96: the launches took the
-// same, 45.3 / 44.6 us against 42.1 / 41.0 at 1024 x 4096 x 4096 NN / NT.)
+// issues half-size products and waits for memory once per K tile.  A K tile of a 128x128 tile takes a workgroup alone on the chip
+// 0.31 .. 0.39 us against 0.21 of products (44 bytes a cycle fetched), one of 256 0.51, which is why 256x128 wins as soon as its tiles
+// fill the chip.  It is not LDS (waves that split K instead of the tile read and write 64 KB of it per K tile instead of 96: 45.3 /
+// 44.6 us against 42.1 / 41.0 at 1024 x 4096 x 4096 NN / NT) and with operands from HBM not power (42 us on zeros too; from the caches
+// 37-42 and 33-34 on zeros).
 // Measured (us a launch, bf16, N(0,1); this kernel / generic engine / 256x256 kernel, each at its best K split):
 // 1024 x 4096 x 4096 NN 40.7 / 65.4 / 51.3, NT 36.2 / 59.1 / 47.5; 512 x 4096 x 4096 24.2 / 39.8 / 35.4;
 // 1237 x 2056 x 5464 46.3 / 53.4 / 52.9; 4096 x 256 x 8192 28.8 / 38.5 / 36.6; 4096 x 2048 x 8192 112 / 183 / 117.

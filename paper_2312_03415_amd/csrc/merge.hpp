@@ -1,7 +1,7 @@
 // M = W + alpha A B for the merged-weight graphs (forward2, Eq. 2; Z1 / Z3 of Algorithms 4 and 5 of arxiv
 // 2312.03415): [i,o] = [i,o] + [i,r][r,o] with r <= 128, bf16 / fp16.  The default chain's rank-r updates
-// (Y += T B, dX += Z1 A^T: the same operation on [n,o] / [n,i], in place) run here as well, and so do the two
-// passes DoRA adds: the squared column norms of W + alpha A B (nothing stored) and W diag(g) + alpha A B.
+// (Y += T B, dX += Z1 A^T: the same operation on [n,o] / [n,i], in place) run here as well, and so do the
+// passes DoRA adds: the squared column norms of W + alpha A B, with that sum stored or not, and W diag(g) + alpha A B.
 //
 // The product is tiny (2 i o r FLOPs); the kernel reads W once and writes M once, so it is bound by
 // HBM bandwidth (2 i o e bytes) and is organised around coalesced 16-byte accesses with many of

@@ -15,11 +15,11 @@
 //    bytes per row of A, half a 128-byte line, and the other half has to come from the neighbouring workgroup's fetch staying
 //    in L2.  With 128-byte strips dA, dB of 4096 x (2048 + 8192) r 16 take 21.4 us, 25.0 without; with fewer blocks the chip's
 //    idle units cost more (skinny_plan).  Single launches keep 32 rows (dB of 4096 x 8192 alone: 18.8 -> 23.4 us).
-//  - NWV = 4 where loads bind: 8 or 16 waves make no plain launch faster (a compute unit fetches 50-60 bytes a ns, operand
-//    B's share included, whatever the number of waves).  A masked problem (LoRA dropout) in the [M,K] orientation is bound by
-//    its waves' mask arithmetic, one chain of instructions per wave: 16 waves (two tiles of loads in flight each) take 22.7
-//    us against 30.5 for T = (X o m) A of 4096 x 8192 r 16 (two K slices), 25.8 against 37.2 for {Z1, Z2} of 4096 x 8192 ->
-//    2048.
+//  - NWV = 4 where loads bind: 8 or 16 waves make no plain launch that fills the chip faster (a compute unit fetches 50-60 bytes a
+//    ns, operand B's share included, whatever the number of waves).  A masked problem (LoRA dropout) in the [M,K] orientation is bound by
+//    its waves' mask arithmetic, one chain of instructions per wave: 16 waves (two tiles of loads in flight each) take 26.1
+//    us against 32.5 for T = (X o m) A of 4096 x 8192 r 16 (two K slices, reduce pass included), 24.6 against 36.2 for {Z1, Z2} of
+//    4096 x 8192 -> 2048.
 //  - The waves' partial accumulators are summed through LDS in wave order and written once.  A grid
 //    that also splits K over workgroups (gridDim.y) writes fp32 partials that a second kernel sums
 //    in slice order.  No atomics: results are identical from run to run.
