@@ -849,8 +849,10 @@ bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, 
   }
   // r > 64: 128x128 tiles, each product cut into about as many slices as make its workgroups equally long: {Z1, Z2} of 8192 x (11008 +
   // 4096) r 128 96.5 us on 128x64 tiles, 74.4 so; 4096 x (2048 + 8192) 36.7 and 33.7; dA, dB of 8192 x (4096 + 4096) 41.6 and 35.6.
-  // (A lone product gains nothing: T of 8192 x 4096 27.8 and 28.7, of 8192 x 11008 62.2 and 61.6.)
-  if (d[0].N > 64 && d[1].N > 64) {
+  // (A lone product gains nothing: T of 8192 x 4096 27.8 and 28.7, of 8192 x 11008 62.2 and 61.6.)  dA, dB over fewer than 44 MB stay on
+  // the narrow ones, which want half the slices: 41 such layers from 32 MB on took 722 us so and 769 on 128x128 (1480 x (5808 + 4920)
+  // r 72 12.5 and 15.3; the other way at most 18.1 and 16.3), 47 of 44 .. 64 MB 1048 and 1038.
+  if (d[0].N > 64 && d[1].N > 64 && (z || bytes >= 44e6)) {
     int64_t wide[2];
     for (int w = 0; w < 2; ++w) wide[w] = ((d[w].M + 127) / 128) * ((d[w].N + 127) / 128);
     for (int s = 1; s <= 16 && (s == 1 || longest / s >= 8); ++s) {

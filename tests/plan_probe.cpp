@@ -75,6 +75,11 @@ int main() {
         if (!int4 && s.workspace_bytes != runlora_call_workspace_bytes(bwd ? -1 : v, bwd ? v : -1, M, N, K0, K1, code, choices)) ++inexact;
       });
       std::printf("%d %d %d %d\n", beyond, beyond_vera, inexact, first);
+    } else if (std::strcmp(kind, "pair") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: the launch of backward 1's dA, dB on 128x128 tiles or not, slices
+      Schedule s;
+      if (!build_backward(1, LayerDims{M, N, K0, K1, DT_BF16}, BwdOperands{}, nullptr, &s)) return 1;
+      for (const Step& t : s.steps)
+        if (t.is_mtpair && t.sk[0].a_strided) std::printf("%d %d %d\n", t.mtpair.wide ? 1 : 0, t.mtpair.splits[0], t.mtpair.splits[1]);
     } else if (std::strncmp(kind, "stream", 6) == 0) {  // M, N = r, K of T = X A, K1 = masked or not: slices, wavefronts, rows of a block
       SkinnyDesc d;
       d.M = M; d.N = N; d.K = K0;

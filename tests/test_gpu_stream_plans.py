@@ -51,6 +51,16 @@ def test_gradients_in_32_and_64_row_blocks(n, i, o, r, dtype):
         assert err < TOL[dtype], (name, err)
 
 
+# dA, dB from 44 MB of operands on: 128x128 tiles, a ragged last tile of each, tokens a row past a K tile; r at the edges of one column tile
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r", [(8257, 1032, 2056, 72), (8193, 520, 3080, 128)])
+def test_gradients_of_wide_pairs(n, i, o, r, dtype):
+    L = synth.Layer("wide", n, i, o, r, dtype, 54)
+    print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
+    for name, err in gradients(L, 0.0, 0):
+        assert err < TOL[dtype], (name, err)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("n,i,o,r", [(520, 2056, 2120, 64), (1032, 4104, 1096, 40), (300, 1000, 3000, 128), (2056, 264, 4104, 72),
                                      (4104, 520, 2056, 128), (1032, 4104, 1096, 256), (2056, 1096, 4104, 136), (200, 392, 264, 200),

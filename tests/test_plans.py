@@ -175,3 +175,11 @@ def test_few_token_route_is_weighed_against_a_split_T(probe):
     r 96: 23.7 us by the few-token route, 18.0; 46 x 1328 -> 72, r 128 27.0 and 15.2)."""
     rows = [(67, 2472, 72, 96), (34, 1200, 80, 128), (132, 1272, 64, 128), (77, 1192, 64, 128), (46, 1328, 72, 128)]
     assert [p[0] for p in probe("few", rows)] == [0] * 5
+
+
+def test_gradient_pairs_of_few_bytes_stay_on_narrow_tiles(probe):
+    """dA, dB, r > 64, over fewer than 44 MB of operands: 1480 x (5808 + 4920) r 72 12.5 us, 15.3 on 128x128 tiles; 8525 x (1144 + 960) r 80 19.8
+    and 23.5; 4858 x (544 + 2640) r 128 16.8 and 19.2.  Above, as priced: 8192 x (4096 + 4096) r 128 41.6 on narrow tiles, 35.6."""
+    small = [(1480, 5808, 4920, 72), (8525, 1144, 960, 80), (4858, 544, 2640, 128)]
+    large = [(8192, 4096, 4096, 128), (8241, 7560, 376, 72), (8257, 1032, 2056, 72), (8193, 520, 3080, 128)]
+    assert [p[0] for p in probe("pair", small + large)] == [0] * 3 + [1] * 4
