@@ -247,13 +247,14 @@ struct MergeDesc {
   uint32_t drop_thr = 0, drop_key = 0, drop_cpr = 0;
 };
 inline bool merge_ok(int dtype, int64_t r) { return dtype != DT_F32 && r <= 128; }
-// the merge kernel's launch shape: gx workgroups of `cols` columns, gy row slices of bpw 32-row blocks each
-// (about two workgroups per compute unit, each walking several row blocks)
+// the merge kernel's launch shape: gx workgroups of 256 columns, gy row slices of bpw 32-row blocks each: as many workgroups as stay on the
+// chip together (four to a compute unit up to r = 32, two beyond), so that what each spends on its columns of B is spent once.  1024 and
+// 512 of them, us (bf16, stored V and sums / M): 2048 x 8192 r 16 16.3 and 16.9 / 15.5 and 17.1, 2048 x 2048 r 32 8.1 and 9.3 / 6.7 and 7.1; 1280 x
+// 7328 r 64 17.2 and 15.4 / 17.2 and 14.0, 4096 x 4096 r 128 26.8 and 23.9 / 26.7 and 23.3.
 inline void merge_grid(int64_t I, int64_t O, int64_t R, int* gx, int* gy, int* bpw) {
-  const int cols = R <= 64 ? 512 : 256;
-  *gx = (int)((O + cols - 1) / cols);
+  *gx = (int)((O + 255) / 256);
   const int nb = (int)((I + 31) / 32);
-  int y = 512 / *gx;
+  int y = (R <= 32 ? 1024 : 512) / *gx;
   if (y < 1) y = 1;
   if (y > nb) y = nb;
   *bpw = (nb + y - 1) / y;

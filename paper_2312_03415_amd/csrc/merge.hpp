@@ -6,13 +6,16 @@
 // The product is tiny (2 i o r FLOPs); the kernel reads W once and writes M once, so it is bound by
 // HBM bandwidth (2 i o e bytes) and is organised around coalesced 16-byte accesses with many of
 // them in flight:
-//  - a workgroup (4 wavefronts) owns a strip of columns (each wave 32*CB of them) and walks a
+//  - a workgroup (4 wavefronts) owns a strip of 256 columns (each wave 64 of them: whole 128-byte lines of W) and walks a
 //    range of 32-row blocks.  The B fragments of its columns are read once (through LDS, with the
-//    transposing LDS load) and stay in registers for the whole walk.
+//    transposing LDS load) and stay in registers for the whole walk.  128 columns a wave hold twice the fragments and accumulators: one
+//    workgroup to a compute unit at r = 64, and a row block's loads, its products and its stores then follow one another.  Stored V and
+//    sums / M, us, 128 columns a wave and 64: 1280 x 7328 r 64 29.9 -> 15.4 / 26.3 -> 14.0, 4096 x 4096 r 64 34.3 -> 21.9 / 29.8 -> 20.6, 2048 x
+//    2048 r 32 11.1 -> 8.1 / 11.5 -> 6.7, 2048 x 8192 r 16 18.4 -> 16.3 / 17.3 -> 15.5 (67 MB: 4.3 TB/s).
 //  - per row block: the A fragment (32 rows x r) comes straight from global memory, r/16 MFMAs per
 //    32x32 block give A B in fp32, the wave passes it through its private LDS region to turn the
 //    MFMA's register layout into rows, adds W (prefetched one row block ahead, 16 bytes per lane,
-//    whole 128/256-byte row segments per wave instruction), rounds once and stores 16 bytes per lane.
+//    whole 128-byte row segments per wave instruction), rounds once and stores 16 bytes per lane.
 //    W is read with non-temporal loads: nothing reads it again soon, while M is read by the next kernel.
 #pragma once
 #include "gemm_engine.hpp"
@@ -36,8 +39,9 @@ struct MergeArgs {
   uint32_t drop_thr, drop_key, drop_cpr;
 };
 
-template <int KSTEPS, int CB>
+template <int KSTEPS>
 struct MergeTile {
+  static constexpr int CB = 2;
   static constexpr int COLS = 32 * CB;        // columns per wave
   static constexpr int LD = COLS + 4;         // fp32 row length of the transposition buffer
   static constexpr int RED_BYTES = 32 * LD * 4, STAGE_BYTES = 16 * KSTEPS * COLS * 2;
@@ -52,9 +56,10 @@ struct MergeTile {
 // 3 us at 4096 x 4096, r 64 (forward 2 of 1024 tokens 72.1 -> 75.5 us, a DoRA layer in f16 102.3 -> 105.3), and a loop for each choice 4 us
 // more at r 32 and 128.  It tests for both at run time all the same: the branches keep a row pass's LDS reads and stores from being
 // gathered over all passes (with none, DoRA's forward took 130.4 us for 124.4 at 4096 x 2048 -> 8192, r 16).
-template <typename T, int KSTEPS, int CB, bool BOTH = false>
+template <typename T, int KSTEPS, bool BOTH>
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
-  using MT = MergeTile<KSTEPS, CB>;
+  using MT = MergeTile<KSTEPS>;
+  constexpr int CB = MT::CB;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -67,34 +72,43 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
   T* Mp = static_cast<T*>(g.M);
 
   // ---- B fragments of this wave's columns: stage B[0:16*KSTEPS, n0:n0+COLS] (zero beyond r / o) in
-  // LDS as [k][COLS], read with the transposing load, keep in registers
+  // LDS as [k][COLS], read with the transposing load, keep in registers.  All of a lane's loads are issued before the first is
+  // used, behind those of the first row block: as a rolled loop each made a trip to memory of its own (4096 x 1280 r 64, one or two row blocks a
+  // workgroup: 19.3 -> 15.9 us).
   constexpr int BLD = MT::COLS;  // read once per workgroup: bank conflicts do not matter here
   T* sB = reinterpret_cast<T*>(wsm);
-  for (int c = lane; c < 16 * KSTEPS * (MT::COLS / 8); c += 64) {
-    const int k = c / (MT::COLS / 8), col = (c % (MT::COLS / 8)) * 8;
-    i32x4 v = {0, 0, 0, 0};
-    if (!g.b_trans && k < g.R && n0 + col < g.O) v = *reinterpret_cast<const i32x4*>(Bp + (int64_t)k * g.ldb + n0 + col);
-    *reinterpret_cast<i32x4*>(sB + k * BLD + col) = v;
-  }
-  if (g.b_trans) {  // B stored [O, R]: 16 bytes = eight k of one column, scattered into the [k][COLS] tile (once per workgroup)
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    for (int c = lane; c < MT::COLS * (2 * KSTEPS); c += 64) {
-      const int col = c / (2 * KSTEPS), k8 = (c % (2 * KSTEPS)) * 8;
-      if (n0 + col < g.O && k8 < g.R) {
-        const i32x4 v = *reinterpret_cast<const i32x4*>(Bp + (int64_t)(n0 + col) * g.ldb + k8);
-        const T* e8 = reinterpret_cast<const T*>(&v);
+  constexpr int NCH = 16 * KSTEPS * (MT::COLS / 8) / 64;  // 16-byte chunks of that tile per lane
+  i32x4 bst[NCH];
+  auto load_b = [&]() {
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+      const int c = lane + 64 * j;
+      i32x4 v = {0, 0, 0, 0};
+      if (!g.b_trans) {
+        const int k = c / (MT::COLS / 8), col = (c % (MT::COLS / 8)) * 8;
+        if (k < g.R && n0 + col < g.O) v = *reinterpret_cast<const i32x4*>(Bp + (int64_t)k * g.ldb + n0 + col);
+      } else {  // B stored [O, R]: 16 bytes = eight k of one column
+        const int col = c / (2 * KSTEPS), k8 = (c % (2 * KSTEPS)) * 8;
+        if (n0 + col < g.O && k8 < g.R) v = *reinterpret_cast<const i32x4*>(Bp + (int64_t)(n0 + col) * g.ldb + k8);
+      }
+      bst[j] = v;
+    }
+  };
+  auto stage_b = [&]() {
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+      const int c = lane + 64 * j;
+      if (!g.b_trans) {
+        const int k = c / (MT::COLS / 8), col = (c % (MT::COLS / 8)) * 8;
+        *reinterpret_cast<i32x4*>(sB + k * BLD + col) = bst[j];
+      } else {  // scattered into the [k][COLS] tile
+        const int col = c / (2 * KSTEPS), k8 = (c % (2 * KSTEPS)) * 8;
+        const T* e8 = reinterpret_cast<const T*>(&bst[j]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) sB[(k8 + e) * BLD + col] = e8[e];
       }
     }
-  }
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's own LDS writes are done (same wave reads them)
-  i32x4 fb[CB][KSTEPS];
-#pragma unroll
-  for (int b = 0; b < CB; ++b)
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) fb[b][ks] = read_frag<T, true, BLD>(sB, b * 32, ks, lane);
-
+  };
   // ---- walk the row blocks
   const int nblocks = (g.I + 31) / 32;
   const int rb0 = blockIdx.y * g.blocks_per_wg;
@@ -128,6 +142,14 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
     }
   };
   if (rb0 < rb1) prefetch(rb0);
+  load_b();
+  stage_b();
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the wave's own LDS writes are done (same wave reads them)
+  i32x4 fb[CB][KSTEPS];
+#pragma unroll
+  for (int b = 0; b < CB; ++b)
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) fb[b][ks] = read_frag<T, true, BLD>(sB, b * 32, ks, lane);
   float* red = reinterpret_cast<float*>(wsm);
   for (int rb = rb0; rb < rb1; ++rb) {
     i32x4 fa[KSTEPS], wcur[MT::PASSES];
