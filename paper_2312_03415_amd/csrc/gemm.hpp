@@ -40,6 +40,8 @@ struct GemmDesc {
   // (first column of C in X) / 4; where masked_segment_ok holds
   bool mask_seg0 = false;
   uint32_t drop_n4 = 0;
+  // A[0] is X with its dropped elements zeroed (GemmArgs::mask_a): rank-r products on the middle-sized kernel (rank_plan)
+  bool mask_a = false;
   // optional [N] (16-byte aligned): C = (the products) diag(cscale) + bias; where column_scale_ok holds
   const float* cscale = nullptr;
   // One-pass LoRA forward, C = A[0] B[0] + round(t_alpha A[0] LA) B[1] in one kernel: nseg = 2, A[1] unused,

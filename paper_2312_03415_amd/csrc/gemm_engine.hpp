@@ -60,6 +60,8 @@ struct GemmArgs {
   // before segment 1's is added to it: C = mask o (A[0] B[0]) + A[1] B[1].  drop_n4 = first column of C in X / 4.
   int mask_seg0;
   uint32_t drop_n4;
+  // != 0 (gemm_mt.hpp; one segment): A is the layer input X and its dropped elements count as zeros
+  int mask_a;
   // optional [N], fp32 (gemm_mc64.hpp, gemm_mt.hpp; A [M,K], B [K,N]): C = (the products) diag(cscale) + bias
   const float* cscale;
   // One-pass LoRA forward (gemm_kernel's FUSE build, Y = X W + (s X A) B of Section 2's forward 1 in one kernel):

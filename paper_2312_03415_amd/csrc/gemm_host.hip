@@ -458,6 +458,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   }
   if (plan.splits > 1 && scratch == nullptr) return hipErrorInvalidValue;
   if (d.cscale != nullptr && !column_scale_ok(d, plan)) return hipErrorInvalidValue;
+  if (d.mask_a && (d.drop_thr == 0 || d.nseg != 1 || plan.cfg != CFG_MTN64 || d.b_kcontig || d.dtype == DT_F32 || long_operand(d))) return hipErrorInvalidValue;
   if (d.mask_seg0 && (d.drop_thr == 0 || !masked_segment_ok(d, plan))) return hipErrorInvalidValue;
   if (d.fuse_t) {
     const bool ok = d.LA != nullptr && d.nseg == 2 && d.K[1] >= 1 && d.K[1] <= kFuseMaxR && d.K[0] >= 1 && !d.a_strided &&
@@ -520,6 +521,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   a.drop_key = d.drop_key;
   a.drop_cpr = d.drop_cpr;
   a.mask_seg0 = d.mask_seg0 ? 1 : 0;
+  a.mask_a = d.mask_a ? 1 : 0;
   a.drop_n4 = d.drop_n4;
   a.cscale = d.cscale;
   a.rotate = d.rotate;
@@ -539,7 +541,7 @@ hipError_t gemm_run(const GemmDesc& d, const GemmPlan& plan, float* scratch, hip
   if (e != hipSuccess) return e;
   if (plan.splits > 1)
     e = splitk_reduce_launch(d.dtype, scratch, plan.splits, (int)d.M, (int)d.N, d.C, d.ldc, d.D, d.ldd, d.alpha,
-                             d.bias, d.mask_seg0 ? DropMask{} : DropMask{d.drop_thr, d.drop_key, d.drop_cpr}, stream);
+                             d.bias, d.mask_seg0 || d.mask_a ? DropMask{} : DropMask{d.drop_thr, d.drop_key, d.drop_cpr}, stream);
   return e;
 }
 
@@ -726,6 +728,14 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
     const double chain = plan.rt == 1 ? 4.4 + 0.35 * tiles : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles);
     if (chain > us) us = chain;
   }
+  for (int w = 0; w < nprob; ++w) {
+    // the masked problem's chain is longer, its mask arithmetic included (T of 280 x 2304 r 64 18.5 us, of 700 x 3000 r 96 32.7; dA, dB of 1237 x
+    // (2056 + 5464) r 64 15.0, of 960 x (768 + 4864) r 128 18.8)
+    if (d[w].drop_thr == 0 || plan.rt == 1) continue;
+    const double tiles = (double)(((d[w].K + 63) / 64 + 4 * plan.splits - 1) / (4 * plan.splits));
+    const double chain = d[w].a_strided ? (plan.rt == 2 ? 6.0 + 1.8 * tiles : 8.0 + 3.2 * tiles) : (plan.rt == 2 ? 5.8 + 1.4 * tiles : 6.9 + 2.2 * tiles);
+    if (chain > us) us = chain;
+  }
   return us + (plan.splits > 1 ? 4.0 + outs * 8.0 * plan.splits / 7.5e6 : 0.0);
 }
 
@@ -747,16 +757,21 @@ GemmDesc rank_desc(int dtype, const SkinnyDesc& d) {
   g.M = t ? d.N : d.M;
   g.N = t ? d.M : d.N;
   g.rotate = g.a_strided ? 0 : 5;
+  g.mask_a = d.drop_thr != 0;
+  g.drop_thr = d.drop_thr; g.drop_key = d.drop_key; g.drop_cpr = d.drop_cpr;
   return g;
 }
 
 // One launch of narrow tiles over operands that come from HBM: 0.53 us per K tile and workgroup (0.45 where a tile's rows
 // are whole lines of a [K, .] operand), twice that where two share a compute unit (see gemm_mt_pair_kernel); never below
 // the operands' bytes at 4.8 TB/s.  Operands that the caches still hold (the activations of a short batch) arrive twice as
-// fast: dA, dB of 1024 x 4096 r 64 take 9.7 us here, 17.5 on the streaming kernel.
-static double rank_time_us(bool a_strided, int64_t wgs, int64_t ktiles, double bytes) {
+// fast: dA, dB of 1024 x 4096 r 64 take 9.7 us here, 17.5 on the streaming kernel.  Masked (LoRA dropout; streaming kernel / here, reduce
+// included): T of 700 x 3000 r 96 32.7 / 14.7 us, {Z1, T} 32.2 / 16.5; of 8192 x (4096 + 4096) r 64 {Z1, T} 46.0 / 39.8, dA, dB 55.0 / 40.7; for short
+// batches the two are level (300 x 768 r 64: T 9.0 / 10.8, dA, dB 10.0 / 10.2).
+static double rank_time_us(bool a_strided, bool masked, int64_t wgs, int64_t ktiles, double bytes) {
   const int64_t rounds = wgs / 512, rest = wgs % 512;
-  const double tk = bytes < 32e6 ? 0.28 : (a_strided ? 0.45 : 0.53);
+  double tk = bytes < 32e6 ? 0.28 : (a_strided ? 0.45 : 0.53);
+  if (masked) tk = 0.7;  // (priced as unmasked, {dA, dB} of 8192 x (4096 + 4096) r 64 take 41.9 us for 35.5, in fewer slices)
   const double us = (bytes < 32e6 ? 5.0 : 7.5) + (double)ktiles * tk * (double)(2 * rounds + (rest > 256 ? 2 : (rest > 0 ? 1 : 0)));
   const double floor_us = 5.0 + bytes / 4.8e6;
   return us > floor_us ? us : floor_us;
@@ -764,14 +779,19 @@ static double rank_time_us(bool a_strided, int64_t wgs, int64_t ktiles, double b
 
 // The same for a pair on 128x128 tiles, one workgroup to a compute unit: they read the long operand once where 128x64 ones read it for every 64
 // columns.  A K tile is 32 KB, 0.65 us at the 50 bytes a ns that a unit fetches (0.45 from the caches).
-static double wide_rank_us(bool a_strided, int64_t wgs, int64_t ktiles, double bytes) {
-  const double tk = bytes < 32e6 ? 0.45 : (a_strided ? 0.6 : 0.65);
+static double wide_rank_us(bool a_strided, bool masked, int64_t wgs, int64_t ktiles, double bytes) {
+  const double tk = masked ? 0.8 : (bytes < 32e6 ? 0.45 : (a_strided ? 0.6 : 0.65));  // ({Z1, T} of 800 x (1024 + 1024) r 128, masked: 20.7 us whole)
   const double us = 7.5 + (double)((wgs + 255) / 256) * (double)ktiles * tk, floor_us = 5.0 + bytes / 4.8e6;
   return us > floor_us ? us : floor_us;
 }
 
+// A masked product leaves one launch of the streaming kernel for two where it takes slices here.  Over small operands the layer's host
+// work is what it waits for, and a launch is 3 us of that: 280 x 2304 -> 768 r 64, T 18.6 us there and 8.5 + 4.5 here, ran 84.7 us a pass on the
+// streaming kernel and 91.1 with T and {Z1, T} in slices; 960 x 768 -> 4864 r 128 106 and 91.
+static double masked_slices_us(const SkinnyDesc& d, double bytes) { return d.drop_thr != 0 && bytes < 4e6 ? 7.5 : 0.0; }
+
 static bool rank_shape_ok(int dtype, const SkinnyDesc& d) {
-  return dtype != DT_F32 && d.N > 32 && d.M > 32 && d.drop_thr == 0;
+  return dtype != DT_F32 && d.N > 32 && d.M > 32 && (d.drop_thr == 0 || (!d.b_kcontig && !d.trans_out));
 }
 
 bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us) {
@@ -788,7 +808,7 @@ bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, doubl
     if ((kt + per - 1) / per != s) continue;  // no empty slice
     const size_t part = s > 1 ? (size_t)s * (size_t)g.M * (size_t)g.N * sizeof(float) : 0;
     if (part > cap) break;
-    const double us = rank_time_us(g.a_strided != 0, nbm * nbn * s, per, bytes) + split_time_us(g.M, g.N, s);
+    const double us = rank_time_us(g.a_strided != 0, d.drop_thr != 0, nbm * nbn * s, per, bytes) + split_time_us(g.M, g.N, s) + (s > 1 ? masked_slices_us(d, bytes) : 0.0);
     if (us >= best) continue;
     best = us;
     found = true;
@@ -840,7 +860,7 @@ bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, 
       }
     }
     if (part > cap) break;
-    us += rank_time_us(d[0].a_strided != 0, wgs, per, bytes) + (part > 0 ? 3.0 : 0.0);
+    us += rank_time_us(d[0].a_strided != 0, d[0].drop_thr != 0 || d[1].drop_thr != 0, wgs, per, bytes) + (part > 0 ? 3.0 + masked_slices_us(d[0].drop_thr != 0 ? d[0] : d[1], bytes) : 0.0);
     if (us < best) {
       best = us;
       plan->partial_bytes = part;
@@ -873,7 +893,7 @@ bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, 
         }
       }
       if (part > cap) break;
-      us += wide_rank_us(d[0].a_strided != 0, wgs, most, bytes) + (part > 0 ? 3.0 : 0.0);
+      us += wide_rank_us(d[0].a_strided != 0, d[0].drop_thr != 0 || d[1].drop_thr != 0, wgs, most, bytes) + (part > 0 ? 3.0 + masked_slices_us(d[0].drop_thr != 0 ? d[0] : d[1], bytes) : 0.0);
       if (us < best) {
         best = us;
         plan->wide = true;
@@ -907,6 +927,8 @@ hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, f
     a[w].C = g.C; a[w].ldc = g.ldc;
     a[w].alpha = g.alpha;
     a[w].rotate = g.a_strided ? 0 : 5;
+    a[w].mask_a = g.mask_a ? 1 : 0;
+    a[w].drop_thr = g.drop_thr; a[w].drop_key = g.drop_key; a[w].drop_cpr = g.drop_cpr;
     a[w].splits = plan.splits[w];
     a[w].tiles_per_split = plan.tiles_per_split[w];
     const int64_t bm = plan.wide ? 128 : kTileBM[plan.cfg[w]], bn = plan.wide ? 128 : kTileBN[plan.cfg[w]];

@@ -99,9 +99,12 @@ template <> struct MtFrag<true> {
 // tile (of this K slice) the dropped accumulators are zeroed (a lane holds four consecutive columns of a row: one hash), and
 // the other segment is added to what is left.
 // COLSCALE: C = (the products) diag(cscale) + bias, see gemm_mc64.hpp
-template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA, bool SEGMASK = false, bool COLSCALE = false>
+// MASKA: A is the input X of a layer with LoRA dropout (T = (X o m) A, dA = (X o m)^T Z1; r > 32).  A wave masks the chunks that it
+// loaded itself, in LDS, between its wait for them and the barrier that hands them over: two hashes a chunk, each formed once.
+template <typename T, int AL, int BL, int BM, int BN, int NS, bool XA, bool SEGMASK = false, bool COLSCALE = false, bool MASKA = false>
 __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, const int by) {
   static_assert(!XA || (AL == 0 && BL == 0), "X [M,K], W and A [K,.]");
+  static_assert(!MASKA || (BM == 128 && !XA && !SEGMASK), "four chunks of X per lane");
   using P = MtTile<AL, BL, BM, BN, NS>;
   constexpr int BK = P::BK, TM = P::TM, TN = P::TN;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
@@ -289,6 +292,37 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
     for (int b = 0; b < TN; ++b) fb[buf][b].touch();
   };
 
+  // MASKA: the dropped elements of this lane's chunks of X zeroed, K tile t of the (one) segment in stage st, which have arrived
+  [[maybe_unused]] int tile_k = cu;  // the tile that is handed over next (in the order of the load cursor)
+  auto mask_tile = [&](int st) {
+    if constexpr (MASKA) {
+      const uint32_t addr = lds_base + (uint32_t)(st * P::STAGE_BYTES + wave * (P::IA * 1024) + lane * 16);
+      i32x4 c[4];
+      asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:1024\n\tds_read_b128 %2, %4 offset:2048\n\t"
+                   "ds_read_b128 %3, %4 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+                   : "=&v"(c[0]), "=&v"(c[1]), "=&v"(c[2]), "=&v"(c[3]) : "v"(addr) : "memory");
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int p = (wave * P::IA + j) * 64 + lane;
+        uint32_t token, col;
+        if constexpr (!P::A_STR) {
+          const int row = p >> 3;
+          token = (uint32_t)(m0 + row);
+          col = (uint32_t)(tile_k * BK) + (uint32_t)(((p & 7) ^ ((row >> 1) & 7)) << 3);
+        } else {
+          const int row = p / (BM / 8);
+          token = (uint32_t)(tile_k * BK + row);
+          col = (uint32_t)m0 + (uint32_t)(((p % (BM / 8)) ^ mt_swz<BM>(row)) << 3);
+        }
+        c[j] = drop_chunk<T>(c[j], token * g.drop_cpr + (col >> 2), g.drop_key, g.drop_thr);
+      }
+      asm volatile("ds_write_b128 %4, %0\n\tds_write_b128 %4, %1 offset:1024\n\tds_write_b128 %4, %2 offset:2048\n\t"
+                   "ds_write_b128 %4, %3 offset:3072\n\ts_waitcnt lgkmcnt(0)"
+                   :: "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "v"(addr) : "memory");
+      if (++tile_k == u1) tile_k = u0;
+    }
+  };
+
   f32x4 acc[TM][TN];  // lane l: row l % 16, columns 4 (l / 16) .. + 3 of each 16x16 block
   static_for<TM * TN>([&](auto e) { acc[decltype(e)::value / TN][decltype(e)::value % TN] = f32x4{0.f, 0.f, 0.f, 0.f}; });
 
@@ -333,6 +367,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
     MT_FENCE();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(mc_wait_imm((NS - 1) * P::LPT, true));  // loads return in order
+    mask_tile(0);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     MT_FENCE();
@@ -351,6 +386,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
       static_for<SY>([&](auto q) { mma(I1{}, q); });
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_waitcnt(mc_wait_imm((NS - 2) * P::LPT, true));
+      mask_tile(stn);
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
       MT_FENCE();
@@ -434,7 +470,7 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
         } else {
           if constexpr (COLSCALE) { v0 *= c8[0]; v1 *= c8[1]; }
           if (g.alpha != 1.f) { v0 *= g.alpha; v1 *= g.alpha; }
-          if (!SEGMASK && g.drop_thr != 0u) {
+          if (!SEGMASK && !MASKA && g.drop_thr != 0u) {
             uint32_t k0[4], k1[4];
             const uint32_t grp4 = (uint32_t)m * g.drop_cpr + (uint32_t)(n >> 2);
             drop_keep4(grp4, g.drop_key, g.drop_thr, k0);
@@ -470,6 +506,10 @@ __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_c
   gemm_mt_body<T, AL, BL, BM, BN, NS, false, false, true>(g, (int)blockIdx.x, (int)blockIdx.y);
 }
 template <typename T, int AL, int BL, int BM, int BN, int NS>
+__global__ __launch_bounds__(256, 2) void gemm_mt_maska_kernel(GemmArgs g) {
+  gemm_mt_body<T, AL, BL, BM, BN, NS, false, false, false, true>(g, (int)blockIdx.x, (int)blockIdx.y);
+}
+template <typename T, int AL, int BL, int BM, int BN, int NS>
 __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_segmask_kernel(GemmArgs g) {
   gemm_mt_body<T, AL, BL, BM, BN, NS, false, true>(g, (int)blockIdx.x, (int)blockIdx.y);
 }
@@ -481,17 +521,28 @@ __global__ __launch_bounds__(256, (BM * BN <= 128 * 128 ? 2 : 1)) void gemm_mt_s
 // however many stages are in flight (three and six measure the same), so that a K tile's 24 KB take 0.53 us.  The streaming
 // kernel (skinny.hpp), whose waves re-read the short operand for every 32 rows, against this one: dA, dB of 8192 x (4096 +
 // 11008) r 128 129 / 61 us, Z1, Z2 120 / 97; dA, dB of 4096 x (5120 + 13824) r 64 59 / 29, of 1024 x 4096 r 64 17.5 / 9.7.
-template <typename T, int AL, int BL0, int BL1, int BM0, int BN0, int BM1, int BN1>
-__global__ __launch_bounds__(256, 2) void gemm_mt_pair_kernel(GemmArgs g0, GemmArgs g1) {
-#if defined(__HIP_DEVICE_COMPILE__)  // the host pass has no use for the body and instantiates it twice over (gemm_mt_kernel's)
+// DROPM: bit w = the A operand of product w is X under LoRA dropout
+template <typename T, int AL, int BL0, int BL1, int BM0, int BN0, int BM1, int BN1, int DROPM>
+__device__ __forceinline__ void gemm_mt_pair_body(const GemmArgs& g0, const GemmArgs& g1) {
   const int tiles0 = g0.nbm * g0.nbn, c0 = tiles0 * g0.splits;
   const int id = (int)blockIdx.x;
   if (id < c0) {
-    gemm_mt_body<T, AL, BL0, BM0, BN0, 3, false>(g0, id % tiles0, id / tiles0);
+    gemm_mt_body<T, AL, BL0, BM0, BN0, 3, false, false, false, (DROPM & 1) != 0>(g0, id % tiles0, id / tiles0);
   } else {
     const int tiles1 = g1.nbm * g1.nbn, j = id - c0;
-    gemm_mt_body<T, AL, BL1, BM1, BN1, 3, false>(g1, j % tiles1, j / tiles1);
+    gemm_mt_body<T, AL, BL1, BM1, BN1, 3, false, false, false, (DROPM & 2) != 0>(g1, j % tiles1, j / tiles1);
   }
+}
+template <typename T, int AL, int BL0, int BL1, int BM0, int BN0, int BM1, int BN1>
+__global__ __launch_bounds__(256, 2) void gemm_mt_pair_kernel(GemmArgs g0, GemmArgs g1) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass has no use for the body and instantiates it twice over (gemm_mt_kernel's)
+  gemm_mt_pair_body<T, AL, BL0, BL1, BM0, BN0, BM1, BN1, 0>(g0, g1);
+#endif
+}
+template <typename T, int AL, int BL0, int BL1, int BM0, int BN0, int BM1, int BN1, int DROPM>
+__global__ __launch_bounds__(256, 2) void gemm_mt_pair_maska_kernel(GemmArgs g0, GemmArgs g1) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  gemm_mt_pair_body<T, AL, BL0, BL1, BM0, BN0, BM1, BN1, DROPM>(g0, g1);
 #endif
 }
 

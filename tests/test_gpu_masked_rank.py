@@ -1,0 +1,54 @@
+"""GPU: rank-r products of X under LoRA dropout with r > 32 on the middle-sized kernel, T = (X o m) A and dA = (X o m)^T Z1, at edges of its
+tiles (128 tokens or columns, 64 of the rank, 64 of the contraction), alone, in pairs, in slices, and on the streaming kernel next to it."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import TOL, elem_excess, layer_on_device, relerr, to_f64, torch_dtype
+from paper_2312_03415_amd import binding as rl
+from paper_2312_03415_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+# (n, i, o, r), is T / the {Z1, T} pair / the {dA, dB} pair on tiles of the middle-sized kernel (ids 12-16)?
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r,mt", [(1025, 2056, 4104, 64, (1, 1, 1)),   # a row, eight columns past the tiles; slices
+                                        (2048, 1024, 2048, 128, (1, 1, 1)), (700, 3000, 704, 96, (1, 1, 1)),
+                                        (129, 4104, 4096, 40, (1, 1, 1)),    # long contraction over few tokens
+                                        (4096, 2048, 2056, 72, (1, 1, 1)),   # 128x128 tiles for a pair
+                                        (300, 512, 512, 48, (0, 0, 1)), (40, 264, 136, 64, (1, 1, 1)), (1500, 1024, 1024, 64, (0, 0, 1))])
+def test_masked_rank_products(n, i, o, r, mt, dtype):
+    import torch
+    L = synth.Layer("maskrank", n, i, o, r, dtype, 71)
+    dev, host = layer_on_device(L)
+    td, code, p, seed, scale = torch_dtype(dtype), rl.dtype_from_name(dtype), 0.3, 1234, 0.5
+    print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
+    mask, pq = oracle.dropout_mask(n, i, p, seed)
+    Xm, s = host["X"] * mask, scale / (1.0 - pq)
+    T, Z1 = s * (Xm @ host["A"]), s * (host["dY"] @ host["B"].T)
+    want = {"T": T, "dA": Xm.T @ Z1, "dB": T.T @ host["dY"], "Y": host["X"] @ host["W"] + T @ host["B"]}
+    nan = float("nan")
+    for bring in ("all", "none to split into"):
+        ws = rl.new_workspace(rl.FWD1, rl.BWD1, n, i, o, r, code)
+        ws.fill_(0xFF)
+        got = {k: torch.full(sh, nan, dtype=td, device="cuda") for k, sh in (("T", (n, r)), ("dA", (i, r)), ("dB", (r, o)), ("Y", (n, o)))}
+        rl.runlora_profile_enable(16)
+        # T alone, kept; then both pairs (T formed again), without dX
+        saved = rl.new_saved(got["T"])
+        rl.runlora_forward(rl.FWD1, dev["X"], dev["W"], dev["A"], dev["B"], got["Y"], saved, workspace=ws, scale=scale, dropout_p=p, dropout_seed=seed)
+        saved.T, saved.ldt = None, 0
+        if bring != "all":  # two rank-r factors and nothing else
+            ws = ws[:2 * ((n * r * 2 + 255) // 256 * 256)]
+        rl.runlora_backward(rl.BWD1, dev["dY"], saved, dev["W"], dev["A"], dev["B"], None, got["dA"], got["dB"], workspace=ws)
+        torch.cuda.synchronize()
+        steps = rl.runlora_profile_collect(16)
+        rl.runlora_profile_disable()
+        if bring == "all":
+            cfgs = [st["tile_cfg"] for st in steps if "Y =" not in st["what"]]
+            assert len(cfgs) == 3 and [int(c >= 12) for c in cfgs] == list(mt), steps
+        for k, w in want.items():
+            g = to_f64(got[k])
+            assert relerr(g, w) < TOL[dtype], (k, bring)
+            if k == "T":  # formed in one step from stored operands: a dropped or kept chunk too many moves every element of its row
+                assert elem_excess(g, w, dtype) < 1.0
