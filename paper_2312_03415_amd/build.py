@@ -1,4 +1,4 @@
-"""Build librunlora.so (HIP for gfx950) and _autograd.so (the native autograd node, host code) in-tree:   python -m paper_2312_03415_amd.build [--force]
+"""Build librunlora.so (HIP for gfx950) and _autograd.so (the native autograd nodes, host code) in-tree:   python -m paper_2312_03415_amd.build [--force]
 
 Objects go to paper_2312_03415_amd/_build/, the libraries to paper_2312_03415_amd/.
 hipcc cross-compiles without a GPU.

@@ -4,7 +4,7 @@ helper that swaps it in for the nn.Linear modules of a model (Section 3 applies 
 attention and MLP linear).
 
 Nothing is computed here: tensors are flattened to [n, d] views, buffers are allocated with torch,
-and every product runs inside the HIP library through binding.runlora_forward / runlora_backward.  The LoRA
+and every product runs inside the HIP library through binding.runlora_forward / runlora_backward.  Each
 layer's node exists twice: in native code (csrc/autograd.cpp), which ordinary calls take, and in Python below,
 for the calls that have to see a Python-level function (tracing, functorch transforms, tensor subclasses, modes).
 
@@ -41,7 +41,9 @@ def _native():
             raise ImportError(f"_autograd.so was not built for {build._ext_abi()}: run `python -m paper_2312_03415_amd.build`")
         from . import _autograd
         address = lambda f: ctypes.cast(f, ctypes.c_void_p).value
-        _autograd.init(address(lib.runlora_forward), address(lib.runlora_backward), address(lib.runlora_call_workspace_bytes), rl._check)
+        entries = (lib.runlora_forward, lib.runlora_backward, lib.runlora_call_workspace_bytes, lib.runlora_vera_forward, lib.runlora_vera_backward,
+                   lib.runlora_vera_workspace_bytes, lib.runlora_dora_forward, lib.runlora_dora_backward, lib.runlora_dora_workspace_bytes)
+        _autograd.init(tuple(address(f) for f in entries), rl._check)
         _native_module = _autograd
     return _native_module
 
@@ -192,6 +194,14 @@ class RunVeRAFunction(torch.autograd.Function):
     """y = x W + bias + scale ((x A) diag(d)) B diag(b) with W, bias, A and B frozen; gradients for x, d and b
     (runlora_vera_forward / runlora_vera_backward: the LoRA graphs on B~ = diag(d) B diag(b))."""
 
+    @classmethod
+    def apply(cls, *args):
+        if cls is RunVeRAFunction:
+            y = _native().vera(*args)
+            if y is not None:
+                return y
+        return super().apply(*args)
+
     @staticmethod
     def forward(ctx, x, W, A, B, d, b, bias, scale, pair):
         fwd, bwd = pair
@@ -277,6 +287,14 @@ class RunDoRAFunction(torch.autograd.Function):
     """y = x ((W + scale A B) diag(m / c)) + bias, c the column norms of W + scale A B held constant in the backward
     pass; gradients for x, A, B and m (runlora_dora_forward / runlora_dora_backward: forward2 and one of the merged
     backward graphs, the merge kernel scaling W's columns on the way)."""
+
+    @classmethod
+    def apply(cls, *args):
+        if cls is RunDoRAFunction:
+            y = _native().dora(*args)
+            if y is not None:
+                return y
+        return super().apply(*args)
 
     @staticmethod
     def forward(ctx, x, W, A, B, m, bias, scale, bwd):
