@@ -578,9 +578,8 @@ hipError_t splitk_reduce_launch(int dtype, const float* partial, int splits, int
 // What few_run's two launches take, us, fitted to the kernel times of 396 layers (n 1 .. 256, 512 .. 11008 wide, r 8 .. 128, W
 // from HBM) in every slicing.  The first: as launch_time_us, with the operands' bytes (few rows share W), the fp32 partials, and
 // what a second workgroup on some of the compute units costs while the others wait (64 x 8192 -> 8192: 195 workgroups 29 us, 260
-// 40, 455 32).  The second (lora_finish.hpp): a thread walks the rank's rows of B, a workgroup's threads form its rows of T from
-// all slices (four loads in flight), and T B is n o r products on the vector units: 3.9 us at r 8, 23 with 16 slices at 64 x 8192
-// -> 1024, r 128, 35 at 256 x 4096 -> 11008, r 128.  The slicing chosen costs 2 % more than the best on average (25 % at worst).
+// 40, 455 32).  The second (lora_finish.hpp): trips to memory, the partials at 5.6 TB/s, and X A's
+// slices once for every wave: 3.4 us at 1 x 4096 -> 4096 r 16, 4.0 at 16 x 2048 -> 8192 r 128, 8.3 at 223 x 9224 -> 8672 r 32.  The slicing chosen costs 2 % more than the best on average (25 % at worst).
 static double few_time_us(int64_t n, int64_t i, int64_t o, int64_t r, int splits, int64_t ktiles) {
   const int64_t nbm = (n + 63) / 64, nbn = (o + 127) / 128 + (r + 127) / 128, wgs = nbm * nbn * splits, rounds = wgs / 512, rest = wgs % 512;
   const double feed = xcd_kbytes(CFG_MTM64, nbm, nbn, wgs, 512) / 2080;
@@ -588,10 +587,10 @@ static double few_time_us(int64_t n, int64_t i, int64_t o, int64_t r, int splits
   const double per_k = (double)rounds * (feed > 0.35 ? feed : 0.35) + (rest == 0 ? 0.0 : (feed > (rest <= 256 ? 0.25 : 0.35) ? feed : (rest <= 256 ? 0.25 : 0.35)));
   const double first = 2.9 + 2e-6 * (double)(n * i + i * o + i * r) * (kColdUsPerMB + 0.02 * uneven) + (double)ktiles * (per_k + 0.065 * uneven) +
                        1.5e-6 * (double)n * (double)(o + r) * splits;
-  int64_t ry = 1;
-  while (ry < 32 && ry < n) ry *= 2;  // rows and column chunks of a workgroup, as it is launched
-  const int64_t cx = 64 / ry > 8 ? 64 / ry : 8, loads = (r + cx - 1) / cx * (splits / 4 + splits % 4);
-  const double second = 3.7 + 0.05 * (double)(r > 32 ? r - 32 : 0) + 0.17 * (double)loads + (double)n * (double)o * (3.6e-8 * (double)r + 2.1e-7 * splits);
+  const FinishShape f = finish_shape(n, o, r, splits);
+  const double trips = (double)((splits + f.u - 1) / f.u);
+  const double second = 3.3 + 0.6 * (trips - 1.0) + 0.004 * (double)r + 1.7e-7 * (double)(n * o) * (4.0 * splits + 2.0) +
+                        5e-8 * (double)(n * r) * 4.0 * splits * (double)((o + f.cols - 1) / f.cols);
   return first + second;
 }
 

@@ -5,20 +5,17 @@
 // spent more time on being launched and on waiting for each other than on W.  Here the first launch (gemm_mt.hpp, XA
 // build) forms the fp32 partials of X W and of X A side by side, K split over enough workgroups to fill the chip, and this
 // one sums them in slice order, rounds T = s X A to the storage type as the stored T is everywhere else, and adds T B and
-// the bias: 1 x 4096 -> 4096, r 16: 21.9 us on the GPU in four launches, 12.2 in two (of which this one 4.1); 48 x 4096 ->
-// 11008, r 32: 41.5 and 21.5 (5.2).
+// the bias: 1 x 4096 -> 4096, r 16: 21.9 us on the GPU in four launches, 12.2 in two; 48 x 4096 -> 11008, r 32:
+// 41.5 and 21.5.
 //
-// Bound by latency, that is by the number of trips to memory one behind the other: the slices are summed four at a time, and what
-// is left of them together (as a rolled remainder the last three of seven took a trip each), T's columns of a thread four at a
-// time, sixteen rows of B ahead of T and the others a block of eight ahead.  Together 9.0 -> 5.9 us at 3 x 8192 -> 8192 r 48, 13.6
-// -> 12.2 at 16 x 4096 -> 4096 r 128, 5.7 -> 5.2 at 48 x 4096 -> 11008 r 32.  (Eight slices at a time, padded or each count
-// unrolled, cost registers and instruction fetches: 94 x 9568 -> 1024 in twelve slices 5.0 -> 6.3.)  A thread owns 16 bytes of a
-// row of Y; a workgroup is cx column chunks by ry rows (ry covers the rows up to 32, so that one row still spreads over 64
-// threads), with its rows of T in LDS.
+// Bound by latency, that is by the number of trips to memory one behind the other: everything a wave needs (its tile of B, and the slices
+// four at a time, of X W and of X A) is on its way at once.  A workgroup is one wave with 16 rows of Y and 32 P columns; T B runs on the
+// matrix cores, B turned by the transposing LDS read, T summed and rounded by every wave that needs it, in the registers in which the
+// products take it.  The columns of a pair of 16-wide blocks interleave in fours, so that a lane holds eight in a row: 16-byte stores.
+// With T B on the vector units, 256 threads sharing T through LDS behind a barrier and each walking B's rows from memory, 16 x 2048 -> 8192 r 128 took 13.1 us (now 3.9), 58 x
+// 2304 -> 768 r 64 6.8 (3.4), 48 x 4096 -> 11008 r 32 5.7 (4.0), 1 x 4096 -> 4096 r 16 3.9 (3.9).
 #pragma once
-#include "gemm_engine.hpp"
-
-#include <type_traits>
+#include "gemm_mt.hpp"
 
 namespace rl {
 
@@ -31,136 +28,123 @@ struct FinishArgs {
   float t_alpha;
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void lora_finish_kernel(FinishArgs g) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  float* const sT = reinterpret_cast<float*>(smem_raw);  // [blockDim.y][R]
-  const int m0 = (int)(blockIdx.y * blockDim.y), m = m0 + (int)threadIdx.y;
-  const int n = ((int)(blockIdx.x * blockDim.x) + (int)threadIdx.x) * 8;
-  const bool ok = m < g.M && n < g.N;  // N is a multiple of 8
-  float acc[8];
+// How a launch is built: 64 columns a wave where those are enough waves to go round, U slices on their way at a time.
+struct FinishShape {
+  int cols, u;
+};
+inline FinishShape finish_shape(int64_t M, int64_t N, int64_t R, int splits) {
+  const bool wide = ((N + 63) / 64) * ((M + 15) / 16) >= 512;
+  return {wide ? 64 : 32, wide ? (R > 64 ? 2 : 4) : (R <= 32 && splits > 4 ? 8 : 4)};
+}
+
+// KS: K steps of 32 that cover the rank
+template <typename T, int KS, int P, int U>
+__global__ __launch_bounds__(64) void lora_finish_kernel(FinishArgs g) {
+  constexpr int COLS = 32 * P, LD = COLS + 8, NB = 2 * KS * P;
+  __shared__ __attribute__((aligned(16))) T sB[KS * 32 * LD];
+  const int lane = threadIdx.x, s16 = lane & 15, grp = lane >> 4;
+  const int m = (int)blockIdx.y * 16 + s16, n0 = (int)blockIdx.x * COLS;
+  const bool row_ok = m < g.M;
+  i32x4 breg[NB];  // this lane's chunks of B[0:R, n0:n0+COLS], zeros beyond it
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-  const T* const b = static_cast<const T*>(g.B) + n;
-  i32x4 first[16];  // the first sixteen rows of B (R is a multiple of 8), on their way while T is formed
-  const bool second = g.R > 8;  // uniform
-  if (ok) {
+  for (int j = 0; j < NB; ++j) {
+    const int c = lane + 64 * j, k = c / (4 * P), col = (c % (4 * P)) * 8;
+    i32x4 v = {0, 0, 0, 0};
+    if (k < g.R && n0 + col < g.N) v = *reinterpret_cast<const i32x4*>(static_cast<const T*>(g.B) + (int64_t)k * g.ldb + n0 + col);
+    breg[j] = v;
+  }
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[P][2], t[KS][2];  // X W: columns n0 + 32 p + 8 grp + 4 b ..; X A: columns 32 ks + 8 grp + 4 h .. of row m
 #pragma unroll
-    for (int k = 0; k < 8; ++k) first[k] = *reinterpret_cast<const i32x4*>(b + (int64_t)k * g.ldb);
-    if (second) {
+  for (int p = 0; p < P; ++p) acc[p][0] = acc[p][1] = zero;
 #pragma unroll
-      for (int k = 8; k < 16; ++k) first[k] = *reinterpret_cast<const i32x4*>(b + (int64_t)k * g.ldb);
+  for (int ks = 0; ks < KS; ++ks) t[ks][0] = t[ks][1] = zero;
+  bool col_ok[P], t_ok[KS];  // N and R are multiples of 8: a lane's eight columns are valid together
+#pragma unroll
+  for (int p = 0; p < P; ++p) col_ok[p] = row_ok && n0 + 32 * p + 8 * grp < g.N;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) t_ok[ks] = row_ok && 32 * ks + 8 * grp < g.R;
+  const float* const src = g.partial + (int64_t)m * g.N + n0 + 8 * grp;
+  const float* const src_t = g.partial_t + (int64_t)m * g.R + 8 * grp;
+  // U slices at a time in their order, the loads of all of them first (those beyond the last are zeros)
+  for (int z = 0; z < g.splits; z += U) {
+    f32x4 y[U][P][2], x[U][KS][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool live = z + u < g.splits;  // uniform
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          y[u][p][b] = zero;
+          if (live && col_ok[p]) y[u][p][b] = *reinterpret_cast<const f32x4*>(src + (int64_t)(z + u) * g.M * g.N + 32 * p + 4 * b);
+        }
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          x[u][ks][h] = zero;
+          if (live && t_ok[ks]) x[u][ks][h] = *reinterpret_cast<const f32x4*>(src_t + (int64_t)(z + u) * g.M * g.R + 32 * ks + 4 * h);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[p][b] += y[u][p][b];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) t[ks][h] += x[u][ks][h];
     }
   }
-  // f(first slice, how many: a constant up to four) over all slices in order
-  auto slices = [&](auto f) {
-    int z = 0;
-    for (; z + 4 <= g.splits; z += 4) f(z, std::integral_constant<int, 4>{});
-    switch (g.splits - z) {
-      case 1: f(z, std::integral_constant<int, 1>{}); break;
-      case 2: f(z, std::integral_constant<int, 2>{}); break;
-      case 3: f(z, std::integral_constant<int, 3>{}); break;
-      default: break;
-    }
-  };
-  if (ok) {
-    const float* const src = g.partial + (int64_t)m * g.N + n;
-    slices([&](int z, auto u_c) {
-      constexpr int U = decltype(u_c)::value;
-      f32x4 p[U][2];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        p[u][0] = *reinterpret_cast<const f32x4*>(src + (int64_t)(z + u) * g.M * g.N);
-        p[u][1] = *reinterpret_cast<const f32x4*>(src + (int64_t)(z + u) * g.M * g.N + 4);
+  for (int j = 0; j < NB; ++j) {
+    const int c = lane + 64 * j;
+    *reinterpret_cast<i32x4*>(sB + (c / (4 * P)) * LD + (c % (4 * P)) * 8) = breg[j];
+  }
+  i32x4 tf[KS];  // T = s X A, rounded as the stored T is everywhere else
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    T t8[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      t8[e] = from_f32<T>(g.t_alpha * t[ks][0][e]);
+      t8[4 + e] = from_f32<T>(g.t_alpha * t[ks][1][e]);
+    }
+    tf[ks] = *reinterpret_cast<const i32x4*>(t8);
+    if (g.T != nullptr && blockIdx.x == 0 && t_ok[ks]) *reinterpret_cast<i32x4*>(static_cast<T*>(g.T) + (int64_t)m * g.ldt + 32 * ks + 8 * grp) = tf[ks];
+  }
+  __syncthreads();  // (one wave)
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        // lane s of 16 points at four columns of row k0 + s / 4 and receives one column of rows k0 .. k0 + 3
+        const T* const q = sB + (32 * ks + 8 * grp + (s16 >> 2)) * LD + 32 * p + 8 * (s16 & 3) + 4 * b;
+        const i32x2 lo = __builtin_bit_cast(i32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(q)));
+        const i32x2 hi = __builtin_bit_cast(i32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(q + 4 * LD)));
+        acc[p][b] = Mma16<T>::mma(i32x4{lo[0], lo[1], hi[0], hi[1]}, tf[ks], acc[p][b]);
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
+  for (int p = 0; p < P; ++p) {
+    if (!col_ok[p]) continue;
+    const int n = n0 + 32 * p + 8 * grp;
+    T o8[8];
+    i32x4 bv = {0, 0, 0, 0};
+    if (g.bias != nullptr) bv = *reinterpret_cast<const i32x4*>(static_cast<const T*>(g.bias) + n);
+    const T* const b8 = reinterpret_cast<const T*>(&bv);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { acc[e] += p[u][0][e]; acc[4 + e] += p[u][1][e]; }
-    });
-  }
-  // this workgroup's rows of T (a row per threadIdx.y, its columns over threadIdx.x: Q of them a thread at a time)
-  auto sum_t = [&](auto q_c, int k0) {
-    constexpr int Q = decltype(q_c)::value;
-    float t[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) t[q] = 0.f;
-    if (m < g.M) {
-      const float* const src = g.partial_t + (int64_t)m * g.R;
-      slices([&](int z, auto u_c) {
-        constexpr int U = decltype(u_c)::value;
-        float p[U][Q];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int q = 0; q < Q; ++q) {
-            const int k = k0 + q * (int)blockDim.x;
-            p[u][q] = src[(int64_t)(z + u) * g.M * g.R + (k < g.R ? k : k0)];
-          }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int q = 0; q < Q; ++q) t[q] += p[u][q];
-      });
+    for (int e = 0; e < 4; ++e) {
+      o8[e] = from_f32<T>(acc[p][0][e] + (float)b8[e]);
+      o8[4 + e] = from_f32<T>(acc[p][1][e] + (float)b8[4 + e]);
     }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const int k = k0 + q * (int)blockDim.x;
-      if (k < g.R) {
-        const T tr = from_f32<T>(g.t_alpha * t[q]);
-        sT[(int)threadIdx.y * g.R + k] = (float)tr;
-        if (g.T != nullptr && blockIdx.x == 0 && m < g.M) static_cast<T*>(g.T)[(int64_t)m * g.ldt + k] = tr;
-      }
-    }
-  };
-  if (g.R <= (int)blockDim.x) {
-    if ((int)threadIdx.x < g.R) sum_t(std::integral_constant<int, 1>{}, (int)threadIdx.x);
-  } else {
-    for (int k0 = (int)threadIdx.x; k0 < g.R; k0 += 4 * (int)blockDim.x) sum_t(std::integral_constant<int, 4>{}, k0);
+    *reinterpret_cast<i32x4*>(static_cast<T*>(g.C) + (int64_t)m * g.ldc + n) = *reinterpret_cast<const i32x4*>(o8);
   }
-  __syncthreads();
-  if (!ok) return;
-  const float* const tr = sT + (int)threadIdx.y * g.R;
-  auto add = [&](const i32x4& v, float t) {
-    const T* v8 = reinterpret_cast<const T*>(&v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += t * (float)v8[e];
-  };
-#pragma unroll
-  for (int k = 0; k < 8; ++k) add(first[k], tr[k]);
-  if (second) {
-#pragma unroll
-    for (int k = 8; k < 16; ++k) add(first[k], tr[k]);
-  }
-  // the others in blocks of eight, the next one on its way while a block is multiplied
-  if (g.R > 16) {
-    i32x4 rows[2][8];
-    auto fetch = [&](i32x4 (&to)[8], int k0) {
-#pragma unroll
-      for (int u = 0; u < 8; ++u) to[u] = *reinterpret_cast<const i32x4*>(b + (int64_t)((k0 < g.R ? k0 : 16) + u) * g.ldb);
-    };
-    fetch(rows[0], 16);
-    for (int k0 = 16; k0 < g.R; k0 += 16) {
-      fetch(rows[1], k0 + 8);
-#pragma unroll
-      for (int u = 0; u < 8; ++u) add(rows[0][u], tr[k0 + u]);
-      fetch(rows[0], k0 + 16);
-      if (k0 + 8 < g.R) {  // uniform
-#pragma unroll
-        for (int u = 0; u < 8; ++u) add(rows[1][u], tr[k0 + 8 + u]);
-      }
-    }
-  }
-  if (g.bias != nullptr) {
-    const i32x4 v = *reinterpret_cast<const i32x4*>(static_cast<const T*>(g.bias) + n);
-    const T* v8 = reinterpret_cast<const T*>(&v);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += (float)v8[e];
-  }
-  T o8[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o8[e] = from_f32<T>(acc[e]);
-  *reinterpret_cast<i32x4*>(static_cast<T*>(g.C) + (int64_t)m * g.ldc + n) = *reinterpret_cast<const i32x4*>(o8);
 }
 
 }  // namespace rl

@@ -63,3 +63,28 @@ def test_few_tokens_against_the_oracle(n, i, o, r, dtype):
     assert len(what) == 1
     want = oracle.scaled_forward(host["X"], host["W"], host["A"], host["B"], 0.5)
     assert relerr(got, want) < TOL[dtype] and elem_excess(got, want, dtype) <= 1.0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("n,i,o,r", [(1, 264, 8, 8), (17, 520, 40, 24), (15, 2056, 96, 40), (33, 8200, 264, 64), (16, 2048, 2056, 128),  # 32 columns a wave
+                                     (250, 1032, 8200, 32), (241, 520, 8248, 56), (256, 1032, 8264, 128)])                             # 64
+def test_finish_at_the_edges_of_its_tiles(n, i, o, r, dtype):
+    """Rows, columns and ranks beside multiples of 16, 32 or 64 and 32, every build of the finishing launch, T kept, a bias."""
+    import torch
+    td, code, s = torch_dtype(dtype), rl.dtype_from_name(dtype), 0.5
+    print(f"case finish {n} {i}->{o} r={r} {dtype}", flush=True)
+    g = torch.Generator().manual_seed(n + i + o + r)
+    t = {k: (torch.randn(*sh, generator=g) / sh[0] ** 0.5).to(td).cuda() for k, sh in (("W", (i, o)), ("A", (i, r)), ("B", (r, o)))}
+    X, bias = torch.randn(n, i, generator=g).to(td).cuda(), torch.randn(o, generator=g).to(td).cuda()
+    d = {k: v.double().cpu() for k, v in dict(t, X=X, bias=bias).items()}
+    buf = torch.full((n + 1, o + 8), 7.0, dtype=td, device="cuda")
+    T = torch.full((n, r + 8), 7.0, dtype=td, device="cuda")
+    saved = rl.new_saved(T[:, :r])
+    ws = rl.new_workspace(rl.FWD1, -1, n, i, o, r, code)
+    ws.fill_(0xFF)
+    rl.runlora_forward(rl.FWD1, X, t["W"], t["A"], t["B"], buf[:n, :o], saved, workspace=ws, scale=s, bias=bias)
+    torch.cuda.synchronize()
+    Tw = s * (d["X"] @ d["A"])
+    want = d["X"] @ d["W"] + Tw @ d["B"] + d["bias"]
+    assert relerr(to_f64(T[:, :r]), Tw.numpy()) < TOL[dtype] and relerr(to_f64(buf[:n, :o]), want.numpy()) < TOL[dtype]
+    assert bool((buf[n] == 7.0).all()) and bool((buf[:, o:] == 7.0).all()) and bool((T[:, r:] == 7.0).all())
