@@ -189,10 +189,10 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap = ~
 // modelled time of that launch (and its reduce pass) in us
 double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan);
 
-// ---- rank-r products with r > 32 on the middle-sized matrix-core kernel, 16-bit types, no mask ------------------
-// One product (gemm_run with the plan) or two in one launch (mt_pair_run); `cap` = scratch bytes the plan may use.  False
-// where the streaming kernel is modelled faster.
-bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us = nullptr);
+// ---- rank-r products with r > 32 on the middle-sized matrix-core kernel, 16-bit types ------------------
+// One product (gemm_run with the plan) or two in one launch (mt_pair_run); `cap` = scratch bytes the plan may use, slice_us = what
+// slices cost besides.  False where the streaming kernel is modelled faster.
+bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us = nullptr, double slice_us = 0.0);
 GemmDesc rank_desc(int dtype, const SkinnyDesc& d);  // the product as gemm_run takes it
 struct MtPairPlan {
   int cfg[2] = {0, 0};  // CFG_MTN64 / CFG_MTM64
@@ -202,7 +202,7 @@ struct MtPairPlan {
   double us = 0;
 };
 // alone_us: what the two take otherwise (0: a launch of the streaming kernel)
-bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, double alone_us = 0.0);
+bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, double alone_us = 0.0, double slice_us = 0.0);
 hipError_t mt_pair_run(int dtype, const SkinnyDesc* d, const MtPairPlan& plan, float* scratch, hipStream_t stream);
 hipError_t skinny_run(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan, float* scratch,
                       hipStream_t stream);

@@ -727,12 +727,12 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
     const double chain = plan.rt == 1 ? 4.4 + 0.35 * tiles : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles);
     if (chain > us) us = chain;
   }
-  for (int w = 0; w < nprob; ++w) {
-    // the masked problem's chain is longer, its mask arithmetic included (T of 280 x 2304 r 64 18.5 us, of 700 x 3000 r 96 32.7; dA, dB of 1237 x
-    // (2056 + 5464) r 64 15.0, of 960 x (768 + 4864) r 128 18.8)
-    if (d[w].drop_thr == 0 || plan.rt == 1) continue;
+  const bool masked = d[0].drop_thr != 0 || (nprob == 2 && d[1].drop_thr != 0);
+  for (int w = 0; w < nprob && masked && plan.rt > 1; ++w) {
+    // the chains of a launch with a masked problem, whose own is longer, its mask arithmetic included (T of 280 x 2304 r 64 18.5 us, of 700 x
+    // 3000 r 96 32.7; {Z1, T} of 960 x (4864 + 768) r 128 34.5; dA, dB of it 18.8, of 1237 x (2056 + 5464) r 64 15.0)
     const double tiles = (double)(((d[w].K + 63) / 64 + 4 * plan.splits - 1) / (4 * plan.splits));
-    const double chain = d[w].a_strided ? (plan.rt == 2 ? 6.0 + 1.8 * tiles : 8.0 + 3.2 * tiles) : (plan.rt == 2 ? 5.8 + 1.4 * tiles : 6.9 + 2.2 * tiles);
+    const double chain = d[w].drop_thr == 0 ? (d[w].a_strided ? 0.0 : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles)) : d[w].a_strided ? (plan.rt == 2 ? 6.0 + 1.8 * tiles : 8.0 + 3.2 * tiles) : (plan.rt == 2 ? 5.8 + 1.4 * tiles : 6.9 + 2.2 * tiles);
     if (chain > us) us = chain;
   }
   return us + (plan.splits > 1 ? 4.0 + outs * 8.0 * plan.splits / 7.5e6 : 0.0);
@@ -784,16 +784,11 @@ static double wide_rank_us(bool a_strided, bool masked, int64_t wgs, int64_t kti
   return us > floor_us ? us : floor_us;
 }
 
-// A masked product leaves one launch of the streaming kernel for two where it takes slices here.  Over small operands the layer's host
-// work is what it waits for, and a launch is 3 us of that: 280 x 2304 -> 768 r 64, T 18.6 us there and 8.5 + 4.5 here, ran 84.7 us a pass on the
-// streaming kernel and 91.1 with T and {Z1, T} in slices; 960 x 768 -> 4864 r 128 106 and 91.
-static double masked_slices_us(const SkinnyDesc& d, double bytes) { return d.drop_thr != 0 && bytes < 4e6 ? 7.5 : 0.0; }
-
 static bool rank_shape_ok(int dtype, const SkinnyDesc& d) {
   return dtype != DT_F32 && d.N > 32 && d.M > 32 && (d.drop_thr == 0 || (!d.b_kcontig && !d.trans_out));
 }
 
-bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us) {
+bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, double* plan_us, double slice_us) {
   if (!rank_shape_ok(dtype, d)) return false;
   const GemmDesc g = rank_desc(dtype, d);
   const int cfg = g.N == d.N ? CFG_MTN64 : CFG_MTM64;
@@ -807,7 +802,7 @@ bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, doubl
     if ((kt + per - 1) / per != s) continue;  // no empty slice
     const size_t part = s > 1 ? (size_t)s * (size_t)g.M * (size_t)g.N * sizeof(float) : 0;
     if (part > cap) break;
-    const double us = rank_time_us(g.a_strided != 0, d.drop_thr != 0, nbm * nbn * s, per, bytes) + split_time_us(g.M, g.N, s) + (s > 1 ? masked_slices_us(d, bytes) : 0.0);
+    const double us = rank_time_us(g.a_strided != 0, d.drop_thr != 0, nbm * nbn * s, per, bytes) + split_time_us(g.M, g.N, s) + (s > 1 ? slice_us : 0.0);
     if (us >= best) continue;
     best = us;
     found = true;
@@ -826,7 +821,7 @@ bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, doubl
   return found;
 }
 
-bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, double alone_us) {
+bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, double alone_us, double slice_us) {
   if (!rank_shape_ok(dtype, d[0]) || !rank_shape_ok(dtype, d[1])) return false;
   int64_t tiles[2], kt[2];
   double bytes = 0, best = 1e30;
@@ -859,7 +854,7 @@ bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, 
       }
     }
     if (part > cap) break;
-    us += rank_time_us(d[0].a_strided != 0, d[0].drop_thr != 0 || d[1].drop_thr != 0, wgs, per, bytes) + (part > 0 ? 3.0 + masked_slices_us(d[0].drop_thr != 0 ? d[0] : d[1], bytes) : 0.0);
+    us += rank_time_us(d[0].a_strided != 0, d[0].drop_thr != 0 || d[1].drop_thr != 0, wgs, per, bytes) + (part > 0 ? 3.0 + slice_us : 0.0);
     if (us < best) {
       best = us;
       plan->partial_bytes = part;
@@ -892,7 +887,7 @@ bool mt_pair_plan(int dtype, const SkinnyDesc* d, size_t cap, MtPairPlan* plan, 
         }
       }
       if (part > cap) break;
-      us += wide_rank_us(d[0].a_strided != 0, d[0].drop_thr != 0 || d[1].drop_thr != 0, wgs, most, bytes) + (part > 0 ? 3.0 + masked_slices_us(d[0].drop_thr != 0 ? d[0] : d[1], bytes) : 0.0);
+      us += wide_rank_us(d[0].a_strided != 0, d[0].drop_thr != 0 || d[1].drop_thr != 0, wgs, most, bytes) + (part > 0 ? 3.0 + slice_us : 0.0);
       if (us < best) {
         best = us;
         plan->wide = true;
