@@ -160,7 +160,7 @@ struct FewPlan {
 };
 constexpr int64_t kFewMaxRows = 256, kFewMaxR = 128;
 // us per MB of operands that few rows read from HBM, beyond launch_time_us (in FewPlan::us; to be added to what it is compared with)
-constexpr double kColdUsPerMB = 0.09;
+constexpr double kColdUsPerMB = 0.03;
 // scratch_bytes: what the call has for partials whatever route it takes
 FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_bytes);
 hipError_t few_run(int dtype, const FewDesc& d, const FewPlan& plan, float* scratch, hipStream_t stream);

@@ -575,22 +575,23 @@ hipError_t splitk_reduce_launch(int dtype, const float* partial, int splits, int
 
 // ---- few-token forward ---------------------------------------------------------------------------------
 
-// What few_run's two launches take, us, fitted to the kernel times of 396 layers (n 1 .. 256, 512 .. 11008 wide, r 8 .. 128, W
-// from HBM) in every slicing.  The first: as launch_time_us, with the operands' bytes (few rows share W), the fp32 partials, and
-// what a second workgroup on some of the compute units costs while the others wait (64 x 8192 -> 8192: 195 workgroups 29 us, 260
-// 40, 455 32).  The second (lora_finish.hpp): trips to memory, the partials at 5.6 TB/s, and X A's
-// slices once for every wave: 3.4 us at 1 x 4096 -> 4096 r 16, 4.0 at 16 x 2048 -> 8192 r 128, 8.3 at 223 x 9224 -> 8672 r 32.  The slicing chosen costs 2 % more than the best on average (25 % at worst).
+// What few_run's two launches take, us, fitted to 2100 of them timed (301 layers, n 1 .. 256, 512 .. 11008 wide, r 8 .. 128, W from HBM, in
+// every slicing; standard deviation 9 %).  The first: K tiles of one, two, ... workgroups on a compute unit, W once from HBM and once more
+// from the caches for every further 64 rows, the partials, and what a second workgroup on some of the units costs while the others wait
+// (64 x 8192 -> 8192: 195 workgroups 29 us, 260 40, 455 32).  The second (lora_finish.hpp): trips to memory, the partials, and what waves read
+// of others' operands: X A's slices once for every block of columns and B once for every 16 rows, which is most of it for many rows at
+// a high rank (48 x 4096 -> 11008 r 32 in two slices 4.0 us, 256 x 4096 -> 11008 r 128 17).  Over those layers the route taken is 1.9 % slower
+// than the best of both routes and all slicings (4.6 % where neither W's further passes nor B's were counted: 245 x 4608 -> 9648 r 128 74.2 us for 51.4).
 static double few_time_us(int64_t n, int64_t i, int64_t o, int64_t r, int splits, int64_t ktiles) {
   const int64_t nbm = (n + 63) / 64, nbn = (o + 127) / 128 + (r + 127) / 128, wgs = nbm * nbn * splits, rounds = wgs / 512, rest = wgs % 512;
-  const double feed = xcd_kbytes(CFG_MTM64, nbm, nbn, wgs, 512) / 2080;
   const double uneven = wgs > 256 && wgs < 512 ? (double)(512 - wgs) / 256.0 : 0.0;
-  const double per_k = (double)rounds * (feed > 0.35 ? feed : 0.35) + (rest == 0 ? 0.0 : (feed > (rest <= 256 ? 0.25 : 0.35) ? feed : (rest <= 256 ? 0.25 : 0.35)));
-  const double first = 2.9 + 2e-6 * (double)(n * i + i * o + i * r) * (kColdUsPerMB + 0.02 * uneven) + (double)ktiles * (per_k + 0.065 * uneven) +
-                       1.5e-6 * (double)n * (double)(o + r) * splits;
+  const double load = 2.0 * (double)rounds + (rest == 0 ? 0.0 : (rest <= 256 ? 1.0 : 2.0)), wmb = 2e-6 * (double)(i * o);
+  const double first = 3.1 + wmb * (0.1 + 0.028 * (double)(nbm - 1) + 0.009 * uneven) + 0.42e-6 * (double)(n * i) +
+                       (double)ktiles * (0.29 * load + 0.0044 * (double)(nbm - 1)) + 0.81e-6 * (double)n * (double)(o + r) * splits;
   const FinishShape f = finish_shape(n, o, r, splits);
   const double trips = (double)((splits + f.u - 1) / f.u);
-  const double second = 3.3 + 0.6 * (trips - 1.0) + 0.004 * (double)r + 1.7e-7 * (double)(n * o) * (4.0 * splits + 2.0) +
-                        5e-8 * (double)(n * r) * 4.0 * splits * (double)((o + f.cols - 1) / f.cols);
+  const double second = 2.8 + 0.93 * (trips - 1.0) + (r > 64 ? 0.9 : 0.0) + 0.62e-6 * (double)(n * o) * (splits + 1.0) +
+                        0.28e-6 * (double)(n * r) * splits * (double)((o + f.cols - 1) / f.cols) + 0.2e-6 * (double)(r * o) * (double)((n + 15) / 16);
   return first + second;
 }
 

@@ -183,3 +183,11 @@ def test_gradient_pairs_of_few_bytes_stay_on_narrow_tiles(probe):
     small = [(1480, 5808, 4920, 72), (8525, 1144, 960, 80), (4858, 544, 2640, 128)]
     large = [(8192, 4096, 4096, 128), (8241, 7560, 376, 72), (8257, 1032, 2056, 72), (8193, 520, 3080, 128)]
     assert [p[0] for p in probe("pair", small + large)] == [0] * 3 + [1] * 4
+
+
+def test_few_token_route_leaves_many_rows_of_large_layers(probe):
+    """Every further 64 rows read W again and every 16 rows B: 245 x 4608 -> 9648 r 128 takes 74.2 us by the few-token route, 51.4 by T = X A
+    and [X|T] [W;B], 256 x 10176 -> 7008 r 64 85.0 and 67.3, 170 x 7824 -> 10128 r 32 77.4 and 68.0; 93 x 2904 -> 8144 r 128 24.3 and 27."""
+    large = [(245, 4608, 9648, 128), (256, 10176, 7008, 64), (170, 7824, 10128, 32), (256, 1752, 10152, 128)]
+    assert [p[0] for p in probe("few", large)] == [0] * 4
+    assert [p[0] for p in probe("few", [(93, 2904, 8144, 128), (32, 4096, 4096, 64), (64, 8192, 8192, 16)])] == [1] * 3
