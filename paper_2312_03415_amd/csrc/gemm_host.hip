@@ -600,7 +600,7 @@ FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_byte
   FewPlan best;
   if (n < 1 || n > kFewMaxRows || r > kFewMaxR || n > (1LL << 30)) return best;
   const int64_t kt = (i + 63) / 64;
-  for (int s = 1; s <= 16 && (s == 1 || kt / s >= 4); ++s) {
+  for (int s = 1; s <= 16 && (s == 1 || kt / s >= 6); ++s) {
     const int64_t per = (kt + s - 1) / s;
     if ((kt + per - 1) / per != s) continue;  // no empty slice
     if ((size_t)s * (size_t)n * (size_t)(o + r) * sizeof(float) > scratch_bytes) break;
