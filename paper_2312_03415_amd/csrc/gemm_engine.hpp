@@ -117,13 +117,13 @@ __device__ __forceinline__ uint32_t drop_mix(uint32_t x) {
   x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
   return x;
 }
-// bit 7 of byte k of the result is set iff byte k of h is >= thr (1 <= thr <= 255), all four bytes at once:
-// the low seven bits are compared by an addition that carries into bit 7 (0x7F + 0x80 at most: no carry between
-// bytes), the top bits decide the rest.  thr is uniform, so its part is scalar arithmetic.
+// bit 7 of byte k of the result is set iff byte k of h is >= thr (1 <= thr <= 255; the other bits mean nothing), all four
+// bytes at once: the low seven bits are compared by an addition that carries into bit 7 (0x7F + 0x80 at most: no carry
+// between bytes), the top bits decide the rest: h & lo beyond a threshold of 128, h | lo below, which is the majority
+// of h, lo and a constant.  thr is uniform, so its part is scalar arithmetic.
 __device__ __forceinline__ uint32_t drop_ge_bytes(uint32_t h, uint32_t thr) {
-  const uint32_t lo = (h & 0x7F7F7F7Fu) + (0x80u - (thr & 0x7Fu)) * 0x01010101u;
-  const uint32_t ge = (thr & 0x80u) ? (h & lo) : (h | lo);
-  return ge & 0x80808080u;
+  const uint32_t lo = (h & 0x7F7F7F7Fu) + (0x80u - (thr & 0x7Fu)) * 0x01010101u, below = (thr & 0x80u) - 0x80u;
+  return (h & lo) | ((h | lo) & below);
 }
 // keep-masks of the four columns of group g: 0xFFFFFFFF / 0 per column
 __device__ __forceinline__ void drop_keep4(uint32_t g, uint32_t key, uint32_t thr, uint32_t (&keep)[4]) {
@@ -142,8 +142,8 @@ __device__ __forceinline__ f32x4 drop_acc4(f32x4 v, uint32_t g, uint32_t key, ui
   }
   return v;
 }
-// a 16-byte chunk of X whose first column belongs to group g (8 columns = groups g, g+1 for 16-bit
-// types; 4 columns = group g for fp32) with the dropped elements zeroed
+// a 16-byte chunk of X whose first column belongs to group g (8 columns = groups g, g+1 for 16-bit types, whose
+// widths are multiples of 8, so that g is even; 4 columns = group g for fp32) with the dropped elements zeroed
 template <typename T>
 __device__ __forceinline__ i32x4 drop_chunk(i32x4 v, uint32_t g, uint32_t key, uint32_t thr) {
   if constexpr (sizeof(T) == 4) {
@@ -151,13 +151,22 @@ __device__ __forceinline__ i32x4 drop_chunk(i32x4 v, uint32_t g, uint32_t key, u
     drop_keep4(g, key, thr, k0);
     return i32x4{(int)((uint32_t)v[0] & k0[0]), (int)((uint32_t)v[1] & k0[1]), (int)((uint32_t)v[2] & k0[2]), (int)((uint32_t)v[3] & k0[3])};
   } else {
-    // per hash: flags -> 0xFF / 0x00 per byte -> each byte doubled into a 16-bit lane mask (byte permute)
-    const uint32_t f0 = drop_ge_bytes(drop_mix(g ^ key), thr), f1 = drop_ge_bytes(drop_mix((g + 1) ^ key), thr);
-    const uint32_t m0 = (f0 - (f0 >> 7)) | f0, m1 = (f1 - (f1 >> 7)) | f1;
-    return i32x4{(int)((uint32_t)v[0] & __builtin_amdgcn_perm(m0, m0, 0x01010000u)),
-                 (int)((uint32_t)v[1] & __builtin_amdgcn_perm(m0, m0, 0x03030202u)),
-                 (int)((uint32_t)v[2] & __builtin_amdgcn_perm(m1, m1, 0x01010000u)),
-                 (int)((uint32_t)v[3] & __builtin_amdgcn_perm(m1, m1, 0x03030202u))};
+    // Two hashes of numbers that differ in bit 0 alone: they still do behind the first shift (which moves no bit there), and their
+    // products by the first multiplier differ by the multiplier, whose sign is that bit's: one multiplication of four saved
+    // (they take four times as long as other instructions).  Flags become 16-bit lane masks by the byte permute, whose selectors 8 to 11 repeat a
+    // sign: of bits 15 and 31 of its second operand and of its first.
+    constexpr uint32_t C1 = 0x7feb352du, C2 = 0x846ca68bu;
+    uint32_t x0 = g ^ key;
+    x0 ^= x0 >> 16;
+    const uint32_t odd = (uint32_t)((int32_t)(x0 << 31) >> 31);  // all ones where bit 0 of x0 is set
+    uint32_t h0 = x0 * C1, h1 = (C1 ^ odd) + h0 - odd;            // (x0 ^ 1) C1
+    h0 ^= h0 >> 15; h0 *= C2; h0 ^= h0 >> 16;
+    h1 ^= h1 >> 15; h1 *= C2; h1 ^= h1 >> 16;
+    const uint32_t f0 = drop_ge_bytes(h0, thr), f1 = drop_ge_bytes(h1, thr), e0 = f0 << 8, e1 = f1 << 8;
+    return i32x4{(int)((uint32_t)v[0] & __builtin_amdgcn_perm(e0, f0, 0x08080A0Au)),
+                 (int)((uint32_t)v[1] & __builtin_amdgcn_perm(e0, f0, 0x09090B0Bu)),
+                 (int)((uint32_t)v[2] & __builtin_amdgcn_perm(e1, f1, 0x08080A0Au)),
+                 (int)((uint32_t)v[3] & __builtin_amdgcn_perm(e1, f1, 0x09090B0Bu))};
   }
 }
 

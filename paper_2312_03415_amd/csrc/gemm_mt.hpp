@@ -304,17 +304,17 @@ __device__ __forceinline__ void gemm_mt_body(const GemmArgs& g, const int bx, co
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int p = (wave * P::IA + j) * 64 + lane;
-        uint32_t token, col;
+        uint32_t lane_g, tile_g;  // the chunk's group of columns: row drop_cpr + column / 4
         if constexpr (!P::A_STR) {
           const int row = p >> 3;
-          token = (uint32_t)(m0 + row);
-          col = (uint32_t)(tile_k * BK) + (uint32_t)(((p & 7) ^ ((row >> 1) & 7)) << 3);
+          lane_g = (uint32_t)(m0 + row) * g.drop_cpr + (uint32_t)(((p & 7) ^ ((row >> 1) & 7)) << 1);
+          tile_g = (uint32_t)(tile_k * (BK / 4));
         } else {
           const int row = p / (BM / 8);
-          token = (uint32_t)(tile_k * BK + row);
-          col = (uint32_t)m0 + (uint32_t)(((p % (BM / 8)) ^ mt_swz<BM>(row)) << 3);
+          lane_g = (uint32_t)row * g.drop_cpr + ((uint32_t)m0 >> 2) + (uint32_t)(((p % (BM / 8)) ^ mt_swz<BM>(row)) << 1);
+          tile_g = (uint32_t)(tile_k * BK) * g.drop_cpr;
         }
-        c[j] = drop_chunk<T>(c[j], token * g.drop_cpr + (col >> 2), g.drop_key, g.drop_thr);
+        c[j] = drop_chunk<T>(c[j], lane_g + tile_g, g.drop_key, g.drop_thr);
       }
       asm volatile("ds_write_b128 %4, %0\n\tds_write_b128 %4, %1 offset:1024\n\tds_write_b128 %4, %2 offset:2048\n\t"
                    "ds_write_b128 %4, %3 offset:3072\n\ts_waitcnt lgkmcnt(0)"

@@ -10,16 +10,16 @@
 //    them: wave w takes K tiles w, w+NWV, ...  Every wavefront runs its own global -> register -> LDS -> MFMA pipeline on a
 //    private LDS region: no workgroup barrier in the loop, the next tile's loads are in flight while the current one is
 //    multiplied.
-//  - MR = 2 (64 rows) is used by paired launches whose A operands are stored [K,M] (N <= 64, no LoRA dropout mask), where the
+//  - MR = 2 (64 rows) is used by paired launches whose A operands are stored [K,M] (N <= 64), where the
 //    64-row blocks fill more than half of the compute units: a block's rows are then columns of A, a 32-column strip is 64
 //    bytes per row of A, half a 128-byte line, and the other half has to come from the neighbouring workgroup's fetch staying
 //    in L2.  With 128-byte strips dA, dB of 4096 x (2048 + 8192) r 16 take 21.4 us, 25.0 without; with fewer blocks the chip's
 //    idle units cost more (skinny_plan).  Single launches keep 32 rows (dB of 4096 x 8192 alone: 18.8 -> 23.4 us).
 //  - NWV = 4 where loads bind: 8 or 16 waves make no plain launch that fills the chip faster (a compute unit fetches 50-60 bytes a
-//    ns, operand B's share included, whatever the number of waves).  A masked problem (LoRA dropout) in the [M,K] orientation is bound by
-//    its waves' mask arithmetic, one chain of instructions per wave: 16 waves (two tiles of loads in flight each) take 26.1
-//    us against 32.5 for T = (X o m) A of 4096 x 8192 r 16 (two K slices, reduce pass included), 24.6 against 36.2 for {Z1, Z2} of
-//    4096 x 8192 -> 2048.
+//    ns, operand B's share included, whatever the number of waves).  A masked problem (LoRA dropout) alone in the [M,K] orientation, whose
+//    mask arithmetic is a chain of instructions per wave, runs 16 (two tiles of loads in flight each): T = (X o m) A of 4096 x 8192 r 16 in two K
+//    slices 20.2 us, on 4 waves 18.9; 1024 x 4096 11.6 and 11.2, 2048 x 8192 r 8 whole 20.2 and 22.2: level since a mask costs half of what it
+//    did when 16 waves took 26.1 us for 32.5.
 //  - The waves' partial accumulators are summed through LDS in wave order and written once.  A grid
 //    that also splits K over workgroups (gridDim.y) writes fp32 partials that a second kernel sums
 //    in slice order.  No atomics: results are identical from run to run.
@@ -131,64 +131,65 @@ __device__ __forceinline__ void skinny_body(const SkinnyProblem& P, int bx, unsi
   const int span = t_end - t_begin;
   const int rot = span > 0 ? (bx * 5) % span : 0;
   int kst[DEPTH];  // k origin of the tile in each register stage (for the dropout mask)
+  // A lane's chunks of a tile at k origin 0, in bytes, beyond the buffer where they lie outside M or N; a tile adds its scalar part and the
+  // check against K.  Sums of 32 bits: what a check lets through is below 2 GiB.  (A whole offset behind && for every load became
+  // a branch around it: the waves, one or two to a SIMD, spent a tile's time on instructions, and the stages' loads got out of order with the
+  // mask's arithmetic between them.  Before / so, us: T of 1024 x 4096 r 16 11.4 / 8.7, 1237 x 2056 r 24 9.1 / 8.2, dA, dB of 5000 x (1024 +
+  // 1024) r 16 18.5 / 17.4; masked 2048 x (2048 + 2048) r 16 13.0 / 9.7, 8192 x (4096 + 4096) r 32 50.4 / 44.9.)
+  uint32_t abase[A_PER], bbase[B_PER];
+#pragma unroll
+  for (int j = 0; j < A_PER; ++j) {
+    const int c = lane + 64 * j;
+    if constexpr (!a_str) {  // tile [32 m][BK k]: 8 chunks per row
+      const int row = c >> 3;
+      abase[j] = m0 + row < M ? ((uint32_t)(m0 + row) * ulda + (uint32_t)((c & 7) * VE)) * (uint32_t)sizeof(T) : OOB;
+    } else {  // tile [BK k][MB m]: MB/VE chunks per row
+      constexpr int CPR = MB / VE;
+      const int col = m0 + (c % CPR) * VE;
+      abase[j] = col < M ? ((uint32_t)(c / CPR) * ulda + (uint32_t)col) * (uint32_t)sizeof(T) : OOB;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < B_PER; ++j) {
+    const int c = lane + 64 * j;
+    if constexpr (!b_kc) {  // tile [BK k][NB n]
+      constexpr int CPR = S::NB / VE;
+      const int col = (c % CPR) * VE;
+      bbase[j] = col < N ? ((uint32_t)(c / CPR) * uldb + (uint32_t)col) * (uint32_t)sizeof(T) : OOB;
+    } else {  // tile [NB n][BK k]: 8 chunks per row
+      const int row = c >> 3;
+      bbase[j] = row < N ? ((uint32_t)row * uldb + (uint32_t)((c & 7) * VE)) * (uint32_t)sizeof(T) : OOB;
+    }
+  }
   auto load_global = [&](int d, int q) {  // q = position in this workgroup's tile sequence
-    const bool live = q < span;
     int tq = q + rot;
     if (tq >= span) tq -= span;
     const int k0 = (t_begin + tq) * BK;
+    const int left = q < span ? K - k0 : 0;  // the tile's share of K; none beyond this workgroup's tiles
     if constexpr (DROP) kst[d] = k0;
+    // (a chunk outside M or N stays outside: its offset has bit 31 set, and a tile within K adds less than 2 GiB)
+    const uint32_t ak = (uint32_t)k0 * (a_str ? ulda : 1u) * (uint32_t)sizeof(T), bk = (uint32_t)k0 * (b_kc ? 1u : uldb) * (uint32_t)sizeof(T);
 #pragma unroll
     for (int j = 0; j < A_PER; ++j) {
-      const int c = lane + 64 * j;
-      bool ok;
-      uint32_t off;
-      if constexpr (!a_str) {  // tile [32 m][BK k]: 8 chunks per row
-        const int row = c >> 3, col = (c & 7) * VE;
-        ok = live && m0 + row < M && k0 + col < K;
-        off = (uint32_t)(m0 + row) * ulda + (uint32_t)(k0 + col);
-      } else {  // tile [BK k][MB m]: MB/VE chunks per row
-        constexpr int CPR = MB / VE;
-        const int row = c / CPR, col = (c % CPR) * VE;
-        ok = live && k0 + row < K && m0 + col < M;
-        off = (uint32_t)(k0 + row) * ulda + (uint32_t)(m0 + col);
-      }
-      ra[d][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, ok ? off * (uint32_t)sizeof(T) : OOB, 0, 0);
+      const int c = lane + 64 * j, k = a_str ? c / (MB / VE) : (c & 7) * VE;
+      ra[d][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrcA, k < left ? abase[j] + ak : OOB, 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < B_PER; ++j) {
-      const int c = lane + 64 * j;
-      bool ok;
-      uint32_t off;
-      if constexpr (!b_kc) {  // tile [BK k][NB n]
-        constexpr int CPR = S::NB / VE;
-        const int row = c / CPR, col = (c % CPR) * VE;
-        ok = live && k0 + row < K && col < N;
-        off = (uint32_t)(k0 + row) * uldb + (uint32_t)col;
-      } else {  // tile [NB n][BK k]: 8 chunks per row
-        const int row = c >> 3, col = (c & 7) * VE;
-        ok = live && row < N && k0 + col < K;
-        off = (uint32_t)row * uldb + (uint32_t)(k0 + col);
-      }
-      rb[d][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrcB, ok ? off * (uint32_t)sizeof(T) : OOB, 0, 0);
+      const int c = lane + 64 * j, k = b_kc ? (c & 7) * VE : c / (S::NB / VE);
+      rb[d][j] = __builtin_amdgcn_raw_buffer_load_b128(rsrcB, k < left ? bbase[j] + bk : OOB, 0, 0);
     }
   };
 
+  // chunk `lane` of a tile at k origin 0: row t of X and its column / 4, as t drop_cpr + column / 4
+  const uint32_t lane_g = !a_str ? (uint32_t)(m0 + (lane >> 3)) * P.drop_cpr + (uint32_t)((lane & 7) * (VE / 4))
+                                 : (uint32_t)(lane / (MB / VE)) * P.drop_cpr + (uint32_t)((m0 + (lane % (MB / VE)) * VE) >> 2);
   auto store_lds = [&](int d) {
-    if constexpr (DROP) {  // A is X under LoRA dropout
+    if constexpr (DROP) {  // A is X under LoRA dropout; a chunk's group of columns: the lane's part and a scalar one
+      const uint32_t tile_g = !a_str ? (uint32_t)kst[d] >> 2 : (uint32_t)kst[d] * P.drop_cpr;
 #pragma unroll
-      for (int j = 0; j < A_PER; ++j) {
-        const int c = lane + 64 * j;
-        uint32_t t, col;  // token (row of X) and first column of X of this chunk
-        if constexpr (!a_str) {
-          t = (uint32_t)(m0 + (c >> 3));
-          col = (uint32_t)(kst[d] + (c & 7) * VE);
-        } else {
-          constexpr int CPR = MB / VE;
-          t = (uint32_t)(kst[d] + c / CPR);
-          col = (uint32_t)(m0 + (c % CPR) * VE);
-        }
-        ra[d][j] = drop_chunk<T>(ra[d][j], t * P.drop_cpr + (col >> 2), P.drop_key, P.drop_thr);
-      }
+      for (int j = 0; j < A_PER; ++j)
+        ra[d][j] = drop_chunk<T>(ra[d][j], lane_g + (tile_g + (uint32_t)j * (!a_str ? 8u : 64u / (MB / VE)) * P.drop_cpr), P.drop_key, P.drop_thr);
     }
 #pragma unroll
     for (int j = 0; j < A_PER; ++j) {
@@ -217,12 +218,16 @@ __device__ __forceinline__ void skinny_body(const SkinnyProblem& P, int bx, unsi
   const int J = (t_end - t_begin + NWV - 1) / NWV;
   const int t0 = wave;
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d) load_global(d, t0 + NWV * d);
+  for (int d = 0; d < DEPTH; ++d) {
+    load_global(d, t0 + NWV * d);
+    __builtin_amdgcn_sched_barrier(0);  // stage after stage, here and in the loop: a wait counts the loads behind those it needs
+  }
   for (int j0 = 0; j0 < J; j0 += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
       store_lds(d);  // same wave wrote/reads this region: LDS operations of one wave stay in order
       load_global(d, t0 + NWV * (j0 + d + DEPTH));
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int ks = 0; ks < BK / S::KS; ++ks) {
         i32x4 fa[MR];
@@ -286,7 +291,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyProblem& P, int bx, unsi
 // AL is common to both problems of a paired launch; BL0 / BL1 are their B layouts.
 // DROPM: bit w set = problem w of the launch is masked (see skinny_body)
 template <typename T, int RT, int NWV, int AL, int BL0, int BL1, int DROPM = 0, int MR = 1>
-__global__ __launch_bounds__(NWV * 64) void skinny_kernel(SkinnyArgs g) {
+__global__ __launch_bounds__(NWV * 64, NWV == 4 && RT * MR == 1 ? 2 : 1) void skinny_kernel(SkinnyArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   // Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2 and its own
   // path to memory.  Renumber so that (a) neighbouring row blocks of a problem run on the same XCD: a
