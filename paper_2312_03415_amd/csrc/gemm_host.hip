@@ -666,8 +666,9 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap) {
   // split over them.  dA, dB in us, 64 rows / 32 rows: 2048 x (2048 + 2048) 12.4 / 8.9, 2048 x (4096 + 4096) 13.4 / 10.3, 4096
   // x (4096 + 4096) 18.8 / 15.6, 8192 x (4096 + 4096) 34 / 30.6, 8192 x (1024 + 4096) 27.7 (four slices) / 22.9; with more
   // blocks 2048 x (2048 + 8192) 15.1 / 16.6, 4096 x (2048 + 8192) 21.1 / 25.4, 8192 x (4096 + 6144) 33 / 48; with few and a long
-  // contraction 8192 x (768 + 3072) 21.4 (four slices) / 24.0.
-  if (nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2 && !masked) {
+  // contraction 8192 x (768 + 3072) 21.4 (four slices) / 24.0.  Masked ones (LoRA dropout) alike: 4096 x (8192 + 2048) 28.7 / 36.8, 8192 x (11008
+  // + 4096) 59.0 / 75.4 (operands from HBM; plain 27.1 / 36.7 and 59.1 / 75.9).
+  if (nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2) {
     const int64_t b64 = count(64);
     if (b64 > 128 || (b64 <= 64 && min_ktiles >= 64)) p.mr = 2;
   }
@@ -693,7 +694,7 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap) {
   // 32 and more of them on 4 waves stay whole up to 64 K tiles: T of 2048 x 4096 12.7 us, 13.2 in two slices, {Z1, T} 12.0 and 13.1;
   // with more the reduce pass pays: Z1 of 1776 x 4536 19.3 us, 16.4 in two, T of 1240 x 5464 19.6 and 16.1, 2048 x 8192 18.4 in two, 16.9 in four.
   int64_t splits = 1;
-  const bool half = nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2 && !masked;
+  const bool half = nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2;
   if (blocks < (half ? 128 : 224)) {
     const bool one_each = !d[0].a_strided && p.rt == 1 && (dtype != DT_F32 || p.nwv == 16);
     splits = one_each ? 256 / blocks : (256 + blocks - 1) / blocks;

@@ -52,3 +52,35 @@ def test_masked_rank_products(n, i, o, r, mt, dtype):
             assert relerr(g, w) < TOL[dtype], (k, bring)
             if k == "T":  # formed in one step from stored operands: a dropped or kept chunk too many moves every element of its row
                 assert elem_excess(g, w, dtype) < 1.0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("n,i,o,r", [(300, 8200, 72, 8), (65, 4104, 4200, 32),    # 64-row blocks of a pair, masked; rows and columns past the tiles
+                                     (129, 8264, 136, 48), (4160, 520, 264, 16),  # r > 32; few blocks and a long contraction
+                                     (70, 2056, 136, 16), (33, 72, 40, 8)])       # 32-row blocks
+def test_masked_streaming_pairs(n, i, o, r, dtype):
+    """{Z1, T} and {dA, dB} on the streaming kernel with rows of X, dY and the outputs further apart than they are long."""
+    import torch
+    if dtype == "f32" and n * i * o > 2e9:
+        pytest.skip("the reference takes long")
+    td, code, p, seed, s = torch_dtype(dtype), rl.dtype_from_name(dtype), 0.3, 77, 0.5
+    print(f"case stream {n} {i}->{o} r={r} {dtype}", flush=True)
+    g = torch.Generator().manual_seed(n + i)
+    mk = lambda rows, cols, var: (torch.randn(rows, cols + 8, generator=g) * var ** 0.5).to(td).cuda()[:, :cols]
+    X, dY, W, A, B = mk(n, i, 1.0), mk(n, o, 1.0), mk(i, o, 1.0 / i), mk(i, r, 1.0 / i), mk(r, o, 1.0 / r)
+    y = torch.empty(n, o, dtype=td, device="cuda")
+    out = [torch.full((a + 1, b + 8), 7.0, dtype=td, device="cuda") for a, b in ((i, r), (r, o))]
+    ws = rl.new_workspace(rl.FWD1, rl.BWD1, n, i, o, r, code)
+    ws.fill_(0xFF)
+    saved = rl.new_saved(None)
+    rl.runlora_forward(rl.FWD1, X, W, A, B, y, saved, workspace=ws, scale=s, dropout_p=p, dropout_seed=seed)
+    rl.runlora_backward(rl.BWD1, dY, saved, W, A, B, None, out[0][:i, :r], out[1][:r, :o], workspace=ws)
+    torch.cuda.synchronize()
+    mask, pq = oracle.dropout_mask(n, i, p, seed)
+    f = lambda t: t.double().cpu().numpy()
+    Xm, sc = f(X) * mask, s / (1.0 - pq)
+    T, Z1 = sc * (Xm @ f(A)), sc * (f(dY) @ f(B).T)
+    for got, want in ((f(y), f(X) @ f(W) + T @ f(B)), (f(out[0][:i, :r]), Xm.T @ Z1), (f(out[1][:r, :o]), T.T @ f(dY))):
+        assert relerr(got, want) < TOL[dtype]
+    for t, (a, b) in zip(out, ((i, r), (r, o))):
+        assert bool((t[a] == 7.0).all()) and bool((t[:, b:] == 7.0).all())
