@@ -676,7 +676,9 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap) {
   // 16 waves for a masked problem of the [M,K] orientation with at least 24 K tiles (T of 8192 x 768, 12 tiles of 64: 10.1 us
   // on 16 waves, 9.0 on 4; 2048 x 2048, 32 tiles: 9.3 and 13.4).  Next to an unmasked problem that streams better on 4 waves
   // (4096 x 2048 -> 8192: 27.8 and 23.6) only while the launch leaves its masked part half a compute unit or more and that
-  // part is no shorter than half of the other (4096 x (4096 + 4096): 17.3 and 22.5; 8192 x (4096 + 4096): 38.5 and 37.4).
+  // part is no shorter than half of the other (4096 x (4096 + 4096): 17.3 and 22.5; 8192 x (4096 + 4096): 38.5 and 37.4).  (Figures from before the
+  // loads went stage after stage, see skinny_body; 16 and 4 waves are level since: 2048 x 2048 8.9 and 8.7, 4096 x (4096 + 4096) 17.0 and 17.0, 1024 x
+  // 4096 whole 11.7 and 13.0, 8192 x (4096 + 4096) 33.6 and 30.2.)
   if (masked && !d[0].a_strided && p.rt == 1) {
     const SkinnyDesc& m = d[0].drop_thr != 0 ? d[0] : d[1];
     const bool alone = nprob == 1 || (blocks <= 256 && 2 * m.K >= (d[0].drop_thr != 0 ? d[1] : d[0]).K);
@@ -731,7 +733,8 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
   }
   const bool masked = d[0].drop_thr != 0 || (nprob == 2 && d[1].drop_thr != 0);
   for (int w = 0; w < nprob && masked && plan.rt > 1; ++w) {
-    // the chains of a launch with a masked problem, whose own is longer, its mask arithmetic included (T of 280 x 2304 r 64 18.5 us, of 700 x
+    // the chains of a launch with a masked problem, whose own is longer, its mask arithmetic included (as they were before skinny_body's loads
+    // went stage after stage, 20-30 % longer than now: T of 300 x 2304 r 64 12.7 us, of 700 x 3000 r 96 23.5, then T of 280 x 2304 r 64 18.5 us, of 700 x
     // 3000 r 96 32.7; {Z1, T} of 960 x (4864 + 768) r 128 34.5; dA, dB of it 18.8, of 1237 x (2056 + 5464) r 64 15.0)
     const double tiles = (double)(((d[w].K + 63) / 64 + 4 * plan.splits - 1) / (4 * plan.splits));
     const double chain = d[w].drop_thr == 0 ? (d[w].a_strided ? 0.0 : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles)) : d[w].a_strided ? (plan.rt == 2 ? 6.0 + 1.8 * tiles : 8.0 + 3.2 * tiles) : (plan.rt == 2 ? 5.8 + 1.4 * tiles : 6.9 + 2.2 * tiles);

@@ -290,6 +290,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyProblem& P, int bx, unsi
 
 // AL is common to both problems of a paired launch; BL0 / BL1 are their B layouts.
 // DROPM: bit w set = problem w of the launch is masked (see skinny_body)
+// Two workgroups of 4 waves share a compute unit where one has a 32x32 block (196-209 registers; 260 without the bound).
 template <typename T, int RT, int NWV, int AL, int BL0, int BL1, int DROPM = 0, int MR = 1>
 __global__ __launch_bounds__(NWV * 64, NWV == 4 && RT * MR == 1 ? 2 : 1) void skinny_kernel(SkinnyArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
