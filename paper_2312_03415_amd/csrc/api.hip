@@ -622,12 +622,12 @@ struct DoraLayout {
 };
 
 size_t dora_head_bytes(int64_t n, int64_t i, int64_t o, int64_t r, int dt, int* norm_rows, int* dm_rows) {
-  int gx = 0, gy = 0, bpw = 0;
-  merge_grid(i, o, r, &gx, &gy, &bpw);
+  int slices = 0, blocks = 0;
+  merge_slices(i, o, r, &slices, &blocks);
   const int dmr = dora_dm_slices(n, o);
-  if (norm_rows) *norm_rows = gy;
+  if (norm_rows) *norm_rows = slices;
   if (dm_rows) *dm_rows = dmr;
-  const size_t rows = (size_t)(gy > dmr ? gy : dmr);
+  const size_t rows = (size_t)(slices > dmr ? slices : dmr);
   return align256((size_t)o * 4) + 2 * align256((size_t)r * (size_t)o * dtype_size(dt)) + align256(rows * (size_t)o * 4);
 }
 

@@ -243,7 +243,7 @@ struct MergeDesc {
   int b_trans = 0;    // B stored [O, R]
   const float* wcol = nullptr;  // optional [O]: M = W diag(wcol) + alpha A B
   // optional: store nothing to M; write the squared column sums of W + alpha A B, one row of O floats per
-  // row slice of the launch (merge_grid's gy rows; the caller adds them up)
+  // row slice (merge_slices; the caller adds them up)
   float* sq_partial = nullptr;
   // drop_thr != 0: M = W + mask o (alpha A B) with the LoRA dropout keep-mask over M's elements (gemm_engine.hpp)
   uint32_t drop_thr = 0, drop_key = 0, drop_cpr = 0;
@@ -261,6 +261,17 @@ inline void merge_grid(int64_t I, int64_t O, int64_t R, int* gx, int* gy, int* b
   if (y > nb) y = nb;
   *bpw = (nb + y - 1) / y;
   *gy = (nb + *bpw - 1) / *bpw;
+}
+// The row slices that squared column sums are taken over: `rows` of them, of `blocks` 32-row blocks each.  They fix the order in which a column's
+// squares are added, and with it the last bits of DoRA's norms, so they do not follow the launch's shape: a workgroup walks one slice or several.
+inline void merge_slices(int64_t I, int64_t O, int64_t R, int* rows, int* blocks) {
+  const int cols = R <= 64 ? 512 : 256;
+  const int nb = (int)((I + 31) / 32);
+  int y = 512 / (int)((O + cols - 1) / cols);
+  if (y < 1) y = 1;
+  if (y > nb) y = nb;
+  *blocks = (nb + y - 1) / y;
+  *rows = (nb + *blocks - 1) / *blocks;
 }
 hipError_t merge_run(int dtype, const MergeDesc& d, hipStream_t stream);
 struct MergeArgs;

@@ -31,9 +31,11 @@ struct MergeArgs {
   float alpha;        // the layer's LoRA scale (1 for the paper's layer)
   int b_trans;        // 1: B is stored [O, R] (the r values of a column contiguous), as A^T of dX += Z1 A^T is
   const float* wcol;  // optional [O]: M = W diag(wcol) + alpha A B (the column-scaled frozen weight of DoRA)
-  // optional [gridDim.y][O]: each workgroup writes, per column, the sum over its rows of (W + alpha A B)^2 in fp32, before any
-  // rounding (the squared column norms, summed over gridDim.y by the caller); without M nothing else is stored
+  // optional [slices][O]: per column, the sum over the rows of a slice (merge_slices; blocks_per_wg is a multiple of its blocks) of
+  // (W + alpha A B)^2 in fp32, before any rounding (the squared column norms, summed over the slices by the caller); without M nothing
+  // else is stored
   float* sq_partial;
+  int slice_blocks;
   // drop_thr != 0: the product is masked before it is added, M = W + mask o (alpha A B), with the LoRA dropout
   // keep-mask of element (row, column) of M (drop_keep4, gemm_engine.hpp; drop_cpr = groups of four columns per row)
   uint32_t drop_thr, drop_key, drop_cpr;
@@ -50,6 +52,10 @@ struct MergeTile {
   static constexpr int LPR = COLS / 8;        // lanes per output row (8 columns each)
   static constexpr int RPP = 64 / LPR;        // rows per pass
   static constexpr int PASSES = 32 / RPP;
+  // Chains a column's squares are added in, row t of a slice in chain t % CHAINS, the chains then one after the other.  Up to r = 64 a
+  // lane's neighbour 32 lanes on holds the rows between its own: the two exchange values and keep half of the columns each.
+  static constexpr bool HALVES = KSTEPS <= 4;
+  static constexpr int CHAINS = HALVES ? RPP / 2 : RPP, SQ = HALVES ? 4 : 8;
 };
 
 // BOTH: sums and M in one pass (V of a DoRA layer).  A build of its own: as one more choice of the other build it cost that one's passes
@@ -116,12 +122,11 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
   if (rb1 > nblocks) rb1 = nblocks;
   const int prow = lane / MT::LPR, pcol = (lane % MT::LPR) * 8;  // this lane's (row in pass, column) for W / M
   const bool col_ok = n0 + pcol < g.O;
-  float gs[8], sq[8];  // W's column scale (1 without one) and the running squared column sums of this lane's 8 columns
+  float gs[8], sq[MT::SQ];  // W's column scale (1 without one) and the running squared column sums of this lane's columns
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    gs[e] = (g.wcol != nullptr && col_ok) ? g.wcol[n0 + pcol + e] : 1.f;
-    sq[e] = 0.f;
-  }
+  for (int e = 0; e < 8; ++e) gs[e] = (g.wcol != nullptr && col_ok) ? g.wcol[n0 + pcol + e] : 1.f;
+#pragma unroll
+  for (int e = 0; e < MT::SQ; ++e) sq[e] = 0.f;
   // W rows and the A fragment of a row block are fetched one block ahead, so that no global-memory
   // latency sits between two blocks
   i32x4 wreg[MT::PASSES], fnext[KSTEPS];
@@ -194,9 +199,17 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
       if (g.sq_partial != nullptr) {  // uniform: rows and columns outside the matrix contribute zeros
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float v0 = (float)w8[e] + g.alpha * s0[e], v1 = (float)w8[4 + e] + g.alpha * s1[e];
-          sq[e] += v0 * v0;
-          sq[4 + e] += v1 * v1;
+          float v0 = (float)w8[e] + g.alpha * s0[e], v1 = (float)w8[4 + e] + g.alpha * s1[e];
+          if constexpr (MT::HALVES) {  // lanes 0-31: columns 0 .. 3 of their row and of the row four on, lanes 32-63: columns 4 .. 7
+            const auto x = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v0), __builtin_bit_cast(uint32_t, v1), false, false);
+            v0 = __builtin_bit_cast(float, (uint32_t)x[0]);
+            v1 = __builtin_bit_cast(float, (uint32_t)x[1]);
+            sq[e] += v0 * v0;
+            sq[e] += v1 * v1;
+          } else {
+            sq[e] += v0 * v0;
+            sq[4 + e] += v1 * v1;
+          }
         }
         if (!BOTH || Mp == nullptr) continue;
       }
@@ -208,15 +221,17 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
       }
       if (col_ok && row < g.I) *reinterpret_cast<i32x4*>(Mp + (int64_t)row * g.ldm + n0 + pcol) = *reinterpret_cast<i32x4*>(o8);
     }
-  }
-  if (g.sq_partial != nullptr) {
-    // the RPP lanes that share a column group add up in a fixed order through the wave's LDS region
-    *reinterpret_cast<f32x4*>(red + prow * MT::COLS + pcol) = f32x4{sq[0], sq[1], sq[2], sq[3]};
-    *reinterpret_cast<f32x4*>(red + prow * MT::COLS + pcol + 4) = f32x4{sq[4], sq[5], sq[6], sq[7]};
-    for (int c = lane; c < MT::COLS; c += 64) {
+    if (g.sq_partial != nullptr && (rb + 1 == rb1 || (rb + 1) % g.slice_blocks == 0)) {  // uniform
+      // the end of a slice: the lanes that share a column add up in a fixed order through the wave's LDS region
+      float* const q = red + (prow % MT::CHAINS) * MT::COLS + pcol + (MT::HALVES ? 4 * hi : 0);
+#pragma unroll
+      for (int e = 0; e < MT::SQ; e += 4) *reinterpret_cast<f32x4*>(q + e) = f32x4{sq[e], sq[e + 1], sq[e + 2], sq[e + 3]};
       float t = 0.f;
-      for (int p = 0; p < MT::RPP; ++p) t += red[p * MT::COLS + c];
-      if (n0 + c < g.O) g.sq_partial[(int64_t)blockIdx.y * g.O + n0 + c] = t;
+#pragma unroll
+      for (int p = 0; p < MT::CHAINS; ++p) t += red[p * MT::COLS + lane];
+      if (n0 + lane < g.O) g.sq_partial[(int64_t)(rb / g.slice_blocks) * g.O + n0 + lane] = t;
+#pragma unroll
+      for (int e = 0; e < MT::SQ; ++e) sq[e] = 0.f;
     }
   }
 }

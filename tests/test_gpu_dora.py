@@ -276,3 +276,39 @@ def test_dora_dB_does_not_depend_on_whether_dm_is_wanted(dtype):
     vec = vectors(L)
     both, alone = (run_dora(L, dev, vec, 5, 0.7, None, want=w) for w in (("dB", "dm"), ("dB",)))
     assert np.array_equal(both["dB"], alone["dB"])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("i,o,r", [(2048, 8192, 16), (1000, 264, 32), (4096, 2056, 64), (4104, 1288, 48), (16456, 136, 8), (5000, 1544, 72), (2056, 4104, 128)])
+def test_column_norms_add_their_squares_in_a_fixed_order(i, o, r, dtype):
+    """c bit for bit: the rows of a column in slices (as many as make 512 workgroups of 512 columns, of 256 beyond r = 64), in a slice
+    four chains of every fourth row (eight beyond r = 64), chains and slices one behind the other.  With A = 0 the squares are exact, so
+    fp32 additions in that order are all there is; W's values span 2^12, so that another order gives other bits."""
+    import torch
+    td, code = torch_dtype(dtype), rl.dtype_from_name(dtype)
+    print(f"case norms {i}x{o} r{r} {dtype}", flush=True)
+    g = torch.Generator().manual_seed(i + o + r)
+    W = (torch.randn(i, o, generator=g) * torch.exp2(8 * torch.rand(i, o, generator=g) - 6)).to(td)
+    chains, strip = (4, 512) if r <= 64 else (8, 256)
+    nb = -(-i // 32)
+    blocks = -(-nb // max(1, min(nb, 512 // -(-o // strip))))
+    slices = -(-nb // blocks)
+    v = np.zeros((slices * blocks * 32, o), np.float32)
+    v[:i] = W.float().numpy()
+    v = (v * v).reshape(slices, blocks * 32 // chains, chains, o)
+
+    def added(terms):
+        t = np.zeros_like(terms[0])
+        for k in range(len(terms)):
+            t = t + terms[k]
+        return t
+    part = added(added(v.transpose(1, 0, 2, 3)).transpose(1, 0, 2))                    # [slices, o]
+    want = np.sqrt(added([added(part[q::4]) if q < slices else np.zeros(o, np.float32) for q in range(4)]))
+    dev = {k: t.to(td).cuda() for k, t in (("X", torch.ones(8, i)), ("A", torch.zeros(i, r)), ("B", torch.randn(r, o, generator=g)), ("m", torch.ones(o)))}
+    ws = torch.empty(rl.runlora_dora_workspace_bytes(2, -1, 8, i, o, r, code), dtype=torch.uint8, device="cuda")
+    for keep in (False, True):
+        ws.fill_(0xFF)
+        Y, c = torch.empty(8, o, dtype=td, device="cuda"), torch.full((o,), float("nan"), device="cuda")
+        M = torch.empty(i, o, dtype=td, device="cuda") if keep else None
+        rl.runlora_dora_forward(2, dev["X"], W.cuda(), dev["A"], dev["B"], dev["m"], Y, rl.new_saved(None, M), c, ws)
+        assert np.array_equal(c.cpu().numpy(), want), (keep, int((c.cpu().numpy() != want).sum()))
