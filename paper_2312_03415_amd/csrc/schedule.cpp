@@ -254,12 +254,11 @@ struct Builder {
     out->steps.push_back(s);
   }
   // forward1 for a few tokens in two launches; false where it does not apply or is modelled slower than forward1's launches
-  // (few rows or a low rank: 48 x 4096 -> 11008, r 32 takes 23 us so and 33 by T = X A and [X|T] [W;B]; at 256 rows, r 128 it
-  // would be 66 and 55).  Layers of more than 16 rows with a rank above the output's width keep the other route, whose T may split
-  // into more scratch than this one has (67 x 2472 -> 72 r 96 18.0 us; 11.3 here since T B runs on the matrix cores: not taken up, no layer
-  // in use has such a rank).  The scratch is what forward1's launches take, but for what they split T with r > 32 into (spare()).
+  // (many rows of a large layer: 48 x 4096 -> 11008, r 32 takes 23 us so and 33 by T = X A and [X|T] [W;B], 256 x 4096 -> 11008, r 128
+  // 66 and 55; a rank above the output's width is no reason: 67 x 2472 -> 72, r 96 11.2 and 19.8).  The scratch is what forward1's
+  // launches take, but for what they split T with r > 32 into (spare()).
   bool few_forward(const char* what, Mat X, Mat W, Mat A, Mat B, Mat Y, Mat T, bool keep_T, const void* bias) {
-    if (L.dtype == DT_F32 || L.w_int4 || L.drop_thr || L.n > kFewMaxRows || L.r > kFewMaxR || (L.r > L.o && L.n > 16)) return false;
+    if (L.dtype == DT_F32 || L.w_int4 || L.drop_thr || L.n > kFewMaxRows || L.r > kFewMaxR) return false;
     // gemm_mt.hpp addresses its operands with 31-bit byte offsets
     if (L.n * X.ld >= (1LL << 30) || L.i * W.ld >= (1LL << 30) || L.i * A.ld >= (1LL << 30)) return false;
     const SkinnyDesc sd = to_skinny({0, 0, L.n, L.r, L.i, X, A, T, true});
