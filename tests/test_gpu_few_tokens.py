@@ -65,10 +65,12 @@ def test_few_tokens_against_the_oracle(n, i, o, r, dtype):
     assert relerr(got, want) < TOL[dtype] and elem_excess(got, want, dtype) <= 1.0
 
 
+# build: rank steps of 32, pairs of 16 columns a wave and slices on their way at a time, as finish_shape chooses them
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("n,i,o,r", [(1, 264, 8, 8), (17, 520, 40, 24), (15, 2056, 96, 40), (33, 8200, 264, 64), (16, 2048, 2056, 128),  # 32 columns a wave
-                                     (250, 1032, 8200, 32), (241, 520, 8248, 56), (256, 1032, 8264, 128)])                             # 64
-def test_finish_at_the_edges_of_its_tiles(n, i, o, r, dtype):
+@pytest.mark.parametrize("n,i,o,r,build", [(1, 1032, 264, 8, (1, 1, 4)), (17, 520, 40, 24, (1, 1, 4)), (15, 4104, 264, 24, (1, 1, 8)), (33, 8200, 264, 64, (2, 1, 4)),
+                                           (15, 2056, 96, 40, (2, 1, 4)), (16, 2048, 2056, 128, (4, 1, 4)), (67, 2472, 72, 96, (4, 1, 4)),
+                                           (250, 1032, 2104, 24, (1, 2, 4)), (249, 1032, 2104, 56, (2, 2, 4)), (131, 1032, 4104, 104, (4, 2, 2))])
+def test_finish_at_the_edges_of_its_tiles(n, i, o, r, build, dtype):
     """Rows, columns and ranks beside multiples of 16, 32 or 64 and 32, every build of the finishing launch, T kept, a bias."""
     import torch
     td, code, s = torch_dtype(dtype), rl.dtype_from_name(dtype), 0.5
@@ -82,8 +84,15 @@ def test_finish_at_the_edges_of_its_tiles(n, i, o, r, dtype):
     saved = rl.new_saved(T[:, :r])
     ws = rl.new_workspace(rl.FWD1, -1, n, i, o, r, code)
     ws.fill_(0xFF)
+    rl.runlora_profile_enable(8)
     rl.runlora_forward(rl.FWD1, X, t["W"], t["A"], t["B"], buf[:n, :o], saved, workspace=ws, scale=s, bias=bias)
     torch.cuda.synchronize()
+    steps = rl.runlora_profile_collect(8)
+    rl.runlora_profile_disable()
+    assert len(steps) == 1, steps                      # the two launches are one step
+    steps_of_32, wide = -(-r // 32), -(-o // 64) * -(-n // 16) >= 512
+    slices = (2 if r > 64 else 4) if wide else (8 if r <= 32 and steps[0]["splits"] > 4 else 4)
+    assert (4 if steps_of_32 > 2 else steps_of_32, 2 if wide else 1, slices) == build, steps
     Tw = s * (d["X"] @ d["A"])
     want = d["X"] @ d["W"] + Tw @ d["B"] + d["bias"]
     assert relerr(to_f64(T[:, :r]), Tw.numpy()) < TOL[dtype] and relerr(to_f64(buf[:n, :o]), want.numpy()) < TOL[dtype]
