@@ -673,40 +673,37 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap) {
     if (b64 > 128 || (b64 <= 64 && min_ktiles >= 64)) p.mr = 2;
   }
   const int64_t blocks = count(32 * p.mr);
-  // 16 waves for a masked problem of the [M,K] orientation with at least 24 K tiles (T of 8192 x 768, 12 tiles of 64: 10.1 us
-  // on 16 waves, 9.0 on 4; 2048 x 2048, 32 tiles: 9.3 and 13.4).  Next to an unmasked problem that streams better on 4 waves
-  // (4096 x 2048 -> 8192: 27.8 and 23.6) only while the launch leaves its masked part half a compute unit or more and that
-  // part is no shorter than half of the other (4096 x (4096 + 4096): 17.3 and 22.5; 8192 x (4096 + 4096): 38.5 and 37.4).  (Figures from before the
-  // loads went stage after stage, see skinny_body; 16 and 4 waves are level since: 2048 x 2048 8.9 and 8.7, 4096 x (4096 + 4096) 17.0 and 17.0, 1024 x
-  // 4096 whole 11.7 and 13.0, 8192 x (4096 + 4096) 33.6 and 30.2.)
-  if (masked && !d[0].a_strided && p.rt == 1) {
-    const SkinnyDesc& m = d[0].drop_thr != 0 ? d[0] : d[1];
-    const bool alone = nprob == 1 || (blocks <= 256 && 2 * m.K >= (d[0].drop_thr != 0 ? d[1] : d[0]).K);
-    if (alone && (m.K + bk - 1) / bk >= 24) p.nwv = 16;
-  }
-  // Split K over workgroups only when there are fewer workgroups than compute units, and keep >= 8 K tiles per wave and slice; with
-  // 16 waves that many per four of them (T of 5 x 3744, fp32, masked: 20.9 us in three slices, 30.8 whole; 2048 x 8192, bf16, 18.3 in
-  // four and 21.8 in two), but twice as many for a pair that fills a quarter of the chip whole ({Z1, T} of 2048 x (4096 + 4096) 15.1
-  // in two slices, 14.2 whole).
+  // A masked problem of the [M,K] orientation whose chains of K tiles are the launch: alone, or next to an unmasked one of at most twice its
+  // contraction where the blocks leave it half a compute unit or more.
+  const SkinnyDesc& m = d[0].drop_thr != 0 ? d[0] : d[nprob - 1];
+  const bool chains = masked && !d[0].a_strided && p.rt == 1 && (nprob == 1 || (blocks <= 256 && 2 * m.K >= (d[0].drop_thr != 0 ? d[1] : d[0]).K));
+  // Split K over workgroups only when there are fewer workgroups than compute units, and keep >= 8 K tiles per wave and slice (T of
+  // 5 x 3744, fp32, masked: 20.9 us in three slices, 30.8 whole), but twice as many for a masked pair that fills a quarter of the chip
+  // whole ({Z1, T} of 2048 x (4096 + 4096) 15.1 in two slices, 14.2 whole).
   // (64-row workgroups: 128-160 of them without a split beat twice as many plus the reduce pass, and so do 32-row ones of a
   // pair that 64-row blocks do not fill.)
-  // In the [M,K] orientation a launch of 16-bit or 16-wave blocks of up to 32 columns takes no more slices than leave every workgroup a
+  // In the [M,K] orientation a launch of 16-bit or masked blocks of up to 32 columns takes no more slices than leave every workgroup a
   // compute unit: T r 16 of 5000 x 5464 19.2 us whole, 22.7 in two, 3232 x 8192 16.1 in two, 21.6 in three, 2560 x 8192 15.5 in three, 18.2
   // in four (in fp32 and with wider blocks a few beyond are no worse: {Z1, T} of 950 x (3000 + 3000), fp32, 17.3 in five, 22.7 whole).
-  // 32 and more of them on 4 waves stay whole up to 64 K tiles: T of 2048 x 4096 12.7 us, 13.2 in two slices, {Z1, T} 12.0 and 13.1;
+  // 32 and more unmasked ones stay whole up to 64 K tiles: T of 2048 x 4096 12.7 us, 13.2 in two slices, {Z1, T} 12.0 and 13.1;
   // with more the reduce pass pays: Z1 of 1776 x 4536 19.3 us, 16.4 in two, T of 1240 x 5464 19.6 and 16.1, 2048 x 8192 18.4 in two, 16.9 in four.
   int64_t splits = 1;
   const bool half = nprob == 2 && d[0].a_strided && d[1].a_strided && p.rt <= 2;
   if (blocks < (half ? 128 : 224)) {
-    const bool one_each = !d[0].a_strided && p.rt == 1 && (dtype != DT_F32 || p.nwv == 16);
+    const bool one_each = !d[0].a_strided && p.rt == 1 && (dtype != DT_F32 || chains);
     splits = one_each ? 256 / blocks : (256 + blocks - 1) / blocks;
-    int64_t slice_max = min_ktiles / (p.nwv == 16 && nprob == 2 && blocks >= 64 ? 64 : 32);
-    if (slice_max < 1 || (one_each && p.nwv == 4 && blocks >= 32 && min_ktiles <= 64)) slice_max = 1;
+    int64_t slice_max = min_ktiles / (chains && nprob == 2 && blocks >= 64 ? 64 : 32);
+    if (slice_max < 1 || (one_each && !chains && blocks >= 32 && min_ktiles <= 64)) slice_max = 1;
     if (splits > slice_max) splits = slice_max;
     if (splits > 16) splits = 16;
   }
   while (splits > 1 && (size_t)splits * (size_t)outs * sizeof(float) > cap) --splits;
   p.splits = (int)splits;
+  // 16 waves for masked chains of at least 48 K tiles that are not split, 4 for every other launch.  us on 16 and 4 waves, of 90 T and 67
+  // {Z1, T} with 24 K tiles and more: T of 6795 x 10496 r 16 28.3 and 33.1, 490 x 3184 r 8 11.1 and 13.1; {Z1, T} of 2212 x (10496 + 768) 22.9
+  // and 28.9, 104 x (3424 + 2048) 11.3 and 12.8.  Shorter or in slices: T of 6262 x 2704 r 32 13.3 and 12.0, 3822 x 4928 r 32 in two slices 18.5
+  // and 16.5, 263 x 2304 fp32 in two 20.2 and 17.9.  All of them: 16 waves 2485 us, 4 waves 2553, so 2424.
+  if (chains && splits == 1 && (m.K + bk - 1) / bk >= 48) p.nwv = 16;
   p.partial_bytes = splits > 1 ? (size_t)splits * (size_t)outs * sizeof(float) : 0;
   return p;
 }

@@ -15,11 +15,10 @@
 //    bytes per row of A, half a 128-byte line, and the other half has to come from the neighbouring workgroup's fetch staying
 //    in L2.  With 128-byte strips dA, dB of 4096 x (2048 + 8192) r 16 take 21.4 us, 25.0 without; with fewer blocks the chip's
 //    idle units cost more (skinny_plan).  Single launches keep 32 rows (dB of 4096 x 8192 alone: 18.8 -> 23.4 us).
-//  - NWV = 4 where loads bind: 8 or 16 waves make no plain launch that fills the chip faster (a compute unit fetches 50-60 bytes a
-//    ns, operand B's share included, whatever the number of waves).  A masked problem (LoRA dropout) alone in the [M,K] orientation, whose
-//    mask arithmetic is a chain of instructions per wave, runs 16 (two tiles of loads in flight each): T = (X o m) A of 4096 x 8192 r 16 in two K
-//    slices 20.2 us, on 4 waves 18.9; 1024 x 4096 11.6 and 11.2, 2048 x 8192 r 8 whole 20.2 and 22.2: level since a mask costs half of what it
-//    did when 16 waves took 26.1 us for 32.5.
+//  - NWV = 4: 8 or 16 waves make no plain launch that fills the chip faster (a compute unit fetches 50-60 bytes a ns, operand B's share
+//    included, whatever the number of waves).  16, with two tiles of loads in flight each, for a long masked problem (LoRA dropout) in the
+//    [M,K] orientation that is not split over workgroups: its mask arithmetic makes a wave's K tiles a chain, T = (X o m) A of 6795 x 10496
+//    r 16 28.3 us on 16 waves, 33.1 on 4 (skinny_plan).
 //  - The waves' partial accumulators are summed through LDS in wave order and written once.  A grid
 //    that also splits K over workgroups (gridDim.y) writes fp32 partials that a second kernel sums
 //    in slice order.  No atomics: results are identical from run to run.
@@ -52,7 +51,7 @@ struct SkinnyArgs {
   SkinnyProblem p[2];
   int nprob;
   int mr;   // 32-row blocks per workgroup (1 or 2): selects the build
-  int nwv;  // wavefronts per workgroup (4, or 16 for a masked launch in the [M,K] orientation): selects the build
+  int nwv;  // wavefronts per workgroup (4, or 16 for long masked launches in the [M,K] orientation): selects the build
 };
 
 template <typename T, int RT, int NWV, int MR>

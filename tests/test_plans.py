@@ -148,13 +148,15 @@ def test_masked_product_falls_back_where_the_workspace_is_that_of_two_launches(p
 
 def test_slices_of_streaming_launches(probe):
     """T = X A, r <= 32: no more workgroups than compute units where it is split (16 bits), a masked product in no fewer slices than the same
-    product without a mask, unless that one's slices leave compute units with two workgroups."""
+    product without a mask, unless that one's slices leave compute units with two workgroups, and on 16 waves where it is whole and long:
+    6795 x 10496 r 16 28.3 us, 33.1 on four; 3822 x 4928 r 32 in two slices 16.5 us on four, 18.5; 6262 x 2704 r 32 12.0 and 13.3."""
     rows = [(n, r, k) for n in (1, 5, 18, 64, 200, 700, 1240, 2048, 3232, 4096, 5000, 7000) for r in (8, 32) for k in (1536, 2048, 3744, 4096, 5464, 8192, 11008)]
     for kind in ("stream16", "stream32"):
         plain, masked = (probe(kind, [(*row, m) for row in rows]) for m in (0, 1))
         for (n, r, k), (s0, _, _), (s1, waves, _) in zip(rows, plain, masked):
             blocks = -(-n // 32)
-            assert waves == 16 and (s1 == 1 or s1 * blocks <= 256), (n, r, k, s1)
+            assert s1 == 1 or s1 * blocks <= 256, (n, r, k, s1)
+            assert waves == (16 if s1 == 1 and -(-k // (64 if kind == "stream16" else 32)) >= 48 else 4), (kind, n, r, k, s1, waves)
             if kind == "stream16":
                 assert s0 == 1 or s0 * blocks <= 256, (n, r, k, s0)
             assert s1 >= s0 or s0 * blocks > 256, (kind, n, r, k, s0, s1)
