@@ -708,7 +708,19 @@ SkinnyPlan skinny_plan(int dtype, int nprob, const SkinnyDesc* d, size_t cap) {
   return p;
 }
 
+// T = (X o m) A alone with r > 32 (LoRA dropout), streaming kernel: a workgroup's chain of K tiles, one workgroup to a compute unit, never
+// below the bytes at 4.8 TB/s.  Fitted to 287 launches (n 64 .. 7816, 512 .. 11008 wide, r 40 .. 128, 16 bits; standard deviation 6 %): 1954 x
+// 1280 r 64 10.5 us (10.2 modelled), 3074 x 2304 r 48 13.0 (13.7), 280 x 2304 r 64 12.3 (13.7), 700 x 3000 r 96 23.7 (24.4).
+static double masked_t_us(const SkinnyDesc& d, const SkinnyPlan& plan) {
+  const int64_t wgs = (d.M + 31) / 32 * plan.splits;
+  const double tiles = (double)(((d.K + 63) / 64 + 4 * plan.splits - 1) / (4 * plan.splits)), outs = (double)d.M * (double)d.N;
+  const double chain = (plan.rt > 2 ? 9.3 + 1.26 * tiles : 5.8 + 0.88 * tiles) * (double)((wgs + 255) / 256);
+  const double floor_us = 5.0 + 2.0 * ((double)d.M * d.K + (double)d.K * d.N + outs) / 4.8e6;
+  return (chain > floor_us ? chain : floor_us) + (plan.splits > 1 ? 5.4 + outs * 8.0 * plan.splits / 7.5e6 : 0.0);
+}
+
 double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPlan& plan) {
+  if (nprob == 1 && dtype != DT_F32 && d[0].drop_thr != 0 && !d[0].a_strided && plan.rt > 1) return masked_t_us(d[0], plan);
   // Rates in TB/s of algorithmic bytes, measured (bf16): up to 32 columns the big operand streams; with 64 and 128 the
   // waves' re-reads of the short operand bind (paired launches at 8192 x (4096 + 11008) r 128: 118 us; at 4096 x (5120 +
   // 13824) r 64: 58 us), single launches fill less of the chip.
@@ -730,9 +742,10 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
   }
   const bool masked = d[0].drop_thr != 0 || (nprob == 2 && d[1].drop_thr != 0);
   for (int w = 0; w < nprob && masked && plan.rt > 1; ++w) {
-    // the chains of a launch with a masked problem, whose own is longer, its mask arithmetic included (as they were before skinny_body's loads
-    // went stage after stage, 20-30 % longer than now: T of 300 x 2304 r 64 12.7 us, of 700 x 3000 r 96 23.5, then T of 280 x 2304 r 64 18.5 us, of 700 x
-    // 3000 r 96 32.7; {Z1, T} of 960 x (4864 + 768) r 128 34.5; dA, dB of it 18.8, of 1237 x (2056 + 5464) r 64 15.0)
+    // The chains of a pair with a masked problem, whose own is longer, its mask arithmetic included.  Shorter by 20-30 % since skinny_body's
+    // loads go stage after stage; but with launches priced as they are now ({Z1, T} of 3074 x (2304 + 1792) r 48 13.7 us, dA, dB of 8192 x
+    // (4096 + 4096) r 64 41.6) and tiles as masked_tile_us prices them, 120 layers that neither was fitted to ran {Z1, T} in 2462 us in place
+    // of 2482, dA, dB in 1984 of 1987, some of them 6 us slower (the best plan for each: 2388, 1903).
     const double tiles = (double)(((d[w].K + 63) / 64 + 4 * plan.splits - 1) / (4 * plan.splits));
     const double chain = d[w].drop_thr == 0 ? (d[w].a_strided ? 0.0 : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles)) : d[w].a_strided ? (plan.rt == 2 ? 6.0 + 1.8 * tiles : 8.0 + 3.2 * tiles) : (plan.rt == 2 ? 5.8 + 1.4 * tiles : 6.9 + 2.2 * tiles);
     if (chain > us) us = chain;
@@ -766,9 +779,8 @@ GemmDesc rank_desc(int dtype, const SkinnyDesc& d) {
 // One launch of narrow tiles over operands that come from HBM: 0.53 us per K tile and workgroup (0.45 where a tile's rows
 // are whole lines of a [K, .] operand), twice that where two share a compute unit (see gemm_mt_pair_kernel); never below
 // the operands' bytes at 4.8 TB/s.  Operands that the caches still hold (the activations of a short batch) arrive twice as
-// fast: dA, dB of 1024 x 4096 r 64 take 9.7 us here, 17.5 on the streaming kernel.  Masked (LoRA dropout; streaming kernel / here, reduce
-// included): T of 700 x 3000 r 96 32.7 / 14.7 us, {Z1, T} 32.2 / 16.5; of 8192 x (4096 + 4096) r 64 {Z1, T} 46.0 / 39.8, dA, dB 55.0 / 40.7; for short
-// batches the two are level (300 x 768 r 64: T 9.0 / 10.8, dA, dB 10.0 / 10.2).
+// fast: dA, dB of 1024 x 4096 r 64 take 9.7 us here, 17.5 on the streaming kernel.  Masked pairs (LoRA dropout; streaming kernel / here, reduce
+// included): {Z1, T} of 700 x 3000 r 96 23.8 / 16 us, of 8192 x (4096 + 4096) r 64 35.5 / 35, dA, dB of that 41.6 / 36.
 static double rank_time_us(bool a_strided, bool masked, int64_t wgs, int64_t ktiles, double bytes) {
   const int64_t rounds = wgs / 512, rest = wgs % 512;
   double tk = bytes < 32e6 ? 0.28 : (a_strided ? 0.45 : 0.53);
@@ -784,6 +796,15 @@ static double wide_rank_us(bool a_strided, bool masked, int64_t wgs, int64_t kti
   const double tk = masked ? 0.8 : (bytes < 32e6 ? 0.45 : (a_strided ? 0.6 : 0.65));  // ({Z1, T} of 800 x (1024 + 1024) r 128, masked: 20.7 us whole)
   const double us = 7.5 + (double)((wgs + 255) / 256) * (double)ktiles * tk, floor_us = 5.0 + bytes / 4.8e6;
   return us > floor_us ? us : floor_us;
+}
+
+// T = (X o m) A alone on 128x64 tiles (LoRA dropout): K tiles of a workgroup, 1.7 times that where two share a compute unit, never below the bytes
+// at 5.3 TB/s, and what its slices cost.  Fitted to 2000 launches of the layers that masked_t_us was (standard deviation 3 %): 700 x 3000 r 96 in
+// ten slices 12.9 us, 23.7 on the streaming kernel; 1954 x 1280 r 64 in five 12.3 and 10.5, 3074 x 2304 r 48 in eight 13.9 and 13.0.
+static double masked_tile_us(int64_t M, int64_t N, int64_t wgs, int64_t ktiles, int splits, double bytes) {
+  const int64_t rounds = wgs / 512, rest = wgs % 512;
+  const double us = 4.9 + (double)ktiles * 0.68 * (1.7 * (double)rounds + (rest > 256 ? 1.7 : (rest > 0 ? 1.0 : 0.0))), floor_us = 5.0 + bytes / 5.3e6;
+  return (us > floor_us ? us : floor_us) + (splits > 1 ? 5.2 + (double)M * (double)N * (8.0 * splits + 2.0) / 5.4e6 : 0.0);
 }
 
 static bool rank_shape_ok(int dtype, const SkinnyDesc& d) {
@@ -804,7 +825,9 @@ bool rank_plan(int dtype, const SkinnyDesc& d, size_t cap, GemmPlan* plan, doubl
     if ((kt + per - 1) / per != s) continue;  // no empty slice
     const size_t part = s > 1 ? (size_t)s * (size_t)g.M * (size_t)g.N * sizeof(float) : 0;
     if (part > cap) break;
-    const double us = rank_time_us(g.a_strided != 0, d.drop_thr != 0, nbm * nbn * s, per, bytes) + split_time_us(g.M, g.N, s) + (s > 1 ? slice_us : 0.0);
+    const double us = (d.drop_thr != 0 && !g.a_strided ? masked_tile_us(g.M, g.N, nbm * nbn * s, per, s, bytes)
+                                                       : rank_time_us(g.a_strided != 0, d.drop_thr != 0, nbm * nbn * s, per, bytes) + split_time_us(g.M, g.N, s)) +
+                      (s > 1 ? slice_us : 0.0);
     if (us >= best) continue;
     best = us;
     found = true;

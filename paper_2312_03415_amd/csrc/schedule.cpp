@@ -29,10 +29,11 @@ struct Builder {
     const size_t have = later_partial > max_partial ? later_partial : max_partial;
     return have < rank_bytes ? rank_bytes : have;
   }
-  // What a masked rank-r product in slices has to gain, us: it leaves one launch of the streaming kernel for two, and a small layer waits for
-  // its host, whose share of a launch is 3 us.  280 x 2304 -> 768 r 64, T 18.6 us there and 8.5 + 4.5 in slices, ran 84.7 us a pass and 91.1 with
-  // T and {Z1, T} in slices, 1357 x 768 -> 616 r 128 79.8 and 85.9; 700 x 3000 -> 704 r 96, 32.7 and 10.3 + 4.0, is worth it.
-  double masked_slice_us() const { return L.drop_thr != 0 && (double)L.n * (double)L.i * (double)L.o < 4e9 ? 8.0 : 0.0; }
+  // What a rank-r product in slices has to gain under LoRA dropout, us: it leaves one launch of the streaming kernel for two, and a small layer
+  // may wait for its host, whose share of a launch is 3 us: half of that for T alone (280 x 2304 r 64 12.3 us on the streaming kernel and 14.7
+  // in slices, 174 x 2816 r 48 15.2 and 12.7), and more for a pair, whose streaming launch is priced too high by as much (skinny_time_us;
+  // 1357 x 768 -> 616 r 128 ran 79.8 us a pass and 85.9 with pairs in slices).
+  double masked_slice_us(bool pair) const { return L.drop_thr != 0 && (double)L.n * (double)L.i * (double)L.o < 4e9 ? (pair ? 8.0 : 1.5) : 0.0; }
   GemmPlan dense_plan(int64_t M, int64_t N, int64_t K0, int64_t K1, bool long_op = false) const {
     if (L.memo != nullptr)
       for (int k = 0; k < L.memo->used; ++k) {
@@ -245,7 +246,7 @@ struct Builder {
     s.skplan = skinny_plan(L.dtype, 1, s.sk, L.stream_bytes);
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
     GemmPlan mp;
-    if (rank_plan(L.dtype, s.sk[0], spare(), &mp, nullptr, masked_slice_us())) {  // r > 32
+    if (rank_plan(L.dtype, s.sk[0], spare(), &mp, nullptr, masked_slice_us(!s.sk[0].drop_thr || s.sk[0].a_strided))) {  // r > 32
       s.nsk = 0;
       s.d = rank_desc(L.dtype, s.sk[0]);
       s.plan = mp;
@@ -345,7 +346,7 @@ struct Builder {
     s.sk[1] = d2;
     s.skplan = skinny_plan(L.dtype, 2, s.sk, L.stream_bytes);
     if (s.skplan.partial_bytes > max_partial) max_partial = s.skplan.partial_bytes;
-    s.is_mtpair = mt_pair_plan(L.dtype, s.sk, spare(), &s.mtpair, 0.0, masked_slice_us());  // r > 32
+    s.is_mtpair = mt_pair_plan(L.dtype, s.sk, spare(), &s.mtpair, 0.0, masked_slice_us(true));  // r > 32
     if (s.is_mtpair && s.mtpair.partial_bytes > max_partial) max_partial = s.mtpair.partial_bytes;
     out->steps.push_back(s);
   }

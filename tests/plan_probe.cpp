@@ -80,6 +80,13 @@ int main() {
       if (!build_backward(1, LayerDims{M, N, K0, K1, DT_BF16}, BwdOperands{}, nullptr, &s)) return 1;
       for (const Step& t : s.steps)
         if (t.is_mtpair && t.sk[0].a_strided) std::printf("%d %d %d\n", t.mtpair.wide ? 1 : 0, t.mtpair.splits[0], t.mtpair.splits[1]);
+    } else if (std::strcmp(kind, "maskt") == 0) {  // M = tokens, N = d_in, K0 = d_out, K1 = r: T of forward 1 with dropout on tiles or not, slices
+      LayerDims L{M, N, K0, K1, DT_BF16};
+      L.drop_thr = 26;
+      Schedule s;
+      if (!build_forward(1, L, FwdOperands{}, nullptr, &s)) return 1;
+      const Step& t = s.steps[0];
+      std::printf("%d %d\n", t.nsk == 0 ? 1 : 0, t.nsk == 0 ? t.plan.splits : t.skplan.splits);
     } else if (std::strncmp(kind, "stream", 6) == 0) {  // M, N = r, K of T = X A, K1 = masked or not: slices, wavefronts, rows of a block
       SkinnyDesc d;
       d.M = M; d.N = N; d.K = K0;

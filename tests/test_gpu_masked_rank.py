@@ -13,11 +13,12 @@ pytestmark = pytest.mark.gpu
 
 # (n, i, o, r), is T / the {Z1, T} pair / the {dA, dB} pair on tiles of the middle-sized kernel (ids 12-16)?
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("n,i,o,r,mt", [(1025, 2056, 4104, 64, (1, 1, 1)),   # a row, eight columns past the tiles; slices
-                                        (2048, 1024, 2048, 128, (1, 1, 1)), (700, 3000, 704, 96, (1, 1, 1)),
+@pytest.mark.parametrize("n,i,o,r,mt", [(1025, 4104, 1032, 64, (1, 1, 1)),   # a row, eight columns past the tiles; slices
+                                        (1025, 2056, 4104, 64, (0, 1, 1)), (2048, 1024, 2048, 128, (0, 1, 1)), (700, 3000, 704, 96, (1, 1, 1)),
                                         (129, 4104, 4096, 40, (1, 1, 1)),    # long contraction over few tokens
-                                        (4096, 2048, 2056, 72, (1, 1, 1)),   # 128x128 tiles for a pair
-                                        (300, 512, 512, 48, (0, 0, 1)), (40, 264, 136, 64, (1, 1, 1)), (1500, 1024, 1024, 64, (0, 0, 0))])
+                                        (4097, 2056, 2056, 72, (1, 1, 1)),   # 128x128 tiles for {Z1, T}
+                                        (2049, 8200, 2568, 128, (1, 1, 1)),  # and for both pairs
+                                        (300, 512, 512, 48, (0, 0, 1)), (40, 264, 136, 64, (0, 1, 1)), (1500, 1024, 1024, 64, (0, 0, 0))])
 def test_masked_rank_products(n, i, o, r, mt, dtype):
     import torch
     L = synth.Layer("maskrank", n, i, o, r, dtype, 71)

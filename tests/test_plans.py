@@ -196,3 +196,13 @@ def test_few_token_route_leaves_many_rows_of_large_layers(probe):
     large = [(245, 4608, 9648, 128), (256, 10176, 7008, 64), (170, 7824, 10128, 32), (256, 1752, 10152, 128)]
     assert [p[0] for p in probe("few", large)] == [0] * 4
     assert [p[0] for p in probe("few", [(93, 2904, 8144, 128), (32, 4096, 4096, 64), (64, 8192, 8192, 16)])] == [1] * 3
+
+
+def test_masked_T_goes_to_tiles_where_they_are_faster(probe):
+    """T = (X o m) A, r > 32.  us on the streaming kernel / on 128x64 tiles with their reduce: 1954 x 1280 r 64 10.5 / 12.3, 2582 x 2048 r 64 13.0 / 14.1,
+    1713 x 1536 r 64 10.4 / 12.1, 3074 x 2304 r 48 13.0 / 13.9, 4628 x 1288 r 128 16.6 / 16.4 and a launch more; 700 x 3000 r 96 23.7 / 12.9, 1062 x 4864 r 128 25.6 / 15.6,
+    5149 x 5120 r 40 34.8 / 19.3, 6568 x 640 r 128 14.5 / 11.9 (whole)."""
+    stream = [(1954, 1280, 5760, 64), (2582, 2048, 768, 64), (1713, 1536, 9128, 64), (3074, 2304, 1792, 48), (4628, 1288, 2968, 128), (280, 2304, 768, 64)]
+    tiles = [(700, 3000, 704, 96), (1062, 4864, 984, 128), (5149, 5120, 2816, 40), (6568, 640, 1280, 128)]
+    assert [p[0] for p in probe("maskt", stream)] == [0] * 6
+    assert [p[0] for p in probe("maskt", tiles)] == [1] * 4
