@@ -345,7 +345,8 @@ bool plain_1d(const at::Tensor& t, int64_t count, const at::Tensor& x) {
   return t.dim() == 1 && t.stride(0) == 1 && t.scalar_type() == x.scalar_type() && t.numel() == count && t.device() == x.device() && t.layout() == at::kStrided;
 }
 
-// x, W, A, B, any vectors of `count` elements (args[4 ..]) and a bias or None as a native node takes them; nothing here raises
+// x, W, A and B (args[0 .. 3]), vectors as long as B has rows (0) or columns (1), and a bias or None as a native node takes them; nothing
+// here raises
 bool operands_ok(PyObject* const* args, PyObject* bias, std::initializer_list<std::pair<PyObject*, int>> vectors) {
   for (int k = 0; k < 4; ++k)
     if (!THPVariable_CheckExact(args[k])) return false;

@@ -159,7 +159,8 @@ struct FewPlan {
   double us = 0;   // modelled time
 };
 constexpr int64_t kFewMaxRows = 256, kFewMaxR = 128;
-// us per MB of operands that few rows read from HBM, beyond launch_time_us (in FewPlan::us; to be added to what it is compared with)
+// What launch_time_us lacks for few rows, us per MB of X and W from HBM, and few_time_us does not: added to the launches that the route is
+// compared with, and taken off its own price where it stands beside launches priced without it (the selector's).
 constexpr double kColdUsPerMB = 0.03;
 // scratch_bytes: what the call has for partials whatever route it takes
 FewPlan few_plan(int64_t n, int64_t i, int64_t o, int64_t r, size_t scratch_bytes);

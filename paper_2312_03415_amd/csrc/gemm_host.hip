@@ -747,7 +747,10 @@ double skinny_time_us(int dtype, int nprob, const SkinnyDesc* d, const SkinnyPla
     // (4096 + 4096) r 64 41.6) and tiles as masked_tile_us prices them, 120 layers that neither was fitted to ran {Z1, T} in 2462 us in place
     // of 2482, dA, dB in 1984 of 1987, some of them 6 us slower (the best plan for each: 2388, 1903).
     const double tiles = (double)(((d[w].K + 63) / 64 + 4 * plan.splits - 1) / (4 * plan.splits));
-    const double chain = d[w].drop_thr == 0 ? (d[w].a_strided ? 0.0 : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles)) : d[w].a_strided ? (plan.rt == 2 ? 6.0 + 1.8 * tiles : 8.0 + 3.2 * tiles) : (plan.rt == 2 ? 5.8 + 1.4 * tiles : 6.9 + 2.2 * tiles);
+    double chain = 0.0;
+    if (d[w].drop_thr == 0) chain = d[w].a_strided ? 0.0 : (plan.rt == 2 ? 5.8 + 0.62 * tiles : 6.9 + 1.27 * tiles);
+    else if (d[w].a_strided) chain = plan.rt == 2 ? 6.0 + 1.8 * tiles : 8.0 + 3.2 * tiles;
+    else chain = plan.rt == 2 ? 5.8 + 1.4 * tiles : 6.9 + 2.2 * tiles;
     if (chain > us) us = chain;
   }
   return us + (plan.splits > 1 ? 4.0 + outs * 8.0 * plan.splits / 7.5e6 : 0.0);

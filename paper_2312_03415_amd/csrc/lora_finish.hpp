@@ -8,12 +8,13 @@
 // the bias: 1 x 4096 -> 4096, r 16: 21.9 us on the GPU in four launches, 12.2 in two; 48 x 4096 -> 11008, r 32:
 // 41.5 and 21.5.
 //
-// Bound by latency, that is by the number of trips to memory one behind the other: everything a wave needs (its tile of B, and the slices
-// four at a time, of X W and of X A) is on its way at once.  A workgroup is one wave with 16 rows of Y and 32 P columns; T B runs on the
-// matrix cores, B turned by the transposing LDS read, T summed and rounded by every wave that needs it, in the registers in which the
-// products take it.  The columns of a pair of 16-wide blocks interleave in fours, so that a lane holds eight in a row: 16-byte stores.
-// With T B on the vector units, 256 threads sharing T through LDS behind a barrier and each walking B's rows from memory, 16 x 2048 -> 8192 r 128 took 13.1 us (now 3.9), 58 x
-// 2304 -> 768 r 64 6.8 (3.4), 48 x 4096 -> 11008 r 32 5.7 (4.0), 1 x 4096 -> 4096 r 16 3.9 (3.9).
+// Bound by latency, that is by the number of trips to memory one behind the other: a wave's tile of B and the first U slices of X W and
+// of X A (all of them, up to U: finish_shape) are on their way at once, further slices U at a time.  A workgroup is one wave with 16 rows
+// of Y and 32 P columns; T B runs on the matrix cores, B turned by the transposing LDS read, T summed and rounded by every wave that
+// needs it, in the registers in which the products take it.  The columns of a pair of 16-wide blocks interleave in fours, so that a lane
+// holds eight in a row: 16-byte stores.
+// With T B on the vector units, 256 threads sharing T through LDS behind a barrier and each walking B's rows from memory, 16 x 2048 ->
+// 8192 r 128 took 13.1 us (now 3.9), 58 x 2304 -> 768 r 64 6.8 (3.4), 48 x 4096 -> 11008 r 32 5.7 (4.0), 1 x 4096 -> 4096 r 16 3.9 (3.9).
 #pragma once
 #include "gemm_mt.hpp"
 
@@ -28,7 +29,8 @@ struct FinishArgs {
   float t_alpha;
 };
 
-// How a launch is built: 64 columns a wave where those are enough waves to go round, U slices on their way at a time.
+// How a launch is built: 64 columns a wave where those are enough waves to go round, and U slices on their way at a time: four, two where
+// 64 columns and a rank beyond 64 leave no registers for more, eight where 32 columns and up to 32 of the rank do and there are more than four.
 struct FinishShape {
   int cols, u;
 };

@@ -281,7 +281,7 @@ struct Builder {
     s.is_few = true;
     s.d.dtype = L.dtype;
     s.few_plan = plan;
-    s.few_plan.us -= cold_us;  // (the selector prices the other forwards without it)
+    s.few_plan.us -= cold_us;  // (beside the other forwards, whose launches the selector prices without it)
     FewDesc& f = s.few;
     f.X = X.ptr; f.ldx = X.ld; f.W = W.ptr; f.ldw = W.ld; f.A = A.ptr; f.lda = A.ld; f.B = B.ptr; f.ldb = B.ld;
     f.Y = const_cast<void*>(Y.ptr); f.ldy = Y.ld;
