@@ -57,10 +57,10 @@ def test_masked_rank_products(n, i, o, r, mt, dtype):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 @pytest.mark.parametrize("n,i,o,r", [(300, 8200, 72, 8), (65, 4104, 4200, 32),    # 64-row blocks of a pair, masked; rows and columns past the tiles
-                                     (129, 8264, 136, 48), (4160, 520, 264, 16),  # r > 32; few blocks and a long contraction
+                                     (1019, 8480, 96, 40), (4160, 520, 264, 16),  # r > 32; few blocks and a long contraction
                                      (70, 2056, 136, 16), (33, 72, 40, 8)])       # 32-row blocks
 def test_masked_streaming_pairs(n, i, o, r, dtype):
-    """{Z1, T} and {dA, dB} on the streaming kernel with rows of X, dY and the outputs further apart than they are long."""
+    """{dA, dB} on the streaming kernel (and {Z1, T} for r <= 32) with rows of X, dY and the outputs further apart than they are long."""
     import torch
     if dtype == "f32" and n * i * o > 2e9:
         pytest.skip("the reference takes long")
@@ -75,8 +75,13 @@ def test_masked_streaming_pairs(n, i, o, r, dtype):
     ws.fill_(0xFF)
     saved = rl.new_saved(None)
     rl.runlora_forward(rl.FWD1, X, W, A, B, y, saved, workspace=ws, scale=s, dropout_p=p, dropout_seed=seed)
+    rl.runlora_profile_enable(8)
     rl.runlora_backward(rl.BWD1, dY, saved, W, A, B, None, out[0][:i, :r], out[1][:r, :o], workspace=ws)
     torch.cuda.synchronize()
+    steps = rl.runlora_profile_collect(8)
+    rl.runlora_profile_disable()
+    streaming = [8 <= st["tile_cfg"] <= 10 for st in steps]
+    assert len(steps) == 2 and streaming[1] and (r > 32 or streaming[0]), steps
     mask, pq = oracle.dropout_mask(n, i, p, seed)
     f = lambda t: t.double().cpu().numpy()
     Xm, sc = f(X) * mask, s / (1.0 - pq)
