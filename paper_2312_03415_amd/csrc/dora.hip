@@ -23,9 +23,12 @@ __global__ __launch_bounds__(kThreads) void dora_scale_kernel(const float* __res
   float cj = 1.f;
   if (partial != nullptr) {
     float sum = 0.f;
-    if (j < O) {
-#pragma unroll 8
-      for (int y = q; y < rows; y += 4) sum += partial[(int64_t)y * O + j];
+    for (int y0 = q; y0 < rows; y0 += 64) {  // sixteen rows on their way at a time, zeros beyond the last
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = j < O && y0 + 4 * u < rows ? partial[(int64_t)(y0 + 4 * u) * O + j] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) sum += v[u];
     }
     part[q][jj] = sum;
     __syncthreads();

@@ -31,11 +31,11 @@ struct MergeArgs {
   float alpha;        // the layer's LoRA scale (1 for the paper's layer)
   int b_trans;        // 1: B is stored [O, R] (the r values of a column contiguous), as A^T of dX += Z1 A^T is
   const float* wcol;  // optional [O]: M = W diag(wcol) + alpha A B (the column-scaled frozen weight of DoRA)
-  // optional [slices][O]: per column, the sum over the rows of a slice (merge_slices; blocks_per_wg is a multiple of its blocks) of
-  // (W + alpha A B)^2 in fp32, before any rounding (the squared column norms, summed over the slices by the caller); without M nothing
-  // else is stored
+  // optional [slices][O]: per column, the sum over the rows of a slice (merge_slices; slice_blocks row blocks, slices_per_wg of them a
+  // workgroup) of (W + alpha A B)^2 in fp32, before any rounding (the squared column norms, summed over the slices by the caller);
+  // without M nothing else is stored
   float* sq_partial;
-  int slice_blocks;
+  int slice_blocks, slices_per_wg;
   // drop_thr != 0: the product is masked before it is added, M = W + mask o (alpha A B), with the LoRA dropout
   // keep-mask of element (row, column) of M (drop_keep4, gemm_engine.hpp; drop_cpr = groups of four columns per row)
   uint32_t drop_thr, drop_key, drop_cpr;
@@ -62,8 +62,9 @@ struct MergeTile {
 // 3 us at 4096 x 4096, r 64 (forward 2 of 1024 tokens 72.1 -> 75.5 us, a DoRA layer in f16 102.3 -> 105.3), and a loop for each choice 4 us
 // more at r 32 and 128.  It tests for both at run time all the same: the branches keep a row pass's LDS reads and stores from being
 // gathered over all passes (with none, DoRA's forward took 130.4 us for 124.4 at 4096 x 2048 -> 8192, r 16).
+// Three workgroups share a compute unit at r 33 .. 64 (160 registers, no spills; 176-184 and two without the bound).
 template <typename T, int KSTEPS, bool BOTH>
-__global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
+__global__ __launch_bounds__(256, KSTEPS == 4 ? 3 : 1) void merge_kernel(MergeArgs g) {
   using MT = MergeTile<KSTEPS>;
   constexpr int CB = MT::CB;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -156,6 +157,12 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) fb[b][ks] = read_frag<T, true, BLD>(sB, b * 32, ks, lane);
   float* red = reinterpret_cast<float*>(wsm);
+  const int slice0 = (int)blockIdx.y * g.slices_per_wg;
+  int slice = slice0, slice_left = g.slice_blocks;
+  float held = 0.f;  // column `lane`'s sum over the slice before
+  auto store_sum = [&]() {
+    if (n0 + lane < g.O) g.sq_partial[(int64_t)(slice - 1) * g.O + n0 + lane] = held;
+  };
   for (int rb = rb0; rb < rb1; ++rb) {
     i32x4 fa[KSTEPS], wcur[MT::PASSES];
 #pragma unroll
@@ -221,7 +228,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
       }
       if (col_ok && row < g.I) *reinterpret_cast<i32x4*>(Mp + (int64_t)row * g.ldm + n0 + pcol) = *reinterpret_cast<i32x4*>(o8);
     }
-    if (g.sq_partial != nullptr && (rb + 1 == rb1 || (rb + 1) % g.slice_blocks == 0)) {  // uniform
+    if (g.sq_partial != nullptr && (--slice_left == 0 || rb + 1 == rb1)) {  // uniform
       // the end of a slice: the lanes that share a column add up in a fixed order through the wave's LDS region
       float* const q = red + (prow % MT::CHAINS) * MT::COLS + pcol + (MT::HALVES ? 4 * hi : 0);
 #pragma unroll
@@ -229,11 +236,15 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs g) {
       float t = 0.f;
 #pragma unroll
       for (int p = 0; p < MT::CHAINS; ++p) t += red[p * MT::COLS + lane];
-      if (n0 + lane < g.O) g.sq_partial[(int64_t)(rb / g.slice_blocks) * g.O + n0 + lane] = t;
+      if (slice > slice0) store_sum();  // (a store here is waited for with the next block's loads: of two slices, none is)
+      held = t;
+      ++slice;
+      slice_left = g.slice_blocks;
 #pragma unroll
       for (int e = 0; e < MT::SQ; ++e) sq[e] = 0.f;
     }
   }
+  if (g.sq_partial != nullptr && slice > slice0) store_sum();
 }
 
 }  // namespace rl
