@@ -251,8 +251,8 @@ struct MergeDesc {
 };
 inline bool merge_ok(int dtype, int64_t r) { return dtype != DT_F32 && r <= 128; }
 // the merge kernel's launch shape: gx workgroups of 256 columns, gy row slices of bpw 32-row blocks each: as many workgroups as stay on the
-// chip together (four to a compute unit up to r = 32, two beyond), so that what each spends on its columns of B is spent once.  1024 and
-// 512 of them, us (bf16, stored V and sums / M): 2048 x 8192 r 16 16.3 and 16.9 / 15.5 and 17.1, 2048 x 2048 r 32 8.1 and 9.3 / 6.7 and 7.1; 1280 x
+// chip together (four to a compute unit up to r = 32, two beyond), so that what each spends on its columns of B is spent once; sums take
+// whole slices instead (merge_slices).  1024 and 512 of them, us (bf16, stored V and sums / M, without that): 2048 x 8192 r 16 16.3 and 16.9 / 15.5 and 17.1, 2048 x 2048 r 32 8.1 and 9.3 / 6.7 and 7.1; 1280 x
 // 7328 r 64 17.2 and 15.4 / 17.2 and 14.0, 4096 x 4096 r 128 26.8 and 23.9 / 26.7 and 23.3.
 inline void merge_grid(int64_t I, int64_t O, int64_t R, int* gx, int* gy, int* bpw) {
   *gx = (int)((O + 255) / 256);

@@ -10,7 +10,7 @@
 //    range of 32-row blocks.  The B fragments of its columns are read once (through LDS, with the
 //    transposing LDS load) and stay in registers for the whole walk.  128 columns a wave hold twice the fragments and accumulators: one
 //    workgroup to a compute unit at r = 64, and a row block's loads, its products and its stores then follow one another.  Stored V and
-//    sums / M, us, 128 columns a wave and 64: 1280 x 7328 r 64 29.9 -> 15.4 / 26.3 -> 14.0, 4096 x 4096 r 64 34.3 -> 21.9 / 29.8 -> 20.6, 2048 x
+//    sums / M, us, 128 columns a wave and 64: 1280 x 7328 r 64 29.9 -> 15.4 (16.7 with the sums in whole slices) / 26.3 -> 14.0, 4096 x 4096 r 64 34.3 -> 21.9 / 29.8 -> 20.6, 2048 x
 //    2048 r 32 11.1 -> 8.1 / 11.5 -> 6.7, 2048 x 8192 r 16 18.4 -> 16.3 / 17.3 -> 15.5 (67 MB: 4.3 TB/s).
 //  - per row block: the A fragment (32 rows x r) comes straight from global memory, r/16 MFMAs per
 //    32x32 block give A B in fp32, the wave passes it through its private LDS region to turn the

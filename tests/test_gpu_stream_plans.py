@@ -30,10 +30,11 @@ def gradients(L, p, seed):
     return [(name, relerr(to_f64(got), w)) for name, got, w in zip(("Y", "dA", "dB"), (Y, dA, dB), want)]
 
 
-# (n, i, o, r): K tiles of the masked product below, at and past 24 (16 bits: 64 columns, fp32: 32), one row and a row more than a
-# block, the masked part shorter than half of the other, r at both ends of a column block and beyond it
+# (n, i, o, r): K tiles of the masked product (16 bits: 64 columns, fp32: 32) below, at and past 24 and 48, whole (16 waves from 48 on) and in
+# slices, one row and a row more than a block, the masked part shorter than half of the other, r at both ends of a column block and beyond it
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
-@pytest.mark.parametrize("n,i,o,r", [(1, 1536, 264, 8), (33, 1472, 72, 16), (97, 1544, 392, 32), (64, 2120, 4504, 24), (200, 4104, 136, 32), (130, 1608, 328, 40)])
+@pytest.mark.parametrize("n,i,o,r", [(1, 1536, 264, 8), (33, 1472, 72, 16), (97, 1544, 392, 32), (64, 2120, 4504, 24), (200, 4104, 136, 32), (130, 1608, 328, 40),
+                                     (33, 3000, 72, 16), (1, 3016, 264, 8), (97, 3080, 392, 32), (65, 4088, 136, 24), (1030, 4104, 136, 16)])
 def test_masked_products_on_many_waves(n, i, o, r, dtype):
     L = synth.Layer("masked", n, i, o, r, dtype, 51)
     print(f"case {n} {i}->{o} r={r} {dtype}", flush=True)
@@ -175,9 +176,8 @@ def test_rank_products_split_into_the_workspace_that_is_there(int4):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_few_tokens_in_every_number_of_slices(dtype):
-    """lora_finish_kernel sums four slices at a time and the one to three that are left together, and takes B's rows in blocks of eight: 1 to
-    16 slices, every remainder with and without a four before it, ranks on both sides of 8, 16, 24 and of its threads' share of T, bit for
-    bit on integers."""
+    """lora_finish_kernel takes the slices four at a time (eight up to r = 32 where there are more than four), zeros beyond the last: 1 to 16 slices,
+    every remainder with and without a four before it, ranks on both sides of 8, 16, 24 and of its steps of 32, bit for bit on integers."""
     import torch
     rng = np.random.default_rng(8)
     td, seen = torch_dtype(dtype), set()
